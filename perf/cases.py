@@ -274,8 +274,8 @@ def work(case):
 def tolerance(case):
     """About four times what another order of the sums shows: every stream encoded or prefilled alone (other tile sizes)
     against the batch gives 2.9e-3 .. 4.1e-3 and at most 0.023 on the encoder states, 4.9e-3 .. 5.6e-3 and at most 0.033 on
-    the decoder side; the log-mel in fp32 is 2.3e-7 and at most 2.3e-5 from the same in fp64, and in bf16 a value next to a
-    rounding boundary moves by one unit in the last place (2^-7 at most)."""
+    the decoder side; the log-mel in fp32 is 2.4e-7 and at most 8.3e-5 (a nearly empty filter) from the same in fp64 over
+    six seeds, and in bf16 a value next to a rounding boundary moves by one unit in the last place (2^-7 at most)."""
     if case["kind"] == "logmel":
-        return {"rel": 1e-3, "max": 1e-2} if case["mel_bf16"] else {"rel": 1e-6, "max": 1e-4}
+        return {"rel": 1e-3, "max": 1e-2} if case["mel_bf16"] else {"rel": 1e-6, "max": 3.5e-4}
     return {"rel": 1.2e-2, "max": 0.1} if case["kind"] == "encode" else {"rel": 1.5e-2, "max": 0.13}
