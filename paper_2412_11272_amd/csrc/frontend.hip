@@ -2,18 +2,22 @@
 // include/wf_encoder.h, which also states the definition).  fp32 throughout: the spectrogram spans
 // eight decades.
 //
-//   frame_map_kernel   packed frame index -> (stream, frame inside the stream); resets the per-stream maxima
-//   stft_mel_kernel    per workgroup 32 consecutive packed frames: the windowed, reflect-padded frames of
-//                      x (+) h are gathered into LDS; the 400-point DFT is a dense contraction against
-//                      cos / -sin tables, run on the fp32 matrix cores (v_mfma_f32_32x32x2_f32): each of
-//                      7 waves owns 32 frequency bins and keeps a cosine and a sine accumulator whose
-//                      registers line up, so the power is a per-register a*a + b*b; the power tile goes
-//                      back to LDS, every thread then does a few mel filters (triangles are narrow: only
-//                      the bins under a filter are visited) and writes log10(max(., 1e-10)); the
-//                      per-stream maximum is an integer atomicMax on an order-preserving key (first in
-//                      LDS per frame, then one global atomic per stream and workgroup), hence
-//                      independent of arrival order
-//   normalize_kernel   clamp to (stream max - 8), (v + 4) / 4, convert, store packed
+//   logmel_kernel   one workgroup per FPB consecutive frames of one stream.  The reflect-padded samples of
+//                   x (+) h are staged in LDS once (consecutive frames share 240 of their 400 samples), the
+//                   400-point DFT is a prime-factor transform 16 x 25 (coprime factors: no twiddles between the
+//                   two): 25 real 16-point transforms per frame, then 8 complex 25-point ones (rows 1..7, and
+//                   rows 0 and 8, which are real, packed into one), each in the registers of one thread.  Bins
+//                   k and 400 - k are conjugate, so rows 0..8 hold all 201 bins and no untangling step is left.
+//                   The power spectrum goes back to LDS, one thread per (frame, filter) adds up the bins under
+//                   its triangle and stores (log10(max(., 1e-10)) + 4) / 4; the block's largest and smallest
+//                   value are kept for the clamp.
+//   clamp_kernel    the stream's maximum from its blocks' maxima (no atomics, nothing to reset), then the clamp
+//                   to 8 decades below it, on the stored values (scaling and rounding are monotone); blocks whose
+//                   smallest value needs no clamp leave without touching their rows.
+//
+// What bounds it: VALU issue, about 7 k lane operations a frame (the dense DFT on the fp32 matrix cores that this
+// replaced took 358 kflop a frame).  55 625 frames of 128 filters: 333 -> 77 us per call (this kernel 47, the clamp 14);
+// one stream of 437 frames: 65 -> 17 us (8 + 4 on the GPU, the rest is the host's two launches).
 #include "../../include/wf_encoder.h"
 
 #include <hip/hip_runtime.h>
@@ -30,9 +34,16 @@
 
 namespace {
 
-constexpr int kHop = 160, kNfft = 400, kBins = 201, kBinsPad = 224, kFramesPerBlock = 32;
-constexpr int kRowStride = kNfft + 1;          // LDS row stride of the frame tile (odd: conflict-free column reads)
+constexpr int kHop = 160, kNfft = 400, kBins = 201;
 constexpr double kPi = 3.14159265358979323846;
+constexpr int kMaxMels = 256;
+constexpr int kMaxTaps = 2 * kBins + 2;        // every bin lies under at most two triangles
+constexpr int kInline = 16;                    // streams whose metadata ride in the kernel arguments
+// Frames per workgroup.  16 frames on 128 threads keep both waves busy in every phase and leave room for five workgroups
+// per CU (30 KB of LDS); 8 frames on 256 threads halve the chain of a workgroup where the chip is not full anyway.
+constexpr int kFramesLarge = 16, kFramesSmall = 8;
+constexpr float kLogFloor = -1.5f;             // (log10(1e-10) + 4) / 4
+constexpr int kSmallBatch = 4096;              // frames from which on the large blocks give every CU one
 
 int ffail(int code, const char *fmt, ...) {
   va_list ap;
@@ -49,140 +60,313 @@ int ffail(int code, const char *fmt, ...) {
                                        "%s: %s", #expr, hipGetErrorString(e_));                \
   } while (0)
 
+// One stream of the batch; entry B closes the two prefix sums.
+struct FeStream {
+  int64_t offset;              // first sample in the caller's buffer
+  int32_t n;                   // samples (hush word excluded)
+  int32_t frame0;              // first packed row
+  int32_t block0;              // first block
+  int32_t pad;
+};
+
 struct FeArgs {
   const float *audio;          // caller's samples
   const float *hush;           // [H]
-  const float *window;         // [400]
-  const float *basis_c;        // [400][224]  cos(2 pi f n / 400), zero for f >= 201
-  const float *basis_s;        // [400][224]  -sin(2 pi f n / 400)
-  const float *fbank;          // [n_mels][224]
-  const int32_t *fb_lo, *fb_hi;// [n_mels] first / one-past-last bin under each filter
-  const int64_t *sample_offset;// [B]
-  const int32_t *n_samples;    // [B]
-  const int32_t *cu_frames;    // [B+1]
-  int32_t *frame_stream;       // [F]
-  int32_t *frame_t;            // [F]
-  float *V;                    // [F][n_mels]  log10 mel before the clamp
-  int32_t *smax;               // [B] order-preserving integer key of the stream maximum
+  const float *window;         // [25][16]: the taps that column n2 of the transform meets, in order
+  const float *taps;           // filter weights, packed filter after filter
+  const uint32_t *filters;     // [n_mels] first bin | bins << 8 | first tap << 16, then the n_empty filters without bins
+  const FeStream *streams;     // [B + 1], or nullptr: the copy below
+  const int32_t *block_stream; // [blocks], with `streams`
+  float2 *range;               // [blocks] smallest and largest value of a block
   void *out;                   // [F][n_mels]
-  int32_t B, F, H, n_mels, out_bf16;
+  int32_t B, H, n_mels, n_taps, n_empty, blocks;
+  FeStream local[kInline + 1];
 };
 
-__device__ __forceinline__ int32_t float_key(float v) {   // monotone float -> int
-  const int32_t b = __float_as_int(v);
-  return b >= 0 ? b : b ^ 0x7fffffff;
-}
-__device__ __forceinline__ float key_float(int32_t k) { return __int_as_float(k >= 0 ? k : k ^ 0x7fffffff); }
+__device__ __forceinline__ FeStream fe_stream(const FeArgs &p, int i) { return p.streams ? p.streams[i] : p.local[i]; }
 
-__global__ void __launch_bounds__(256) frame_map_kernel(FeArgs p) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < p.B) p.smax[r] = float_key(-INFINITY);
-  if (r >= p.F) return;
-  const int i = wf::find_stream(p.cu_frames, p.B, r);
-  p.frame_stream[r] = i;
-  p.frame_t[r] = r - p.cu_frames[i];
+__device__ __forceinline__ int fe_find(const FeArgs &p, int block) {
+  if (p.streams) return p.block_stream[block];
+  int i = 0;                                   // a handful of independent compares instead of a dependent search
+#pragma unroll
+  for (int k = 1; k < kInline; ++k) i += (k < p.B && block >= p.local[k].block0) ? 1 : 0;
+  return i;
 }
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-__global__ void __launch_bounds__(448) stft_mel_kernel(FeArgs p) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];
-  float *sFrames = lds;                                   // [32][401] windowed frames; later reused as sPower [32][224]
-  __shared__ int sStream[kFramesPerBlock], sT[kFramesPerBlock], sN[kFramesPerBlock], sRowMax[kFramesPerBlock];
-  __shared__ long sOff[kFramesPerBlock];
-  const int f0 = blockIdx.x * kFramesPerBlock;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lg = lane >> 5;
-
-  if (tid < kFramesPerBlock) {                             // per-frame metadata, once
-    int row = f0 + tid;
-    row = row < p.F ? row : p.F - 1;                       // rows past the end are computed but never stored
-    const int i = p.frame_stream[row];
-    sStream[tid] = i;
-    sT[tid] = p.frame_t[row];
-    sN[tid] = p.n_samples[i];
-    sOff[tid] = p.sample_offset[i];
-    sRowMax[tid] = float_key(-INFINITY);
-  }
-  __syncthreads();
-
-  // ---- gather: sample n of frame (stream i, t) is xp[160 t + n] with xp = reflect-padded x (+) h
-  for (int e = tid; e < kFramesPerBlock * kNfft; e += 448) {
-    const int fr = e / kNfft, n = e - fr * kNfft;
-    const int N = sN[fr], Np = N + p.H;
-    int s = kHop * sT[fr] + n - kNfft / 2;
-    s = s < 0 ? -s : s;
-    s = s >= Np ? 2 * (Np - 1) - s : s;
-    const float x = s < N ? p.audio[sOff[fr] + s] : p.hush[s - N];
-    sFrames[fr * kRowStride + n] = x * p.window[n];
-  }
-  __syncthreads();
-
-  // ---- DFT on the fp32 matrix cores: D[frame][bin] += A[frame][k] B[k][bin], two k per instruction.
-  // First operand: lane (frame l32, k = lg); second operand: lane (bin l32, k = lg).
-  f32x16 acc_c, acc_s;
+// X[0..8] of 16 real values (W = exp(-2 pi i / 16)): re[1..7], im[1..7], and the real X[0] = re[0], X[8] = im[0].
+__device__ __forceinline__ void dft16_real(const float (&x)[16], float (&re)[8], float (&im)[8]) {
+  constexpr float s = 0.70710678118654752f, c1 = 0.92387953251128676f, c3 = 0.38268343236508977f;
+  float a[8], b[8];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { acc_c[r] = 0.0f; acc_s[r] = 0.0f; }
-  const int bin = wave * 32 + l32;
-  const float *fa = sFrames + l32 * kRowStride + lg;
-  const float *bc = p.basis_c + lg * kBinsPad + bin;
-  const float *bs = p.basis_s + lg * kBinsPad + bin;
-#pragma unroll 8
-  for (int k = 0; k < kNfft; k += 2) {
-    const float a = fa[k];
-    const float c = bc[k * kBinsPad];
-    const float s = bs[k * kBinsPad];
-    acc_c = __builtin_amdgcn_mfma_f32_32x32x2f32(a, c, acc_c, 0, 0, 0);
-    acc_s = __builtin_amdgcn_mfma_f32_32x32x2f32(a, s, acc_s, 0, 0, 0);
-  }
-  __syncthreads();                                          // all waves are done reading the frames
-  // accumulator register r of lane (l32, lg) is frame 8*(r/4) + 4*lg + r%4, bin (wave*32 + l32)
-  float *sPower = lds;                                      // [32][224]
+  for (int n = 0; n < 8; ++n) { a[n] = x[n] + x[n + 8]; b[n] = x[n] - x[n + 8]; }
+  const float e0 = a[0] + a[4], e1 = a[1] + a[5], e2 = a[2] + a[6], e3 = a[3] + a[7];
+  const float d0 = a[0] - a[4], d1 = a[1] - a[5], d2 = a[2] - a[6], d3 = a[3] - a[7];
+  re[0] = (e0 + e2) + (e1 + e3);
+  im[0] = (e0 + e2) - (e1 + e3);
+  re[4] = e0 - e2;
+  im[4] = e3 - e1;
+  const float dm = s * (d1 - d3), dp = s * (d1 + d3);
+  re[2] = d0 + dm; im[2] = -(d2 + dp);
+  re[6] = d0 - dm; im[6] = d2 - dp;
+  // odd bins: n and 8 - n share cosines (opposite sign) and sines
+  const float p1 = b[1] - b[7], p2 = s * (b[2] - b[6]), p3 = b[3] - b[5];
+  const float q1 = b[1] + b[7], q2 = s * (b[2] + b[6]), q3 = b[3] + b[5];
+  const float u = b[0] + p2, v = b[0] - p2, w = b[4] + q2, z = q2 - b[4];
+  const float r1 = c1 * p1 + c3 * p3, r3 = c3 * p1 - c1 * p3;
+  const float t1 = c3 * q1 + c1 * q3, t3 = c1 * q1 - c3 * q3;
+  re[1] = u + r1; im[1] = -(w + t1);
+  re[7] = u - r1; im[7] = w - t1;              // sin of 7 pi n / 8: b4 and the even term change sign
+  re[3] = v + r3; im[3] = -(z + t3);
+  re[5] = v - r3; im[5] = z - t3;
+}
+
+// Five-point transform of (r, i)[0..4], in place.
+__device__ __forceinline__ void dft5(float (&r)[5], float (&i)[5]) {
+  constexpr float c1 = 0.30901699437494742f, c2 = -0.80901699437494742f, s1 = 0.95105651629515357f, s2 = 0.58778525229247313f;
+  const float ar = r[1] + r[4], ai = i[1] + i[4], br = r[2] + r[3], bi = i[2] + i[3];
+  const float dr = r[1] - r[4], di = i[1] - i[4], er = r[2] - r[3], ei = i[2] - i[3];
+  const float m1r = r[0] + c1 * ar + c2 * br, m1i = i[0] + c1 * ai + c2 * bi;
+  const float m2r = r[0] + c2 * ar + c1 * br, m2i = i[0] + c2 * ai + c1 * bi;
+  const float n1r = s1 * dr + s2 * er, n1i = s1 * di + s2 * ei;
+  const float n2r = s2 * dr - s1 * er, n2i = s2 * di - s1 * ei;
+  r[0] += ar + br;
+  i[0] += ai + bi;
+  r[1] = m1r + n1i; i[1] = m1i - n1r;
+  r[4] = m1r - n1i; i[4] = m1i + n1r;
+  r[2] = m2r + n2i; i[2] = m2i - n2r;
+  r[3] = m2r - n2i; i[3] = m2i + n2r;
+}
+
+struct Tw { float c, s; };
+// exp(-2 pi i m / 25) for the products m = a b of the 5 x 5 split
+__device__ constexpr Tw kTw25[17] = {
+    {1.0f, 0.0f}, {0.96858316112863108f, -0.24868988716485479f}, {0.87630668004386360f, -0.48175367410171532f},
+    {0.72896862742141155f, -0.68454710592868862f}, {0.53582679497899666f, -0.84432792550201508f}, {0.0f, 0.0f},
+    {0.06279051952931337f, -0.99802672842827156f}, {0.0f, 0.0f}, {-0.42577929156507266f, -0.90482705246601958f},
+    {-0.63742398974868970f, -0.77051324277578925f}, {0.0f, 0.0f}, {0.0f, 0.0f}, {-0.99211470131447788f, -0.12533323356430426f},
+    {0.0f, 0.0f}, {0.0f, 0.0f}, {0.0f, 0.0f}, {-0.63742398974868952f, 0.77051324277578936f}};
+
+// 25-point transform as 5 x 5: input n = 5 n1 + n2 at [n1][n2] of (r, i), output k = k1 + 5 k2 at [k1][k2].
+__device__ __forceinline__ void dft25(float (&r)[5][5], float (&i)[5][5]) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int fr = 8 * (r >> 2) + 4 * lg + (r & 3);
-    sPower[fr * kBinsPad + bin] = acc_c[r] * acc_c[r] + acc_s[r] * acc_s[r];
+  for (int n2 = 0; n2 < 5; ++n2) {             // over n1, in place: [k1][n2]
+    float tr[5], ti[5];
+#pragma unroll
+    for (int n1 = 0; n1 < 5; ++n1) { tr[n1] = r[n1][n2]; ti[n1] = i[n1][n2]; }
+    dft5(tr, ti);
+#pragma unroll
+    for (int k1 = 0; k1 < 5; ++k1) {
+      const Tw w = kTw25[k1 * n2];
+      r[k1][n2] = k1 * n2 == 0 ? tr[k1] : tr[k1] * w.c - ti[k1] * w.s;
+      i[k1][n2] = k1 * n2 == 0 ? ti[k1] : tr[k1] * w.s + ti[k1] * w.c;
+    }
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < 5; ++k1) dft5(r[k1], i[k1]);   // over n2: [k1][k2]
+}
+
+// FPB frames per workgroup of NT threads.
+template <int FPB, int NT, typename TOUT>
+__global__ void __launch_bounds__(NT) logmel_kernel(FeArgs p) {
+  constexpr int kHopStride = kHop + kHop / 32;            // staged sample n sits at n + n / 32: frames are an odd stride apart
+  constexpr int kStaged = kHop * (FPB - 1) + kNfft;
+  constexpr int kSpec = 201;                              // row stride of the half-transformed frames in float2 (odd)
+  constexpr int kWork = kStaged + kStaged / 32 + 1 > FPB * kSpec * 2 ? kStaged + kStaged / 32 + 1 : FPB * kSpec * 2;
+  __shared__ __attribute__((aligned(16))) float work[kWork];   // staged samples, then half-transformed rows, then the power
+  __shared__ __attribute__((aligned(16))) float sWindow[kNfft];
+  __shared__ float sTaps[kMaxTaps];
+  __shared__ uint32_t sFilters[kMaxMels];
+  __shared__ float sMin[NT / 64], sMax[NT / 64];
+  const int tid = threadIdx.x;
+  const int stream = fe_find(p, blockIdx.x);
+  const FeStream st = fe_stream(p, stream), nx = fe_stream(p, stream + 1);
+  const int t0 = ((int)blockIdx.x - st.block0) * FPB;
+  const int T = nx.frame0 - st.frame0;
+  const int nf = min(FPB, T - t0);                        // frames of this block (at least one)
+  const int Np = st.n + p.H;
+
+  // ---- samples 160 t0 - 200 ... of the reflect-padded x (+) h: all of a thread's loads are issued before the first
+  // is used (an address select instead of a branch between x and h keeps them independent)
+  const float *x = p.audio + st.offset;
+  constexpr int kLoads = (kStaged + NT - 1) / NT;
+  const int s0 = kHop * t0 - kNfft / 2;
+  float v[kLoads];
+  if (s0 >= 0 && s0 + kLoads * NT <= st.n) {              // wholly inside x: no index arithmetic
+    const float *xs = x + s0 + tid;
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) v[q] = xs[q * NT];
+  } else {
+    const int n_staged = kHop * (nf - 1) + kNfft;
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      int s = s0 + min(q * NT + tid, n_staged - 1);       // past the last frame: a valid sample, never used
+      s = s < 0 ? -s : s;
+      s = s >= Np ? 2 * (Np - 1) - s : s;
+      const float *src = s < st.n ? x + s : p.hush + (s - st.n);
+      v[q] = *src;
+    }
+  }
+  for (int k = tid; k < kNfft; k += NT) sWindow[k] = p.window[k];
+  for (int k = tid; k < p.n_taps; k += NT) sTaps[k] = p.taps[k];
+  for (int k = tid; k < p.n_mels; k += NT) sFilters[k] = p.filters[k];
+#pragma unroll
+  for (int q = 0; q < kLoads; ++q) {
+    const int e = q * NT + tid;
+    if (e < kStaged) work[e + (e >> 5)] = v[q];
   }
   __syncthreads();
 
-  // ---- mel filters + log10, one (frame, filter) pair per thread and step; row maxima in LDS
-  for (int e = tid; e < kFramesPerBlock * p.n_mels; e += 448) {
-    const int fr = e / p.n_mels, j = e - fr * p.n_mels;
-    const int row = f0 + fr;
-    if (row >= p.F) break;
-    float m = 0.0f;
-    const float *w = p.fbank + j * kBinsPad;
-    for (int f = p.fb_lo[j]; f < p.fb_hi[j]; ++f) m = fmaf(w[f], sPower[fr * kBinsPad + f], m);
-    const float v = log10f(fmaxf(m, 1e-10f));
-    p.V[(size_t)row * p.n_mels + j] = v;
-    atomicMax(&sRowMax[fr], float_key(v));
+  // ---- 16-point transforms: task (frame f, column n2) takes samples 25 n1 + 16 n2 mod 400
+  constexpr int kTasks = FPB * 25, kRounds = (kTasks + NT - 1) / NT;
+  float re[kRounds][8], im[kRounds][8];
+#pragma unroll
+  for (int q = 0; q < kRounds; ++q) {
+    const int task = q * NT + tid;
+    if (task < kTasks) {
+      const int f = task % FPB, n2 = task / FPB;
+      float v[16];
+      int n = 16 * n2;
+#pragma unroll
+      for (int n1 = 0; n1 < 16; ++n1) {
+        v[n1] = work[kHopStride * f + n + (n >> 5)] * sWindow[n2 * 16 + n1];
+        n += 25;
+        n = n >= kNfft ? n - kNfft : n;
+      }
+      dft16_real(v, re[q], im[q]);
+    }
+  }
+  __syncthreads();                                        // the samples are consumed: their memory takes the rows
+  float2 *rows = (float2 *)work;                          // [FPB][8 rows][25]
+#pragma unroll
+  for (int q = 0; q < kRounds; ++q) {
+    const int task = q * NT + tid;
+    if (task < kTasks) {
+      const int f = task % FPB, n2 = task / FPB;
+#pragma unroll
+      for (int k1 = 0; k1 < 8; ++k1) rows[f * kSpec + k1 * 25 + n2] = make_float2(re[q][k1], im[q][k1]);
+    }
   }
   __syncthreads();
-  // one global atomic per stream present in the block (its frames are consecutive)
-  if (tid == 0) {
-    const int nrows = min(kFramesPerBlock, p.F - f0);
-    int cur = sStream[0], key = sRowMax[0];
-    for (int fr = 1; fr < nrows; ++fr) {
-      if (sStream[fr] != cur) {
-        atomicMax(p.smax + cur, key);
-        cur = sStream[fr];
-        key = sRowMax[fr];
-      } else {
-        key = max(key, sRowMax[fr]);
+
+  // ---- 25-point transforms: task (frame f, row r); bin k has k mod 16 = its row and k mod 25 = its output, so
+  // output k2 of row r is bin 225 r + 176 k2 mod 400
+  constexpr int kRowTasks = FPB * 8;
+  static_assert(kRowTasks <= NT, "one 25-point transform per thread");
+  float zr[5][5], zi[5][5];
+  const int f = tid % FPB, r = tid / FPB;
+  if (tid < kRowTasks) {
+#pragma unroll
+    for (int n = 0; n < 25; ++n) {
+      const float2 v = rows[f * kSpec + r * 25 + n];
+      zr[n / 5][n % 5] = v.x;
+      zi[n / 5][n % 5] = v.y;
+    }
+    dft25(zr, zi);
+  }
+  __syncthreads();                                        // rows are consumed: their memory takes the power, [FPB][201]
+  float *power = work;
+  if (tid < kRowTasks) {
+    float *dst = power + f * kSpec;
+    if (r > 0) {
+      int base = 225 * r % 400;
+#pragma unroll
+      for (int k2 = 0; k2 < 25; ++k2) {
+        int k = base + 176 * k2 % 400;
+        k = k >= 400 ? k - 400 : k;
+        const float a = zr[k2 % 5][k2 / 5], b = zi[k2 % 5][k2 / 5];
+        dst[min(k, 400 - k)] = a * a + b * b;
+      }
+    } else {                                              // rows 0 and 8, both real: their spectra are Z + Z* and Z - Z*
+#pragma unroll
+      for (int k2 = 0; k2 < 13; ++k2) {
+        const int m = (25 - k2) % 25;
+        const float a = zr[k2 % 5][k2 / 5], b = zi[k2 % 5][k2 / 5], c = zr[m % 5][m / 5], d = zi[m % 5][m / 5];
+        const int k = 176 * k2 % 400, k8 = (200 + 176 * k2) % 400;
+        dst[k <= 200 ? k : 400 - k] = 0.25f * ((a + c) * (a + c) + (b - d) * (b - d));
+        dst[k8 <= 200 ? k8 : 400 - k8] = 0.25f * ((a - c) * (a - c) + (b + d) * (b + d));
       }
     }
-    atomicMax(p.smax + cur, key);
+  }
+  __syncthreads();
+
+  // ---- mel filters and log, neighbouring threads on neighbouring filters; a thread takes its filter over G frames at
+  // once, so that the taps are read once and the G sums and logarithms are independent
+  constexpr int G = 4;
+  static_assert(FPB % G == 0, "whole groups of frames");
+  float lo = INFINITY, hi = -INFINITY;
+  TOUT *out = (TOUT *)p.out + (size_t)(st.frame0 + t0) * p.n_mels;
+  for (int e = tid; e < FPB / G * p.n_mels; e += NT) {
+    const int g = e / p.n_mels, j = e - g * p.n_mels;
+    const uint32_t d = sFilters[j];
+    const float *pw = power + g * G * kSpec + (d & 255), *w = sTaps + (d >> 16);
+    const int n = (d >> 8) & 255;
+    float m[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) m[q] = 0.0f;
+#pragma unroll 2
+    for (int k = 0; k < n; ++k) {
+      const float t = w[k];
+#pragma unroll
+      for (int q = 0; q < G; ++q) m[q] = fmaf(t, pw[q * kSpec + k], m[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const float y = (log10f(fmaxf(m[q], 1e-10f)) + 4.0f) * 0.25f;
+      if (g * G + q < nf) {
+        out[(size_t)(g * G + q) * p.n_mels + j] = (TOUT)y;
+        lo = fminf(lo, n > 0 ? y : INFINITY);      // the others are clamp_kernel's own business
+        hi = fmaxf(hi, y);
+      }
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = fminf(lo, __shfl_xor(lo, off));
+    hi = fmaxf(hi, __shfl_xor(hi, off));
+  }
+  if ((tid & 63) == 0) { sMin[tid >> 6] = lo; sMax[tid >> 6] = hi; }
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) { lo = fminf(lo, sMin[w]); hi = fmaxf(hi, sMax[w]); }
+    p.range[blockIdx.x] = make_float2(lo, hi);
   }
 }
 
-template <typename TOUT>
-__global__ void __launch_bounds__(256) normalize_kernel(FeArgs p) {
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (long)p.F * p.n_mels) return;
-  const int row = (int)(e / p.n_mels);
-  const float top = key_float(p.smax[p.frame_stream[row]]);
-  const float v = fmaxf(p.V[e], top - 8.0f);
-  ((TOUT *)p.out)[e] = (TOUT)((v + 4.0f) * 0.25f);
+// The clamp of the stored values, one wave per block: 8 decades below the stream's largest value are 2 units of the
+// stored scale.  The filters no bin lies under (the lowest ones of 128: they are narrower than the 40 Hz between bins)
+// sit at the floor of the logarithm and would force every row to be read again; their few columns are written directly.
+template <int FPB, typename TOUT>
+__global__ void __launch_bounds__(256) clamp_kernel(FeArgs p) {
+  const int lane = threadIdx.x & 63;
+  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (b >= p.blocks) return;
+  const int stream = fe_find(p, b);
+  const float low = p.range[b].x;
+  const FeStream st = fe_stream(p, stream), nx = fe_stream(p, stream + 1);
+  float top = -INFINITY;
+  for (int k = st.block0 + lane; k < nx.block0; k += 64) top = fmaxf(top, p.range[k].y);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  const float floor_v = top - 2.0f;
+  const TOUT fl = (TOUT)floor_v;
+  const int r0 = st.frame0 + (b - st.block0) * FPB, rows = min(FPB, nx.frame0 - r0);
+  TOUT *o = (TOUT *)p.out + (size_t)r0 * p.n_mels;
+  if (low < floor_v) {
+    for (int e = lane; e < rows * p.n_mels; e += 64)
+      if ((float)o[e] < (float)fl) o[e] = fl;
+  } else if (kLogFloor < floor_v) {
+    for (int e = lane; e < rows * p.n_empty; e += 64) {
+      const int r = e / p.n_empty;
+      o[(size_t)r * p.n_mels + p.filters[p.n_mels + e - r * p.n_empty]] = fl;
+    }
+  }
+}
+
+template <int FPB, int NT, typename TOUT>
+void launch_logmel(const FeArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL((logmel_kernel<FPB, NT, TOUT>), dim3(a.blocks), dim3(NT), 0, s, a);
+  hipLaunchKernelGGL((clamp_kernel<FPB, TOUT>), dim3((a.blocks + 3) / 4), dim3(256), 0, s, a);
 }
 
 }  // namespace
@@ -194,16 +378,17 @@ constexpr int kIdxSlots = 32;
 
 struct wf_frontend {
   wf_frontend_config cfg{};
-  int64_t max_frames = 0;
+  int64_t max_frames = 0, max_blocks = 0;
+  int n_taps = 0, n_empty = 0;
   std::vector<void *> allocs;
-  float *hush = nullptr, *window = nullptr, *basis_c = nullptr, *basis_s = nullptr, *fbank = nullptr, *V = nullptr;
-  int32_t *fb_lo = nullptr, *fb_hi = nullptr, *frame_stream = nullptr, *frame_t = nullptr, *smax = nullptr;
-  unsigned char *idx_dev = nullptr;      // [B] int64 offsets | [B] int32 n_samples | [B+1] int32 cu_frames
+  float *hush = nullptr, *window = nullptr, *taps = nullptr;
+  uint32_t *filters = nullptr;
+  float2 *range = nullptr;
+  unsigned char *idx_dev = nullptr;      // FeStream[max_streams + 1] | int32 block_stream[max_blocks]
   unsigned char *idx_host[kIdxSlots] = {};
   hipEvent_t idx_evt[kIdxSlots] = {};
   bool idx_used[kIdxSlots] = {};
   int idx_next = 0;
-  size_t idx_bytes = 0;
 };
 
 namespace {
@@ -238,53 +423,47 @@ int fe_create(wf_frontend *fe, const wf_frontend_config *cfg, const float *hush_
   std::vector<float> hush((size_t)(H > 0 ? H : 1), 0.0f);
   if (H > 0) memcpy(hush.data(), hush_audio, (size_t)H * 4);
   if ((rc = fe_upload(fe, &fe->hush, hush))) return rc;
-  std::vector<float> win(kNfft), bc((size_t)kNfft * kBinsPad, 0.0f), bs((size_t)kNfft * kBinsPad, 0.0f);
-  for (int n = 0; n < kNfft; ++n) {
-    win[n] = (float)(0.5 - 0.5 * std::cos(2.0 * kPi * n / kNfft));
-    for (int f = 0; f < kBins; ++f) {
-      const int ph = (int)(((long)f * n) % kNfft);            // exact phase reduction before cos/sin
-      bc[(size_t)n * kBinsPad + f] = (float)std::cos(2.0 * kPi * ph / kNfft);
-      bs[(size_t)n * kBinsPad + f] = (float)(-std::sin(2.0 * kPi * ph / kNfft));
-    }
-  }
+  std::vector<float> win(kNfft);
+  for (int n2 = 0; n2 < 25; ++n2)
+    for (int n1 = 0; n1 < 16; ++n1) win[n2 * 16 + n1] = (float)(0.5 - 0.5 * std::cos(2.0 * kPi * ((25 * n1 + 16 * n2) % kNfft) / kNfft));
   if ((rc = fe_upload(fe, &fe->window, win))) return rc;
-  if ((rc = fe_upload(fe, &fe->basis_c, bc))) return rc;
-  if ((rc = fe_upload(fe, &fe->basis_s, bs))) return rc;
   // triangular filters, unit peak, equally spaced on the mel scale over [0, 8000] Hz
   std::vector<double> edges(n_mels + 2);
   const double m_hi = hz_to_mel(8000.0);
   for (int k = 0; k < n_mels + 2; ++k) edges[k] = mel_to_hz(m_hi * k / (n_mels + 1));
-  std::vector<float> fb((size_t)n_mels * kBinsPad, 0.0f);
-  std::vector<int32_t> lo(n_mels), hi(n_mels);
+  std::vector<float> taps;
+  std::vector<uint32_t> filters(n_mels);
   for (int k = 0; k < n_mels; ++k) {
-    int first = kBins, last = 0;
+    int first = 0, n = 0;
+    const size_t tap0 = taps.size();
     for (int f = 0; f < kBins; ++f) {
       const double hz = f * 40.0;
       const double up = (hz - edges[k]) / (edges[k + 1] - edges[k]);
       const double down = (edges[k + 2] - hz) / (edges[k + 2] - edges[k + 1]);
       const double w = std::fmax(0.0, std::fmin(up, down));
-      fb[(size_t)k * kBinsPad + f] = (float)w;
-      if (w > 0.0) { first = f < first ? f : first; last = f + 1 > last ? f + 1 : last; }
+      if (w > 0.0) {                                            // the bins under a triangle are consecutive
+        if (n == 0) first = f;
+        taps.push_back((float)w);
+        ++n;
+      }
     }
-    lo[k] = first < last ? first : 0;
-    hi[k] = first < last ? last : 0;
+    filters[k] = (uint32_t)first | (uint32_t)n << 8 | (uint32_t)tap0 << 16;
+    if (n == 0) filters.push_back((uint32_t)k);
   }
-  if ((rc = fe_upload(fe, &fe->fbank, fb))) return rc;
-  if ((rc = fe_upload(fe, &fe->fb_lo, lo))) return rc;
-  if ((rc = fe_upload(fe, &fe->fb_hi, hi))) return rc;
-  if ((rc = fe_alloc(fe, (void **)&fe->V, (size_t)fe->max_frames * n_mels * 4))) return rc;
-  if ((rc = fe_alloc(fe, (void **)&fe->frame_stream, (size_t)fe->max_frames * 4))) return rc;
-  if ((rc = fe_alloc(fe, (void **)&fe->frame_t, (size_t)fe->max_frames * 4))) return rc;
-  if ((rc = fe_alloc(fe, (void **)&fe->smax, (size_t)cfg->max_streams * 4))) return rc;
-  fe->idx_bytes = (size_t)cfg->max_streams * 8 + (size_t)cfg->max_streams * 4 + (size_t)(cfg->max_streams + 1) * 4;
-  fe->idx_bytes = (fe->idx_bytes + 15) / 16 * 16;
-  if ((rc = fe_alloc(fe, (void **)&fe->idx_dev, fe->idx_bytes))) return rc;
+  fe->n_taps = (int)taps.size();
+  fe->n_empty = (int)filters.size() - n_mels;
+  if (fe->n_taps > kMaxTaps) return ffail(WF_E_INVALID_ARG, "%d filter taps, at most %d", fe->n_taps, kMaxTaps);
+  if (taps.empty()) taps.push_back(0.0f);
+  if ((rc = fe_upload(fe, &fe->taps, taps))) return rc;
+  if ((rc = fe_upload(fe, &fe->filters, filters))) return rc;
+  fe->max_blocks = fe->max_frames / kFramesSmall + cfg->max_streams;
+  if ((rc = fe_alloc(fe, (void **)&fe->range, (size_t)fe->max_blocks * sizeof(float2)))) return rc;
+  const size_t idx_bytes = ((size_t)cfg->max_streams + 1) * sizeof(FeStream) + (size_t)fe->max_blocks * 4;
+  if ((rc = fe_alloc(fe, (void **)&fe->idx_dev, idx_bytes))) return rc;
   for (int i = 0; i < kIdxSlots; ++i) {
-    FE_HIP_TRY(hipHostMalloc((void **)&fe->idx_host[i], fe->idx_bytes, hipHostMallocDefault));
+    FE_HIP_TRY(hipHostMalloc((void **)&fe->idx_host[i], idx_bytes, hipHostMallocDefault));
     FE_HIP_TRY(hipEventCreateWithFlags(&fe->idx_evt[i], hipEventDisableTiming));
   }
-  FE_HIP_TRY(hipFuncSetAttribute((const void *)stft_mel_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 kFramesPerBlock * kRowStride * 4));
   FE_HIP_TRY(hipDeviceSynchronize());
   return WF_OK;
 }
@@ -336,15 +515,7 @@ int wf_logmel_batch(wf_frontend *fe, const float *audio_dev, const int64_t *samp
   if (B < 1) return ffail(WF_E_INVALID_ARG, "B = %d, need B >= 1", B);
   if (B > fe->cfg.max_streams) return ffail(WF_E_CAPACITY, "B = %d exceeds max_streams = %d", B, fe->cfg.max_streams);
   const int H = fe->cfg.hush_samples;
-  const int slot = fe->idx_next;
-  if (fe->idx_used[slot]) FE_HIP_TRY(hipEventSynchronize(fe->idx_evt[slot]));
-  unsigned char *hs = fe->idx_host[slot];
-  const int S = fe->cfg.max_streams;
-  int64_t *h_off = (int64_t *)hs;
-  int32_t *h_n = (int32_t *)(hs + (size_t)S * 8);
-  int32_t *h_cu = h_n + S;
   int64_t total = 0, frames = 0;
-  h_cu[0] = 0;
   for (int i = 0; i < B; ++i) {
     if (n_samples[i] < 0 || sample_offset[i] < 0) return ffail(WF_E_INVALID_ARG, "stream %d: negative length or offset", i);
     const int64_t Np = (int64_t)n_samples[i] + H;
@@ -353,36 +524,56 @@ int wf_logmel_batch(wf_frontend *fe, const float *audio_dev, const int64_t *samp
     if (total > fe->cfg.max_total_samples)
       return ffail(WF_E_CAPACITY, "total samples incl. hush exceed max_total_samples = %lld (at stream %d)", (long long)fe->cfg.max_total_samples, i);
     frames += Np / kHop;
-    h_off[i] = sample_offset[i];
-    h_n[i] = n_samples[i];
-    h_cu[i + 1] = (int32_t)frames;
   }
   if (frames > mel_capacity_frames)
     return ffail(WF_E_CAPACITY, "batch produces %lld frames but mel_capacity_frames = %lld", (long long)frames, (long long)mel_capacity_frames);
-  if (cu_frames_host) memcpy(cu_frames_host, h_cu, (size_t)(B + 1) * 4);
   hipStream_t s = (hipStream_t)hip_stream;
-  FE_HIP_TRY(hipMemcpyAsync(fe->idx_dev, hs, fe->idx_bytes, hipMemcpyHostToDevice, s));
-  FE_HIP_TRY(hipEventRecord(fe->idx_evt[slot], s));
-  fe->idx_used[slot] = true;
-  fe->idx_next = (slot + 1) % kIdxSlots;
-  if (frames == 0) return WF_OK;
 
+  // A batch that would not give every compute unit a large block takes small ones: more of them, each shorter.
+  const bool small = frames < kSmallBatch;
+  const int fpb = small ? kFramesSmall : kFramesLarge;
   FeArgs a{};
-  a.audio = audio_dev; a.hush = fe->hush; a.window = fe->window; a.basis_c = fe->basis_c; a.basis_s = fe->basis_s;
-  a.fbank = fe->fbank; a.fb_lo = fe->fb_lo; a.fb_hi = fe->fb_hi;
-  a.sample_offset = (const int64_t *)fe->idx_dev;
-  a.n_samples = (const int32_t *)(fe->idx_dev + (size_t)S * 8);
-  a.cu_frames = a.n_samples + S;
-  a.frame_stream = fe->frame_stream; a.frame_t = fe->frame_t; a.V = fe->V; a.smax = fe->smax; a.out = mel_out_dev;
-  a.B = B; a.F = (int32_t)frames; a.H = H; a.n_mels = fe->cfg.n_mels; a.out_bf16 = mel_dtype == WF_DTYPE_BF16;
-  const int F = (int)frames;
-  const int nmap = F > B ? F : B;
-  hipLaunchKernelGGL(frame_map_kernel, dim3((nmap + 255) / 256), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(stft_mel_kernel, dim3((F + kFramesPerBlock - 1) / kFramesPerBlock), dim3(448),
-                     kFramesPerBlock * kRowStride * 4, s, a);
-  const long n = (long)F * a.n_mels;
-  if (a.out_bf16) hipLaunchKernelGGL(normalize_kernel<__bf16>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(normalize_kernel<float>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+  a.audio = audio_dev; a.hush = fe->hush; a.window = fe->window; a.taps = fe->taps; a.filters = fe->filters;
+  a.range = fe->range; a.out = mel_out_dev;
+  a.B = B; a.H = H; a.n_mels = fe->cfg.n_mels; a.n_taps = fe->n_taps; a.n_empty = fe->n_empty;
+  const bool out_bf16 = mel_dtype == WF_DTYPE_BF16;
+  // ---- stream metadata: in the kernel arguments where they fit (no copy ahead of the kernels), else by an upload
+  const bool inl = B <= kInline;
+  const int slot = fe->idx_next;
+  if (!inl && fe->idx_used[slot]) FE_HIP_TRY(hipEventSynchronize(fe->idx_evt[slot]));
+  FeStream *meta = inl ? a.local : (FeStream *)fe->idx_host[slot];
+  int32_t *bs = inl ? nullptr : (int32_t *)(fe->idx_host[slot] + ((size_t)fe->cfg.max_streams + 1) * sizeof(FeStream));
+  int32_t f0 = 0, blocks = 0;
+  for (int i = 0; i < B; ++i) {
+    const int32_t T = (int32_t)(((int64_t)n_samples[i] + H) / kHop);
+    meta[i] = FeStream{sample_offset[i], n_samples[i], f0, blocks, 0};
+    if (cu_frames_host) cu_frames_host[i] = f0;
+    f0 += T;
+    const int32_t nb = (T + fpb - 1) / fpb;
+    if (bs)
+      for (int32_t b = 0; b < nb; ++b) bs[blocks + b] = i;
+    blocks += nb;
+  }
+  meta[B] = FeStream{0, 0, f0, blocks, 0};
+  if (cu_frames_host) cu_frames_host[B] = f0;
+  if (blocks == 0) return WF_OK;
+  a.blocks = blocks;
+  if (!inl) {
+    const size_t head = ((size_t)fe->cfg.max_streams + 1) * sizeof(FeStream);
+    FE_HIP_TRY(hipMemcpyAsync(fe->idx_dev, fe->idx_host[slot], head + (size_t)blocks * 4, hipMemcpyHostToDevice, s));
+    FE_HIP_TRY(hipEventRecord(fe->idx_evt[slot], s));
+    fe->idx_used[slot] = true;
+    fe->idx_next = (slot + 1) % kIdxSlots;
+    a.streams = (const FeStream *)fe->idx_dev;
+    a.block_stream = (const int32_t *)(fe->idx_dev + head);
+  }
+  if (small) {
+    if (out_bf16) launch_logmel<kFramesSmall, 256, __bf16>(a, s);
+    else launch_logmel<kFramesSmall, 256, float>(a, s);
+  } else {
+    if (out_bf16) launch_logmel<kFramesLarge, 128, __bf16>(a, s);
+    else launch_logmel<kFramesLarge, 128, float>(a, s);
+  }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return ffail(WF_E_HIP, "front-end launch: %s", hipGetErrorString(err));
   return WF_OK;

@@ -10,7 +10,7 @@ from paper_2412_11272_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# fp32 DFT on the matrix cores against fp64: the normalised log-mel lives in about [-1, 1.5];
+# fp32 DFT against fp64: the normalised log-mel lives in about [-1, 1.5];
 # an amplitude error of 1e-7 of the loudest bin on a bin 8 decades down is 4e-4 in log10, 1e-4 after the /4
 LOGMEL_ATOL = 1e-4
 
@@ -49,6 +49,35 @@ def test_logmel_without_hush_short_and_bf16():
     assert np.abs(got - ref).max() <= LOGMEL_ATOL
     got, ref, _ = _run(80, [8000, 3210], synth.make_hush_audio(5), out_dtype=torch.bfloat16)
     assert np.abs(got - ref).max() <= 8e-3            # one bf16 rounding of values up to ~1.5
+
+
+@pytest.mark.parametrize("n_mels", [80, 128])
+@pytest.mark.parametrize("lens", [
+    [160 * t + (i % 3) for i, t in enumerate([7, 8, 9, 15, 16, 17, 31, 33])],        # edges of 8- and 16-frame blocks
+    [160 * t for t in range(3, 20)],                                                 # one more stream than the arguments hold
+    [160 * 2100 + 5, 160 * 17, 160 * 2000, 201],                                     # large blocks
+    [160 * (8 + 13 * i) for i in range(40)],                                         # large blocks, uploaded stream table
+])
+def test_logmel_blocks_and_clamp(lens, n_mels):
+    """Every block size and both ways of handing over the stream table; half of every stream is digital silence, so the
+    clamp to 8 decades below the stream's maximum acts on whole blocks."""
+    import torch
+    audios = [synth.make_audio(n, 31 + i) for i, n in enumerate(lens)]
+    for a in audios:
+        a[len(a) // 2:] = 0.0
+    flat, offs = np.concatenate(audios), np.concatenate([[0], np.cumsum(lens)[:-1]])
+    fe = wf.Frontend(n_mels, None, len(lens), sum(lens))
+    try:
+        dev = torch.from_numpy(flat).cuda()
+        got, cu = fe.logmel(dev, offs, lens)
+        half, _ = fe.logmel(dev, offs, lens, out_dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+    finally:
+        fe.close()
+    ref, cu_ref = F.log_mel_batch(audios, None, n_mels)
+    assert cu.tolist() == cu_ref.tolist()
+    assert np.abs(got.cpu().numpy() - ref).max() <= LOGMEL_ATOL
+    assert torch.equal(half, got.to(torch.bfloat16))
 
 
 def test_logmel_errors():
