@@ -22,9 +22,21 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", 
          *os.environ.get("WF_HIPCC_EXTRA", "").split()]
 
 
+# A wave of the pipelined GEMM owns up to 512 registers, half of which only the matrix instructions can address: its
+# accumulators have to live there.
+ACCUM_FILES = {"gemm_pipe.hip"}
+
+
+def _flags(src: str) -> list:
+    if os.path.basename(src) not in ACCUM_FILES:
+        return FLAGS
+    i = FLAGS.index("-amdgpu-mfma-vgpr-form=1")
+    return FLAGS[:i - 1] + FLAGS[i + 1:]
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ_DIR, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
+    cmd = [HIPCC, *_flags(src), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
@@ -56,10 +68,10 @@ def build_sanitized_host_driver(driver_src: str, out_path: str) -> str:
     os.makedirs(obj_dir, exist_ok=True)
     san = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-sanitize-recover=undefined",
            "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
-    flags = [f for f in FLAGS if f != "-O3"] + ["-O1"] + san
     srcs = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
     def comp(src, lang=()):
+        flags = [f for f in _flags(src) if f != "-O3"] + ["-O1"] + san
         obj = os.path.join(obj_dir, os.path.basename(src) + ".o")
         r = subprocess.run([HIPCC, *lang, *flags, "-c", src, "-o", obj], capture_output=True, text=True)
         if r.returncode != 0:

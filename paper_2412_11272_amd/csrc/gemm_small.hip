@@ -20,6 +20,8 @@
 //     to bf16 -- exactly what the LayerNorm kernel would have stored.  This removes two kernels per transformer
 //     block; with a few hundred tokens each kernel in the chain costs 5-7 us whatever it does.
 
+#include <algorithm>
+
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -272,7 +274,7 @@ hipError_t launch_small(const GemmArgs &a, hipStream_t s) {
 
 }  // namespace
 
-bool gemm_small_applies(int32_t M) { return M <= 1024; }
+bool gemm_small_applies(int32_t M, int32_t N, int32_t K) { return M <= kSmallRows && std::min(N, K) <= 512 && std::max(N, K) <= 2048; }
 
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;

@@ -57,7 +57,7 @@ struct GemmArgs {
   // of out, starting at its column 0 -- one product feeding two buffers (queries | keys and values).  n_split % 8 == 0.
   void *out2;
   int32_t n_split, ldo2;
-  int32_t prefer_large;     // stay on the large-batch kernels whatever M is (a product that streams a huge weight matrix)
+  int32_t prefer_large;     // never the small-batch kernel (a product that streams a huge weight matrix, a wide model)
   int32_t prefer_small;     // run on the small-batch kernel even if M is above its usual limit (the first convolution
                             // of a small batch has twice as many rows as the batch has tokens)
 };
@@ -89,9 +89,14 @@ struct PrepArgs {
 
 // bf16 MFMA path -------------------------------------------------------------------------------
 hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
-// small row counts (gemm_small_applies(M)): 32 x 32 tiles, reduction split over the waves, optional fused LayerNorm
-bool gemm_small_applies(int32_t M);
+// small batches (kSmallRows rows) of narrow models: 32-row tiles, reduction split over the waves, optional fused LayerNorm.
+// Whether a product of a small batch goes there depends on its width and depth only, not on the number of rows.
+constexpr int32_t kSmallRows = 1024;
+bool gemm_small_applies(int32_t M, int32_t N, int32_t K);
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
+// products with at most one tile per compute unit, and convolutions whose taps are no whole K steps
+bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K);
+hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s);
 hipError_t launch_layernorm(const float *x, const float *g, const float *b, void *out, int out_bf16,
                             int32_t M, int32_t d, float eps, hipStream_t s);

@@ -100,6 +100,35 @@ def test_linear_bf16_at_the_edges_of_every_kernel_choice():
     assert picks == {(0, 0), (128, 128), (256, 256), (320, 256)}
 
 
+# One shape per tile of the one-tile-per-CU kernel (smallest tile that leaves at most 256: 32 x 64 ... 192 x 256), row counts off
+# the tile's edges, reductions shorter than the LDS ring, and one row
+PIPE_SHAPES = [(1, 768, 64), (200, 768, 768), (425, 1280, 1280), (861, 768, 3072), (1203, 1280, 704), (1601, 1280, 640),
+               (2603, 1024, 192), (5001, 1024, 2048), (6399, 1280, 2560), (7301, 1280, 2560), (7900, 1280, 2624)]
+
+
+@pytest.mark.parametrize("M,N,K", PIPE_SHAPES)
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_linear_bf16_one_tile_per_cu(M, N, K, epi):
+    _linear_case(M, N, K, epi, 300 + M)
+
+
+@pytest.mark.parametrize("N,K", [(1280, 5120), (3072, 768)])
+def test_linear_rows_do_not_depend_on_the_kernel(N, K):
+    """Every tile of the pipelined and the large-batch kernels adds a row up in the same order: the first rows of a product
+    have the same bits whatever the number of rows (and so the kernel and the tile) is."""
+    import torch
+    g = torch.Generator().manual_seed(N + K)
+    a = torch.randn(12001, K, generator=g).bfloat16().cuda()
+    w = (0.05 * torch.randn(N, K, generator=g)).bfloat16().cuda()
+    b = torch.randn(N, generator=g).cuda()
+    full = torch.empty((12001, N), dtype=torch.bfloat16, device="cuda")
+    wf.op_linear(wf.WF_PRECISION_BF16, a, w, b, full, 0)
+    for M in (1, 130, 600, 1301, 2600, 4097, 6401):
+        out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        wf.op_linear(wf.WF_PRECISION_BF16, a[:M], w, b, out, 0)
+        assert torch.equal(out, full[:M]), M
+
+
 def test_linear_bf16_random_shapes():
     """Seeded random shapes across all kernel choices (row counts 1 .. 9000, widths and depths in the kernels' units)."""
     rng = np.random.default_rng(77)
