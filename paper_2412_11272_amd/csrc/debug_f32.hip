@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs p) {
       if (EPI == EPI_BIAS) *o = v;
       else if (EPI == EPI_BIAS_GELU) *o = gelu_erf(v);
       else if (EPI == EPI_BIAS_RESID) *o += v;
-      else if (EPI == EPI_BIAS_F32) *o = v;
+      else if (EPI == EPI_BIAS_F32) { if (p.n_valid <= 0 || n < p.n_valid) *o = v; }
       else *o = gelu_erf(v) + p.pos[(size_t)p.row_pos[m] * p.N + n];
     }
   }

@@ -40,7 +40,7 @@ struct wf_decoder : DevCtx {
   float *pos_emb = nullptr, *zero_bias = nullptr, *lnf_g = nullptr, *lnf_b = nullptr;
   std::vector<DecLayerDev> layers;
   // workspace
-  float *x = nullptr, *lbuf = nullptr;
+  float *x = nullptr;
   void *u = nullptr, *qbuf = nullptr, *skv = nullptr, *h = nullptr, *ulast = nullptr;
   int32_t *idx_dev = nullptr;
   int64_t idx_ints = 0;
@@ -137,7 +137,6 @@ int dec_create_impl(wf_decoder *e, const wf_decoder_config *cfg, const wf_decode
   if ((rc = dev_alloc(e, &e->skv, P * 2 * d * e->es))) return rc;
   if ((rc = dev_alloc(e, &e->h, P * f * e->es))) return rc;
   if ((rc = dev_alloc(e, &e->ulast, S * d * e->es))) return rc;
-  if ((rc = dev_alloc(e, (void **)&e->lbuf, S * (size_t)e->vpad * 4))) return rc;
   e->max_work = (int64_t)P / attention_q_tile() + (int64_t)S + 1;
   e->idx_ints = 2 * (int64_t)P + 3 * ((int64_t)S + 1) + 2 * e->max_work;
   if ((rc = dev_alloc(e, (void **)&e->idx_dev, (size_t)e->idx_ints * 4))) return rc;
@@ -279,18 +278,31 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
     hipError_t err = launch_embed(e->tok_emb, act_bf16, e->pos_emb, d_tok, d_pos, e->x, Pt, d, s);
     if (err != hipSuccess) return fail(WF_E_HIP, "embed launch: %s", hipGetErrorString(err));
   }
+  // A few prompts on a narrow model: the three products that follow a LayerNorm run on the small-batch kernel, which
+  // normalises its operand itself (decided by the model's width and the batch, the same for all of them).
+  const bool small = e->bf16 && gemm_small_applies(Pt, 3 * d, d) && gemm_small_applies(Pt, f, d);
+  auto after_ln = [&](int cls, const float *g, const float *b, GemmArgs a, Epilogue ep) -> int {
+    int rc;
+    if (small) {
+      a.A = e->x; a.ln_g = g; a.ln_b = b; a.ln_eps = c.ln_eps;
+    } else {
+      if ((rc = run_ln(e, s, DC_LN, e->x, g, b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
+      a.A = e->u;
+    }
+    a.M = Pt; a.K = d; a.lda = d;
+    return run_gemm(e, s, cls, a, small ? A_LN : A_PLAIN, ep, d, (int)es, Pt, d);
+  };
   for (int l = 0; l < c.n_layers; ++l) {
     const DecLayerDev &w = e->layers[l];
     char *skv = self_kv_out_dev ? (char *)self_kv_out_dev + (size_t)l * self_kv_capacity_tokens * 2 * d * es : (char *)e->skv;
     const char *xkv = (const char *)cross_kv_dev + (size_t)l * kv_capacity_tokens * 2 * d * es;
     // causal self-attention among the prompt tokens
-    if ((rc = run_ln(e, s, DC_LN, e->x, w.ln1_g, w.ln1_b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
     if (e->bf16) {     // one product for q | k | v: the first d result columns go to the query buffer, the rest to the K/V cache
       GemmArgs a{};
-      a.A = e->u; a.W = w.wqkv; a.bias = w.bqkv; a.out = e->qbuf; a.M = Pt; a.N = 3 * d; a.K = d; a.lda = d; a.ldo = d;
-      a.out2 = skv; a.n_split = d; a.ldo2 = 2 * d;
-      if ((rc = run_gemm(e, s, DC_SELF_QKV, a, A_PLAIN, EPI_BIAS, d, (int)es, Pt, d))) return rc;
+      a.W = w.wqkv; a.bias = w.bqkv; a.out = e->qbuf; a.N = 3 * d; a.ldo = d; a.out2 = skv; a.n_split = d; a.ldo2 = 2 * d;
+      if ((rc = after_ln(DC_SELF_QKV, w.ln1_g, w.ln1_b, a, EPI_BIAS))) return rc;
     } else {
+      if ((rc = run_ln(e, s, DC_LN, e->x, w.ln1_g, w.ln1_b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
       if ((rc = run_linear(e, s, DC_SELF_Q, e->u, d, w.wq, w.bq, e->qbuf, d, Pt, d, d, EPI_BIAS))) return rc;
       if ((rc = run_linear(e, s, DC_SELF_KV, e->u, d, w.wkv, w.bkv, skv, 2 * d, Pt, 2 * d, d, EPI_BIAS))) return rc;
     }
@@ -303,8 +315,11 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
     }
     if ((rc = run_linear(e, s, DC_SELF_OUT, e->u, d, w.wo, w.bo, e->x, d, Pt, d, d, EPI_BIAS_RESID))) return rc;
     // cross-attention over the stream's encoder tokens
-    if ((rc = run_ln(e, s, DC_LN, e->x, w.lnx_g, w.lnx_b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
-    if ((rc = run_linear(e, s, DC_CROSS_Q, e->u, d, w.xwq, w.xbq, e->qbuf, d, Pt, d, d, EPI_BIAS))) return rc;
+    {
+      GemmArgs a{};
+      a.W = w.xwq; a.bias = w.xbq; a.out = e->qbuf; a.N = d; a.ldo = d;
+      if ((rc = after_ln(DC_CROSS_Q, w.lnx_g, w.lnx_b, a, EPI_BIAS))) return rc;
+    }
     {
       AttnArgs a{};
       a.q = e->qbuf; a.ldq = d; a.k = xkv; a.v = xkv + (size_t)d * es; a.ldkv = 2 * d; a.out = e->u;
@@ -314,27 +329,23 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
     }
     if ((rc = run_linear(e, s, DC_CROSS_OUT, e->u, d, w.xwo, w.xbo, e->x, d, Pt, d, d, EPI_BIAS_RESID))) return rc;
     // MLP
-    if ((rc = run_ln(e, s, DC_LN, e->x, w.ln2_g, w.ln2_b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
-    if ((rc = run_linear(e, s, DC_FC1, e->u, d, w.w1, w.b1, e->h, f, Pt, f, d, EPI_BIAS_GELU))) return rc;
+    {
+      GemmArgs a{};
+      a.W = w.w1; a.bias = w.b1; a.out = e->h; a.N = f; a.ldo = f;
+      if ((rc = after_ln(DC_FC1, w.ln2_g, w.ln2_b, a, EPI_BIAS_GELU))) return rc;
+    }
     if ((rc = run_linear(e, s, DC_FC2, e->h, f, w.w2, w.b2, e->x, d, Pt, d, f, EPI_BIAS_RESID))) return rc;
   }
-  if ((rc = run_ln(e, s, DC_LNF, e->x, e->lnf_g, e->lnf_b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
   if (hidden_out_dev &&
       (rc = run_ln(e, s, DC_LNF, e->x, e->lnf_g, e->lnf_b, hidden_out_dev, hidden_dtype == WF_DTYPE_BF16, Pt, d, c.ln_eps)))
     return rc;
-  if (logits_out_dev) {
-    hipError_t err = launch_gather_rows(e->u, d_last, e->ulast, B, (int)(d * es), s);
-    if (err != hipSuccess) return fail(WF_E_HIP, "gather launch: %s", hipGetErrorString(err));
-    // (the weight-streaming logits product keeps the 128-wide tile even for a handful of rows: measured 46 us against
-    // 63 us on the small-batch kernel for 64 x 51866 x 1280)
-    {
-      GemmArgs a{};
-      a.A = e->ulast; a.W = e->tok_emb; a.bias = e->zero_bias; a.out = e->lbuf; a.M = B; a.N = e->vpad; a.K = d; a.lda = d; a.ldo = e->vpad;
-      a.prefer_large = 1;
-      if ((rc = run_gemm(e, s, DC_LOGITS, a, A_PLAIN, EPI_BIAS_F32, d, 4, B, d))) return rc;
-      WF_HIP_TRY(hipMemcpy2DAsync(logits_out_dev, (size_t)c.n_vocab * 4, e->lbuf, (size_t)e->vpad * 4, (size_t)c.n_vocab * 4, B,
-                                  hipMemcpyDeviceToDevice, s));
-    }
+  if (logits_out_dev) {     // the final LayerNorm of every stream's last prompt position, then its product with the embedding
+    if ((rc = run_ln(e, s, DC_LNF, e->x, e->lnf_g, e->lnf_b, e->ulast, act_bf16, B, d, c.ln_eps, d_last))) return rc;
+    GemmArgs a{};
+    a.A = e->ulast; a.W = e->tok_emb; a.bias = e->zero_bias; a.out = logits_out_dev; a.M = B; a.N = e->vpad; a.K = d; a.lda = d;
+    a.ldo = c.n_vocab; a.n_valid = c.n_vocab;
+    a.prefer_large = 1;
+    if ((rc = run_gemm(e, s, DC_LOGITS, a, A_PLAIN, EPI_BIAS_F32, d, 4, B, d))) return rc;
   }
   return WF_OK;
 }

@@ -720,7 +720,7 @@ int wf_op_layernorm(const float *x_dev, const float *g_dev, const float *b_dev, 
                     int32_t d, float eps, void *hip_stream) {
   if (!x_dev || !g_dev || !b_dev || !out_dev) return fail(WF_E_INVALID_ARG, "NULL pointer");
   if (M < 1 || d < 4 || d % 4 || d > 2048) return fail(WF_E_INVALID_ARG, "need M >= 1, d %% 4 == 0, d <= 2048");
-  hipError_t err = launch_layernorm(x_dev, g_dev, b_dev, out_dev, out_dtype == WF_DTYPE_BF16, M, d, eps, (hipStream_t)hip_stream);
+  hipError_t err = launch_layernorm(x_dev, nullptr, g_dev, b_dev, out_dev, out_dtype == WF_DTYPE_BF16, M, d, eps, (hipStream_t)hip_stream);
   if (err != hipSuccess) return fail(WF_E_HIP, "layernorm launch: %s", hipGetErrorString(err));
   return WF_OK;
 }

@@ -395,7 +395,8 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   // after the third tap): the pipelined kernel.  It adds a row up in the same order as the kernels below, so the choice
   // may depend on the number of rows (a batch cut into lanes gives the bits of the whole batch).
   const bool whole_taps = amode == A_PLAIN || (a.C % BK == 0 && 3 * a.C == a.K && !a.w_panels);
-  if (epi != EPI_BIAS_F32 && (!whole_taps || gemm_pipe_applies(a.M, a.N, a.K))) return launch_gemm_pipe(a, amode, epi, s);
+  if (epi == EPI_BIAS_F32 ? gemm_pipe_logits_applies(a.M, a.N) : !whole_taps || gemm_pipe_applies(a.M, a.N, a.K))
+    return launch_gemm_pipe(a, amode, epi, s);
   const bool big = use_large_tile(a);
   if (amode == A_PLAIN) {
     // streaming stores for bf16 results no cache level could hand on whole (threshold: twice the 32 MB of L2)

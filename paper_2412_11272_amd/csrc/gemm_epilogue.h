@@ -126,7 +126,14 @@ __device__ __forceinline__ void store_subtile(const GemmArgs &p, unsigned char *
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] += res[ps & 1][it][e];
         }
-        if (m < p.M) *(f32x4 *)((float *)p.out + (size_t)m * p.ldo + nw0 + ps % NPC * PW + c * 4) = v;
+        const int n = nw0 + ps % NPC * PW + c * 4;
+        if (EPI == EPI_BIAS_F32 && p.n_valid > 0) {      // rows of odd length: single words
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (m < p.M && n + e < p.n_valid) ((float *)p.out)[(size_t)m * p.ldo + n + e] = v[e];
+        } else if (m < p.M) {
+          *(f32x4 *)((float *)p.out + (size_t)m * p.ldo + n) = v;
+        }
       }
       __builtin_amdgcn_s_waitcnt(0xC07F);          // reads done before the next pass overwrites the slice
     }

@@ -242,8 +242,6 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += x[e];
       *o = v;
-    } else if constexpr (EPI == EPI_BIAS_F32) {
-      *(f32x4 *)((float *)p.out + (size_t)m * p.ldo + nn) = v;
     } else {
       const f32x4 pe = *(const f32x4 *)(p.pos + (size_t)prow * p.N + nn);
 #pragma unroll
@@ -286,7 +284,6 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
       case EPI_BIAS: return launch_small<A_PLAIN, EPI_BIAS>(a, s);
       case EPI_BIAS_GELU: return launch_small<A_PLAIN, EPI_BIAS_GELU>(a, s);
       case EPI_BIAS_RESID: return launch_small<A_PLAIN, EPI_BIAS_RESID>(a, s);
-      case EPI_BIAS_F32: return launch_small<A_PLAIN, EPI_BIAS_F32>(a, s);
       default: return hipErrorInvalidValue;
     }
   }

@@ -229,9 +229,9 @@ inline int run_linear(DevCtx *e, hipStream_t s, int cls, const void *A, int lda,
 }
 
 inline int run_ln(DevCtx *e, hipStream_t s, int cls, const float *x, const float *g, const float *b, void *out, int out_bf16,
-                  int M, int d, float eps) {
+                  int M, int d, float eps, const int32_t *rows = nullptr) {
   Scope sc(e, s, cls, 0.0, (double)M * d * (4 + (out_bf16 ? 2 : 4)));
-  hipError_t err = launch_layernorm(x, g, b, out, out_bf16, M, d, eps, s);
+  hipError_t err = launch_layernorm(x, rows, g, b, out, out_bf16, M, d, eps, s);
   if (err != hipSuccess) return fail(WF_E_HIP, "%s launch: %s", e->class_names[cls], hipGetErrorString(err));
   return WF_OK;
 }

@@ -57,6 +57,9 @@ struct GemmArgs {
   // of out, starting at its column 0 -- one product feeding two buffers (queries | keys and values).  n_split % 8 == 0.
   void *out2;
   int32_t n_split, ldo2;
+  // EPI_BIAS_F32 only: columns [n_valid, N) of the result are not stored (the weight rows that pad a vocabulary to whole
+  // tiles), ldo = n_valid may be odd; 0: all columns, ldo a multiple of 4
+  int32_t n_valid;
   int32_t prefer_large;     // never the small-batch kernel (a product that streams a huge weight matrix, a wide model)
   int32_t prefer_small;     // run on the small-batch kernel even if M is above its usual limit (the first convolution
                             // of a small batch has twice as many rows as the batch has tokens)
@@ -96,16 +99,16 @@ bool gemm_small_applies(int32_t M, int32_t N, int32_t K);
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 // products with at most one tile per compute unit, and convolutions whose taps are no whole K steps
 bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K);
+bool gemm_pipe_logits_applies(int32_t M, int32_t N);      // EPI_BIAS_F32
 hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s);
-hipError_t launch_layernorm(const float *x, const float *g, const float *b, void *out, int out_bf16,
+// out[i] = LayerNorm(x[rows[i]]), rows == NULL: x[i]
+hipError_t launch_layernorm(const float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
                             int32_t M, int32_t d, float eps, hipStream_t s);
 hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s);
 // x[r, :] = table[tok[r], :] + pos[pos_idx[r], :]  (fp32 out; table bf16 or fp32, pos fp32)
 hipError_t launch_embed(const void *table, int table_bf16, const float *pos, const int32_t *tok, const int32_t *pos_idx,
                         float *x, int32_t rows, int32_t d, hipStream_t s);
-// dst[i, :] = src[row[i], :] for rows of row_bytes bytes (multiple of 16)
-hipError_t launch_gather_rows(const void *src, const int32_t *row, void *dst, int32_t n, int32_t row_bytes, hipStream_t s);
 int attention_q_tile();     // query rows per attention work item
 int gemm_dl_tile_map(int32_t M, int32_t N, int32_t bm, int32_t bn, int32_t *units, int32_t cap);   // diagnostic, host only
 void gemm_tile_choice(int32_t M, int32_t N, int32_t *bm, int32_t *bn);                                                  // diagnostic, host only

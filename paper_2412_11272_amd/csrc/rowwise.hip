@@ -54,26 +54,33 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
 
 // ---------------------------------------------------------------------------------------------
 // LayerNorm: one wave per row, the row lives in registers between the two statistics passes
-// (mean, then centred variance -- the biased one), fp32 statistics.
-template <typename TOUT, int MAXV>   // MAXV float4 per lane: d <= 256 * MAXV
-__global__ void __launch_bounds__(256) layernorm_kernel(const float *__restrict__ x, const float *__restrict__ g,
-                                                        const float *__restrict__ b, TOUT *__restrict__ out,
-                                                        int M, int d, float eps) {
+// (mean, then centred variance -- the biased one), fp32 statistics.  rows: out[i] = LayerNorm(x[rows[i]]) (NULL: x[i]).
+// EARLY: gain and shift are requested together with the row.  For a few hundred rows a call is one chain of latencies, and
+// loading them after the statistics puts a second memory latency into it (425 x 1280: 6.2 -> 5.4 us); once the chip is full
+// the registers they occupy cost more (6361 x 1280: 12.6 us late, 17.3 early).
+template <typename TOUT, int MAXV, bool EARLY>   // MAXV float4 per lane: d <= 256 * MAXV
+__global__ void __launch_bounds__(256) layernorm_kernel(const float *__restrict__ x, const int32_t *__restrict__ rows,
+                                                        const float *__restrict__ g, const float *__restrict__ b,
+                                                        TOUT *__restrict__ out, int M, int d, float eps) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
   const int lane = threadIdx.x & 63;
   const int nv = d >> 2;                               // float4 per row
-  const f32x4 *xr = (const f32x4 *)(x + (size_t)row * d);
-  f32x4 v[MAXV];
-  float sum = 0.0f;
+  const f32x4 *xr = (const f32x4 *)(x + (size_t)(rows ? rows[row] : row) * d);
+  const f32x4 *gr = (const f32x4 *)g, *br = (const f32x4 *)b;
+  f32x4 v[MAXV], gg[EARLY ? MAXV : 1], bb[EARLY ? MAXV : 1];
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
     const int idx = lane + i * 64;
     if (idx < nv) {
       v[i] = xr[idx];
-      sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
+      if constexpr (EARLY) { gg[i] = gr[idx]; bb[i] = br[idx]; }
     }
   }
+  float sum = 0.0f;
+#pragma unroll
+  for (int i = 0; i < MAXV; ++i)
+    if (lane + i * 64 < nv) sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
   const float mu = sum / (float)d;
@@ -89,15 +96,15 @@ __global__ void __launch_bounds__(256) layernorm_kernel(const float *__restrict_
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
   const float rstd = rsqrtf(sq / (float)d + eps);
-  const f32x4 *gr = (const f32x4 *)g, *br = (const f32x4 *)b;
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
     const int idx = lane + i * 64;
     if (idx < nv) {
-      const f32x4 gg = gr[idx], bb = br[idx];
-      f32x4 y;
+      f32x4 gi, bi, y;
+      if constexpr (EARLY) { gi = gg[i]; bi = bb[i]; }
+      else { gi = gr[idx]; bi = br[idx]; }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) y[e] = (v[i][e] - mu) * rstd * gg[e] + bb[e];
+      for (int e = 0; e < 4; ++e) y[e] = (v[i][e] - mu) * rstd * gi[e] + bi[e];
       if constexpr (sizeof(TOUT) == 2) {
         *(bf16x4 *)((__bf16 *)out + (size_t)row * d + idx * 4) = to_bf16x4(y);
       } else {
@@ -125,16 +132,6 @@ __global__ void __launch_bounds__(256) embed_kernel(const TTAB *__restrict__ tab
   *(f32x4 *)(x + (size_t)r * d + c) = v;
 }
 
-// dst[i, :] = src[row[i], :], 16 bytes per thread.
-__global__ void __launch_bounds__(256) gather_rows_kernel(const unsigned char *__restrict__ src, const int32_t *__restrict__ row,
-                                                          unsigned char *__restrict__ dst, int n, int row_bytes) {
-  const int cpr = row_bytes >> 4;
-  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long)n * cpr) return;
-  const int i = (int)(gid / cpr), c = (int)(gid % cpr);
-  *(f32x4 *)(dst + (size_t)i * row_bytes + c * 16) = *(const f32x4 *)(src + (size_t)row[i] * row_bytes + c * 16);
-}
-
 }  // namespace
 
 hipError_t launch_embed(const void *table, int table_bf16, const float *pos, const int32_t *tok, const int32_t *pos_idx,
@@ -148,30 +145,23 @@ hipError_t launch_embed(const void *table, int table_bf16, const float *pos, con
   return hipGetLastError();
 }
 
-hipError_t launch_gather_rows(const void *src, const int32_t *row, void *dst, int32_t n, int32_t row_bytes, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  if (row_bytes % 16 != 0) return hipErrorInvalidValue;
-  const long t = (long)n * (row_bytes / 16);
-  hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((t + 255) / 256)), dim3(256), 0, s, (const unsigned char *)src, row,
-                     (unsigned char *)dst, n, row_bytes);
-  return hipGetLastError();
-}
-
-hipError_t launch_layernorm(const float *x, const float *g, const float *b, void *out, int out_bf16,
+hipError_t launch_layernorm(const float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
                             int32_t M, int32_t d, float eps, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (d % 4 != 0 || d > 256 * 8) return hipErrorInvalidValue;
   const dim3 grid((M + 3) / 4), block(256);
-  if (d <= 256 * 2) {
-    if (out_bf16) hipLaunchKernelGGL((layernorm_kernel<__bf16, 2>), grid, block, 0, s, x, g, b, (__bf16 *)out, M, d, eps);
-    else hipLaunchKernelGGL((layernorm_kernel<float, 2>), grid, block, 0, s, x, g, b, (float *)out, M, d, eps);
-  } else if (d <= 256 * 5) {
-    if (out_bf16) hipLaunchKernelGGL((layernorm_kernel<__bf16, 5>), grid, block, 0, s, x, g, b, (__bf16 *)out, M, d, eps);
-    else hipLaunchKernelGGL((layernorm_kernel<float, 5>), grid, block, 0, s, x, g, b, (float *)out, M, d, eps);
-  } else {
-    if (out_bf16) hipLaunchKernelGGL((layernorm_kernel<__bf16, 8>), grid, block, 0, s, x, g, b, (__bf16 *)out, M, d, eps);
-    else hipLaunchKernelGGL((layernorm_kernel<float, 8>), grid, block, 0, s, x, g, b, (float *)out, M, d, eps);
-  }
+  const bool early = M <= 2048;        // two workgroups per compute unit
+#define WF_LN1(T, V, E) hipLaunchKernelGGL((layernorm_kernel<T, V, E>), grid, block, 0, s, x, rows, g, b, (T *)out, M, d, eps)
+#define WF_LN(V)                                                                           \
+  do {                                                                                     \
+    if (out_bf16) { if (early) WF_LN1(__bf16, V, true); else WF_LN1(__bf16, V, false); }   \
+    else { if (early) WF_LN1(float, V, true); else WF_LN1(float, V, false); }              \
+  } while (0)
+  if (d <= 256 * 2) WF_LN(2);
+  else if (d <= 256 * 5) WF_LN(5);
+  else WF_LN(8);
+#undef WF_LN
+#undef WF_LN1
   return hipGetLastError();
 }
 
