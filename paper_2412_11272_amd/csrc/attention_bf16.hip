@@ -55,10 +55,11 @@ __device__ __forceinline__ int v_swizzle(int r) {
   return ((q & 1) << 2) | (q >> 1);
 }
 
-template <bool CAUSAL>
-__global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char sK[2][BKV * 128];
-  __shared__ __attribute__((aligned(1024))) unsigned char sV[2][BKV * 128];
+// KS: number of four-wave groups that share the keys of a work item (group g walks the tiles g, g + KS, ...; the partial
+// results meet in LDS at the end).  launch_attention_bf16 says when it is 2.
+template <bool CAUSAL, int KS>
+__global__ void __launch_bounds__(256 * KS, KS > 1 ? 4 : 1) attention_bf16_kernel(AttnArgs p) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_att[];   // per key group: K[2][8 KB], V[2][8 KB]
 
   // The grid has the head count rounded up to a multiple of 8.  Consecutive workgroups go to the 8 XCDs in
   // turn, so slot s of every work item lands on XCD s % 8; slot s holds head (s - rot) mod heads8, with rot
@@ -80,7 +81,9 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int gwave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = gwave & 3, kg = KS > 1 ? gwave >> 2 : 0;    // wave inside its key group, key group
+  unsigned char *const sK = smem_att + kg * 32768, *const sV = sK + 16384;
   const int l32 = lane & 31, lg = lane >> 5;
   const int ldq = p.ldq, ld = p.ldkv;
   const __bf16 *Qb = (const __bf16 *)p.q + (size_t)tok0 * ldq + head * 64;
@@ -110,8 +113,7 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
 
   // Tile loads: 16 instructions of 8 rows per tile (8 for K, 8 for V), 4 per wave.
   const int lrow = lane >> 3;
-  auto issue = [&](int kt) {
-    const int buf = kt & 1;
+  auto issue = [&](int kt, int buf) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int g = i * 4 + wave;                       // 0..7: K row group, 8..15: V row group
@@ -120,7 +122,7 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
       key = key < L ? key : L - 1;                      // clamped rows are masked out of the softmax below
       const int lch = (lane & 7) ^ (g < 8 ? (rt >> 1) & 7 : v_swizzle(rt));
       const __bf16 *src = (g < 8 ? Kb : Vb) + (size_t)key * ld + lch * 8;
-      unsigned char *dst = (g < 8 ? sK[buf] : sV[buf]) + (g & 7) * 1024;
+      unsigned char *dst = (g < 8 ? sK : sV) + buf * 8192 + (g & 7) * 1024;
       __builtin_amdgcn_global_load_lds((const glb_void *)src, (lds_void *)dst, 16, 0, 0);
     }
   };
@@ -132,15 +134,17 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
 
   const int k_end = CAUSAL ? min(L, q0 + BQ) : L;          // keys this work item can see at all
   const int n_tiles = (k_end + BKV - 1) / BKV;
-  issue(0);
-  for (int kt = 0; kt < n_tiles; ++kt) {
+  if (KS == 1 || kg < n_tiles) issue(kg, 0);
+  for (int it = 0; it * KS < n_tiles; ++it) {   // every group makes the same number of turns (they share the barriers)
+    const int kt = it * KS + kg;
     const int key0 = kt * BKV;
     __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0): my share of tile kt has landed
     __builtin_amdgcn_s_barrier();               // everyone's has; the other buffer is no longer being read
-    if (kt + 1 < n_tiles) issue(kt + 1);
+    if (kt + KS < n_tiles) issue(kt + KS, (it + 1) & 1);
     if (!wave_active) continue;
+    if (KS > 1 && kt >= n_tiles) continue;
     if (CAUSAL && key0 > qw0 + 31) continue;
-    const unsigned char *cK = sK[kt & 1], *cV = sV[kt & 1];
+    const unsigned char *cK = sK + (it & 1) * 8192, *cV = sV + (it & 1) * 8192;
 
     // ---- S^T = K Q^T : two 32-key blocks, reduction over the 64 features in 4 steps
     f32x16 s[2];
@@ -193,7 +197,8 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
         for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
       m_run = m_new;
     }
-    const float mc = m_run * c;
+    // (a later group's first tile may hold nothing but -inf logits: its weights are 0, not NaN)
+    const float mc = KS > 1 && m_run == -INFINITY ? 0.0f : m_run * c;
     float psum = 0.0f;
     bf16x8 pf[2][2];
 #pragma unroll
@@ -235,21 +240,77 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
     }
   }
 
-  if (!wave_active) return;
+  if (KS == 1 && !wave_active) return;
   const float l_tot = l_run + __shfl_xor(l_run, 32);
-  const float inv = 1.0f / l_tot;
-  if (q_valid) {
-    __bf16 *orow = (__bf16 *)p.out + (size_t)(tok0 + qrow) * p.d_model + head * 64;
+  __bf16 *orow = (__bf16 *)p.out + (size_t)(tok0 + qrow) * p.d_model + head * 64;
+  if constexpr (KS == 1) {
+    const float inv = 1.0f / l_tot;
+    if (q_valid) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = o[t][g * 4 + e] * inv;
+          *(bf16x4 *)(orow + t * 32 + g * 8 + lg * 4) = to_bf16x4(v);
+        }
+    }
+  } else {
+    // Merge: the partial outputs (8 four-feature pieces a lane) are laid over the tile buffers, reference and sum behind
+    // them; group g then rescales and adds the pieces 8 g / KS .. in group order (deterministic) and stores them.
+    f32x4 *sO = (f32x4 *)smem_att;                             // [group][wave][piece][lane]
+    float *sML = (float *)(smem_att + KS * 32768);             // [group][wave][2][lane]
+    __syncthreads();                                           // every wave is done with the tiles
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        f32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = o[t][g * 4 + e] * inv;
-        *(bf16x4 *)(orow + t * 32 + g * 8 + lg * 4) = to_bf16x4(v);
+        const f32x4 v = {o[t][g * 4], o[t][g * 4 + 1], o[t][g * 4 + 2], o[t][g * 4 + 3]};
+        sO[(gwave * 8 + t * 4 + g) * 64 + lane] = v;
       }
+    sML[gwave * 128 + lane] = m_run;
+    sML[gwave * 128 + 64 + lane] = l_tot;
+    __syncthreads();
+    if (!q_valid) return;
+    float M = -INFINITY, sc[KS], l_all = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) M = fmaxf(M, sML[(k * 4 + wave) * 128 + lane]);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      const float mk = sML[(k * 4 + wave) * 128 + lane];
+      sc[k] = mk == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((mk - M) * c);   // 0: a group without a visible key
+      l_all += sML[(k * 4 + wave) * 128 + 64 + lane] * sc[k];
+    }
+    const float inv = 1.0f / l_all;
+#pragma unroll
+    for (int i = 0; i < 8 / KS; ++i) {
+      const int piece = kg * (8 / KS) + i;                     // features 32 (piece / 4) + 8 (piece % 4) + 4 lg
+      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const f32x4 w = sO[((k * 4 + wave) * 8 + piece) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += w[e] * sc[k];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] *= inv;
+      *(bf16x4 *)(orow + (piece >> 2) * 32 + (piece & 3) * 8 + lg * 4) = to_bf16x4(v);
+    }
   }
+}
+
+template <bool CAUSAL, int KS>
+hipError_t launch_keys(const AttnArgs &a, hipStream_t s) {
+  constexpr int smem = KS * 32768 + (KS > 1 ? KS * 2048 : 0);
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [&] {
+    attr_err = hipFuncSetAttribute((const void *)attention_bf16_kernel<CAUSAL, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  hipLaunchKernelGGL((attention_bf16_kernel<CAUSAL, KS>), dim3(a.n_work * ((a.n_heads + 7) & ~7)), dim3(256 * KS), smem, s, a);
+  return hipGetLastError();
 }
 
 
@@ -258,12 +319,14 @@ __global__ void __launch_bounds__(256) attention_bf16_kernel(AttnArgs p) {
 // tokens).  There the kernel's duration is the length of one workgroup's chain of key tiles, so the chain is cut
 // four ways: a workgroup takes 32 queries of one (stream, head) and its four waves walk the key tiles w, w + 4,
 // w + 8, ... each with its own running maximum, sum and output accumulators, reading tiles it loads itself into
-// LDS buffers of its own (no workgroup barrier inside the loop).  At the end the four partial results are rescaled
+// an LDS buffer of its own (no workgroup barrier inside the loop).  One buffer, not two: two take the LDS of a whole
+// compute unit, with one a second workgroup fits and its waves cover the loads (20 heads x 350 tokens 11.2 -> 8.8 us,
+// 6 x 1200 19.4 -> 15.4; within 0.1 us on the smallest calls).  At the end the four partial results are rescaled
 // to the common maximum and added in wave order through LDS (deterministic).  Same arithmetic per tile as
 // attention_bf16_kernel; the grouping of the tiles differs, so results agree to fp32 rounding of the sums, not bit
 // for bit.
 __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_ks[];   // per wave: K[2][8 KB] then V[2][8 KB]
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_ks[];   // per wave: K [8 KB], V [8 KB]
 
   const int heads8 = (p.n_heads + 7) & ~7;
   const int unit = blockIdx.x / heads8;               // (work item, quarter of its 128 queries)
@@ -288,7 +351,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   const __bf16 *Qb = (const __bf16 *)p.q + (size_t)tok0 * ldq + head * 64;
   const __bf16 *Kb = (const __bf16 *)p.k + (size_t)ktok0 * ld + head * 64;
   const __bf16 *Vb = (const __bf16 *)p.v + (size_t)ktok0 * ld + head * 64;
-  unsigned char *myK = smem_ks + wave * 32768, *myV = myK + 16384;
+  unsigned char *myK = smem_ks + wave * 16384, *myV = myK + 8192;
 
   int qrow = q0 + l32;
   const bool q_valid = qrow < Lq;
@@ -307,7 +370,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
 
   // one wave loads a whole tile: 8 instructions of 8 rows for K, 8 for V
   const int lrow = lane >> 3;
-  auto issue = [&](int kt, int buf) {
+  auto issue = [&](int kt) {
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
       const int rt = g * 8 + lrow;
@@ -315,8 +378,8 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
       key = key < L ? key : L - 1;
       const __bf16 *srck = Kb + (size_t)key * ld + ((lane & 7) ^ ((rt >> 1) & 7)) * 8;
       const __bf16 *srcv = Vb + (size_t)key * ld + ((lane & 7) ^ v_swizzle(rt)) * 8;
-      __builtin_amdgcn_global_load_lds((const glb_void *)srck, (lds_void *)(myK + buf * 8192 + g * 1024), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const glb_void *)srcv, (lds_void *)(myV + buf * 8192 + g * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const glb_void *)srck, (lds_void *)(myK + g * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const glb_void *)srcv, (lds_void *)(myV + g * 1024), 16, 0, 0);
     }
   };
   const int r16 = lane & 15;
@@ -324,13 +387,11 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   const int tr_feat = ((lane >> 4) & 1) * 16 + (r16 & 3) * 4;
 
   const int n_tiles = (L + BKV - 1) / BKV;
-  int buf = 0;
-  if (wave < n_tiles) issue(wave, 0);
-  for (int kt = wave; kt < n_tiles; kt += 4, buf ^= 1) {
+  if (wave < n_tiles) issue(wave);
+  for (int kt = wave; kt < n_tiles; kt += 4) {
     const int key0 = kt * BKV;
     __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0): this wave's tile kt has landed (nobody else touches these buffers)
-    if (kt + 4 < n_tiles) issue(kt + 4, buf ^ 1);
-    const unsigned char *cK = myK + buf * 8192, *cV = myV + buf * 8192;
+    const unsigned char *cK = myK, *cV = myV;
     f32x16 s[2];
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2) {
@@ -358,7 +419,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[kb2][r]);
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-    const float m_new = fmaxf(m_run, tmax);       // finite: every tile has at least one valid key
+    const float m_new = fmaxf(m_run, tmax);
     if (__any(m_new > m_run)) {
       const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
       l_run *= alpha;
@@ -368,7 +429,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
         for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
       m_run = m_new;
     }
-    const float mc = m_run * c;
+    const float mc = m_run == -INFINITY ? 0.0f : m_run * c;   // a tile of -inf logits in front of others weighs 0, not NaN
     float psum = 0.0f;
     bf16x8 pf[2][2];
 #pragma unroll
@@ -402,6 +463,13 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
           const bf16x8 vf = __builtin_shufflevector(w0, w1b, 0, 1, 2, 3, 4, 5, 6, 7);
           o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[kb2][h], o[t], 0, 0, 0);
         }
+    }
+    if (kt + 4 < n_tiles) {
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): the tile has been read, its buffer may be refilled
+      __builtin_amdgcn_sched_barrier(0);
+      issue(kt + 4);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
@@ -453,33 +521,45 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   }
 }
 
+hipError_t launch_keysplit(const AttnArgs &a, hipStream_t s) {
+  constexpr int smem = 4 * 16384;
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [&] {
+    attr_err = hipFuncSetAttribute((const void *)attention_bf16_keysplit_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  hipLaunchKernelGGL(attention_bf16_keysplit_kernel, dim3(4 * a.n_work * ((a.n_heads + 7) & ~7)), dim3(256), smem, s, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 int attention_q_tile() { return BQ; }
 
+// Calls that leave the chip short of waves last as long as one workgroup's walk over the key tiles (1.05 us a tile), so the
+// keys are shared out when there are at least three tiles to share (192 keys: 12 heads x 6 streams x 160 keys lose 1.3 to
+// 2.4 us, 16 x 4 x 200 gain 0.2):
+//   * 32-query workgroups with the keys cut four ways while they fit the chip at two per compute unit (20 heads x 425 tokens
+//     11.3 -> 9.3 us, 16 x 1000 20.8 -> 14.4, 8 x 1525 27.9 -> 17.8; 20 x 900 = 580 workgroups 16.4 -> 19.2), and whatever
+//     the number of keys while they fit at one per CU (6 heads x 75 tokens 5.8 -> 5.4);
+//   * else 128-query work items with two key groups while there is at most one per CU (20 x 900 19.9 -> 16.4, 12 x 1500
+//     28.8 -> 22.4; with more the one-group form is as fast, from 16 heads x 8 x 325 on 10 % faster).
+// The row counts of the whole batch decide, never those of one lane: a batch cut into lanes gives the same bits.
 hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
   if (a.n_work <= 0) return hipSuccess;
   if (a.d_model != a.n_heads * 64) return hipErrorInvalidValue;
   if (a.ldq % 8 != 0 || a.ldkv % 8 != 0 || !a.q || !a.k || !a.v || !a.cu_q || !a.cu_kv) return hipErrorInvalidValue;
-  const dim3 grid(a.n_work * ((a.n_heads + 7) & ~7));
   if (a.causal) {
     if (a.cu_q != a.cu_kv) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attention_bf16_kernel<true>, grid, dim3(256), 0, s, a);
-  } else if (std::min<long>(4L * a.n_work, a.M / 32 + a.B) * a.n_heads <= 256) {
-    // so few queries that even 32-query workgroups (one per compute unit: they take 128 KB of LDS) fit the chip in one go:
-    // cut the key loop four ways instead.  (8 streams of 325 tokens x 16 heads = 1408 such workgroups ran 12 % slower.)
-    constexpr int smem = 4 * 32768;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] {
-      attr_err = hipFuncSetAttribute((const void *)attention_bf16_keysplit_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    });
-    if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL(attention_bf16_keysplit_kernel, dim3(4 * grid.x), dim3(256), smem, s, a);
-  } else {
-    hipLaunchKernelGGL(attention_bf16_kernel<false>, grid, dim3(256), 0, s, a);
+    return launch_keys<true, 1>(a, s);
   }
-  return hipGetLastError();
+  constexpr long cus = 256;
+  const bool share = (a.Mkv > 0 ? a.Mkv : a.M) >= 192L * a.B;
+  const long blocks32 = std::min<long>(4L * a.n_work, a.M / 32 + a.B) * a.n_heads, blocks128 = ((long)a.M / BQ + a.B) * a.n_heads;
+  if (blocks32 <= cus || (share && blocks32 <= 2 * cus)) return launch_keysplit(a, s);
+  if (share && blocks128 <= cus) return launch_keys<false, 2>(a, s);
+  return launch_keys<false, 1>(a, s);
 }
 
 }  // namespace wf

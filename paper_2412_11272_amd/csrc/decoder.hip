@@ -324,7 +324,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
       AttnArgs a{};
       a.q = e->qbuf; a.ldq = d; a.k = xkv; a.v = xkv + (size_t)d * es; a.ldkv = 2 * d; a.out = e->u;
       a.cu_q = d_cup; a.cu_kv = d_cus; a.work = d_work; a.n_work = n_work; a.n_heads = c.n_heads; a.d_model = d;
-      a.B = B; a.M = Pt; a.causal = 0; a.scale = 0.125f;
+      a.B = B; a.M = Pt; a.Mkv = M; a.causal = 0; a.scale = 0.125f;
       if ((rc = run_attention(e, s, DC_CROSS_ATTN, a, cross_flops, ((double)Pt * 2 + (double)M * 2) * d * es))) return rc;
     }
     if ((rc = run_linear(e, s, DC_CROSS_OUT, e->u, d, w.xwo, w.xbo, e->x, d, Pt, d, d, EPI_BIAS_RESID))) return rc;

@@ -249,3 +249,44 @@ def test_attention(lens, n_heads, sharp, precision):
     assert np.all(np.isfinite(got))
     # bf16: P is rounded to bf16 before the P.V product and the output is bf16
     assert _rel(got, ref) < (1e-2 if precision == wf.WF_PRECISION_BF16 else 1e-5)
+
+
+# The forms that share a query block's keys out: 32-query workgroups beyond one per compute unit (two per CU at most, streams
+# of 192 keys and more on average), then two key groups per 128-query item.  Last tiles of one key, streams of fewer tiles
+# than waves or groups, and the first call past the second form.
+SPLIT_CASES = [([1345], 8), ([321, 63, 385, 129, 1, 257], 8), ([1, 1100], 20), ([641, 65, 1000], 12), ([1025, 64, 193], 20), ([705, 640], 20), ([1409], 20),
+               ([1400, 193], 20)]
+
+
+@pytest.mark.parametrize("lens,n_heads", SPLIT_CASES)
+def test_attention_shared_keys(lens, n_heads):
+    test_attention(lens, n_heads, 6.0, wf.WF_PRECISION_BF16)
+
+
+@pytest.mark.parametrize("lens,n_heads", [([900], 8), ([1000, 300], 12)])
+def test_attention_tile_of_minus_infinity(lens, n_heads):
+    """Keys whose logits overflow to -inf weigh nothing, wherever their tile falls in the split of the keys."""
+    import torch
+    d, M = 64 * n_heads, sum(lens)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rng = np.random.default_rng(M)
+    qkv = rng.standard_normal((M, 3 * d)).astype(np.float32)
+    qkv[:, :d] = np.abs(qkv[:, :d]) + 1.0
+    live = np.ones(M, bool)
+    live[64:192] = False                                     # the first tiles of the second and third wave / the second group
+    qkv[64:192, d:2 * d] = -3e38
+    t = torch.from_numpy(qkv).bfloat16()
+    x = t.float().numpy().astype(np.float64)
+    ref = []
+    for a, b in zip(cu[:-1], cu[1:]):
+        k = np.arange(a, b)[live[a:b]]
+        ref.append(np.concatenate([_softmax(x[a:b, 64 * h:64 * h + 64] @ x[k, d + 64 * h:d + 64 * h + 64].T / 8.0) @
+                                   x[k, 2 * d + 64 * h:2 * d + 64 * h + 64] for h in range(n_heads)], axis=1))
+    out = torch.full((M, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wf.op_attention(wf.WF_PRECISION_BF16, t.cuda(), out, cu, n_heads)
+    assert _rel(out.float().cpu().numpy(), np.concatenate(ref)) < 1e-2
+
+
+def _softmax(s):
+    e = np.exp(s - s.max(axis=1, keepdims=True))
+    return e / e.sum(axis=1, keepdims=True)
