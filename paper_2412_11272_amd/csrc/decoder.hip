@@ -41,6 +41,7 @@ struct wf_decoder : DevCtx {
   std::vector<DecLayerDev> layers;
   // workspace
   float *x = nullptr;
+  float *part = nullptr;            // parts of a residual product whose reduction is cut (kPartialFloats)
   void *u = nullptr, *qbuf = nullptr, *skv = nullptr, *h = nullptr, *ulast = nullptr;
   int32_t *idx_dev = nullptr;
   int64_t idx_ints = 0;
@@ -132,6 +133,7 @@ int dec_create_impl(wf_decoder *e, const wf_decoder_config *cfg, const wf_decode
   }
   const size_t P = cfg->max_prompt_tokens, S = cfg->max_streams;
   if ((rc = dev_alloc(e, (void **)&e->x, P * d * 4))) return rc;
+  if (e->bf16 && (rc = dev_alloc(e, (void **)&e->part, (size_t)kPartialFloats * 4))) return rc;
   if ((rc = dev_alloc(e, &e->u, P * d * e->es))) return rc;
   if ((rc = dev_alloc(e, &e->qbuf, P * d * e->es))) return rc;
   if ((rc = dev_alloc(e, &e->skv, P * 2 * d * e->es))) return rc;
@@ -281,12 +283,18 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
   // A few prompts on a narrow model: the three products that follow a LayerNorm run on the small-batch kernel, which
   // normalises its operand itself (decided by the model's width and the batch, the same for all of them).
   const bool small = e->bf16 && gemm_small_applies(Pt, 3 * d, d) && gemm_small_applies(Pt, f, d);
+  Partials pt{};       // sums of the last residual product that the next LayerNorm takes into x
+  auto resid = [&](int cls, const void *A, int K, const void *W, const float *bias) -> int {
+    GemmArgs a{};
+    a.A = A; a.W = W; a.bias = bias; a.M = Pt; a.N = d; a.K = K; a.lda = K; a.ldo = d;
+    return run_resid(e, s, cls, a, e->x, e->part, e->bf16 && !small && !gemm_small_applies(Pt, d, K), &pt);
+  };
   auto after_ln = [&](int cls, const float *g, const float *b, GemmArgs a, Epilogue ep) -> int {
     int rc;
     if (small) {
       a.A = e->x; a.ln_g = g; a.ln_b = b; a.ln_eps = c.ln_eps;
     } else {
-      if ((rc = run_ln(e, s, DC_LN, e->x, g, b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
+      if ((rc = run_ln(e, s, DC_LN, e->x, g, b, e->u, act_bf16, Pt, d, c.ln_eps, nullptr, &pt))) return rc;
       a.A = e->u;
     }
     a.M = Pt; a.K = d; a.lda = d;
@@ -313,7 +321,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
       a.B = B; a.M = Pt; a.causal = 1; a.scale = 0.125f;
       if ((rc = run_attention(e, s, DC_SELF_ATTN, a, self_flops, (double)Pt * 4 * d * es))) return rc;
     }
-    if ((rc = run_linear(e, s, DC_SELF_OUT, e->u, d, w.wo, w.bo, e->x, d, Pt, d, d, EPI_BIAS_RESID))) return rc;
+    if ((rc = resid(DC_SELF_OUT, e->u, d, w.wo, w.bo))) return rc;
     // cross-attention over the stream's encoder tokens
     {
       GemmArgs a{};
@@ -327,20 +335,20 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
       a.B = B; a.M = Pt; a.Mkv = M; a.causal = 0; a.scale = 0.125f;
       if ((rc = run_attention(e, s, DC_CROSS_ATTN, a, cross_flops, ((double)Pt * 2 + (double)M * 2) * d * es))) return rc;
     }
-    if ((rc = run_linear(e, s, DC_CROSS_OUT, e->u, d, w.xwo, w.xbo, e->x, d, Pt, d, d, EPI_BIAS_RESID))) return rc;
+    if ((rc = resid(DC_CROSS_OUT, e->u, d, w.xwo, w.xbo))) return rc;
     // MLP
     {
       GemmArgs a{};
       a.W = w.w1; a.bias = w.b1; a.out = e->h; a.N = f; a.ldo = f;
       if ((rc = after_ln(DC_FC1, w.ln2_g, w.ln2_b, a, EPI_BIAS_GELU))) return rc;
     }
-    if ((rc = run_linear(e, s, DC_FC2, e->h, f, w.w2, w.b2, e->x, d, Pt, d, f, EPI_BIAS_RESID))) return rc;
+    if ((rc = resid(DC_FC2, e->h, f, w.w2, w.b2))) return rc;
   }
   if (hidden_out_dev &&
-      (rc = run_ln(e, s, DC_LNF, e->x, e->lnf_g, e->lnf_b, hidden_out_dev, hidden_dtype == WF_DTYPE_BF16, Pt, d, c.ln_eps)))
+      (rc = run_ln(e, s, DC_LNF, e->x, e->lnf_g, e->lnf_b, hidden_out_dev, hidden_dtype == WF_DTYPE_BF16, Pt, d, c.ln_eps, nullptr, &pt)))
     return rc;
   if (logits_out_dev) {     // the final LayerNorm of every stream's last prompt position, then its product with the embedding
-    if ((rc = run_ln(e, s, DC_LNF, e->x, e->lnf_g, e->lnf_b, e->ulast, act_bf16, B, d, c.ln_eps, d_last))) return rc;
+    if ((rc = run_ln(e, s, DC_LNF, e->x, e->lnf_g, e->lnf_b, e->ulast, act_bf16, B, d, c.ln_eps, d_last, &pt))) return rc;
     GemmArgs a{};
     a.A = e->ulast; a.W = e->tok_emb; a.bias = e->zero_bias; a.out = logits_out_dev; a.M = B; a.N = e->vpad; a.K = d; a.lda = d;
     a.ldo = c.n_vocab; a.n_valid = c.n_vocab;

@@ -66,6 +66,7 @@ struct wf_encoder : DevCtx {
   // workspace
   void *packed = nullptr, *G = nullptr, *u = nullptr, *qkv = nullptr, *h = nullptr;
   float *x = nullptr;
+  float *part = nullptr;            // parts of a residual product whose reduction is cut (kPartialFloats)
   int32_t *frame_src = nullptr, *frame_flags = nullptr, *tok_src = nullptr, *tok_flags = nullptr, *tok_pos = nullptr;
   int32_t *idx_dev = nullptr;
   int64_t idx_ints = 0;
@@ -281,6 +282,7 @@ static int create_impl(wf_encoder *e, const wf_config *cfg, const wf_weights *w)
   if ((rc = dev_alloc(e, &e->packed, (size_t)F * C * e->es))) return rc;
   if ((rc = dev_alloc(e, &e->G, (size_t)F * d * e->es))) return rc;
   if ((rc = dev_alloc(e, (void **)&e->x, (size_t)Mx * d * 4))) return rc;
+  if (e->bf16 && (rc = dev_alloc(e, (void **)&e->part, (size_t)kPartialFloats * 4))) return rc;
   if ((rc = dev_alloc(e, &e->u, (size_t)Mx * d * e->es))) return rc;
   if ((rc = dev_alloc(e, &e->qkv, (size_t)Mx * 3 * d * e->es))) return rc;
   // the MLP's hidden activations are kept in panel layout on the bf16 path: whole 256-row panels per lane
@@ -439,9 +441,12 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
       const double L = h_cu_seq[i + 1] - h_cu_seq[i];
       attn_flops += 4.0 * L * L * d;
     }
+    // Residual products of a few rows leave partial sums for the LayerNorm after them (one lane only: the memory is shared).
+    const bool may_split = e->bf16 && !small && n_lanes == 1;
+    Partials pt{};
     for (int l = 0; l < c.n_layers; ++l) {
       const LayerDev &w = e->layers[l];
-      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln1_g, w.ln1_b, u, act_bf16, Mg, d, c.ln_eps))) return rc;
+      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln1_g, w.ln1_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt))) return rc;
       {
         GemmArgs a{};
         a.prefer_large = !small; a.A = u; a.W = w.wqkv; a.bias = w.bqkv; a.out = qkv; a.M = Mg; a.N = 3 * d; a.K = d; a.lda = d; a.ldo = 3 * d;
@@ -461,11 +466,11 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
       }
       {
         GemmArgs a{};
-        a.prefer_large = !small; a.A = u; a.W = w.wo; a.bias = w.bo; a.out = x; a.M = Mg; a.N = d; a.K = d; a.lda = d; a.ldo = d;
+        a.prefer_large = !small; a.A = u; a.W = w.wo; a.bias = w.bo; a.M = Mg; a.N = d; a.K = d; a.lda = d; a.ldo = d;
         a.w_panels = panels;
-        if ((rc = run_gemm(e, ls, KC_OUT, a, A_PLAIN, EPI_BIAS_RESID, d, 4, Mg, d))) return rc;
+        if ((rc = run_resid(e, ls, KC_OUT, a, x, e->part, may_split, &pt))) return rc;
       }
-      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln2_g, w.ln2_b, u, act_bf16, Mg, d, c.ln_eps))) return rc;
+      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln2_g, w.ln2_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt))) return rc;
       {   // fc1 writes the hidden activations as [rows/256][f/64][256][64] panels: one contiguous 32 KB block per
           // K step of fc2's activation operand (whose rows would otherwise be 2 f bytes apart in memory)
         GemmArgs a{};
@@ -476,15 +481,15 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
       }
       {
         GemmArgs a{};
-        a.prefer_large = !small; a.A = hbuf; a.W = w.w2; a.bias = w.b2; a.out = x; a.M = Mg; a.N = d; a.K = f; a.lda = f; a.ldo = d;
+        a.prefer_large = !small; a.A = hbuf; a.W = w.w2; a.bias = w.b2; a.M = Mg; a.N = d; a.K = f; a.lda = f; a.ldo = d;
         a.a_panels = hpanels; a.w_panels = panels;
-        if ((rc = run_gemm(e, ls, KC_FC2, a, A_PLAIN, EPI_BIAS_RESID, f, 4, Mg, f))) return rc;
+        if ((rc = run_resid(e, ls, KC_FC2, a, x, e->part, may_split, &pt))) return rc;
       }
     }
     // a9: final LayerNorm straight into the caller's buffer
     char *out = (char *)out_dev + (size_t)r0 * d * (out_dtype == WF_DTYPE_BF16 ? 2 : 4);
     (void)Bg;
-    return run_ln(e, ls, KC_LNF, x, e->lnf_g, e->lnf_b, out, out_dtype == WF_DTYPE_BF16, Mg, d, c.ln_eps);
+    return run_ln(e, ls, KC_LNF, x, e->lnf_g, e->lnf_b, out, out_dtype == WF_DTYPE_BF16, Mg, d, c.ln_eps, nullptr, &pt);
   };
 
   int64_t h_row0[kMaxLanes + 1];                           // every lane's hidden activations start on a panel boundary
@@ -720,7 +725,7 @@ int wf_op_layernorm(const float *x_dev, const float *g_dev, const float *b_dev, 
                     int32_t d, float eps, void *hip_stream) {
   if (!x_dev || !g_dev || !b_dev || !out_dev) return fail(WF_E_INVALID_ARG, "NULL pointer");
   if (M < 1 || d < 4 || d % 4 || d > 2048) return fail(WF_E_INVALID_ARG, "need M >= 1, d %% 4 == 0, d <= 2048");
-  hipError_t err = launch_layernorm(x_dev, nullptr, g_dev, b_dev, out_dev, out_dtype == WF_DTYPE_BF16, M, d, eps, (hipStream_t)hip_stream);
+  hipError_t err = launch_layernorm(const_cast<float *>(x_dev), nullptr, g_dev, b_dev, out_dev, out_dtype == WF_DTYPE_BF16, M, d, eps, (hipStream_t)hip_stream);
   if (err != hipSuccess) return fail(WF_E_HIP, "layernorm launch: %s", hipGetErrorString(err));
   return WF_OK;
 }

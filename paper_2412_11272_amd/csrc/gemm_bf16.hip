@@ -378,7 +378,7 @@ int large_tile_rows(int M, int N) {
 
 hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if ((a.prefer_small || (!a.prefer_large && gemm_small_applies(a.M, a.N, a.K)) || amode == A_LN) && !a.a_panels && !a.out_panels)
+  if (epi != EPI_PARTIAL && (a.prefer_small || (!a.prefer_large && gemm_small_applies(a.M, a.N, a.K)) || amode == A_LN) && !a.a_panels && !a.out_panels)
     return launch_gemm_small(a, amode, epi, s);
   if (amode == A_LN) return hipErrorInvalidValue;      // the fused LayerNorm operand exists in the small-batch kernel only
   if (a.N % 128 != 0 || a.K % BK != 0 || a.K <= 0) return hipErrorInvalidValue;
@@ -395,6 +395,7 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   // after the third tap): the pipelined kernel.  It adds a row up in the same order as the kernels below, so the choice
   // may depend on the number of rows (a batch cut into lanes gives the bits of the whole batch).
   const bool whole_taps = amode == A_PLAIN || (a.C % BK == 0 && 3 * a.C == a.K && !a.w_panels);
+  if (epi == EPI_PARTIAL) return launch_gemm_pipe(a, amode, epi, s);
   if (epi == EPI_BIAS_F32 ? gemm_pipe_logits_applies(a.M, a.N) : !whole_taps || gemm_pipe_applies(a.M, a.N, a.K))
     return launch_gemm_pipe(a, amode, epi, s);
   const bool big = use_large_tile(a);

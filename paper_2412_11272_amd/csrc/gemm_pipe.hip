@@ -81,15 +81,19 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
   const int l16 = lane & 15, lq = lane >> 4, rr = lane >> 3;
 
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = p.N / BN;
-  const int n_tiles = tiles_m * tiles_n, per_xcd = (n_tiles + 7) >> 3;
-  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (tile >= n_tiles || (int)(blockIdx.x >> 3) >= per_xcd) return;
+  const int splits = EPI == EPI_PARTIAL ? p.k_splits : 1;
+  const int n_tiles = tiles_m * tiles_n, n_units = n_tiles * splits, per_xcd = (n_units + 7) >> 3;
+  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (unit >= n_units || (int)(blockIdx.x >> 3) >= per_xcd) return;
+  const int split = EPI == EPI_PARTIAL ? unit / n_tiles : 0, tile = unit - split * n_tiles;    // a split's tiles share operands
   const int G = min(p.group_n, tiles_n), gs = tiles_m * G;
   const int grp = tile / gs, rem = tile - grp * gs, gw = min(G, tiles_n - grp * G);
   const int m0 = rem / gw * BM, n0 = (grp * G + rem % gw) * BN;
 
   // ---- loads: instruction i of this wave fetches rows (4 i + wave) * 8 .. + 7 of the tile
-  const int nk = p.K >> 6;
+  const int nkt = p.K >> 6;                        // K steps of the whole reduction, and [k0, k0 + nk) of this part
+  const int k0 = EPI == EPI_PARTIAL ? nkt * split / splits : 0;
+  const int nk = EPI == EPI_PARTIAL ? nkt * (split + 1) / splits - k0 : nkt;
   const size_t a_bytes = p.a_panels ? (size_t)((p.M + 255) >> 8) * 256 * p.K * 2 : ((size_t)(p.M - 1) * p.lda + p.K) * 2;
   const __amdgpu_buffer_rsrc_t ra =
       __builtin_amdgcn_make_buffer_rsrc((void *)p.A, 0, AMODE == A_CONV3 ? (int)kOutside : (int)a_bytes, 0x00027000);
@@ -104,7 +108,7 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
 #pragma unroll
   for (int i = 0; i < WL; ++i) {
     const int n = n0 + (i * 4 + wave) * 8;
-    wbase[i] = p.w_panels ? (((n >> 8) * nk) << 15) + ((n & 255) << 7) : n * p.K * 2;
+    wbase[i] = (p.w_panels ? (((n >> 8) * nkt) << 15) + ((n & 255) << 7) : n * p.K * 2) + k0 * wstep;
   }
   if constexpr (AMODE == A_CONV3) {
 #pragma unroll
@@ -118,7 +122,7 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       const int r0 = min(m0 + (i * 4 + wave) * 8, (p.M - 1) & ~7);        // a group past the last row repeats the last one
-      abase[i] = p.a_panels ? (((r0 >> 8) * nk) << 15) + ((r0 & 255) << 7) : r0 * p.lda * 2;
+      abase[i] = (p.a_panels ? (((r0 >> 8) * nkt) << 15) + ((r0 & 255) << 7) : r0 * p.lda * 2) + k0 * astep;
     }
   }
   // Loads [first, last) of a refill: the weights of K step kw into ring slot sw_, then the activations of K step kx into
@@ -156,7 +160,8 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
   f32x4 acc[TB][FB];
 #pragma unroll
   for (int j = 0; j < FB; ++j) {
-    const f32x4 b = *(const f32x4 *)(p.bias + n0 + wn * TN + j * 16 + lq * 4);
+    f32x4 b = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (EPI != EPI_PARTIAL) b = *(const f32x4 *)(p.bias + n0 + wn * TN + j * 16 + lq * 4);
 #pragma unroll
     for (int i = 0; i < TB; ++i) acc[i][j] = b;
   }
@@ -234,7 +239,8 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
 
   __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0) lgkmcnt(0)
   __builtin_amdgcn_s_barrier();                    // every wave is done with the stages
-  store_subtile<TM, TN, EPI, false>(p, smem + wave * (TM * 256), acc, m0 + wm * TM, n0 + wn * TN, lane);
+  if constexpr (EPI == EPI_PARTIAL) p.out = (float *)p.out + (size_t)split * p.M * p.N;
+  store_subtile<TM, TN, EPI == EPI_PARTIAL ? (int)EPI_BIAS_F32 : EPI, false>(p, smem + wave * (TM * 256), acc, m0 + wm * TM, n0 + wn * TN, lane);
 #endif
 }
 
@@ -247,7 +253,7 @@ hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem); });
   if (attr_err != hipSuccess) return attr_err;
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = a.N / BN, tiles = tiles_m * tiles_n;
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = a.N / BN, tiles = tiles_m * tiles_n * (EPI == EPI_PARTIAL ? a.k_splits : 1);
   // Tile columns per group: the 32 tiles an XCD works on at a time should form a block of about 5 x 6 tiles, which needs
   // the fewest operand panels in its L2; few rows of tiles need no grouping.
   a.group_n = tiles_m <= 6 ? 1 : tiles_n <= 6 ? tiles_n : tiles_n % 5 == 0 ? 5 : 4;
@@ -269,6 +275,10 @@ hipError_t launch_index(int t, const GemmArgs &a, hipStream_t s) {
     case 3: return launch_tile<128, 64, 6, 6, true, EPI, AMODE>(a, s);
     case 4: return launch_tile<96, 128, 5, 5, true, EPI, AMODE>(a, s);
     case 5: return launch_tile<128, 128, 4, 4, false, EPI, AMODE>(a, s);
+    default: break;
+  }
+  if constexpr (EPI == EPI_PARTIAL) return hipErrorInvalidValue;
+  else switch (t) {
     case 6: return launch_tile<192, 128, 4, 3, false, EPI, AMODE>(a, s);
     case 7: return launch_tile<128, 256, 3, 3, false, EPI, AMODE>(a, s);
     case 8: return launch_tile<160, 256, 3, 3, false, EPI, AMODE>(a, s);
@@ -290,7 +300,37 @@ int pick_tile(int M, int N, int K) {
   return -1;
 }
 
+// A residual product of a few hundred rows is one tile per compute unit at most, on half of them, and lasts as long as a
+// tile's walk over K.  Its reduction is then cut into parts (at most one workgroup per CU in all) that the LayerNorm after
+// it adds up; nothing is launched for that.  The estimate below (us) fits sweeps of every tile and 2 to 4 parts over 75 to
+// 1025 rows of d = 768, 1024, 1280: the K step of the kernel's header, dearer in the two largest tiles, and 1.7 ns per
+// thousand result values and part; an uncut product pays for the residual once as well.  It has to promise 0.7 us.
+// 425 x 1280 x 5120: 23.4 -> 14.2 us (LayerNorm + 0.5), 425 x 1280 x 1280: 10.0 -> 8.8 us.
+struct Split { int tile, parts; };
+Split pick_split(int M, int N, int K) {
+  const int t1 = pick_tile(M, N, K), nk = K >> 6;
+  if (t1 < 0 || t1 > kTile128 || N > 2048) return {t1, 1};      // (the LayerNorm takes rows of up to 2048 values)
+  auto step = [](int t) { return (0.07 + 0.00875 * (kTiles[t].bm + kTiles[t].bn) / 8) * (t < 4 ? 1.0 : t == 4 ? 1.15 : 1.35); };
+  const double part = 1.7e-6 * M * N;
+  Split best{t1, 1};
+  double cost = nk * step(t1) + part + 0.25 - 0.7;
+  for (int t = 0; t <= kTile128; ++t) {
+    if (N % kTiles[t].bn) continue;
+    const long tiles = (long)((M + kTiles[t].bm - 1) / kTiles[t].bm) * (N / kTiles[t].bn);
+    for (int parts = 2; parts <= 4; ++parts) {
+      if (tiles * parts > 256 || nk < 2 * parts || (int64_t)parts * M * N > kPartialFloats) continue;
+      const double c = (nk + parts - 1) / parts * step(t) + parts * part;
+      if (c < cost) { cost = c; best = {t, parts}; }
+    }
+  }
+  return best;
+}
+
 }  // namespace
+
+int gemm_split_choice(int32_t M, int32_t N, int32_t K) {
+  return M > 0 && N % 64 == 0 && K % 64 == 0 ? pick_split(M, N, K).parts : 1;
+}
 
 bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K) { return pick_tile(M, N, K) >= 0; }
 
@@ -302,6 +342,11 @@ hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   if (epi == EPI_BIAS_F32) {
     if (amode != A_PLAIN || !gemm_pipe_logits_applies(a.M, a.N) || a.K % 64 || a.K <= 0) return hipErrorInvalidValue;
     return launch_tile<64, 256, 4, 4, false, EPI_BIAS_F32, A_PLAIN>(a, s);
+  }
+  if (epi == EPI_PARTIAL) {
+    const Split c = pick_split(a.M, a.N, a.K);
+    if (amode != A_PLAIN || a.k_splits != c.parts || c.parts < 2) return hipErrorInvalidValue;
+    return launch_index<EPI_PARTIAL, A_PLAIN>(c.tile, a, s);
   }
   int t = pick_tile(a.M, a.N, a.K);
   if (t < 0) t = kTile128;           // more than one tile per CU: convolutions whose taps are no whole K steps

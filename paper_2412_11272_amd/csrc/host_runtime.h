@@ -228,10 +228,25 @@ inline int run_linear(DevCtx *e, hipStream_t s, int cls, const void *A, int lda,
   return run_gemm(e, s, cls, a, A_PLAIN, ep, K, out_bytes, M, K);
 }
 
-inline int run_ln(DevCtx *e, hipStream_t s, int cls, const float *x, const float *g, const float *b, void *out, int out_bf16,
-                  int M, int d, float eps, const int32_t *rows = nullptr) {
-  Scope sc(e, s, cls, 0.0, (double)M * d * (4 + (out_bf16 ? 2 : 4)));
-  hipError_t err = launch_layernorm(x, rows, g, b, out, out_bf16, M, d, eps, s);
+// x += A W^T + b, or, where cutting the reduction pays, the parts of that sum in `part` (kPartialFloats floats) for the
+// run_ln that has to follow (may_split).
+inline int run_resid(DevCtx *e, hipStream_t s, int cls, GemmArgs a, float *x, float *part, bool may_split, Partials *pt) {
+  a.out = x;
+  const int n = may_split && part ? gemm_split_choice(a.M, a.N, a.K) : 1;
+  if (n > 1) {
+    a.out = part; a.ldo = a.N; a.k_splits = n;
+    *pt = Partials{part, a.bias, n, a.M};
+  }
+  return run_gemm(e, s, cls, a, A_PLAIN, n > 1 ? EPI_PARTIAL : EPI_BIAS_RESID, a.K, 4 * n, a.M, a.K);
+}
+
+// pt: parts left by run_resid, taken into x here (and cleared).
+inline int run_ln(DevCtx *e, hipStream_t s, int cls, float *x, const float *g, const float *b, void *out, int out_bf16,
+                  int M, int d, float eps, const int32_t *rows = nullptr, Partials *pt = nullptr) {
+  const Partials p = pt ? *pt : Partials{};
+  if (pt && !rows) *pt = Partials{};
+  Scope sc(e, s, cls, 0.0, (double)M * d * (4 + (out_bf16 ? 2 : 4) + (p.n ? 4 * p.n + 4 : 0)));
+  hipError_t err = launch_layernorm(x, rows, g, b, out, out_bf16, M, d, eps, s, p);
   if (err != hipSuccess) return fail(WF_E_HIP, "%s launch: %s", e->class_names[cls], hipGetErrorString(err));
   return WF_OK;
 }

@@ -26,6 +26,8 @@ enum Epilogue : int {
   EPI_BIAS_RESID = 2,      // out(fp32) += acc + bias, in place         (out-projection, fc2)
   EPI_BIAS_GELU_POS = 3,   // out(fp32) = GELU(acc + bias) + pos[row_pos[r]]   (second convolution)
   EPI_BIAS_F32 = 4,        // out(fp32) = acc + bias                    (logits)
+  EPI_PARTIAL = 5,         // out(fp32)[s][M][N] = acc of the s-th of k_splits parts of the reduction; the LayerNorm that
+                           // follows adds the parts and the bias to the residual stream
 };
 
 struct GemmArgs {
@@ -60,6 +62,7 @@ struct GemmArgs {
   // EPI_BIAS_F32 only: columns [n_valid, N) of the result are not stored (the weight rows that pad a vocabulary to whole
   // tiles), ldo = n_valid may be odd; 0: all columns, ldo a multiple of 4
   int32_t n_valid;
+  int32_t k_splits;         // EPI_PARTIAL only
   int32_t prefer_large;     // never the small-batch kernel (a product that streams a huge weight matrix, a wide model)
   int32_t prefer_small;     // run on the small-batch kernel even if M is above its usual limit (the first convolution
                             // of a small batch has twice as many rows as the batch has tokens)
@@ -102,10 +105,19 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
 bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K);
 bool gemm_pipe_logits_applies(int32_t M, int32_t N);      // EPI_BIAS_F32
 hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
+// Parts the reduction of a residual product should be cut into (1: none); k_splits * M * N <= kPartialFloats
+constexpr int64_t kPartialFloats = 256L * 128 * 128;
+int gemm_split_choice(int32_t M, int32_t N, int32_t K);
 hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s);
-// out[i] = LayerNorm(x[rows[i]]), rows == NULL: x[i]
-hipError_t launch_layernorm(const float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
-                            int32_t M, int32_t d, float eps, hipStream_t s);
+// Parts of the residual product in front of a LayerNorm (EPI_PARTIAL): x += part[0] + .. + part[n - 1] + bias first
+struct Partials {
+  const float *part;        // [n][M][d]
+  const float *bias;        // [d]
+  int32_t n, M;             // n = 0: none
+};
+// out[i] = LayerNorm(x[rows[i]]), rows == NULL: x[i].  x is written only with partials and without rows.
+hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
+                            int32_t M, int32_t d, float eps, hipStream_t s, Partials pt = {});
 hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s);
 // x[r, :] = table[tok[r], :] + pos[pos_idx[r], :]  (fp32 out; table bf16 or fp32, pos fp32)
 hipError_t launch_embed(const void *table, int table_bf16, const float *pos, const int32_t *tok, const int32_t *pos_idx,

@@ -58,15 +58,18 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
 // EARLY: gain and shift are requested together with the row.  For a few hundred rows a call is one chain of latencies, and
 // loading them after the statistics puts a second memory latency into it (425 x 1280: 6.2 -> 5.4 us); once the chip is full
 // the registers they occupy cost more (6361 x 1280: 12.6 us late, 17.3 early).
-template <typename TOUT, int MAXV, bool EARLY>   // MAXV float4 per lane: d <= 256 * MAXV
-__global__ void __launch_bounds__(256) layernorm_kernel(const float *__restrict__ x, const int32_t *__restrict__ rows,
+// NP > 0: the residual product in front left its result as NP partial sums; they and its bias are added to the row first
+// (part after part: deterministic) and the new row is stored.
+template <typename TOUT, int MAXV, bool EARLY, int NP = 0>   // MAXV float4 per lane: d <= 256 * MAXV
+__global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, const int32_t *__restrict__ rows,
                                                         const float *__restrict__ g, const float *__restrict__ b,
-                                                        TOUT *__restrict__ out, int M, int d, float eps) {
+                                                        TOUT *__restrict__ out, int M, int d, float eps, Partials pt) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
   const int lane = threadIdx.x & 63;
   const int nv = d >> 2;                               // float4 per row
-  const f32x4 *xr = (const f32x4 *)(x + (size_t)(rows ? rows[row] : row) * d);
+  const int xrow = rows ? rows[row] : row;
+  f32x4 *xr = (f32x4 *)(x + (size_t)xrow * d);
   const f32x4 *gr = (const f32x4 *)g, *br = (const f32x4 *)b;
   f32x4 v[MAXV], gg[EARLY ? MAXV : 1], bb[EARLY ? MAXV : 1];
 #pragma unroll
@@ -75,6 +78,32 @@ __global__ void __launch_bounds__(256) layernorm_kernel(const float *__restrict_
     if (idx < nv) {
       v[i] = xr[idx];
       if constexpr (EARLY) { gg[i] = gr[idx]; bb[i] = br[idx]; }
+    }
+  }
+  if constexpr (NP > 0) {
+    f32x4 w[NP][MAXV], wb[MAXV];
+#pragma unroll
+    for (int i = 0; i < MAXV; ++i) {
+      const int idx = lane + i * 64;
+      if (idx < nv) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) w[k][i] = ((const f32x4 *)(pt.part + ((size_t)k * pt.M + xrow) * d))[idx];
+        wb[i] = ((const f32x4 *)pt.bias)[idx];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < MAXV; ++i) {
+      const int idx = lane + i * 64;
+      if (idx < nv) {
+        f32x4 t = wb[i];
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[e] += w[k][i][e];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i][e] += t[e];
+        if (!rows) xr[idx] = v[i];
+      }
     }
   }
   float sum = 0.0f;
@@ -145,23 +174,32 @@ hipError_t launch_embed(const void *table, int table_bf16, const float *pos, con
   return hipGetLastError();
 }
 
-hipError_t launch_layernorm(const float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
-                            int32_t M, int32_t d, float eps, hipStream_t s) {
+hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
+                            int32_t M, int32_t d, float eps, hipStream_t s, Partials pt) {
   if (M <= 0) return hipSuccess;
+  if (pt.n == 1 || pt.n < 0 || pt.n > 4 || (pt.n && (!pt.part || !pt.bias || pt.M < M))) return hipErrorInvalidValue;
   if (d % 4 != 0 || d > 256 * 8) return hipErrorInvalidValue;
   const dim3 grid((M + 3) / 4), block(256);
   const bool early = M <= 2048;        // two workgroups per compute unit
-#define WF_LN1(T, V, E) hipLaunchKernelGGL((layernorm_kernel<T, V, E>), grid, block, 0, s, x, rows, g, b, (T *)out, M, d, eps)
+#define WF_LN2(T, V, E, P) hipLaunchKernelGGL((layernorm_kernel<T, V, E, P>), grid, block, 0, s, x, rows, g, b, (T *)out, M, d, eps, pt)
+#define WF_LN1(T, V, E)                    \
+  do {                                     \
+    if (pt.n == 2) WF_LN2(T, V, true, 2);  \
+    else if (pt.n == 3) WF_LN2(T, V, true, 3); \
+    else if (pt.n == 4) WF_LN2(T, V, true, 4); \
+    else WF_LN2(T, V, E, 0);               \
+  } while (0)
 #define WF_LN(V)                                                                           \
   do {                                                                                     \
-    if (out_bf16) { if (early) WF_LN1(__bf16, V, true); else WF_LN1(__bf16, V, false); }   \
-    else { if (early) WF_LN1(float, V, true); else WF_LN1(float, V, false); }              \
+    if (out_bf16) { if (early) { WF_LN1(__bf16, V, true); } else { WF_LN1(__bf16, V, false); } }   \
+    else { if (early) { WF_LN1(float, V, true); } else { WF_LN1(float, V, false); } }              \
   } while (0)
   if (d <= 256 * 2) WF_LN(2);
   else if (d <= 256 * 5) WF_LN(5);
   else WF_LN(8);
 #undef WF_LN
 #undef WF_LN1
+#undef WF_LN2
   return hipGetLastError();
 }
 

@@ -224,3 +224,27 @@ def test_full_size_cross_kv_every_row_and_prefill_on_a_spread_of_streams(capsys)
         with capsys.disabled():
             print(f"[prefill large-v3] stream {i}: {enc_lens[i]} encoder tokens, hidden {eh:.3e} logits {el:.3e}", flush=True)
         assert eh <= H.BF16_TOL and el <= H.BF16_TOL
+
+
+def test_prefill_with_cut_residual_products():
+    """Few prompt rows on a wide model: the last block's partial sums are taken up by whichever final LayerNorm runs (all rows,
+    the last positions only, or both)."""
+    import torch
+    shape = synth.DecoderShape(1280, 2, 20, 5120, 1000, 448)
+    w = synth.make_decoder_weights(shape, 51, affine_random=True)
+    enc = synth.make_enc_states(180, 1280, 52)
+    cu = np.asarray([0, 130, 180], np.int32)
+    prompts = synth.make_prompts([101, 20], shape.n_vocab, 53)
+    ref_h, ref_l, _ = D.prefill_batch(w, shape.n_heads, prompts, enc, cu)
+    dec = wf.Decoder(shape, w, 2, 180, 121, wf.WF_PRECISION_BF16)
+    try:
+        kv = dec.cross_kv(torch.from_numpy(enc).cuda().bfloat16())
+        both = dec.prefill(prompts, cu, kv, hidden_dtype=torch.float32)
+        hidden = dec.prefill(prompts, cu, kv, hidden_dtype=torch.float32, want_logits=False)
+        logits = dec.prefill(prompts, cu, kv)          # no hidden_dtype: no hidden states
+        torch.cuda.synchronize()
+        assert H.rel_err(both["hidden"].cpu().numpy(), ref_h) <= H.BF16_TOL
+        assert H.rel_err(both["logits"].cpu().numpy(), ref_l) <= H.BF16_TOL
+        assert torch.equal(both["hidden"], hidden["hidden"]) and torch.equal(both["logits"], logits["logits"])
+    finally:
+        dec.close()

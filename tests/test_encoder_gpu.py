@@ -207,3 +207,25 @@ def test_many_short_streams():
         enc.close()
         assert cu.tolist() == cu_ref.tolist()
         assert H.rel_err(got, ref) <= tol
+
+
+# Residual products of few rows on a wide model leave partial sums to the LayerNorm behind them: two to four parts, parts of
+# unequal depth, tiles of 32 to 128 rows with a ragged last one, one product of a block cut and the other not.
+@pytest.mark.parametrize("d,heads,frames,hush", [(1280, 20, [150], 0), (1280, 20, [800], 50), (1280, 20, [600, 601, 1], 50), (1024, 16, [799], 50),
+                                                 (768, 12, [301, 300], 25), (768, 12, [2049], 0), (640, 10, [65], 0)])
+def test_cut_residual_products(d, heads, frames, hush):
+    import torch
+    wl = synth.Workload("wide", synth.Shape(80, d, 2, heads, 4 * d), frames, hush_frames=hush, seed_index=11)
+    w, h, mels = synth.materialize(wl, affine_random=True)
+    ref, cu_ref = O.encode_batch(w, heads, mels, h if hush else None)
+    enc = wf.encoder_for_workload(wl, w, h, wf.WF_PRECISION_BF16)
+    try:
+        flat, offs, nf = wf.pack_mels(mels)
+        mel = torch.from_numpy(flat).cuda()
+        out, cu = enc.encode(mel, offs, nf)
+        got = out.float().cpu().numpy()
+        again = enc.encode(mel, offs, nf)[0].float().cpu().numpy()
+    finally:
+        enc.close()
+    assert cu.tolist() == cu_ref.tolist() and np.array_equal(got, again)
+    assert np.all(np.isfinite(got)) and H.rel_err(got, ref) <= H.BF16_TOL
