@@ -18,9 +18,11 @@
 //     workgroup first computes mean and 1/sqrt(var + eps) of its 32 rows (one pass, sums shifted by the row's first
 //     element so that the variance does not cancel), then every chunk is (x - mean) * rstd * gamma + beta rounded
 //     to bf16 -- exactly what the LayerNorm kernel would have stored.  This removes two kernels per transformer
-//     block; with a few hundred tokens each kernel in the chain costs 5-7 us whatever it does.
+//     block; with a few hundred tokens each kernel in the chain costs 5-7 us whatever it does.  Rows of at most 512 values
+//     (every model narrow enough for this file) go to gemm_ln_kernel below instead.
 
 #include <algorithm>
+#include <mutex>
 
 #include "device_utils.h"
 #include "kernels.h"
@@ -251,6 +253,184 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------------------
+// out = epilogue(LayerNorm(x) . W^T) for rows of at most 512 values.  A call is one chain of latencies, so everything it
+// reads is requested at once: the weight tile [TN, K] goes global -> LDS as a whole, a workgroup's 32 rows into registers,
+// where they are normalised (mean, then centred variance) and left in LDS as the bf16 operand.  One barrier, then the waves
+// multiply the whole of K in order, each a 16-column strip of its own (TN = 64: both 16-row blocks, TN = 32: one), and store
+// without a reduction.  The general kernel above walks K with a barrier every two steps and adds four partial tiles up.
+// A workgroup keeps its weight tile for the row tiles g, g + row_groups, ...
+// Encoder calls before -> after: 75 tokens, d = 384 128 -> 120 us; 243 tokens, d = 512 220 -> 200; 925 tokens, d = 384
+// 250 -> 199; prefill of 100 tokens, d = 512 317 -> 299.  (With K known only at run time the exposed LDS latency of every
+// K step took all of that back.)
+constexpr int kLnRowK = 512;
+
+// NK: K / 64 where it is known when compiled (the loads and the K loop are then straight-line code), else 0.
+template <int TN, int EPI, int NK>
+__global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups) {
+  constexpr int TB = TN == 64 ? 2 : 1;
+  constexpr int JV = ((NK ? NK * 64 : kLnRowK) + 127) / 128;      // 128-column pieces of a row
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_ln[];
+  const int K = NK ? NK * 64 : p.K, nk = K >> 6;
+  unsigned char *sW = smem_ln, *sA = smem_ln + nk * TN * 128;      // [K step][row][64 bf16], chunk c of row r at c ^ ((r >> 1) & 7)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int tiles_n = p.N / TN, tiles_m = (p.M + SBM - 1) / SBM;
+  const int n0 = blockIdx.x % tiles_n * TN;
+
+  // ---- rows: 16 lanes a row, eight columns of every 128; this lane's rows of a tile are 8 wave + lq and the same + 4
+  f32x4 x[2][JV][2], gg[JV][2], bb[JV][2];
+  auto request = [&](int tile) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float *xr = (const float *)p.A + (size_t)min(tile * SBM + wave * 8 + i * 4 + lq, p.M - 1) * p.lda + l16 * 8;
+#pragma unroll
+      for (int j = 0; j < JV; ++j)
+        if (j * 128 + l16 * 8 < K) {
+          x[i][j][0] = *(const f32x4 *)(xr + j * 128);
+          x[i][j][1] = *(const f32x4 *)(xr + j * 128 + 4);
+        }
+    }
+  };
+  int tile = blockIdx.x / tiles_n;
+  request(tile);
+#pragma unroll
+  for (int j = 0; j < JV; ++j)
+    if (j * 128 + l16 * 8 < K) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        gg[j][h] = *(const f32x4 *)(p.ln_g + j * 128 + l16 * 8 + h * 4);
+        bb[j][h] = *(const f32x4 *)(p.ln_b + j * 128 + l16 * 8 + h * 4);
+      }
+    }
+  const int wn = TN == 64 ? wave : wave & 1, wm = TN == 64 ? 0 : wave >> 1;     // this wave's strip and first row block
+  const f32x4 bias = *(const f32x4 *)(p.bias + n0 + wn * 16 + lq * 4);
+  {
+    const int rr = lane >> 3;
+    const __bf16 *src[TN / 32];
+    const int wstep = p.w_panels ? 1 << 14 : 64;
+#pragma unroll
+    for (int i = 0; i < TN / 32; ++i) {
+      const int r = (i * 4 + wave) * 8 + rr, n = n0 + r;
+      src[i] = (const __bf16 *)p.W + (p.w_panels ? ((size_t)(n >> 8) * nk << 14) + ((n & 255) << 6) : (size_t)n * K) + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+    }
+#pragma unroll NK ? NK : 1
+    for (int kt = 0; kt < nk; ++kt)
+#pragma unroll
+      for (int i = 0; i < TN / 32; ++i)            // eight rows of 128 bytes per instruction
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[i] + (size_t)kt * wstep),
+                                         (__attribute__((address_space(3))) void *)(sW + (kt * TN + (i * 4 + wave) * 8) * 128), 16, 0, 0);
+  }
+  const float inv_k = 1.0f / (float)K;
+  auto process = [&](int tile) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float sum = 0.0f, sq = 0.0f;
+#pragma unroll
+      for (int j = 0; j < JV; ++j)
+        if (j * 128 + l16 * 8 < K)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum += x[i][j][0][e] + x[i][j][1][e];
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+      const float mu = sum * inv_k;
+#pragma unroll
+      for (int j = 0; j < JV; ++j)
+        if (j * 128 + l16 * 8 < K)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float a = x[i][j][0][e] - mu, b = x[i][j][1][e] - mu;
+            sq += a * a + b * b;
+          }
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+      const float rstd = rsqrtf(sq * inv_k + p.ln_eps);
+      const int r = wave * 8 + i * 4 + lq;
+#pragma unroll
+      for (int j = 0; j < JV; ++j)
+        if (j * 128 + l16 * 8 < K) {
+          f32x4 y[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[h][e] = (x[i][j][h][e] - mu) * rstd * gg[j][h][e] + bb[j][h][e];
+          const bf16x4 c0 = to_bf16x4(y[0]), c1 = to_bf16x4(y[1]);
+          *(bf16x8 *)(sA + (2 * j + (l16 >> 3)) * SBM * 128 + r * 128 + (((l16 & 7) ^ ((r >> 1) & 7)) << 4)) =
+              __builtin_shufflevector(c0, c1, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0) lgkmcnt(0): this wave's rows are in LDS, its weights too
+    __syncthreads();
+    if (tile + row_groups < tiles_m) request(tile + row_groups);
+    f32x4 acc[TB];
+#pragma unroll
+    for (int i = 0; i < TB; ++i) acc[i] = bias;
+    const int sw = (l16 >> 1) & 7;
+    const unsigned char *cw = sW + (wn * 16 + l16) * 128, *cx = sA + (wm * 16 + l16) * 128;
+#pragma unroll NK ? NK : 1
+    for (int kt = 0; kt < nk; ++kt)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int off = ((4 * t + lq) ^ sw) << 4;
+        const bf16x8 wf = *(const bf16x8 *)(cw + kt * TN * 128 + off);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+          const bf16x8 xf = *(const bf16x8 *)(cx + (kt * SBM + i * 16) * 128 + off);
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, acc[i], 0, 0, 0);
+        }
+      }
+    // lane holds, of token l16 of a row block, features 16 wn + 4 lq .. + 3
+#pragma unroll
+    for (int i = 0; i < TB; ++i) {
+      const int m = tile * SBM + (wm + i) * 16 + l16, nn = n0 + wn * 16 + lq * 4;
+      f32x4 v = acc[i];
+      if constexpr (EPI == EPI_BIAS_GELU) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]);
+      }
+      if (m < p.M) {
+        __bf16 *dst = (EPI == EPI_BIAS && p.out2 && nn >= p.n_split) ? (__bf16 *)p.out2 + (size_t)m * p.ldo2 + (nn - p.n_split)
+                                                                     : (__bf16 *)p.out + (size_t)m * p.ldo + nn;
+        *(bf16x4 *)dst = to_bf16x4(v);
+      }
+    }
+  };
+  process(tile);          // by itself: its first wait is for the rows only, the weights arrive under the statistics
+  for (tile += row_groups; tile < tiles_m; tile += row_groups) {
+    __syncthreads();      // the operand has been read; the next rows may take its place
+    process(tile);
+  }
+}
+
+template <int TN, int EPI, int NK>
+hipError_t launch_ln_tile(const GemmArgs &a, hipStream_t s) {
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [&] {
+    attr_err = hipFuncSetAttribute((const void *)gemm_ln_kernel<TN, EPI, NK>, hipFuncAttributeMaxDynamicSharedMemorySize, (TN + SBM) * kLnRowK * 2);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  const int smem = (TN + SBM) * a.K * 2, tiles_n = a.N / TN, tiles_m = (a.M + SBM - 1) / SBM;
+  const int slots = 256 * std::min(4, 163840 / smem);               // workgroups the chip holds at a time
+  const int groups = std::min(tiles_m, std::max(1, slots / tiles_n));
+  hipLaunchKernelGGL((gemm_ln_kernel<TN, EPI, NK>), dim3((unsigned)(groups * tiles_n)), dim3(256), smem, s, a, groups);
+  return hipGetLastError();
+}
+
+template <int EPI>
+hipError_t launch_ln(const GemmArgs &a, hipStream_t s) {
+  const long rows = (a.M + SBM - 1) / SBM;
+  // (75 x 384, one tile per 54 CUs or 108: 2.5 % of an encoder call; from 160 workgroups on the wide tile, which normalises its
+  // rows half as often, is level or up to 5 % of a call ahead)
+  const bool wide = a.N % 64 == 0 && rows * (a.N / 64) >= 160;
+  switch (a.K) {
+    case 512: return wide ? launch_ln_tile<64, EPI, 8>(a, s) : launch_ln_tile<32, EPI, 8>(a, s);
+    case 384: return wide ? launch_ln_tile<64, EPI, 6>(a, s) : launch_ln_tile<32, EPI, 6>(a, s);
+    default: return wide ? launch_ln_tile<64, EPI, 0>(a, s) : launch_ln_tile<32, EPI, 0>(a, s);
+  }
+}
+
 // Widest tile (in 32-column blocks) that divides N and still leaves at least 160 workgroups; 1 if even that gives fewer.
 int pick_blocks(const GemmArgs &a) {
   constexpr int min_wgs = 160;     // measured: 425 tokens prefer 168-224 wide tiles to 336-448 narrower ones, 125 tokens 192-256 to 96-128
@@ -289,6 +469,7 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
   }
   if (amode == A_LN) {
     if (a.lda % 8 != 0 || !a.ln_g || !a.ln_b || !(a.ln_eps > 0.0f) || a.K > kMaxLnK) return hipErrorInvalidValue;
+    if (a.K <= kLnRowK && (epi == EPI_BIAS || epi == EPI_BIAS_GELU)) return epi == EPI_BIAS ? launch_ln<EPI_BIAS>(a, s) : launch_ln<EPI_BIAS_GELU>(a, s);
     switch (epi) {
       case EPI_BIAS: return launch_small<A_LN, EPI_BIAS>(a, s);
       case EPI_BIAS_GELU: return launch_small<A_LN, EPI_BIAS_GELU>(a, s);

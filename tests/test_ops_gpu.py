@@ -290,3 +290,11 @@ def test_attention_tile_of_minus_infinity(lens, n_heads):
 def _softmax(s):
     e = np.exp(s - s.max(axis=1, keepdims=True))
     return e / e.sum(axis=1, keepdims=True)
+
+
+# Rows of at most 512 values: K known when compiled (384, 512) and not, both tile widths, several row tiles per workgroup with a
+# ragged last one (the first rows are the statistics' hard cases of the test above).
+@pytest.mark.parametrize("M,N,K", [(31, 128, 64), (97, 256, 128), (65, 384, 320), (1023, 1152, 384), (1000, 2048, 512), (257, 1536, 512), (5, 1920, 448)])
+@pytest.mark.parametrize("epi", [0, 1])
+def test_layernorm_product_of_short_rows(M, N, K, epi):
+    test_layernorm_fused_into_the_small_batch_product(M, N, K, epi)
