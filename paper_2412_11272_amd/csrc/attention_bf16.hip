@@ -58,7 +58,7 @@ __device__ __forceinline__ int v_swizzle(int r) {
 // KS: number of four-wave groups that share the keys of a work item (group g walks the tiles g, g + KS, ...; the partial
 // results meet in LDS at the end).  launch_attention_bf16 says when it is 2.
 template <bool CAUSAL, int KS>
-__global__ void __launch_bounds__(256 * KS, KS > 1 ? 4 : 1) attention_bf16_kernel(AttnArgs p) {
+__global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_att[];   // per key group: K[2][8 KB], V[2][8 KB]
 
   // The grid has the head count rounded up to a multiple of 8.  Consecutive workgroups go to the 8 XCDs in

@@ -289,13 +289,16 @@ hipError_t launch_index(int t, const GemmArgs &a, hipStream_t s) {
 // The smallest tile that leaves at most one per compute unit, if that beats the kernels with two smaller workgroups per
 // CU, whose epilogues overlap other tiles' K loops: always up to 128 x 128 (1.04 to 1.9 times, 64 .. 5400 rows), with larger
 // tiles when the reduction is at least twice as long as the result is wide, so that the K loop dominates (1.03 to 1.47; short
-// reductions lose up to 15 %: 6361 x 1280 x 1280 28.6 -> 32.8 us, 2600 x 3072 x 1024 20.5 -> 22.9).  -1: none.
+// reductions lose up to 15 %: 6361 x 1280 x 1280 28.6 -> 32.8 us, 2600 x 3072 x 1024 20.5 -> 22.9) and there are at most
+// 10 240 rows: more come in two lanes, whose kernels share the chip, and there the compute units a kernel takes count as well
+// as its time (11 500 x 1024 x 4096 103 us on 184 units, 89 on 236: an encoder call 17.4 -> 17.7 ms; 9000 x 1280 x 5120: 27.0
+// -> 26.3).  -1: none.
 int pick_tile(int M, int N, int K) {
   for (int t = 0; t < kTileCount; ++t) {
     if (N % kTiles[t].bn) continue;
     const long tiles = (long)((M + kTiles[t].bm - 1) / kTiles[t].bm) * (N / kTiles[t].bn);
     if (tiles > 256) continue;
-    if (t <= kTile128 || K >= 2 * N) return t;
+    if (t <= kTile128 || (K >= 2 * N && M <= 10240)) return t;
   }
   return -1;
 }
@@ -349,6 +352,10 @@ hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
     return launch_index<EPI_PARTIAL, A_PLAIN>(c.tile, a, s);
   }
   int t = pick_tile(a.M, a.N, a.K);
+  // A first convolution of many rows has four K steps or so: two stages per operand, so that two workgroups share a CU and one's
+  // epilogue runs beside the other's loads (43 000 x 1024 x 256: 137 us with the four-stage form).
+  if (t < 0 && amode == A_CONV3 && epi == EPI_BIAS_GELU && !a.a_panels && a.N % 128 == 0 && a.K % 64 == 0 && a.K > 0)
+    return launch_tile<128, 128, 2, 2, false, EPI_BIAS_GELU, A_CONV3>(a, s);
   if (t < 0) t = kTile128;           // more than one tile per CU: convolutions whose taps are no whole K steps
   if (a.N % kTiles[t].bn || a.K % 64 || a.K <= 0) return hipErrorInvalidValue;
   if (amode == A_PLAIN) {

@@ -68,8 +68,9 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
   if (row >= M) return;
   const int lane = threadIdx.x & 63;
   const int nv = d >> 2;                               // float4 per row
-  const int xrow = rows ? rows[row] : row;
-  f32x4 *xr = (f32x4 *)(x + (size_t)xrow * d);
+  int xrow = row;
+  if constexpr (EARLY) xrow = rows ? rows[row] : row;
+  const f32x4 *xr = (const f32x4 *)(x + (size_t)xrow * d);
   const f32x4 *gr = (const f32x4 *)g, *br = (const f32x4 *)b;
   f32x4 v[MAXV], gg[EARLY ? MAXV : 1], bb[EARLY ? MAXV : 1];
 #pragma unroll
@@ -102,7 +103,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
           for (int e = 0; e < 4; ++e) t[e] += w[k][i][e];
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[i][e] += t[e];
-        if (!rows) xr[idx] = v[i];
+        if (!rows) ((f32x4 *)(x + (size_t)xrow * d))[idx] = v[i];
       }
     }
   }
@@ -180,7 +181,7 @@ hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const
   if (pt.n == 1 || pt.n < 0 || pt.n > 4 || (pt.n && (!pt.part || !pt.bias || pt.M < M))) return hipErrorInvalidValue;
   if (d % 4 != 0 || d > 256 * 8) return hipErrorInvalidValue;
   const dim3 grid((M + 3) / 4), block(256);
-  const bool early = M <= 2048;        // two workgroups per compute unit
+  const bool early = M <= 2048 || rows;        // two workgroups per compute unit; rows by index exist in that form only
 #define WF_LN2(T, V, E, P) hipLaunchKernelGGL((layernorm_kernel<T, V, E, P>), grid, block, 0, s, x, rows, g, b, (T *)out, M, d, eps, pt)
 #define WF_LN1(T, V, E)                    \
   do {                                     \
