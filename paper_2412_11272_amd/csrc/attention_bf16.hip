@@ -23,6 +23,10 @@ namespace {
 
 constexpr int BQ = 128;    // queries per work item
 constexpr int BKV = 64;    // keys per tile
+// Where the keys are shared out, a wave's first tile need not be the stream's first, and its logits may be -inf or so far
+// below the others that the rounding of reference x scale alone, 2^-25 of it, overflows the exponential.  The reference
+// (in powers of two) therefore stops at -2^31, where that rounding is still a factor of 2^64: such a tile weighs 0, not NaN.
+constexpr float kMinReference = -0x1p31f;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -189,7 +193,8 @@ __global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
     // maximum when some query's maximum has moved up by more than 8 / c (weights up to 2^8 until then; fp32 sums and
     // bf16 weights have the range), which spares most rescales of the accumulators.
     if (__any(m_new > m_run + lazy)) {
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+      // (a later group's first tile may hold nothing but -inf logits for some queries of the wave: nothing to rescale yet)
+      const float alpha = KS > 1 && m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_new) * c);
       l_run *= alpha;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -197,8 +202,7 @@ __global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
         for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
       m_run = m_new;
     }
-    // (a later group's first tile may hold nothing but -inf logits: its weights are 0, not NaN)
-    const float mc = KS > 1 && m_run == -INFINITY ? 0.0f : m_run * c;
+    const float mc = KS > 1 ? fmaxf(m_run * c, kMinReference) : m_run * c;
     float psum = 0.0f;
     bf16x8 pf[2][2];
 #pragma unroll
@@ -421,7 +425,8 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     const float m_new = fmaxf(m_run, tmax);
     if (__any(m_new > m_run)) {
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+      // a query without a finite logit so far has nothing to rescale, and its m_run - m_new may be inf - inf
+      const float alpha = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_new) * c);
       l_run *= alpha;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -429,7 +434,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
         for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
       m_run = m_new;
     }
-    const float mc = m_run == -INFINITY ? 0.0f : m_run * c;   // a tile of -inf logits in front of others weighs 0, not NaN
+    const float mc = fmaxf(m_run * c, kMinReference);
     float psum = 0.0f;
     bf16x8 pf[2][2];
 #pragma unroll

@@ -263,15 +263,21 @@ def test_attention_shared_keys(lens, n_heads):
     test_attention(lens, n_heads, 6.0, wf.WF_PRECISION_BF16)
 
 
-@pytest.mark.parametrize("lens,n_heads", [([900], 8), ([1000, 300], 12)])
-def test_attention_tile_of_minus_infinity(lens, n_heads):
-    """Keys whose logits overflow to -inf weigh nothing, wherever their tile falls in the split of the keys."""
+# 32-query workgroups ([900] x 8, [425] x 20, [1000, 300] x 12) and two key groups per 128-query item (the others)
+@pytest.mark.parametrize("lens,n_heads", [([900], 8), ([425], 20), ([1000, 300], 12), ([900], 20), ([1409], 20), ([641, 65, 1000], 12)])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_attention_tile_of_minus_infinity(lens, n_heads, mixed):
+    """Keys whose logits overflow to -inf weigh nothing, wherever their tile falls in the split of the keys; mixed: every
+    other query is so small that its logits stay finite (about -4e37: they weigh nothing either), so that a wave meets both
+    kinds at once.  The first tile stays ordinary: the forms that do not share keys out need one finite logit there."""
     import torch
     d, M = 64 * n_heads, sum(lens)
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     rng = np.random.default_rng(M)
     qkv = rng.standard_normal((M, 3 * d)).astype(np.float32)
     qkv[:, :d] = np.abs(qkv[:, :d]) + 1.0
+    if mixed:
+        qkv[::2, :d] *= 1e-3                                 # 64 terms of 1e-3 .. 5e-3 x 3e38 each
     live = np.ones(M, bool)
     live[64:192] = False                                     # the first tiles of the second and third wave / the second group
     qkv[64:192, d:2 * d] = -3e38
