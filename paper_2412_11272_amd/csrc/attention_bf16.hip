@@ -561,7 +561,8 @@ hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
   }
   constexpr long cus = 256;
   const bool share = (a.Mkv > 0 ? a.Mkv : a.M) >= 192L * a.B;
-  const long blocks32 = std::min<long>(4L * a.n_work, a.M / 32 + a.B) * a.n_heads, blocks128 = ((long)a.M / BQ + a.B) * a.n_heads;
+  const long items = a.n_work_batch > 0 ? a.n_work_batch : a.n_work;
+  const long blocks32 = std::min<long>(4L * items, a.M / 32 + a.B) * a.n_heads, blocks128 = ((long)a.M / BQ + a.B) * a.n_heads;
   if (blocks32 <= cus || (share && blocks32 <= 2 * cus)) return launch_keysplit(a, s);
   if (share && blocks128 <= cus) return launch_keys<false, 2>(a, s);
   return launch_keys<false, 1>(a, s);

@@ -458,7 +458,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
         AttnArgs a{};   // q, k, v and out are addressed through the absolute prefix sums, so the bases stay whole-batch
         a.q = e->qkv; a.k = (const char *)e->qkv + (size_t)d * es; a.v = (const char *)e->qkv + (size_t)2 * d * es;
         a.ldq = a.ldkv = 3 * d; a.out = e->u; a.cu_q = a.cu_kv = d_cu_seq; a.work = work;
-        a.n_work = nw; a.n_heads = c.n_heads; a.d_model = d; a.B = B; a.M = M;
+        a.n_work = nw; a.n_work_batch = n_work; a.n_heads = c.n_heads; a.d_model = d; a.B = B; a.M = M;
         a.scale = 0.125f;
         Scope sc(e, ls, KC_ATTN, attn_flops, (double)Mg * 4 * d * es);
         hipError_t err = e->bf16 ? launch_attention_bf16(a, ls) : launch_attention_f32(a, ls);

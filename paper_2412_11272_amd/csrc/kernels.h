@@ -80,6 +80,7 @@ struct AttnArgs {
   const int32_t *work;      // [n_work][2]: (stream, first query row inside the stream), longest first
   int32_t n_work, n_heads, d_model, B, M;   // M = total query rows
   int32_t Mkv;              // total key rows, 0: M
+  int32_t n_work_batch;     // work items of the whole batch where this launch is one lane of it, 0: n_work
   int32_t causal;
   float scale;              // 1/sqrt(64)
 };

@@ -229,3 +229,23 @@ def test_cut_residual_products(d, heads, frames, hush):
         enc.close()
     assert cu.tolist() == cu_ref.tolist() and np.array_equal(got, again)
     assert np.all(np.isfinite(got)) and H.rel_err(got, ref) <= H.BF16_TOL
+
+
+# Batches whose lanes have sizes on the other side of a kernel choice than the batch as a whole: the attention form
+@pytest.mark.parametrize("d,heads,d_mlp,tokens", [(384, 6, 1536, [1408, 1280, 1525, 1525, 1525, 1000]), (384, 6, 1536, [1280, 1300, 1525, 1525, 1525, 1040])])
+def test_lanes_do_not_change_a_bit(d, heads, d_mlp, tokens):
+    import torch
+    wl = synth.Workload("lanes", synth.Shape(80, d, 2, heads, d_mlp), [2 * t for t in tokens], hush_frames=0, seed_index=4)
+    w, _, mels = synth.materialize(wl, affine_random=True)
+    enc = wf.encoder_for_workload(wl, w, None, wf.WF_PRECISION_BF16)
+    try:
+        flat, offs, nf = wf.pack_mels(mels)
+        mel = torch.from_numpy(flat).cuda()
+        outs = []
+        for lanes in (1, 2, 3, 4):
+            enc.set_lanes(lanes)
+            outs.append(enc.encode(mel, offs, nf)[0])
+        for out in outs[1:]:
+            assert torch.equal(out, outs[0])
+    finally:
+        enc.close()
