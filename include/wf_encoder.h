@@ -208,6 +208,14 @@ int wf_gemm_tile_map(int32_t M, int32_t N, int32_t tile_m, int32_t tile_n, int32
 int wf_gemm_tile_choice(int32_t M, int32_t N, int32_t *tile_m, int32_t *tile_n);
 
 /*
+ * Diagnostic, host only: the form the bf16 attention takes for B streams of cu_q (HOST [B+1] prefix sums) queries over cu_kv
+ * (HOST [B+1]) keys and n_heads heads: 0 = 128-query items that walk all keys, 1 = the same with two groups of waves sharing
+ * the keys, 2 / 3 = 32-query items with the keys cut four ways and one / two tile buffers a wave.  It runs the rule the
+ * launch uses, so a test can pin which form a batch gets.  Negative WF_E_* code on bad arguments.
+ */
+int wf_attention_form(const int32_t *cu_q, const int32_t *cu_kv, int32_t B, int32_t n_heads);
+
+/*
  * Diagnostic, host only: the GELU the bf16 kernels apply in their epilogues (erf form by a clamped odd polynomial, no
  * transcendental instruction), evaluated on the host with the same source code; out[i] = GELU(z[i]) for n HOST
  * values.  A test bounds its distance from the exact erf form (Section "Operations": the encoder is the stock

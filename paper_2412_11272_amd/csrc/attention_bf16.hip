@@ -63,7 +63,10 @@ __device__ __forceinline__ int v_swizzle(int r) {
 // results meet in LDS at the end).  launch_attention_bf16 says when it is 2.
 template <bool CAUSAL, int KS>
 __global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_att[];   // per key group: K[2][8 KB], V[2][8 KB]
+  // per key group: K[2][8 KB], V[2][8 KB].  One group alone fits the static limit, and its tile addresses are then constants.
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_groups[];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem_one[KS == 1 ? 32768 : 16];
+  unsigned char *const smem_att = KS == 1 ? smem_one : smem_groups;
 
   // The grid has the head count rounded up to a multiple of 8.  Consecutive workgroups go to the 8 XCDs in
   // turn, so slot s of every work item lands on XCD s % 8; slot s holds head (s - rot) mod heads8, with rot
@@ -306,7 +309,7 @@ __global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
 
 template <bool CAUSAL, int KS>
 hipError_t launch_keys(const AttnArgs &a, hipStream_t s) {
-  constexpr int smem = KS * 32768 + (KS > 1 ? KS * 2048 : 0);
+  constexpr int smem = KS > 1 ? KS * (32768 + 2048) : 0;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] {
@@ -323,18 +326,22 @@ hipError_t launch_keys(const AttnArgs &a, hipStream_t s) {
 // tokens).  There the kernel's duration is the length of one workgroup's chain of key tiles, so the chain is cut
 // four ways: a workgroup takes 32 queries of one (stream, head) and its four waves walk the key tiles w, w + 4,
 // w + 8, ... each with its own running maximum, sum and output accumulators, reading tiles it loads itself into
-// an LDS buffer of its own (no workgroup barrier inside the loop).  One buffer, not two: two take the LDS of a whole
-// compute unit, with one a second workgroup fits and its waves cover the loads (20 heads x 350 tokens 11.2 -> 8.8 us,
-// 6 x 1200 19.4 -> 15.4; within 0.1 us on the smallest calls).  At the end the four partial results are rescaled
+// LDS buffers of its own (no workgroup barrier inside the loop): NB = 2 of them where a workgroup has a compute unit to
+// itself, 1 where a second workgroup on the CU covers the loads (20 heads x 350 tokens 11.2 -> 8.8 us, 6 x 1200 19.4 ->
+// 15.4, where two buffers would take two rounds; see attention_form).  At the end the four partial results are rescaled
 // to the common maximum and added in wave order through LDS (deterministic).  Same arithmetic per tile as
 // attention_bf16_kernel; the grouping of the tiles differs, so results agree to fp32 rounding of the sums, not bit
 // for bit.
+template <int NB>
 __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_ks[];   // per wave: K [8 KB], V [8 KB]
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_ks[];   // per wave: K [NB][8 KB], V [NB][8 KB]
 
   const int heads8 = (p.n_heads + 7) & ~7;
-  const int unit = blockIdx.x / heads8;               // (work item, quarter of its 128 queries)
-  const int item = unit >> 2, sub = unit & 3;
+  // All first quarters of the items' 128 queries, then all second ones, ..: prompts shorter than a quarter leave three of
+  // four workgroups without queries, and interleaved with the others those would keep three quarters of the CUs empty (the
+  // dispatcher deals consecutive workgroups out round robin).
+  const int unit = blockIdx.x / heads8;
+  const int item = unit % p.n_work, sub = unit / p.n_work;
   const int w1 = p.work[2 * item + 1];
   const int rot = (((w1 >> 20) & 7) * (p.n_heads & 7)) & 7;
   const int head = (blockIdx.x % heads8 + heads8 - rot) % heads8;
@@ -355,7 +362,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   const __bf16 *Qb = (const __bf16 *)p.q + (size_t)tok0 * ldq + head * 64;
   const __bf16 *Kb = (const __bf16 *)p.k + (size_t)ktok0 * ld + head * 64;
   const __bf16 *Vb = (const __bf16 *)p.v + (size_t)ktok0 * ld + head * 64;
-  unsigned char *myK = smem_ks + wave * 16384, *myV = myK + 8192;
+  unsigned char *myK = smem_ks + wave * NB * 16384, *myV = myK + NB * 8192;
 
   int qrow = q0 + l32;
   const bool q_valid = qrow < Lq;
@@ -374,7 +381,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
 
   // one wave loads a whole tile: 8 instructions of 8 rows for K, 8 for V
   const int lrow = lane >> 3;
-  auto issue = [&](int kt) {
+  auto issue = [&](int kt, int buf) {
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
       const int rt = g * 8 + lrow;
@@ -382,8 +389,8 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
       key = key < L ? key : L - 1;
       const __bf16 *srck = Kb + (size_t)key * ld + ((lane & 7) ^ ((rt >> 1) & 7)) * 8;
       const __bf16 *srcv = Vb + (size_t)key * ld + ((lane & 7) ^ v_swizzle(rt)) * 8;
-      __builtin_amdgcn_global_load_lds((const glb_void *)srck, (lds_void *)(myK + g * 1024), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const glb_void *)srcv, (lds_void *)(myV + g * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const glb_void *)srck, (lds_void *)(myK + buf * 8192 + g * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const glb_void *)srcv, (lds_void *)(myV + buf * 8192 + g * 1024), 16, 0, 0);
     }
   };
   const int r16 = lane & 15;
@@ -391,11 +398,13 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   const int tr_feat = ((lane >> 4) & 1) * 16 + (r16 & 3) * 4;
 
   const int n_tiles = (L + BKV - 1) / BKV;
-  if (wave < n_tiles) issue(wave);
-  for (int kt = wave; kt < n_tiles; kt += 4) {
+  int buf = 0;
+  if (wave < n_tiles) issue(wave, 0);
+  for (int kt = wave; kt < n_tiles; kt += 4, buf ^= NB - 1) {
     const int key0 = kt * BKV;
     __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0): this wave's tile kt has landed (nobody else touches these buffers)
-    const unsigned char *cK = myK, *cV = myV;
+    if (NB == 2 && kt + 4 < n_tiles) issue(kt + 4, buf ^ 1);
+    const unsigned char *cK = myK + buf * 8192, *cV = myV + buf * 8192;
     f32x16 s[2];
 #pragma unroll
     for (int kb2 = 0; kb2 < 2; ++kb2) {
@@ -469,11 +478,11 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
           o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[kb2][h], o[t], 0, 0, 0);
         }
     }
-    if (kt + 4 < n_tiles) {
+    if (NB == 1 && kt + 4 < n_tiles) {
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0): the tile has been read, its buffer may be refilled
       __builtin_amdgcn_sched_barrier(0);
-      issue(kt + 4);
+      issue(kt + 4, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -526,15 +535,16 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   }
 }
 
+template <int NB>
 hipError_t launch_keysplit(const AttnArgs &a, hipStream_t s) {
-  constexpr int smem = 4 * 16384;
+  constexpr int smem = 4 * NB * 16384;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] {
-    attr_err = hipFuncSetAttribute((const void *)attention_bf16_keysplit_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    attr_err = hipFuncSetAttribute((const void *)attention_bf16_keysplit_kernel<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
   if (attr_err != hipSuccess) return attr_err;
-  hipLaunchKernelGGL(attention_bf16_keysplit_kernel, dim3(4 * a.n_work * ((a.n_heads + 7) & ~7)), dim3(256), smem, s, a);
+  hipLaunchKernelGGL(attention_bf16_keysplit_kernel<NB>, dim3(4 * a.n_work * ((a.n_heads + 7) & ~7)), dim3(256), smem, s, a);
   return hipGetLastError();
 }
 
@@ -543,14 +553,40 @@ hipError_t launch_keysplit(const AttnArgs &a, hipStream_t s) {
 int attention_q_tile() { return BQ; }
 
 // Calls that leave the chip short of waves last as long as one workgroup's walk over the key tiles (1.05 us a tile), so the
-// keys are shared out when there are at least three tiles to share (192 keys: 12 heads x 6 streams x 160 keys lose 1.3 to
-// 2.4 us, 16 x 4 x 200 gain 0.2):
-//   * 32-query workgroups with the keys cut four ways while they fit the chip at two per compute unit (20 heads x 425 tokens
-//     11.3 -> 9.3 us, 16 x 1000 20.8 -> 14.4, 8 x 1525 27.9 -> 17.8; 20 x 900 = 580 workgroups 16.4 -> 19.2), and whatever
-//     the number of keys while they fit at one per CU (6 heads x 75 tokens 5.8 -> 5.4);
-//   * else 128-query work items with two key groups while there is at most one per CU (20 x 900 19.9 -> 16.4, 12 x 1500
-//     28.8 -> 22.4; with more the one-group form is as fast, from 16 heads x 8 x 325 on 10 % faster).
-// The row counts of the whole batch decide, never those of one lane: a batch cut into lanes gives the same bits.
+// keys are shared out.  Let x be the busy 32-query workgroups of the XCD that gets most of them (32 CUs each):
+//   * at most one per CU, however short the keys: 32-query workgroups, keys cut four ways, with two tile buffers a wave (128 KB
+//     of LDS) while x <= 32, else one (64 KB), so that two fit a CU and none waits for a second round.  With heads that do not
+//     fill the 8 XCDs evenly and last quarters without queries the dispatcher deals two to some CUs from x = 25 on.  (Two
+//     buffers against one: 16 heads x 8 prompts of 20 x 1500 keys, x = 26, 17.4 and 27.2 us; 20 x 350, x = 36, 12.1 and 9.9.)
+//   * up to two per CU, and at least three tiles (192 keys) to share: one buffer, a second workgroup covers the loads: 1.00 ..
+//     1.16 times as fast as unshared at 192 .. 400 keys and x = 32 .. 48, 1.15 .. 1.5 times beyond; x up to 64 only where the
+//     XCDs are filled evenly (20 heads x 6 prompts x 1500 keys, x = 60: 30.4 us against 25.4 with two key groups).
+//   * else 128-query items with two key groups while there is at most one per CU (20 x 900 19.9 -> 16.4 us, 12 x 1500 28.8 ->
+//     22.4; with more the one-group form is as fast, from 16 heads x 8 x 325 on 10 % faster, and so it is with XCDs that are
+//     filled unevenly and nearly full while a stream has few tiles: 20 x 3 x 425 14.9 us against 16.4).
+// The whole batch's counts decide, never those of one lane: a batch cut into lanes gives the same bits.
+AttnForm attention_form(int32_t n_heads, int32_t B, int64_t M, int64_t Mkv, int64_t n_work) {
+  constexpr long cus = 256, per_xcd = cus / 8;
+  const long heads8 = (n_heads + 7) & ~7, units = std::min<long>(4L * n_work, M / 32 + B);
+  // heads of B equal streams on the fullest XCD (the kernels' slot s of a stream of rank r holds head s - rot(r))
+  long most = 0;
+  for (int x = 0; x < 8; ++x) {
+    long n = 0;
+    for (int r = 0; r < std::min(B, 8); ++r) {
+      const long rot = (r * (n_heads & 7)) & 7;
+      for (long slot = x; slot < heads8; slot += 8)
+        if ((slot + heads8 - rot) % heads8 < n_heads) n += (B - r + 7) / 8;
+    }
+    most = std::max(most, n);
+  }
+  const long busy = most * units;                        // x = busy / B
+  const bool even = n_heads % 8 == 0;
+  if (units * n_heads <= cus) return busy <= (even || units == 4L * n_work ? per_xcd : per_xcd * 3 / 4) * B ? ATTN_KEYS4_TWO_BUFFERS : ATTN_KEYS4;
+  if (Mkv < 192L * B || (M / BQ + B) * n_heads > cus) return ATTN_PLAIN;
+  if (!even && Mkv < 512L * B && most * (M / BQ + B) > 30L * B) return ATTN_PLAIN;
+  return busy <= (even || B == 1 ? 2 * per_xcd : per_xcd * 3 / 2) * B ? ATTN_KEYS4 : ATTN_KEYS2;
+}
+
 hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
   if (a.n_work <= 0) return hipSuccess;
   if (a.d_model != a.n_heads * 64) return hipErrorInvalidValue;
@@ -559,13 +595,12 @@ hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
     if (a.cu_q != a.cu_kv) return hipErrorInvalidValue;
     return launch_keys<true, 1>(a, s);
   }
-  constexpr long cus = 256;
-  const bool share = (a.Mkv > 0 ? a.Mkv : a.M) >= 192L * a.B;
-  const long items = a.n_work_batch > 0 ? a.n_work_batch : a.n_work;
-  const long blocks32 = std::min<long>(4L * items, a.M / 32 + a.B) * a.n_heads, blocks128 = ((long)a.M / BQ + a.B) * a.n_heads;
-  if (blocks32 <= cus || (share && blocks32 <= 2 * cus)) return launch_keysplit(a, s);
-  if (share && blocks128 <= cus) return launch_keys<false, 2>(a, s);
-  return launch_keys<false, 1>(a, s);
+  switch (attention_form(a.n_heads, a.B, a.M, a.Mkv > 0 ? a.Mkv : a.M, a.n_work_batch > 0 ? a.n_work_batch : a.n_work)) {
+    case ATTN_KEYS4_TWO_BUFFERS: return launch_keysplit<2>(a, s);
+    case ATTN_KEYS4: return launch_keysplit<1>(a, s);
+    case ATTN_KEYS2: return launch_keys<false, 2>(a, s);
+    default: return launch_keys<false, 1>(a, s);
+  }
 }
 
 }  // namespace wf

@@ -688,6 +688,16 @@ int wf_gemm_tile_choice(int32_t M, int32_t N, int32_t *tile_m, int32_t *tile_n) 
   return WF_OK;
 }
 
+int wf_attention_form(const int32_t *cu_q, const int32_t *cu_kv, int32_t B, int32_t n_heads) {
+  if (!cu_q || !cu_kv || B < 1 || n_heads < 1) return fail(WF_E_INVALID_ARG, "NULL pointer, or B or n_heads < 1");
+  int64_t n_work = 0;
+  for (int i = 0; i < B; ++i) {
+    if (cu_q[i + 1] <= cu_q[i] || cu_kv[i + 1] <= cu_kv[i]) return fail(WF_E_INVALID_ARG, "stream %d is empty", i);
+    n_work += (cu_q[i + 1] - cu_q[i] + attention_q_tile() - 1) / attention_q_tile();
+  }
+  return attention_form(n_heads, B, cu_q[B] - cu_q[0], cu_kv[B] - cu_kv[0], n_work);
+}
+
 // ---- operator-level entry points -------------------------------------------------------------
 int wf_op_linear(int32_t precision, const void *a_dev, const void *w_dev, const float *bias_dev, void *out_dev, int32_t M,
                  int32_t N, int32_t K, int32_t epilogue, void *hip_stream) {

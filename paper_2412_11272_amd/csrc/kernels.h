@@ -109,6 +109,9 @@ hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
 // Parts the reduction of a residual product should be cut into (1: none); k_splits * M * N <= kPartialFloats
 constexpr int64_t kPartialFloats = 256L * 128 * 128;
 int gemm_split_choice(int32_t M, int32_t N, int32_t K);
+// Forms of the non-causal attention (attention_bf16.hip); the choice is a function of the whole batch's sizes
+enum AttnForm : int { ATTN_PLAIN = 0, ATTN_KEYS2 = 1, ATTN_KEYS4 = 2, ATTN_KEYS4_TWO_BUFFERS = 3 };
+AttnForm attention_form(int32_t n_heads, int32_t B, int64_t M, int64_t Mkv, int64_t n_work);
 hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s);
 // Parts of the residual product in front of a LayerNorm (EPI_PARTIAL): x += part[0] + .. + part[n - 1] + bias first
 struct Partials {

@@ -248,3 +248,26 @@ def test_prefill_with_cut_residual_products():
         assert torch.equal(both["hidden"], hidden["hidden"]) and torch.equal(both["logits"], logits["logits"])
     finally:
         dec.close()
+
+
+@pytest.mark.parametrize("heads,prompts,enc_len,form", [(6, [4, 1, 33] * 7, 210, 3), (8, [100, 128, 65] * 4, 200, 2), (6, [4] * 64, 200, 0),
+                                                        (12, [70] * 12, 200, 1)])
+def test_prefill_cross_attention_forms(heads, prompts, enc_len, form):
+    """Prompts of a few tokens (whose items leave quarters without queries) and of a whole item over every form of the
+    cross-attention; encoder lengths differ from stream to stream."""
+    import torch
+    enc_lens = [enc_len - (i % 3) for i in range(len(prompts))]
+    assert wf.attention_form(heads, prompts, enc_lens) == form
+    shape = synth.DecoderShape(64 * heads, 1, heads, 256, 300, 448)
+    w = synth.make_decoder_weights(shape, 61, affine_random=True)
+    cu = np.concatenate([[0], np.cumsum(enc_lens)]).astype(np.int32)
+    enc = synth.make_enc_states(int(cu[-1]), shape.d_model, 62)
+    tokens = synth.make_prompts(prompts, shape.n_vocab, 63)
+    ref_h, ref_l, _ = D.prefill_batch(w, heads, tokens, enc, cu)
+    dec = wf.Decoder(shape, w, len(prompts), int(cu[-1]), sum(prompts), wf.WF_PRECISION_BF16)
+    try:
+        got = dec.prefill(tokens, cu, dec.cross_kv(torch.from_numpy(enc).cuda().bfloat16()), hidden_dtype=torch.float32)
+        torch.cuda.synchronize()
+        assert H.rel_err(got["hidden"].cpu().numpy(), ref_h) <= H.BF16_TOL and H.rel_err(got["logits"].cpu().numpy(), ref_l) <= H.BF16_TOL
+    finally:
+        dec.close()

@@ -149,6 +149,24 @@ def test_gemm_tile_choice_follows_the_last_round_of_the_chip():
         wf.gemm_tile_choice(100, 100)
 
 
+def test_attention_form_follows_the_busy_workgroups():
+    """Single streams, equal batches and short prompts over long contexts on both sides of each limit (one 32-query workgroup
+    per CU, two per CU, one 128-query item per CU): the form with the least time of each measured size."""
+    form = wf.attention_form
+    assert form(6, [75]) == 3 and form(8, [900]) == 3 and form(8, [1100]) == 2 and form(16, [1000]) == 2 and form(16, [1100]) == 1
+    assert form(20, [300]) == 2 and form(20, [425]) == 2 and form(20, [900]) == 1 and form(20, [200]) == 3
+    assert form(16, [325] * 8) == 0 and form(12, [160] * 6) == 0 and form(12, [1500]) == 1
+    assert form(20, [425] * 3) == 0 and form(12, [325] * 6) == 0 and form(12, [1100, 1100]) == 1 and form(20, [325] * 3) == 1
+    # prompts of a few tokens: what counts is the quarters that have queries, not the items
+    assert form(6, [4] * 64, [425] * 64) == 0 and form(8, [4] * 48, [900] * 48) == 0 and form(12, [4] * 32, [1500] * 32) == 0
+    assert form(16, [20] * 8, [1500] * 8) == 3 and form(20, [100] * 3, [1500] * 3) == 3 and form(20, [128] * 6, [1500] * 6) == 1
+    assert form(16, [128] * 6, [1500] * 6) == 2 and form(12, [70] * 12, [900] * 12) == 1
+    # heads that do not fill the XCDs evenly reach two rounds sooner, unless every quarter has queries
+    assert form(12, [70] * 6, [1500] * 6) == 2 and form(12, [70] * 6, [150] * 6) == 2 and form(16, [70] * 4, [150] * 4) == 3
+    with pytest.raises(wf.WfError):
+        form(8, [5, 0])
+
+
 def test_kernel_gelu_stays_close_to_the_erf_form():
     """The polynomial GELU of the bf16 epilogues, run on the host by the library's own code, against the oracle's erf
     form: absolute error <= 1.5e-4 for |z| <= 4 and <= 6e-5 |z| beyond (Phi saturates at 0.99994 past the clamp),

@@ -251,11 +251,15 @@ def test_attention(lens, n_heads, sharp, precision):
     assert _rel(got, ref) < (1e-2 if precision == wf.WF_PRECISION_BF16 else 1e-5)
 
 
-# The forms that share a query block's keys out: 32-query workgroups beyond one per compute unit (two per CU at most, streams
-# of 192 keys and more on average), then two key groups per 128-query item.  Last tiles of one key, streams of fewer tiles
-# than waves or groups, and the first call past the second form.
+# The forms that share a query block's keys out (wf.attention_form): 32-query items with two tile buffers a wave (3) or one
+# (2), two key groups per 128-query item (1), and calls just past them (0).  Last tiles of one key, streams of fewer tiles than
+# waves or groups, last quarters without queries, heads that leave XCD slots empty.
 SPLIT_CASES = [([1345], 8), ([321, 63, 385, 129, 1, 257], 8), ([1, 1100], 20), ([641, 65, 1000], 12), ([1025, 64, 193], 20), ([705, 640], 20), ([1409], 20),
-               ([1400, 193], 20)]
+               ([1400, 193], 20), ([1, 33, 129, 161, 97], 8), ([65, 1, 130, 31], 12), ([7] * 30, 6), ([425], 20), ([600, 1, 300], 6)]
+
+
+def test_attention_cases_reach_every_form():
+    assert {wf.attention_form(h, lens) for lens, h in SPLIT_CASES} == {0, 1, 2, 3}
 
 
 @pytest.mark.parametrize("lens,n_heads", SPLIT_CASES)
@@ -263,10 +267,10 @@ def test_attention_shared_keys(lens, n_heads):
     test_attention(lens, n_heads, 6.0, wf.WF_PRECISION_BF16)
 
 
-# 32-query workgroups ([900] x 8, [425] x 20, [1000, 300] x 12) and two key groups per 128-query item (the others)
-@pytest.mark.parametrize("lens,n_heads", [([900], 8), ([425], 20), ([1000, 300], 12), ([900], 20), ([1409], 20), ([641, 65, 1000], 12)])
+@pytest.mark.parametrize("lens,n_heads,form", [([900], 8, 3), ([425], 20, 2), ([1345], 8, 2), ([1000, 300], 12, 1), ([900], 20, 1), ([1409], 20, 1),
+                                               ([641, 65, 1000], 12, 1)])
 @pytest.mark.parametrize("mixed", [False, True])
-def test_attention_tile_of_minus_infinity(lens, n_heads, mixed):
+def test_attention_tile_of_minus_infinity(lens, n_heads, form, mixed):
     """Keys whose logits overflow to -inf weigh nothing, wherever their tile falls in the split of the keys; mixed: every
     other query is so small that its logits stay finite (about -4e37: they weigh nothing either), so that a wave meets both
     kinds at once.  The first tile stays ordinary: the forms that do not share keys out need one finite logit there."""
