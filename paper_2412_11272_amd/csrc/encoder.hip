@@ -413,11 +413,11 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
     char *qkv = (char *)e->qkv + (size_t)r0 * 3 * d * es;
     char *hbuf = (char *)e->h + (size_t)h_row0 * f * es;           // panel-aligned start of this lane's hidden activations
     const int panels = e->bf16 ? 1 : 0;                            // the fp32 debug kernels keep everything row-major
-    // A group of at most about a thousand tokens of a narrow model runs on the small-batch GEMM (all of its products, so
-    // that a row's arithmetic does not depend on which other streams share the batch), which also normalises its activation
-    // operand itself: the two LayerNorm launches of a block disappear and the MLP's hidden activations stay row-major.
+    // A batch of at most about a thousand tokens of a narrow model runs on the small-batch GEMM (all of its products, so
+    // that a row's arithmetic does not depend on which other streams share the batch; the whole batch decides, not the lane:
+    // a long stream may leave a short one a lane to itself), which also normalises its activation operand itself: the two LayerNorm launches of a block disappear and the MLP's hidden activations stay row-major.
     // (Every column tile recomputes the statistics of its rows: at d = 1280 that costs more than the LayerNorm kernel.)
-    const bool small = e->bf16 && gemm_small_applies(Mg, 3 * d, d) && gemm_small_applies(Mg, f, d) && gemm_small_applies(Mg, d, 3 * d);
+    const bool small = e->bf16 && gemm_small_applies(M, 3 * d, d) && gemm_small_applies(M, f, d) && gemm_small_applies(M, d, 3 * d);
     const int hpanels = small ? 0 : panels;
     int rc;
     {   // a1: conv1 + GELU as a GEMM over 3-frame windows (row maps hold absolute rows of the packed input)
