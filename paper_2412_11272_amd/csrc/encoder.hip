@@ -47,6 +47,7 @@ struct LayerDev {
 }  // namespace
 
 constexpr int kMaxLanes = 4;
+constexpr int kLaneTokens = 4096;         // tokens a lane has at least: a batch of fewer than twice as many runs on one
 
 struct wf_encoder : DevCtx {
   wf_config cfg{};
@@ -357,7 +358,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
   memcpy(h_off, frame_offset, (size_t)B * 4);
   memcpy(h_nf, n_frames, (size_t)B * 4);
   // ---- lanes: contiguous groups of streams with about the same number of tokens each
-  int n_lanes = std::min(std::min(e->n_lanes, B), std::max(1, M / 4096));
+  int n_lanes = std::min(std::min(e->n_lanes, B), std::max(1, M / kLaneTokens));
   if (!e->bf16) n_lanes = 1;             // the fp32 debug attention walks every row of the batch
   int lane_b[kMaxLanes + 1], lane_w0[kMaxLanes + 1];
   lane_b[0] = 0;
@@ -441,8 +442,9 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
       const double L = h_cu_seq[i + 1] - h_cu_seq[i];
       attn_flops += 4.0 * L * L * d;
     }
-    // Residual products of a few rows leave partial sums for the LayerNorm after them (one lane only: the memory is shared).
-    const bool may_split = e->bf16 && !small && n_lanes == 1;
+    // Residual products of a few rows leave partial sums for the LayerNorm after them: in batches that always run on one lane
+    // (the memory is shared between lanes, and the order of the sums must not depend on how many there are).
+    const bool may_split = e->bf16 && !small && M < 2 * kLaneTokens;
     Partials pt{};
     for (int l = 0; l < c.n_layers; ++l) {
       const LayerDev &w = e->layers[l];
