@@ -95,8 +95,12 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
   const int k0 = EPI == EPI_PARTIAL ? nkt * split / splits : 0;
   const int nk = EPI == EPI_PARTIAL ? nkt * (split + 1) / splits - k0 : nkt;
   const size_t a_bytes = p.a_panels ? (size_t)((p.M + 255) >> 8) * 256 * p.K * 2 : ((size_t)(p.M - 1) * p.lda + p.K) * 2;
-  const __amdgpu_buffer_rsrc_t ra =
-      __builtin_amdgcn_make_buffer_rsrc((void *)p.A, 0, AMODE == A_CONV3 ? (int)kOutside : (int)a_bytes, 0x00027000);
+  // The gathered operand may exceed what 32 bits reach (row_src counts rows of the whole packed batch), so its buffer starts at
+  // the tile's first window and the offsets are differences (windows come in ascending order, a tile's within a few rows).
+  int src0 = 0;
+  if constexpr (AMODE == A_CONV3) src0 = __builtin_amdgcn_readfirstlane(p.row_src[m0]);
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      (char *)p.A + (AMODE == A_CONV3 ? (long)src0 * p.C * 2 : 0L), 0, AMODE == A_CONV3 ? (int)kOutside : (int)a_bytes, 0x00027000);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       (void *)p.W, 0, (int)((size_t)(p.w_panels ? (p.N + 255) & ~255 : p.N) * p.K * 2), 0x00027000);
   const int piece = ((lane & 7) ^ ((4 * wave + (rr >> 1)) & 7)) << 4;       // (row >> 1) & 7 of every row this lane fetches
@@ -114,7 +118,7 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       const int row = min(m0 + (i * 4 + wave) * 8 + rr, p.M - 1);
-      aoff[i] = p.row_src[row] * p.C * 2 + piece;
+      aoff[i] = (p.row_src[row] - src0) * p.C * 2 + piece;
       aflags[i] = p.row_flags[row];
     }
   } else {

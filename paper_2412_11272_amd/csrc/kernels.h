@@ -46,7 +46,7 @@ struct GemmArgs {
   // multiple of 256); out_panels: a bf16 result is written in it.
   int32_t a_panels, w_panels, out_panels;
   // A_CONV3 only
-  const int32_t *row_src;
+  const int32_t *row_src;   // [M], ascending; -1 is a window that starts before the matrix, with its first tap masked
   const int32_t *row_flags;
   int32_t C;                // channels per tap; 3*C <= K, elements at k >= 3*C read as zero
   // EPI_BIAS_GELU_POS only

@@ -251,3 +251,24 @@ def test_lanes_do_not_change_a_bit(d, heads, d_mlp, tokens):
             assert torch.equal(out, outs[0])
     finally:
         enc.close()
+
+
+def test_packed_features_beyond_4_gib():
+    """The packed log-mel matrix is the only one that may be wider than the widest activation (2 x 80 bins against 128) and so
+    pass 4 GiB in a configuration that is accepted: 9400 streams of 30 s that all read the same frames give the same rows."""
+    import torch
+    shape = synth.Shape(80, 128, 1, 2, 128)
+    B, T = 9400, 3000
+    w = synth.make_weights(shape, 71)
+    mel = synth.make_mels(shape, [T], 72)[0]
+    assert B * T * shape.n_mels * 2 > 1 << 32
+    enc = wf.Encoder(wf.make_config(shape, 0, B, B * T, T, wf.WF_PRECISION_BF16), w, None)
+    try:
+        out, cu = enc.encode(torch.from_numpy(mel).cuda(), [0] * B, [T] * B, out_dtype=torch.bfloat16)
+        rows = out.view(B, T // 2, 128)
+        assert cu[-1] == B * (T // 2) and torch.isfinite(rows[0]).all()
+        assert torch.equal(rows[1:], rows[:1].expand(B - 1, -1, -1))
+        one, _ = enc.encode(torch.from_numpy(mel).cuda(), [0], [T])
+        assert H.rel_err(one.float().cpu().numpy(), rows[0].double().cpu().numpy()) <= H.BF16_TOL
+    finally:
+        enc.close()
