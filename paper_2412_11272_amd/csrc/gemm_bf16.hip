@@ -374,12 +374,19 @@ int large_tile_rows(int M, int N) {
   return t320 < t256 ? 320 : 256;
 }
 
+// Does a product run on the small-batch kernel?  (What is too narrow for the tiles below is refused by all of them.)
+bool takes_small(const GemmArgs &a, AMode amode, Epilogue epi) {
+  if (epi == EPI_PARTIAL || a.a_panels || a.out_panels) return false;
+  if (a.prefer_small || amode == A_LN) return true;
+  if (a.prefer_large) return false;
+  return gemm_small_applies(a.M, a.N, a.K) || (amode == A_PLAIN && a.N % 128 == 0 && gemm_small_few_rows(a.M, a.N, a.K, epi));
+}
+
 }  // namespace
 
 hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if (epi != EPI_PARTIAL && (a.prefer_small || (!a.prefer_large && gemm_small_applies(a.M, a.N, a.K)) || amode == A_LN) && !a.a_panels && !a.out_panels)
-    return launch_gemm_small(a, amode, epi, s);
+  if (takes_small(a, amode, epi)) return launch_gemm_small(a, amode, epi, s);
   if (amode == A_LN) return hipErrorInvalidValue;      // the fused LayerNorm operand exists in the small-batch kernel only
   if (a.N % 128 != 0 || a.K % BK != 0 || a.K <= 0) return hipErrorInvalidValue;
   // operands are addressed with 32-bit byte offsets from their base

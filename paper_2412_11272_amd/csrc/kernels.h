@@ -101,6 +101,7 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
 // Whether a product of a small batch goes there depends on its width and depth only, not on the number of rows.
 constexpr int32_t kSmallRows = 1024;
 bool gemm_small_applies(int32_t M, int32_t N, int32_t K);
+bool gemm_small_few_rows(int32_t M, int32_t N, int32_t K, Epilogue epi);      // plain products of a few rows, any width
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 // products with at most one tile per compute unit, and convolutions whose taps are no whole K steps
 bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K);

@@ -112,6 +112,14 @@ def test_linear_bf16_one_tile_per_cu(M, N, K, epi):
     _linear_case(M, N, K, epi, 300 + M)
 
 
+# Both sides of the limit up to which products of a few rows run on the small-batch kernel (one 32 x 32 tile per CU, 4 MB of
+# weights unless the result is a residual update)
+@pytest.mark.parametrize("M,N,K,epi", [(M, N, K, epi) for N, K, m in ((768, 768, 320), (1024, 1024, 256), (1280, 1280, 192), (2048, 1024, 128), (1152, 896, 224))
+                                       for M in (m, m + 1) for epi in (0, 1, 2)] + [(192, 1280, 5120, 2), (193, 1280, 5120, 2), (31, 2176, 1024, 0)])
+def test_linear_bf16_few_rows(M, N, K, epi):
+    _linear_case(M, N, K, epi, 500 + M + N + epi)
+
+
 @pytest.mark.parametrize("N,K", [(1280, 5120), (3072, 768)])
 def test_linear_rows_do_not_depend_on_the_kernel(N, K):
     """Every tile of the pipelined and the large-batch kernels adds a row up in the same order: the first rows of a product
