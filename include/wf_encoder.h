@@ -201,11 +201,19 @@ int wf_device_info(int32_t *compute_units, int32_t *clock_khz);
 int wf_gemm_tile_map(int32_t M, int32_t N, int32_t tile_m, int32_t tile_n, int32_t *units, int32_t capacity);
 
 /*
- * Diagnostic, host only: the tile (rows x columns of the result per workgroup) the bf16 MFMA GEMM picks for a plain
- * M x N product: 320 x 256 or 256 x 256 for large batches (whichever finishes its last round of the chip earlier),
- * 128 x 128 below that, 0 x 0 when M is small enough for the small-batch kernel.  N must be a multiple of 128.
+ * Diagnostic, host only: the tile (rows x columns of the result per workgroup) the large-batch bf16 GEMM takes for a plain
+ * M x N product: 320 x 256 or 256 x 256 (whichever finishes its last round of the chip earlier), 128 x 128 below that,
+ * 0 x 0 up to 1024 rows.  N must be a multiple of 128.  Products that leave each compute unit at most one tile run on other
+ * kernels, which depends on their depth K as well: see wf_gemm_kernel_choice.
  */
 int wf_gemm_tile_choice(int32_t M, int32_t N, int32_t *tile_m, int32_t *tile_n);
+
+/*
+ * Diagnostic, host only: the kernel a wf_op_linear call in bf16 runs on and its tile: 0 = small-batch kernel (tile 0 x 0: 32
+ * rows, columns by the number of workgroups), 1 = pipelined kernel (at most one tile per compute unit), 2 = large-batch
+ * kernels.  Same decision code as the launch.  Negative WF_E_* code on bad arguments.
+ */
+int wf_gemm_kernel_choice(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t *tile_m, int32_t *tile_n);
 
 /*
  * Diagnostic, host only: the form the bf16 attention takes for B streams of cu_q (HOST [B+1] prefix sums) queries over cu_kv

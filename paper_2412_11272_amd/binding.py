@@ -101,7 +101,7 @@ EXPORTS = ["wf_encoder_create", "wf_encode_batch", "wf_encoder_destroy", "wf_las
            "wf_rounds_destroy", "wf_run_rounds",
            "wf_beam_pruner_create", "wf_beam_pruner_step", "wf_beam_pruner_reset", "wf_beam_prune_session",
            "wf_beam_pruner_destroy", "wf_op_attention_noalloc",
-           "wf_encoder_set_graphs", "wf_encoder_graph_stats", "wf_gemm_tile_map", "wf_gemm_tile_choice", "wf_attention_form", "wf_gelu_host", "wf_device_info", "wf_op_ln_linear"]
+           "wf_encoder_set_graphs", "wf_encoder_graph_stats", "wf_gemm_tile_map", "wf_gemm_tile_choice", "wf_gemm_kernel_choice", "wf_attention_form", "wf_gelu_host", "wf_device_info", "wf_op_ln_linear"]
 
 
 def lib() -> C.CDLL:
@@ -153,6 +153,7 @@ def lib() -> C.CDLL:
                                   C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
     L.wf_gemm_tile_map.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, _ip, C.c_int32]
     L.wf_gemm_tile_choice.argtypes = [C.c_int32, C.c_int32, _ip, _ip]
+    L.wf_gemm_kernel_choice.argtypes = [C.c_int32] * 4 + [_ip, _ip]
     L.wf_attention_form.argtypes = [_ip, _ip, C.c_int32, C.c_int32]
     L.wf_gelu_host.argtypes = [C.POINTER(C.c_float), C.POINTER(C.c_float), C.c_int32]
     L.wf_encoder_set_graphs.argtypes = [C.c_void_p, C.c_int32]
@@ -590,10 +591,19 @@ def gemm_tile_map(M: int, N: int, tile_m: int = 256, tile_n: int = 256) -> np.nd
 
 
 def gemm_tile_choice(M: int, N: int) -> tuple:
-    """(tile rows, tile columns) the bf16 MFMA GEMM picks for an M x N product; (0, 0) = small-batch kernel (host only)."""
+    """(tile rows, tile columns) of the large-batch bf16 GEMM for an M x N product; (0, 0) up to 1024 rows (host only)."""
     tm, tn = C.c_int32(0), C.c_int32(0)
     _check(lib().wf_gemm_tile_choice(M, N, C.byref(tm), C.byref(tn)))
     return tm.value, tn.value
+
+
+def gemm_kernel_choice(M: int, N: int, K: int, epilogue: int = 0) -> tuple:
+    """(kernel, tile rows, tile columns) op_linear takes in bf16: kernel 0 small-batch (tile 0 x 0), 1 pipelined, 2 large-batch
+    (host only)."""
+    tm, tn = C.c_int32(0), C.c_int32(0)
+    kernel = lib().wf_gemm_kernel_choice(M, N, K, epilogue, C.byref(tm), C.byref(tn))
+    _check(min(kernel, 0))
+    return kernel, tm.value, tn.value
 
 
 def attention_form(n_heads: int, q_lens: Sequence[int], kv_lens: Optional[Sequence[int]] = None) -> int:

@@ -442,14 +442,28 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   }
 }
 
-// Diagnostic: tile rows x columns of the kernels of this file for a plain M x N product (0 x 0: a small batch, which never
-// reaches them; products with at most one tile per compute unit run on the pipelined kernel and its tiles instead).
+// Diagnostic: tile rows x columns that the kernels of this file take for a plain M x N product (0 x 0 up to 1024 rows, where
+// few products reach them); whether a product of some depth does is gemm_kernel_choice's business.
 void gemm_tile_choice(int32_t M, int32_t N, int32_t *bm, int32_t *bn) {
   GemmArgs a{};
   a.M = M; a.N = N;
   if (M <= kSmallRows) { *bm = 0; *bn = 0; }
   else if (!use_large_tile(a)) { *bm = 128; *bn = 128; }
   else { *bm = large_tile_rows(M, N); *bn = 256; }
+}
+
+// Diagnostic: the kernel wf_op_linear's product runs on and its tile: 0 small-batch (32 rows, as many columns as leave enough
+// workgroups: 0 x 0), 1 pipelined, 2 the kernels of this file.
+int gemm_kernel_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *bm, int32_t *bn) {
+  GemmArgs a{};
+  a.M = M; a.N = N; a.K = K;
+  *bm = 0; *bn = 0;
+  if (takes_small(a, A_PLAIN, epi)) return 0;
+  if (gemm_pipe_tile(M, N, K, bm, bn)) return 1;
+  const bool big = use_large_tile(a);
+  *bm = big ? large_tile_rows(M, N) : 128;
+  *bn = big ? 256 : 128;
+  return 2;
 }
 
 // Diagnostic: the work units the direct-load GEMM launches for an M x N result with bm x bn tiles, as

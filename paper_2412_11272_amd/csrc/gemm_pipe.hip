@@ -339,7 +339,14 @@ int gemm_split_choice(int32_t M, int32_t N, int32_t K) {
   return M > 0 && N % 64 == 0 && K % 64 == 0 ? pick_split(M, N, K).parts : 1;
 }
 
-bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K) { return pick_tile(M, N, K) >= 0; }
+bool gemm_pipe_tile(int32_t M, int32_t N, int32_t K, int32_t *bm, int32_t *bn) {
+  const int t = pick_tile(M, N, K);
+  if (t < 0) return false;
+  if (bm) *bm = kTiles[t].bm;
+  if (bn) *bn = kTiles[t].bn;
+  return true;
+}
+bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K) { return gemm_pipe_tile(M, N, K, nullptr, nullptr); }
 
 // The logits of a few rows: the product streams the embedding matrix, so a row tile no taller than the batch and a column tile
 // that gives every compute unit one (64 x 51 866 x 1280: 43 -> 33 us, 1 x 51 865 x 512: 16.6 -> 13.7).

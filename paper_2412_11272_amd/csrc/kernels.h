@@ -105,6 +105,7 @@ bool gemm_small_few_rows(int32_t M, int32_t N, int32_t K, Epilogue epi);      //
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 // products with at most one tile per compute unit, and convolutions whose taps are no whole K steps
 bool gemm_pipe_applies(int32_t M, int32_t N, int32_t K);
+bool gemm_pipe_tile(int32_t M, int32_t N, int32_t K, int32_t *bm, int32_t *bn);      // the same, with the tile it takes
 bool gemm_pipe_logits_applies(int32_t M, int32_t N);      // EPI_BIAS_F32
 hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 // Parts the reduction of a residual product should be cut into (1: none); k_splits * M * N <= kPartialFloats
@@ -130,6 +131,7 @@ hipError_t launch_embed(const void *table, int table_bf16, const float *pos, con
 int attention_q_tile();     // query rows per attention work item
 int gemm_dl_tile_map(int32_t M, int32_t N, int32_t bm, int32_t bn, int32_t *units, int32_t cap);   // diagnostic, host only
 void gemm_tile_choice(int32_t M, int32_t N, int32_t *bm, int32_t *bn);                                                  // diagnostic, host only
+int gemm_kernel_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *bm, int32_t *bn);                        // diagnostic, host only
 
 // fp32 debug path ------------------------------------------------------------------------------
 hipError_t launch_gemm_f32(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);

@@ -271,3 +271,27 @@ def test_prefill_cross_attention_forms(heads, prompts, enc_len, form):
         assert H.rel_err(got["hidden"].cpu().numpy(), ref_h) <= H.BF16_TOL and H.rel_err(got["logits"].cpu().numpy(), ref_l) <= H.BF16_TOL
     finally:
         dec.close()
+
+
+@pytest.mark.parametrize("n_vocab,streams", [(1000, 70), (51865, 65), (300, 64), (51866, 3)])
+def test_logits_rows_of_odd_length(n_vocab, streams):
+    """Logits go straight to rows of n_vocab values: up to 64 streams from the pipelined kernel, beyond that from the 128 x 128
+    (1000 ids) and 256 x 256 tiles (51865), none of them writing past a row's end."""
+    import torch
+    shape = synth.DecoderShape(128, 1, 2, 128, n_vocab, 16)
+    w = synth.make_decoder_weights(shape, 81, affine_random=True)
+    enc_lens, prompts = [3 + i % 4 for i in range(streams)], [1 + i % 3 for i in range(streams)]
+    cu = np.concatenate([[0], np.cumsum(enc_lens)]).astype(np.int32)
+    enc = synth.make_enc_states(int(cu[-1]), 128, 82)
+    tokens = synth.make_prompts(prompts, n_vocab, 83)
+    _, ref, _ = D.prefill_batch(w, 2, tokens, enc, cu)
+    dec = wf.Decoder(shape, w, streams, int(cu[-1]), sum(prompts), wf.WF_PRECISION_BF16)
+    try:
+        room = torch.full(((streams + 1) * n_vocab,), -7.5, device="cuda")
+        logits = room[:streams * n_vocab].view(streams, n_vocab)
+        dec.prefill(tokens, cu, dec.cross_kv(torch.from_numpy(enc).cuda().bfloat16()), logits=logits)
+        torch.cuda.synchronize()
+        assert H.rel_err(logits.cpu().numpy(), ref) <= H.BF16_TOL
+        assert bool((room[streams * n_vocab:] == -7.5).all())
+    finally:
+        dec.close()

@@ -135,7 +135,7 @@ def test_gemm_work_units_cover_every_tile_exactly_once(M, N, tm, tn):
 
 
 def test_gemm_tile_choice_follows_the_last_round_of_the_chip():
-    """Small batches -> small-batch kernel; in-between -> 128 x 128; large -> 320 or 256 rows, whichever needs fewer
+    """Up to 1024 rows -> none of the large-batch tiles; in-between -> 128 x 128; large -> 320 or 256 rows, whichever needs fewer
     (weighted) rounds of 256 workgroups.  The headline configuration's four projections all take 320 rows."""
     assert wf.gemm_tile_choice(75, 384) == (0, 0) and wf.gemm_tile_choice(1024, 5120) == (0, 0)
     assert wf.gemm_tile_choice(6400, 1280) == (128, 128) and wf.gemm_tile_choice(2600, 3072) == (128, 128)
@@ -147,6 +147,18 @@ def test_gemm_tile_choice_follows_the_last_round_of_the_chip():
     assert wf.gemm_tile_choice(12000, 5120) == (320, 256)
     with pytest.raises(wf.WfError):
         wf.gemm_tile_choice(100, 100)
+
+
+def test_gemm_kernel_choice_of_few_and_medium_rows():
+    """Products of a few rows: the small-batch kernel up to one 32 x 32 tile per CU and 4 MB of weights, whatever the depth for
+    a residual update; then the pipelined kernel's smallest tile with at most one per CU; then two 128 x 128 per CU."""
+    pick = wf.gemm_kernel_choice
+    assert pick(320, 768, 768) == (0, 0, 0) and pick(321, 768, 768)[0] == 1 and pick(192, 1280, 1280)[0] == 0 and pick(193, 1280, 1280)[0] == 1
+    assert pick(1, 3072, 768) == (1, 32, 64) and pick(100, 1280, 5120, 0)[0] == 1 and pick(100, 1280, 5120, 2)[0] == 0
+    assert pick(1024, 512, 512) == (0, 0, 0) and pick(1024, 5120, 1280)[0] == 2 and pick(1025, 512, 512) == (1, 64, 64)
+    assert pick(2600, 1024, 4096) == (1, 96, 128) and pick(2600, 3072, 1024) == (2, 128, 128) and pick(10240, 1280, 5120)[0] == 2
+    with pytest.raises(wf.WfError):
+        pick(100, 100, 64)
 
 
 def test_attention_form_follows_the_busy_workgroups():

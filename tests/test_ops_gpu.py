@@ -19,20 +19,21 @@ def _rel(got, ref):
 
 
 # M spans: one partial small tile, several small tiles + ragged tail, enough rows for the large tile, and
-# (the last two) the row count of a 64-stream prompt prefill, where the small tile has to fill the chip
+# the row count of a 64-stream prompt prefill, where the small tile has to fill the chip
 LINEAR_SHAPES = [(75, 384, 384), (300, 1152, 384), (1000, 128, 1536), (257, 256, 64),
                  (12500, 3840, 1280), (12345, 1280, 5120), (12301, 5120, 1280),
                  (6401, 1280, 1280), (6400, 1280, 5120), (10001, 2560, 640),
-                 # at most one 128 x 128 tile per CU: the four-stage operand ring, incl. its shortest K (4 and 5 steps)
+                 # at most one tile per CU: the pipelined kernel, incl. reductions as short as its operand ring
                  (2600, 1024, 4096), (4951, 768, 256), (1500, 2048, 320)]
 
 
 def test_linear_shapes_reach_every_tile_family():
-    """Small-batch kernel, 128 x 128, 256 x 256 and 320 x 256 tiles (the last both with streaming stores, result
-    >= 64 MB, and with plain ones) all occur among the shapes of test_linear_bf16."""
-    picks = {(M, N): wf.gemm_tile_choice(M, N) for M, N, _ in LINEAR_SHAPES}
-    assert set(picks.values()) == {(0, 0), (128, 128), (256, 256), (320, 256)}
-    assert picks[(12500, 3840)] == (320, 256) and picks[(10001, 2560)] == (320, 256) and picks[(12301, 5120)] == (256, 256)
+    """Small-batch kernel, pipelined kernel, 128 x 128, 256 x 256 and 320 x 256 tiles (the last both with streaming stores,
+    result >= 64 MB, and with plain ones) all occur among the shapes of test_linear_bf16."""
+    picks = {s: wf.gemm_kernel_choice(*s) for s in LINEAR_SHAPES}
+    assert {p[0] for p in picks.values()} == {0, 1, 2}
+    assert {p[1:] for p in picks.values() if p[0] == 2} == {(128, 128), (256, 256), (320, 256)}
+    assert all(picks[s] == (2, 320, 256) for s in ((12500, 3840, 1280), (10001, 2560, 640))) and picks[(12301, 5120, 1280)] == (2, 256, 256)
 
 
 @pytest.mark.parametrize("M,N,K", LINEAR_SHAPES)
@@ -82,28 +83,36 @@ def _linear_case(M, N, K, epi, seed):
     torch.cuda.synchronize()
     got = out.float().cpu().numpy()
     assert np.all(np.isfinite(got)), (M, N, K, epi)
-    assert _rel(got, ref) < (5e-3 if epi != 2 else 2e-5), (M, N, K, epi, wf.gemm_tile_choice(M, N))
+    assert _rel(got, ref) < (5e-3 if epi != 2 else 2e-5), (M, N, K, epi, wf.gemm_kernel_choice(M, N, K, epi))
 
 
 def test_linear_bf16_at_the_edges_of_every_kernel_choice():
-    """Row counts on both sides of each switch of the launcher: small-batch kernel / 128 x 128 tile (1024 rows), one
-    tile per CU with four operand stages / two per CU (256 tiles of 128 x 128), 128 x 128 / large tile (160 tiles of
-    256 x 256), 256 / 320 rows; K loops of 1 to 5 steps; every epilogue."""
-    cases = [(1024, 256, 192), (1025, 256, 192), (1025, 128, 64), (4096, 1024, 256), (4097, 1024, 320),
-             (3840, 2560, 128), (4096, 2560, 128), (4097, 2560, 64), (5100, 2560, 256), (5121, 2560, 192),
-             (8191, 1280, 320), (8193, 1280, 64), (6400, 2560, 128), (6657, 2560, 192)]
-    picks = set()
-    for i, (M, N, K) in enumerate(cases):
-        picks.add(wf.gemm_tile_choice(M, N))
+    """Row counts on both sides of each switch of the launcher: small-batch / pipelined kernel (1024 rows of a narrow product),
+    pipelined kernel / two 128 x 128 workgroups per CU (256 tiles), 128 x 128 / large tile (160 tiles of 256 x 256),
+    256 / 320 rows; K loops of 1 to 5 steps; every epilogue."""
+    pipe, small, mid, big, tall = 1, (0, 0, 0), (2, 128, 128), (2, 256, 256), (2, 320, 256)
+    cases = [(1024, 256, 192, small), (1025, 256, 192, pipe), (1025, 128, 64, small), (2049, 128, 64, pipe), (4096, 1024, 256, pipe),
+             (4097, 1024, 320, mid), (3840, 2560, 128, mid), (4096, 2560, 128, big), (4097, 2560, 64, big), (5100, 2560, 256, big),
+             (5121, 2560, 192, big), (8191, 1280, 320, big), (8193, 1280, 64, big), (6400, 2560, 128, big), (6657, 2560, 192, tall)]
+    for i, (M, N, K, kernel) in enumerate(cases):
+        got = wf.gemm_kernel_choice(M, N, K)
+        assert (got[0] if kernel == pipe else got) == kernel, (M, N, K, got)
         for epi in (0, 1, 2):
             _linear_case(M, N, K, epi, 1000 + 3 * i + epi)
-    assert picks == {(0, 0), (128, 128), (256, 256), (320, 256)}
 
 
-# One shape per tile of the one-tile-per-CU kernel (smallest tile that leaves at most 256: 32 x 64 ... 192 x 256), row counts off
-# the tile's edges, reductions shorter than the LDS ring, and one row
+# At least one shape per tile of the one-tile-per-CU kernel (the smallest tile that leaves at most 256), row counts off the tile's
+# edges, reductions shorter than the LDS ring, one row (the first two run on the small-batch kernel)
 PIPE_SHAPES = [(1, 768, 64), (200, 768, 768), (425, 1280, 1280), (861, 768, 3072), (1203, 1280, 704), (1601, 1280, 640),
-               (2603, 1024, 192), (5001, 1024, 2048), (6399, 1280, 2560), (7301, 1280, 2560), (7900, 1280, 2624)]
+               (2603, 1024, 192), (5001, 1024, 2048), (6399, 1280, 2560), (7301, 1280, 2560), (7900, 1280, 2624),
+               (99, 3072, 1024), (1, 2176, 1024), (1101, 1280, 192), (4999, 768, 128), (9001, 1280, 2560)]
+
+
+def test_pipe_shapes_reach_every_tile():
+    picks = [wf.gemm_kernel_choice(*s) for s in PIPE_SHAPES]
+    assert [p[0] for p in picks] == [0, 0] + [1] * (len(picks) - 2)
+    assert {p[1:] for p in picks[2:]} == {(32, 64), (64, 64), (96, 64), (128, 64), (96, 128), (128, 128), (192, 128), (128, 256), (160, 256),
+                                          (192, 256)}
 
 
 @pytest.mark.parametrize("M,N,K", PIPE_SHAPES)
