@@ -58,6 +58,8 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
 // EARLY: gain and shift are requested together with the row.  For a few hundred rows a call is one chain of latencies, and
 // loading them after the statistics puts a second memory latency into it (425 x 1280: 6.2 -> 5.4 us); once the chip is full
 // the registers they occupy cost more (6361 x 1280: 12.6 us late, 17.3 early).
+// (The late form adds a piece up as it arrives: with the additions after all loads the compiler's other order of copies costs
+// large calls 13 %, 31 694 x 1280 52.6 -> 59.6 us.)
 // NP > 0: the residual product in front left its result as NP partial sums; they and its bias are added to the row first
 // (part after part: deterministic) and the new row is stored.
 template <typename TOUT, int MAXV, bool EARLY, int NP = 0>   // MAXV float4 per lane: d <= 256 * MAXV
@@ -73,12 +75,14 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
   const f32x4 *xr = (const f32x4 *)(x + (size_t)xrow * d);
   const f32x4 *gr = (const f32x4 *)g, *br = (const f32x4 *)b;
   f32x4 v[MAXV], gg[EARLY ? MAXV : 1], bb[EARLY ? MAXV : 1];
+  float sum = 0.0f;
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
     const int idx = lane + i * 64;
     if (idx < nv) {
       v[i] = xr[idx];
       if constexpr (EARLY) { gg[i] = gr[idx]; bb[i] = br[idx]; }
+      else sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
     }
   }
   if constexpr (NP > 0) {
@@ -107,10 +111,11 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
       }
     }
   }
-  float sum = 0.0f;
+  if constexpr (EARLY) {
 #pragma unroll
-  for (int i = 0; i < MAXV; ++i)
-    if (lane + i * 64 < nv) sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
+    for (int i = 0; i < MAXV; ++i)
+      if (lane + i * 64 < nv) sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
+  }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
   const float mu = sum / (float)d;
