@@ -169,8 +169,8 @@ int wf_encoder_kernel_stats(wf_encoder *enc, wf_kernel_stat *stats, int32_t n_st
 int wf_encoder_set_lanes(wf_encoder *enc, int32_t n_lanes);
 int wf_encoder_get_lanes(const wf_encoder *enc);
 /* Replay of small batches (opt-in, default off).  A batch that runs on one lane (fewer than 8192 tokens) consists
- * of 4 + 7 n_layers short dependent kernels (paper, Section "Operations": one stream's buffer per round is the
- * method's own case, 75 .. 750 tokens).  With wf_encoder_set_graphs(enc, 1), wf_encode_batch keeps up to 64 captured
+ * of 4 + 7 n_layers short dependent kernels, 4 + 5 n_layers where the products normalise their operand themselves (paper,
+ * Section "Operations": one stream's buffer per round is the method's own case, 75 .. 750 tokens).  With wf_encoder_set_graphs(enc, 1), wf_encode_batch keeps up to 64 captured
  * HIP graphs of that launch sequence, keyed on everything that shapes the launches or is baked into their arguments: B, every
  * n_frames[i] and frame_offset[i], mel_dev, out_dev and the two dtypes.  A key seen for the second time is captured
  * (on a stream of the encoder, never the caller's; no memset or memcpy node: each entry owns a device copy of its
@@ -245,7 +245,7 @@ int wf_gelu_host(const float *z, float *out, int32_t n);
  *                   out dtype WF_DTYPE_*; d % 4 == 0, d <= 2048.
  * wf_op_ln_linear   bf16 path, small batches only (M <= 1024, else WF_E_CAPACITY): out = epilogue(LayerNorm(x) . w^T + bias)
  *                   with x fp32 [M, K] normalised on the way into the product (K <= 2048), w bf16 [N, K] row-major,
- *                   out bf16 [M, N]; epilogue 0 or 1 as above.  What QKV and fc1 run as for a single stream's buffer.
+ *                   out bf16 [M, N]; epilogue 0 or 1 as above.  What QKV and fc1 of a narrow model run as for a single stream's buffer.
  * wf_op_attention   bidirectional softmax attention restricted to each stream, head size 64:
  *                   qkv [M, 3 * 64 * n_heads] (q | k | v), out [M, 64 * n_heads], cu_seqlens_host
  *                   [B+1] with cu_seqlens_host[0] == 0 and no empty stream.  Allocates a small

@@ -536,7 +536,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
 
   hipStream_t s = (hipStream_t)hip_stream;
   // ---- small batches: replay a captured graph of the same launch sequence.  A batch of a few thousand tokens is
-  // bound by the cost of issuing its 4 + 7 n_layers launches one by one; everything that shapes those launches or is
+  // bound by the cost of issuing its 4 + 5 or 7 n_layers launches one by one; everything that shapes those launches or is
   // baked into their arguments (stream lengths and offsets, the two caller buffers, the dtypes) is the cache key, so
   // a replay needs no upload at all: each entry keeps its own device copy of the index arrays.  A key is captured
   // the second time it is seen; other batches take the direct path below.

@@ -5,7 +5,8 @@
 // (BM / 2) x (BN / 2) quarter with v_mfma_f32_16x16x32_bf16.  K advances 64 at a time through a ring of LDS stages that
 // takes all of the LDS (2 to 8 stages), fragments are double-buffered in registers.  The arithmetic is that of the
 // large-batch kernels of gemm_bf16.hip (accumulators start from the bias, K in order, the same instruction), so a row's
-// bits do not depend on which of these kernels or tiles computes it.
+// bits do not depend on which of these kernels or tiles computes it, as long as its reduction is not cut (EPI_PARTIAL, a choice
+// that goes by the rows of the whole batch: a stream alone and beside others may then differ in the last bits of fp32 sums).
 //
 // What bounds it and why it is built this way (all figures from one card, weights not in the L2):
 //   * With one wave per SIMD nothing but the wave's own instruction order keeps the matrix pipe fed.  A global -> LDS load
@@ -294,9 +295,11 @@ hipError_t launch_index(int t, const GemmArgs &a, hipStream_t s) {
 // CU, whose epilogues overlap other tiles' K loops: always up to 128 x 128 (1.04 to 1.9 times, 64 .. 5400 rows), with larger
 // tiles when the reduction is at least twice as long as the result is wide, so that the K loop dominates (1.03 to 1.47; short
 // reductions lose up to 15 %: 6361 x 1280 x 1280 28.6 -> 32.8 us, 2600 x 3072 x 1024 20.5 -> 22.9) and there are at most
-// 10 240 rows: more come in two lanes, whose kernels share the chip, and there the compute units a kernel takes count as well
-// as its time (11 500 x 1024 x 4096 103 us on 184 units, 89 on 236: an encoder call 17.4 -> 17.7 ms; 9000 x 1280 x 5120: 27.0
-// -> 26.3).  -1: none.
+// 10 240 rows.  That limit is a compromise: a call that shares the chip with nothing gains beyond it too (an encoder call of
+// 11 000 rows of 768 on one lane 4.08 -> 3.74 ms without it, a prefill of 20 000 rows of 512 2.19 -> 2.04), two lanes of 11 000
+// rows each gain at 768 (6.62 -> 6.47 ms) and lose at 1024 (17.99 -> 18.10), where the compute units a kernel takes count as well
+// as its time.  (Lanes of 4096 to 10 240 rows keep the larger tiles: 9000 x 1280 in two lanes 15.1 ms with, 16.0 without.)
+// -1: none.
 int pick_tile(int M, int N, int K) {
   for (int t = 0; t < kTileCount; ++t) {
     if (N % kTiles[t].bn) continue;
@@ -364,7 +367,8 @@ hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   }
   int t = pick_tile(a.M, a.N, a.K);
   // A first convolution of many rows has four K steps or so: two stages per operand, so that two workgroups share a CU and one's
-  // epilogue runs beside the other's loads (about 22 800 x 1024 x 256: 137 -> 55 us against the four-stage form).
+  // epilogue runs beside the other's loads (22 800 x 1024 x 256: 34 us a launch; the kernel that staged its operands in registers
+  // took 49).
   if (t < 0 && amode == A_CONV3 && epi == EPI_BIAS_GELU && !a.a_panels && a.N % 128 == 0 && a.K % 64 == 0 && a.K > 0)
     return launch_tile<128, 128, 2, 2, false, EPI_BIAS_GELU, A_CONV3>(a, s);
   if (t < 0) t = kTile128;           // more than one tile per CU: convolutions whose taps are no whole K steps

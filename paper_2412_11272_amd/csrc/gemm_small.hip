@@ -2,7 +2,8 @@
 // method itself runs, Section "Operations"), where nothing is bound by the matrix pipe and everything by how long
 // the chain of dependent steps of one workgroup is and by how many workgroups share the work.
 //
-//   out = epilogue(A . W^T),  A [M, K], W [N, K], fp32 accumulation, M up to about a thousand rows.
+//   out = epilogue(A . W^T),  A [M, K], W [N, K], fp32 accumulation, M up to about a thousand rows of a narrow model, or few
+//   enough rows of any product (gemm_small_few_rows).
 //
 // Differences from the large-batch kernels of gemm_bf16.hip:
 //   * 32-row output tiles, 32, 64 or 128 columns wide (NB column blocks of 32), so that even a 75-token batch spreads
@@ -19,7 +20,7 @@
 //     element so that the variance does not cancel), then every chunk is (x - mean) * rstd * gamma + beta rounded
 //     to bf16 -- exactly what the LayerNorm kernel would have stored.  This removes two kernels per transformer
 //     block; with a few hundred tokens each kernel in the chain costs 5-7 us whatever it does.  Rows of at most 512 values
-//     (every model narrow enough for this file) go to gemm_ln_kernel below instead.
+//     (every model narrow enough for this file) go to gemm_ln_kernel below instead; deeper ones come from wf_op_ln_linear only.
 
 #include <algorithm>
 #include <mutex>
