@@ -15,9 +15,9 @@
 //                   to 8 decades below it, on the stored values (scaling and rounding are monotone); blocks whose
 //                   smallest value needs no clamp leave without touching their rows.
 //
-// What bounds it: VALU issue with too few waves to cover the waits.  20 k lane operations a frame (counted, idle
-// lanes included); the VALU of a SIMD is busy 54 % of the kernel, the LDS 25 % (a quarter of that bank conflicts), and the ten waves
-// a CU holds next to 30 KB of LDS a workgroup spend 45 % of their time at barriers and loads.  (The dense DFT on the fp32
+// What bounds it: VALU issue, with too few waves to cover all waits.  20 k lane operations a frame (counted, idle lanes
+// included); the VALU of a SIMD is busy 71 % of the kernel, the LDS 32 % (a quarter of that bank conflicts), and the ten waves a CU
+// holds next to 30 KB of LDS a workgroup spend 45 % of their time at barriers and loads.  (The dense DFT on the fp32
 // matrix cores that this replaced took 358 kflop a frame.)  55 625 frames of 128 filters: 333 -> 77 us per call (this kernel 47, the
 // clamp 14, the rest the upload of the stream table and the host's launches); one stream of 437 frames: 65 -> 17 us (8 + 4 on
 // the GPU, two launches, no upload).
