@@ -58,8 +58,8 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
 // EARLY: gain and shift are requested together with the row.  For a few hundred rows a call is one chain of latencies, and
 // loading them after the statistics puts a second memory latency into it (425 x 1280: 6.2 -> 5.4 us); once the chip is full
 // the registers they occupy cost more (6361 x 1280: 12.6 us late, 17.3 early).
-// (The late form adds a piece up as it arrives: with the additions after all loads the compiler's other order of copies costs
-// large calls 13 %, 31 694 x 1280 52.6 -> 59.6 us.)
+// (ADD: the late form of wide rows adds a piece up as it arrives.  With the additions after all loads the compiler's other order of
+// copies costs large calls 13 %, 31 694 x 1280 52.6 -> 59.6 us; rows of up to 512 values gain 5 % by it, 31 694 x 384 15.3 -> 14.5.)
 // NP > 0: the residual product in front left its result as NP partial sums; they and its bias are added to the row first
 // (part after part: deterministic) and the new row is stored.
 template <typename TOUT, int MAXV, bool EARLY, int NP = 0>   // MAXV float4 per lane: d <= 256 * MAXV
@@ -75,6 +75,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
   const f32x4 *xr = (const f32x4 *)(x + (size_t)xrow * d);
   const f32x4 *gr = (const f32x4 *)g, *br = (const f32x4 *)b;
   f32x4 v[MAXV], gg[EARLY ? MAXV : 1], bb[EARLY ? MAXV : 1];
+  constexpr bool ADD = !EARLY && NP == 0 && MAXV > 2;
   float sum = 0.0f;
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
@@ -82,7 +83,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
     if (idx < nv) {
       v[i] = xr[idx];
       if constexpr (EARLY) { gg[i] = gr[idx]; bb[i] = br[idx]; }
-      else sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
+      if constexpr (ADD) sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
     }
   }
   if constexpr (NP > 0) {
@@ -111,7 +112,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
       }
     }
   }
-  if constexpr (EARLY) {
+  if constexpr (!ADD) {
 #pragma unroll
     for (int i = 0; i < MAXV; ++i)
       if (lane + i * 64 < nv) sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
