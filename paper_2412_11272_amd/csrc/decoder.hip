@@ -269,7 +269,10 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
   const int n_work = build_work(h_cup, B, attention_q_tile(), h_work, cost.data());
   const size_t idx_ints = (size_t)2 * Pt + 3 * S1 + 2 * (size_t)n_work;
   hipStream_t s = (hipStream_t)hip_stream;
-  if ((rc = staging_submit(e, slot, e->idx_dev, idx_ints * 4, s))) return rc;
+  // What fits a launch's arguments needs no copy ahead of the first kernel (100 tokens, d = 512 295.9 -> 289.6 us).
+  InlineInts in{};
+  if (idx_ints <= (size_t)kInlineInts) in = InlineInts{e->idx_dev, hs, (int32_t)idx_ints};
+  else if ((rc = staging_submit(e, slot, e->idx_dev, idx_ints * 4, s))) return rc;
   const int32_t *d_tok = e->idx_dev, *d_pos = d_tok + Pt, *d_cup = d_tok + 2 * Pt, *d_cus = d_cup + S1, *d_last = d_cus + S1,
                 *d_work = d_last + S1;
 
@@ -277,7 +280,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
   const size_t es = e->es;
   {
     Scope sc(e, s, DC_EMBED, 0.0, (double)Pt * d * (es + 4 + 4));
-    hipError_t err = launch_embed(e->tok_emb, act_bf16, e->pos_emb, d_tok, d_pos, e->x, Pt, d, s);
+    hipError_t err = launch_embed(e->tok_emb, act_bf16, e->pos_emb, d_tok, d_pos, e->x, Pt, d, s, in);
     if (err != hipSuccess) return fail(WF_E_HIP, "embed launch: %s", hipGetErrorString(err));
   }
   // A few prompts on a narrow model: the three products that follow a LayerNorm run on the small-batch kernel, which

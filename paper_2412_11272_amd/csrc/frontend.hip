@@ -18,9 +18,9 @@
 // What bounds it: VALU issue, with too few waves to cover all waits.  20 k lane operations a frame (counted, idle lanes
 // included); the VALU of a SIMD is busy 71 % of the kernel, the LDS 32 % (a quarter of that bank conflicts), and the ten waves a CU
 // holds next to 30 KB of LDS a workgroup spend 45 % of their time at barriers and loads.  (The dense DFT on the fp32
-// matrix cores that this replaced took 358 kflop a frame.)  55 625 frames of 128 filters: 333 -> 77 us per call (this kernel 47, the
-// clamp 14, the rest the upload of the stream table and the host's launches); one stream of 437 frames: 65 -> 17 us (8 + 4 on
-// the GPU, two launches, no upload).
+// matrix cores that this replaced took 358 kflop a frame.)  55 625 frames of 128 filters: 333 -> 57 us per call (this kernel 47, the
+// clamp 10; 77 while the table of 64 streams came by a copy); one stream of 437 frames: 65 -> 17 us (8 + 4 on the GPU, two
+// launches, no upload).
 #include "../../include/wf_encoder.h"
 
 #include <hip/hip_runtime.h>
@@ -41,7 +41,7 @@ constexpr int kHop = 160, kNfft = 400, kBins = 201;
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kMaxMels = 256;
 constexpr int kMaxTaps = 2 * kBins + 2;        // every bin lies under at most two triangles
-constexpr int kInline = 16;                    // streams whose metadata ride in the kernel arguments
+constexpr int kInline = 64;                    // streams whose metadata ride in the kernel arguments (one per lane in fe_find)
 // Frames per workgroup.  16 frames on 128 threads keep both waves busy in every phase and leave room for five workgroups
 // per CU (30 KB of LDS); 8 frames on 256 threads halve the chain of a workgroup where the chip is not full anyway.
 constexpr int kFramesLarge = 16, kFramesSmall = 8;
@@ -90,10 +90,10 @@ __device__ __forceinline__ FeStream fe_stream(const FeArgs &p, int i) { return p
 
 __device__ __forceinline__ int fe_find(const FeArgs &p, int block) {
   if (p.streams) return p.block_stream[block];
-  int i = 0;                                   // a handful of independent compares instead of a dependent search
-#pragma unroll
-  for (int k = 1; k < kInline; ++k) i += (k < p.B && block >= p.local[k].block0) ? 1 : 0;
-  return i;
+  if (p.B == 1) return 0;
+  const int lane = threadIdx.x & 63;           // one stream per lane and one vote instead of a dependent search
+  const bool after = lane < p.B && block >= p.local[lane < p.B ? lane : 0].block0;
+  return __popcll(__ballot(after)) - 1;
 }
 
 // X[0..8] of 16 real values (W = exp(-2 pi i / 16)): re[1..7], im[1..7], and the real X[0] = re[0], X[8] = im[0].

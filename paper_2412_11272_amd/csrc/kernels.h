@@ -124,10 +124,20 @@ struct Partials {
 // out[i] = LayerNorm(x[rows[i]]), rows == NULL: x[i].  x is written only with partials and without rows.
 hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
                             int32_t M, int32_t d, float eps, hipStream_t s, Partials pt = {});
-hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s);
-// x[r, :] = table[tok[r], :] + pos[pos_idx[r], :]  (fp32 out; table bf16 or fp32, pos fp32)
+// The first kernel of a call may bring the call's index arrays along in its arguments (at most kInlineInts of them: a launch takes
+// 4 KB) and leave them at `dst` for the kernels after it, which spares the call a copy ahead of its first kernel.
+constexpr int32_t kInlineInts = 960;
+struct InlineInts {
+  int32_t *dst;             // device, n ints
+  const int32_t *src;       // host
+  int32_t n;                // 0: the arrays are on the device already
+};
+// (a.cu_frames, cu_seqlens, frame_offset and n_frames are the first 4 (B + 1) of the ints, in that order)
+hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s, InlineInts in = {});
+// x[r, :] = table[tok[r], :] + pos[pos_idx[r], :]  (fp32 out; table bf16 or fp32, pos fp32); tok and pos_idx are the first 2 rows
+// of the ints, in that order
 hipError_t launch_embed(const void *table, int table_bf16, const float *pos, const int32_t *tok, const int32_t *pos_idx,
-                        float *x, int32_t rows, int32_t d, hipStream_t s);
+                        float *x, int32_t rows, int32_t d, hipStream_t s, InlineInts in = {});
 int attention_q_tile();     // query rows per attention work item
 int gemm_dl_tile_map(int32_t M, int32_t N, int32_t bm, int32_t bn, int32_t *units, int32_t cap);   // diagnostic, host only
 void gemm_tile_choice(int32_t M, int32_t N, int32_t *bm, int32_t *bn);                                                  // diagnostic, host only

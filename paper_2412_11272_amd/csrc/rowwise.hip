@@ -1,5 +1,7 @@
 // Bandwidth-bound kernels: ragged pack + hush append (with the row maps the convolutions need) and
 // LayerNorm.  Both read and write every byte exactly once with 16-byte accesses.
+#include <cstring>
+
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -14,20 +16,22 @@ namespace {
 //           no left neighbour and the last no right neighbour (zero padding is per stream);
 //       (3) conv2 row map: token j of stream i reads frames 2j-1, 2j, 2j+1 of that stream.
 // One thread per 8 mel bins (threads [0, total_frames * n_mels/8)), then one thread per token.
-template <typename TIN, typename TOUT>
-__global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
+// The index arrays are read from cu_frames .. n_frames, wherever those lie (device memory or LDS).
+template <typename TIN, typename TOUT, typename TID>
+__device__ __forceinline__ void prep_thread(const PrepArgs &p, const int32_t *cu_frames, const int32_t *cu_seqlens,
+                                            const int32_t *frame_offset, const int32_t *n_frames) {
   const int cpr = p.n_mels >> 3;                       // 8-element chunks per frame
-  const long n_pack = (long)p.total_frames * cpr;
-  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const TID n_pack = (TID)p.total_frames * cpr;
+  const TID gid = (TID)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid < n_pack) {
-    const int r = (int)(gid / cpr), c = (int)(gid % cpr);
-    const int i = find_stream(p.cu_frames, p.B, r);
-    const int t = r - p.cu_frames[i];
-    const int T = p.n_frames[i];
-    const int Tp = p.cu_frames[i + 1] - p.cu_frames[i];
+    const int r = (int)(gid / cpr), c = (int)(gid - (TID)r * cpr);
+    const int i = find_stream(cu_frames, p.B, r);
+    const int t = r - cu_frames[i];
+    const int T = n_frames[i];
+    const int Tp = cu_frames[i + 1] - cu_frames[i];
     TOUT *dst = (TOUT *)p.packed + (size_t)r * p.n_mels + c * 8;
     if (t < T) {
-      const TIN *src = (const TIN *)p.mel + ((size_t)p.frame_offset[i] + t) * p.n_mels + c * 8;
+      const TIN *src = (const TIN *)p.mel + ((size_t)frame_offset[i] + t) * p.n_mels + c * 8;
 #pragma unroll
       for (int e = 0; e < 8; ++e) dst[e] = (TOUT)(float)src[e];
     } else {
@@ -41,15 +45,38 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
     }
     return;
   }
-  const long m = gid - n_pack;
-  if (m < p.M) {
-    const int i = find_stream(p.cu_seqlens, p.B, (int)m);
-    const int j = (int)m - p.cu_seqlens[i];
-    const int Tp = p.cu_frames[i + 1] - p.cu_frames[i];
-    p.tok_src[m] = p.cu_frames[i] + 2 * j - 1;
+  const TID m = gid - n_pack;
+  if (m < (TID)p.M) {
+    const int i = find_stream(cu_seqlens, p.B, (int)m);
+    const int j = (int)m - cu_seqlens[i];
+    const int Tp = cu_frames[i + 1] - cu_frames[i];
+    p.tok_src[m] = cu_frames[i] + 2 * j - 1;
     p.tok_flags[m] = (j == 0 ? 1 : 0) | (2 * j + 1 >= Tp ? 2 : 0);
     p.tok_pos[m] = j;
   }
+}
+
+template <typename TIN, typename TOUT>
+__global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
+  prep_thread<TIN, TOUT, long>(p, p.cu_frames, p.cu_seqlens, p.frame_offset, p.n_frames);
+}
+
+// The index arrays come along in the arguments; block 0 also leaves them on the device for the kernels that follow.
+struct IntsArg { int32_t n; int32_t v[kInlineInts]; };
+
+__device__ __forceinline__ void stage_ints(int32_t *lds, const IntsArg &a, int n, int32_t *dst) {
+  for (int i = threadIdx.x; i < n; i += 256) lds[i] = a.v[i];
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < a.n; i += 256) dst[i] = a.v[i];
+  __syncthreads();
+}
+
+template <typename TIN, typename TOUT>
+__global__ void __launch_bounds__(256) prep_inline_kernel(PrepArgs p, int32_t *dst, IntsArg a) {
+  __shared__ int32_t s[kInlineInts];
+  const int S1 = p.B + 1;
+  stage_ints(s, a, 4 * S1, dst);
+  prep_thread<TIN, TOUT, unsigned>(p, s, s + S1, s + 2 * S1, s + 3 * S1);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -152,14 +179,13 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
 
 // ---------------------------------------------------------------------------------------------
 // Decoder input: x[r, :] = table[tok[r], :] + pos[pos_idx[r], :], one thread per 4 features.
-template <typename TTAB>
-__global__ void __launch_bounds__(256) embed_kernel(const TTAB *__restrict__ table, const float *__restrict__ pos,
-                                                    const int32_t *__restrict__ tok, const int32_t *__restrict__ pos_idx,
-                                                    float *__restrict__ x, int rows, int d) {
+template <typename TTAB, typename TID>
+__device__ __forceinline__ void embed_thread(const TTAB *__restrict__ table, const float *__restrict__ pos, const int32_t *tok,
+                                             const int32_t *pos_idx, float *__restrict__ x, int rows, int d) {
   const int cpr = d >> 2;
-  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long)rows * cpr) return;
-  const int r = (int)(gid / cpr), c = (int)(gid % cpr) * 4;
+  const TID gid = (TID)blockIdx.x * blockDim.x + threadIdx.x;
+  if (gid >= (TID)rows * cpr) return;
+  const int r = (int)(gid / cpr), c = (int)(gid - (TID)r * cpr) * 4;
   const TTAB *t = table + (size_t)tok[r] * d + c;
   const f32x4 pe = *(const f32x4 *)(pos + (size_t)pos_idx[r] * d + c);
   f32x4 v;
@@ -168,14 +194,45 @@ __global__ void __launch_bounds__(256) embed_kernel(const TTAB *__restrict__ tab
   *(f32x4 *)(x + (size_t)r * d + c) = v;
 }
 
+template <typename TTAB>
+__global__ void __launch_bounds__(256) embed_kernel(const TTAB *__restrict__ table, const float *__restrict__ pos,
+                                                    const int32_t *__restrict__ tok, const int32_t *__restrict__ pos_idx,
+                                                    float *__restrict__ x, int rows, int d) {
+  embed_thread<TTAB, long>(table, pos, tok, pos_idx, x, rows, d);
+}
+
+template <typename TTAB>
+__global__ void __launch_bounds__(256) embed_inline_kernel(const TTAB *__restrict__ table, const float *__restrict__ pos,
+                                                           float *__restrict__ x, int rows, int d, int32_t *dst, IntsArg a) {
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < a.n; i += 256) dst[i] = a.v[i];
+  embed_thread<TTAB, unsigned>(table, pos, a.v, a.v + rows, x, rows, d);
+}
+
+// The caller's ints as a kernel argument.
+hipError_t take_ints(const InlineInts &in, int need, IntsArg *a) {
+  if (!in.dst || !in.src || in.n < need || in.n > kInlineInts) return hipErrorInvalidValue;
+  a->n = in.n;
+  memcpy(a->v, in.src, (size_t)in.n * 4);
+  return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t launch_embed(const void *table, int table_bf16, const float *pos, const int32_t *tok, const int32_t *pos_idx,
-                        float *x, int32_t rows, int32_t d, hipStream_t s) {
+                        float *x, int32_t rows, int32_t d, hipStream_t s, InlineInts in) {
   if (rows <= 0) return hipSuccess;
   if (d % 4 != 0) return hipErrorInvalidValue;
   const long n = (long)rows * (d / 4);
   const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+  if (in.n > 0) {
+    IntsArg a;
+    const hipError_t err = take_ints(in, 2 * rows, &a);
+    if (err != hipSuccess) return err;
+    if (table_bf16) hipLaunchKernelGGL(embed_inline_kernel<__bf16>, grid, block, 0, s, (const __bf16 *)table, pos, x, rows, d, in.dst, a);
+    else hipLaunchKernelGGL(embed_inline_kernel<float>, grid, block, 0, s, (const float *)table, pos, x, rows, d, in.dst, a);
+    return hipGetLastError();
+  }
   if (table_bf16) hipLaunchKernelGGL(embed_kernel<__bf16>, grid, block, 0, s, (const __bf16 *)table, pos, tok, pos_idx, x, rows, d);
   else hipLaunchKernelGGL(embed_kernel<float>, grid, block, 0, s, (const float *)table, pos, tok, pos_idx, x, rows, d);
   return hipGetLastError();
@@ -210,10 +267,20 @@ hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const
   return hipGetLastError();
 }
 
-hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s) {
+hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s, InlineInts in) {
   const long n = (long)a.total_frames * (a.n_mels / 8) + a.M;
   if (n <= 0) return hipSuccess;
   const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+  if (in.n > 0) {
+    IntsArg ints;
+    const hipError_t err = take_ints(in, 4 * (a.B + 1), &ints);
+    if (err != hipSuccess || n >= (1L << 31)) return err != hipSuccess ? err : hipErrorInvalidValue;
+#define WF_PREP(TI, TO) hipLaunchKernelGGL((prep_inline_kernel<TI, TO>), grid, block, 0, s, a, in.dst, ints)
+    if (packed_bf16) { if (a.mel_is_bf16) WF_PREP(__bf16, __bf16); else WF_PREP(float, __bf16); }
+    else { if (a.mel_is_bf16) WF_PREP(__bf16, float); else WF_PREP(float, float); }
+#undef WF_PREP
+    return hipGetLastError();
+  }
   if (packed_bf16) {
     if (a.mel_is_bf16) hipLaunchKernelGGL((prep_kernel<__bf16, __bf16>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((prep_kernel<float, __bf16>), grid, block, 0, s, a);
