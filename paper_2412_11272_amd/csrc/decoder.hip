@@ -290,6 +290,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
   auto resid = [&](int cls, const void *A, int K, const void *W, const float *bias) -> int {
     GemmArgs a{};
     a.A = A; a.W = W; a.bias = bias; a.M = Pt; a.N = d; a.K = K; a.lda = K; a.ldo = d;
+    a.prefer_small = e->bf16 && gemm_slice_applies(Pt, d, K, true);
     return run_resid(e, s, cls, a, e->x, e->part, e->bf16 && !small && !gemm_small_applies(Pt, d, K), &pt);
   };
   auto after_ln = [&](int cls, const float *g, const float *b, GemmArgs a, Epilogue ep) -> int {
@@ -301,6 +302,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
       a.A = e->u;
     }
     a.M = Pt; a.K = d; a.lda = d;
+    a.prefer_small = e->bf16 && gemm_slice_applies(Pt, a.N, d, false);
     return run_gemm(e, s, cls, a, small ? A_LN : A_PLAIN, ep, d, (int)es, Pt, d);
   };
   for (int l = 0; l < c.n_layers; ++l) {

@@ -420,21 +420,28 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
     // (Every column tile recomputes the statistics of its rows: at d = 1280 that costs more than the LayerNorm kernel.)
     const bool small = e->bf16 && gemm_small_applies(M, 3 * d, d) && gemm_small_applies(M, f, d) && gemm_small_applies(M, d, 3 * d);
     const int hpanels = small ? 0 : panels;
+    // A batch of a few hundred tokens of a wide model takes the same kernel for the products it is the faster one for (batches that
+    // always run on one lane: these products add a row up in another order).
+    auto place = [&](GemmArgs &a, bool may_cut = false) {
+      a.prefer_small = e->bf16 && (small || (M < 2 * kLaneTokens && gemm_slice_applies(a.M, a.N, a.K, may_cut)));
+      a.prefer_large = !a.prefer_small;
+    };
     int rc;
     {   // a1: conv1 + GELU as a GEMM over 3-frame windows (row maps hold absolute rows of the packed input)
       GemmArgs a{};
       a.A = e->packed; a.W = e->conv1_w; a.bias = e->conv1_b; a.out = G;
       a.M = Fg; a.N = d; a.K = e->k1p; a.lda = C; a.ldo = d;
       a.row_src = e->frame_src + f0; a.row_flags = e->frame_flags + f0; a.C = C;
-      a.prefer_small = small; a.prefer_large = !small;
+      place(a);
       if ((rc = run_gemm(e, ls, KC_CONV1, a, A_CONV3, EPI_BIAS_GELU, 3 * C, (int)es, Fg, C))) return rc;
     }
     {   // a2: conv2 (stride 2) + GELU + positions -> fp32 residual stream
       GemmArgs a{};
-      a.prefer_large = !small; a.A = e->G; a.W = e->conv2_w; a.bias = e->conv2_b; a.out = x;
+      a.A = e->G; a.W = e->conv2_w; a.bias = e->conv2_b; a.out = x;
       a.M = Mg; a.N = d; a.K = 3 * d; a.lda = d; a.ldo = d;
       a.row_src = e->tok_src + r0; a.row_flags = e->tok_flags + r0; a.C = d;
       a.pos = e->pos; a.row_pos = e->tok_pos + r0;
+      place(a);
       if ((rc = run_gemm(e, ls, KC_CONV2, a, A_CONV3, EPI_BIAS_GELU_POS, 3 * d, 4, Fg, d))) return rc;
     }
     double attn_flops = 0.0;
@@ -451,8 +458,9 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
       if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln1_g, w.ln1_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt))) return rc;
       {
         GemmArgs a{};
-        a.prefer_large = !small; a.A = u; a.W = w.wqkv; a.bias = w.bqkv; a.out = qkv; a.M = Mg; a.N = 3 * d; a.K = d; a.lda = d; a.ldo = 3 * d;
+        a.A = u; a.W = w.wqkv; a.bias = w.bqkv; a.out = qkv; a.M = Mg; a.N = 3 * d; a.K = d; a.lda = d; a.ldo = 3 * d;
         a.w_panels = panels;
+        place(a);
         if (small) { a.A = x; a.ln_g = w.ln1_g; a.ln_b = w.ln1_b; a.ln_eps = c.ln_eps; }
         if ((rc = run_gemm(e, ls, KC_QKV, a, small ? A_LN : A_PLAIN, EPI_BIAS, d, (int)es, Mg, d))) return rc;
       }
@@ -468,23 +476,26 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
       }
       {
         GemmArgs a{};
-        a.prefer_large = !small; a.A = u; a.W = w.wo; a.bias = w.bo; a.M = Mg; a.N = d; a.K = d; a.lda = d; a.ldo = d;
+        a.A = u; a.W = w.wo; a.bias = w.bo; a.M = Mg; a.N = d; a.K = d; a.lda = d; a.ldo = d;
         a.w_panels = panels;
+        place(a, true);
         if ((rc = run_resid(e, ls, KC_OUT, a, x, e->part, may_split, &pt))) return rc;
       }
       if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln2_g, w.ln2_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt))) return rc;
       {   // fc1 writes the hidden activations as [rows/256][f/64][256][64] panels: one contiguous 32 KB block per
           // K step of fc2's activation operand (whose rows would otherwise be 2 f bytes apart in memory)
         GemmArgs a{};
-        a.prefer_large = !small; a.A = u; a.W = w.w1; a.bias = w.b1; a.out = hbuf; a.M = Mg; a.N = f; a.K = d; a.lda = d; a.ldo = f;
+        a.A = u; a.W = w.w1; a.bias = w.b1; a.out = hbuf; a.M = Mg; a.N = f; a.K = d; a.lda = d; a.ldo = f;
         a.out_panels = hpanels; a.w_panels = panels;
+        place(a);
         if (small) { a.A = x; a.ln_g = w.ln2_g; a.ln_b = w.ln2_b; a.ln_eps = c.ln_eps; }
         if ((rc = run_gemm(e, ls, KC_FC1, a, small ? A_LN : A_PLAIN, EPI_BIAS_GELU, d, (int)es, Mg, d))) return rc;
       }
       {
         GemmArgs a{};
-        a.prefer_large = !small; a.A = hbuf; a.W = w.w2; a.bias = w.b2; a.M = Mg; a.N = d; a.K = f; a.lda = f; a.ldo = d;
+        a.A = hbuf; a.W = w.w2; a.bias = w.b2; a.M = Mg; a.N = d; a.K = f; a.lda = f; a.ldo = d;
         a.a_panels = hpanels; a.w_panels = panels;
+        place(a, true);
         if ((rc = run_resid(e, ls, KC_FC2, a, x, e->part, may_split, &pt))) return rc;
       }
     }

@@ -376,10 +376,11 @@ int large_tile_rows(int M, int N) {
 
 // Does a product run on the small-batch kernel?  (What is too narrow for the tiles below is refused by all of them.)
 bool takes_small(const GemmArgs &a, AMode amode, Epilogue epi) {
-  if (epi == EPI_PARTIAL || a.a_panels || a.out_panels) return false;
+  if (epi == EPI_PARTIAL) return false;
   if (a.prefer_small || amode == A_LN) return true;
-  if (a.prefer_large) return false;
-  return gemm_small_applies(a.M, a.N, a.K) || (amode == A_PLAIN && a.N % 128 == 0 && gemm_small_few_rows(a.M, a.N, a.K, epi));
+  if (a.prefer_large || a.a_panels || a.out_panels) return false;
+  if (gemm_small_applies(a.M, a.N, a.K)) return amode != A_PLAIN || a.N % 64 || (long)((a.M + 63) / 64) * (a.N / 64) <= 256 || !gemm_pipe_applies(a.M, a.N, a.K);
+  return amode == A_PLAIN && a.N % 128 == 0 && gemm_small_few_rows(a.M, a.N, a.K, epi);
 }
 
 }  // namespace

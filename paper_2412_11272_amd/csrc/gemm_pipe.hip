@@ -20,6 +20,7 @@
 // Against the 128 x 128 kernel with two workgroups per CU it replaced (us, same shapes): 3156 x 768 x 3072 31.8 -> 22,
 // 2600 x 1024 x 4096 41 -> 28.5, 6400 x 1280 x 5120 86 -> 74; against the small-batch kernel at 425 rows: 1280 x 5120
 // 28.9 -> 20.5, 3840 x 1280 16.9 -> 10.2.
+#include <cmath>
 #include <mutex>
 
 #include "gemm_epilogue.h"
@@ -316,21 +317,21 @@ int pick_tile(int M, int N, int K) {
 // 1025 rows of d = 768, 1024, 1280: the K step of the kernel's header, dearer in the two largest tiles, and 1.7 ns per
 // thousand result values and part; an uncut product pays for the residual once as well.  It has to promise 0.7 us.
 // 425 x 1280 x 5120: 23.4 -> 14.2 us (LayerNorm + 0.5), 425 x 1280 x 1280: 10.0 -> 8.8 us.
-struct Split { int tile, parts; };
+struct Split { int tile, parts; double us; };
 Split pick_split(int M, int N, int K) {
   const int t1 = pick_tile(M, N, K), nk = K >> 6;
-  if (t1 < 0 || t1 > kTile128 || N > 2048) return {t1, 1};      // (the LayerNorm takes rows of up to 2048 values)
+  if (t1 < 0 || t1 > kTile128 || N > 2048) return {t1, 1, INFINITY};      // (the LayerNorm takes rows of up to 2048 values)
   auto step = [](int t) { return (0.07 + 0.00875 * (kTiles[t].bm + kTiles[t].bn) / 8) * (t < 4 ? 1.0 : t == 4 ? 1.15 : 1.35); };
   const double part = 1.7e-6 * M * N;
-  Split best{t1, 1};
-  double cost = nk * step(t1) + part + 0.25 - 0.7;
+  Split best{t1, 1, nk * step(t1) + part + 0.25};
+  double cost = best.us - 0.7;
   for (int t = 0; t <= kTile128; ++t) {
     if (N % kTiles[t].bn) continue;
     const long tiles = (long)((M + kTiles[t].bm - 1) / kTiles[t].bm) * (N / kTiles[t].bn);
     for (int parts = 2; parts <= 4; ++parts) {
       if (tiles * parts > 256 || nk < 2 * parts || (int64_t)parts * M * N > kPartialFloats) continue;
       const double c = (nk + parts - 1) / parts * step(t) + parts * part;
-      if (c < cost) { cost = c; best = {t, parts}; }
+      if (c < cost) { cost = c; best = {t, parts, c}; }
     }
   }
   return best;
@@ -340,6 +341,10 @@ Split pick_split(int M, int N, int K) {
 
 int gemm_split_choice(int32_t M, int32_t N, int32_t K) {
   return M > 0 && N % 64 == 0 && K % 64 == 0 ? pick_split(M, N, K).parts : 1;
+}
+
+double gemm_cut_estimate(int32_t M, int32_t N, int32_t K) {
+  return M > 0 && N % 64 == 0 && K % 64 == 0 ? pick_split(M, N, K).us : INFINITY;
 }
 
 bool gemm_pipe_tile(int32_t M, int32_t N, int32_t K, int32_t *bm, int32_t *bn) {

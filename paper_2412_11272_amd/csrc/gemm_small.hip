@@ -1,26 +1,15 @@
-// bf16 MFMA GEMM for SMALL row counts (a single stream's buffer, a few hundred tokens: the case the paper's
+// bf16 MFMA GEMMs for SMALL row counts (a single stream's buffer, a few hundred tokens: the case the paper's
 // method itself runs, Section "Operations"), where nothing is bound by the matrix pipe and everything by how long
 // the chain of dependent steps of one workgroup is and by how many workgroups share the work.
 //
 //   out = epilogue(A . W^T),  A [M, K], W [N, K], fp32 accumulation, M up to about a thousand rows of a narrow model, or few
-//   enough rows of any product (gemm_small_few_rows).
+//   enough rows of any product (gemm_small_few_rows, gemm_slice_applies).
 //
-// Differences from the large-batch kernels of gemm_bf16.hip:
-//   * 32-row output tiles, 32, 64 or 128 columns wide (NB column blocks of 32), so that even a 75-token batch spreads
-//     over dozens of compute units (75 x 384: 36 workgroups instead of 3); the launcher takes the widest tile that
-//     still leaves about 160 workgroups, because every column tile re-reads (and with A_LN re-normalises) the same
-//     32 activation rows;
-//   * the four waves of a workgroup split the reduction: in every 64-deep K step wave w multiplies the k slice
-//     [16 w, 16 w + 16) with one 32x32x16 MFMA, and the four partial tiles are added in a fixed order through LDS
-//     at the end (deterministic);
-//   * operand chunks are requested eight (widest tile: four) K steps ahead into registers, so the K loop runs at the rate the chunks
-//     arrive instead of one memory latency per step, and two K steps are staged in LDS per barrier;
-//   * A_LN: the activation operand is LayerNorm(x) of an fp32 matrix x, normalised on the way into LDS.  The
-//     workgroup first computes mean and 1/sqrt(var + eps) of its 32 rows (one pass, sums shifted by the row's first
-//     element so that the variance does not cancel), then every chunk is (x - mean) * rstd * gamma + beta rounded
-//     to bf16 -- exactly what the LayerNorm kernel would have stored.  This removes two kernels per transformer
-//     block; with a few hundred tokens each kernel in the chain costs 5-7 us whatever it does.  Rows of at most 512 values
-//     (every model narrow enough for this file) go to gemm_ln_kernel below instead; deeper ones come from wf_op_ln_linear only.
+//   gemm_slice_kernel   the operand is in memory as it is needed: plain rows or the windows of a convolution
+//   gemm_ln_kernel      the operand is LayerNorm(x) of an fp32 matrix x with rows of at most 512 values (every model narrow enough
+//                       for this file), normalised on the way in.  This removes two kernels per transformer block; with a few
+//                       hundred tokens each kernel in the chain costs 3-5 us whatever it does.
+//   gemm_small_kernel   the same for longer rows (wf_op_ln_linear only)
 
 #include <algorithm>
 #include <mutex>
@@ -37,7 +26,14 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int SBM = 32, SBN = 32, SBK = 64;
 constexpr int kMaxLnK = 2048;     // A_LN keeps the LayerNorm gain and shift of the whole row in LDS
 
-template <int AMODE, int EPI, int NB>
+// LayerNorm(x) operand of any depth up to kMaxLnK.  32-row tiles, 32, 64 or 128 columns wide (NB column blocks of 32): the launcher takes
+// the widest that still leaves about 160 workgroups, because every column tile re-normalises the same 32 rows.  The four waves split
+// the reduction: in every 64-deep K step wave w multiplies the k slice [16 w, 16 w + 16) with one 32x32x16 MFMA, and the four
+// partial tiles are added in a fixed order through LDS at the end (deterministic).  Chunks are requested eight (widest tile: four)
+// K steps ahead into registers, two K steps are staged in LDS per barrier.  The workgroup first computes mean and 1/sqrt(var + eps)
+// of its 32 rows (one pass, sums shifted by the row's first element so that the variance does not cancel), then every
+// chunk is (x - mean) * rstd * gamma + beta rounded to bf16 -- exactly what the LayerNorm kernel would have stored.
+template <int EPI, int NB>
 __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
   constexpr int TN = NB * SBN;                                               // tile width in columns
   constexpr int DEPTH = NB >= 4 ? 4 : 8;                                     // K steps in flight (register ring)
@@ -49,7 +45,7 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
   unsigned char(*sA)[SBM * 128] = (unsigned char(*)[SBM * 128])sMem;                     // [stage][row][64 bf16]
   unsigned char(*sW)[TN * 128] = (unsigned char(*)[TN * 128])(sMem + NS * SBM * 128);
   float(*sPart)[SBM][TN + 4] = (float(*)[SBM][TN + 4])sMem;
-  __shared__ __attribute__((aligned(16))) float sGain[AMODE == A_LN ? kMaxLnK : 4], sShift[AMODE == A_LN ? kMaxLnK : 4];
+  __shared__ __attribute__((aligned(16))) float sGain[kMaxLnK], sShift[kMaxLnK];
 
   const int tiles_n = p.N / TN;
   const int m0 = (blockIdx.x / tiles_n) * SBM, n0 = (blockIdx.x % tiles_n) * TN;
@@ -69,57 +65,34 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
     wptr[j] = p.w_panels ? W + ((size_t)(n >> 8) * (p.K >> 6) << 14) + ((n & 255) << 6) + ch * 8 : W + (size_t)n * p.K + ch * 8;
   }
   const int wstep = p.w_panels ? 1 << 14 : SBK;
-  const __bf16 *aptr = nullptr;
-  const float *xptr = nullptr;
-  int flags = 0;
-  if constexpr (AMODE == A_PLAIN) aptr = (const __bf16 *)p.A + (size_t)row * p.lda + ch * 8;
-  else if constexpr (AMODE == A_CONV3) {
-    aptr = (const __bf16 *)p.A + (long)p.row_src[row] * p.C + ch * 8;
-    flags = p.row_flags[row];
-  } else xptr = (const float *)p.A + (size_t)row * p.lda + ch * 8;
+  const float *xptr = (const float *)p.A + (size_t)row * p.lda + ch * 8;
 
-  [[maybe_unused]] float mu = 0.0f, rstd = 0.0f;     // A_LN: statistics of this thread's row
+  float mu = 0.0f, rstd = 0.0f;                  // statistics of this thread's row
   // ---- operand pipeline: chunks of K step kt + DEPTH - 1 are requested while step kt is multiplied
   u32x4 wreg[DEPTH][NB];
-  [[maybe_unused]] u32x4 areg[DEPTH];
-  [[maybe_unused]] f32x4 xreg[DEPTH][2];
+  f32x4 xreg[DEPTH][2];
   const int nk = p.K / SBK;
   auto request = [&](int kt, int slot) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) wreg[slot][j] = *(const u32x4 *)(wptr[j] + (size_t)kt * wstep);
-    if constexpr (AMODE == A_PLAIN) {
-      areg[slot] = *(const u32x4 *)(aptr + kt * SBK);
-    } else if constexpr (AMODE == A_CONV3) {
-      const int kk = kt * SBK + ch * 8;          // chunks never straddle taps: C % 8 == 0
-      const int tap = kk / p.C;
-      const bool ok = (kk < 3 * p.C) && !((tap == 0) && (flags & 1)) && !((tap == 2) && (flags & 2));
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (ok) v = *(const u32x4 *)(aptr + kt * SBK);
-      areg[slot] = v;
-    } else {
-      xreg[slot][0] = *(const f32x4 *)(xptr + kt * SBK);
-      xreg[slot][1] = *(const f32x4 *)(xptr + kt * SBK + 4);
-    }
+    xreg[slot][0] = *(const f32x4 *)(xptr + kt * SBK);
+    xreg[slot][1] = *(const f32x4 *)(xptr + kt * SBK + 4);
   };
   auto commit = [&](int kt, int slot) {          // registers -> LDS stage kt % NS
     unsigned char *dA = sA[kt & (NS - 1)] + lds_off, *dW = sW[kt & (NS - 1)] + lds_off;
 #pragma unroll
     for (int j = 0; j < NB; ++j) *(u32x4 *)(dW + j * SBN * 128) = wreg[slot][j];
-    if constexpr (AMODE == A_LN) {
-      const int k = kt * SBK + ch * 8;
-      const f32x4 g0 = *(const f32x4 *)&sGain[k], g1 = *(const f32x4 *)&sGain[k + 4];
-      const f32x4 b0 = *(const f32x4 *)&sShift[k], b1 = *(const f32x4 *)&sShift[k + 4];
-      f32x4 y0, y1;
+    const int k = kt * SBK + ch * 8;
+    const f32x4 g0 = *(const f32x4 *)&sGain[k], g1 = *(const f32x4 *)&sGain[k + 4];
+    const f32x4 b0 = *(const f32x4 *)&sShift[k], b1 = *(const f32x4 *)&sShift[k + 4];
+    f32x4 y0, y1;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        y0[e] = (xreg[slot][0][e] - mu) * rstd * g0[e] + b0[e];
-        y1[e] = (xreg[slot][1][e] - mu) * rstd * g1[e] + b1[e];
-      }
-      const bf16x4 c0 = to_bf16x4(y0), c1 = to_bf16x4(y1);
-      *(bf16x8 *)dA = __builtin_shufflevector(c0, c1, 0, 1, 2, 3, 4, 5, 6, 7);
-    } else {
-      *(u32x4 *)dA = areg[slot];
+    for (int e = 0; e < 4; ++e) {
+      y0[e] = (xreg[slot][0][e] - mu) * rstd * g0[e] + b0[e];
+      y1[e] = (xreg[slot][1][e] - mu) * rstd * g1[e] + b1[e];
     }
+    const bf16x4 c0 = to_bf16x4(y0), c1 = to_bf16x4(y1);
+    *(bf16x8 *)dA = __builtin_shufflevector(c0, c1, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
   f32x16 acc[NB];
@@ -130,9 +103,9 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d)
     if (d < nk) request(d, d);
-  // ---- A_LN: statistics of the tile's 32 rows (after the first operand requests, so that their latencies overlap).
+  // ---- statistics of the tile's 32 rows (after the first operand requests, so that their latencies overlap).
   // Eight threads per row, each over every eighth 32-byte piece, eight pieces requested at a time.
-  if constexpr (AMODE == A_LN) {
+  {
     for (int k = tid * 4; k < p.K; k += 1024) {   // gain and shift of the whole row -> LDS (a load per K step would sit
       *(f32x4 *)&sGain[k] = *(const f32x4 *)(p.ln_g + k);   // on the critical path of every step)
       *(f32x4 *)&sShift[k] = *(const f32x4 *)(p.ln_b + k);
@@ -215,8 +188,6 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
   // thread -> row er, 4 consecutive features from ec in each of the NB column blocks
   const int er = tid >> 3, m = m0 + er;
   if (m >= p.M) return;
-  [[maybe_unused]] int prow = 0;
-  if constexpr (EPI == EPI_BIAS_GELU_POS) prow = p.row_pos[m];
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int ec = j * SBN + (tid & 7) * 4;
@@ -235,21 +206,10 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
       __bf16 *dst = (p.out2 && nn >= p.n_split) ? (__bf16 *)p.out2 + (size_t)m * p.ldo2 + (nn - p.n_split)
                                                  : (__bf16 *)p.out + (size_t)m * p.ldo + nn;
       *(bf16x4 *)dst = to_bf16x4(v);
-    } else if constexpr (EPI == EPI_BIAS_GELU) {
+    } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]);
       *(bf16x4 *)((__bf16 *)p.out + (size_t)m * p.ldo + nn) = to_bf16x4(v);
-    } else if constexpr (EPI == EPI_BIAS_RESID) {
-      f32x4 *o = (f32x4 *)((float *)p.out + (size_t)m * p.ldo + nn);
-      const f32x4 x = *o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] += x[e];
-      *o = v;
-    } else {
-      const f32x4 pe = *(const f32x4 *)(p.pos + (size_t)prow * p.N + nn);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]) + pe[e];
-      *(f32x4 *)((float *)p.out + (size_t)m * p.ldo + nn) = v;
     }
   }
 }
@@ -432,6 +392,253 @@ hipError_t launch_ln(const GemmArgs &a, hipStream_t s) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------------------
+// Products whose operand is in memory as it is needed (plain rows, windows of a convolution).  A workgroup's chain of latencies is
+// all there is to such a call, so nothing in it waits for anything but its own operands: the eight waves share the reduction
+// (wave w takes the 64-deep K steps w, w + 8, ..), each fetches its steps into an LDS ring of its own, all of them requested at
+// the start where they fit, and multiplies them without a barrier.  One barrier later the eight partial tiles are added up
+// in wave order.  Which steps a wave takes and in which order does not depend on the tile, so a row's bits do not either.
+//
+// What bounds it: a launch (1.8 us for a kernel that reads and stores one value), one memory latency, then the operand bytes of a
+// tile at 64 bytes a clock, the rate of one L1, or of all tiles at about 19 TB/s over the chip.
+// Against the kernel it replaced (four waves walking K together with a barrier every two steps; us a launch in a chain of launches):
+// 75 x 384 x 384 2.9 -> 2.6, 75 x 384 x 1536 5.1 -> 3.2, 244 x 512 x 2048 6.7 -> 4.3, 1000 x 512 x 2048 10.6 -> 7.5, 100 x 1280 x 5120
+// 13.6 -> 8.1.  Encoder calls: 75 tokens, d = 384 109.6 -> 93, 243 tokens, d = 512 192.7 -> 171; 50 tokens, d = 1024 1046 -> 880.
+template <int TM, int TN, int SLOTS>
+constexpr int slice_smem() {
+  constexpr int stages = 8 * SLOTS * (TM + TN) * 128, parts = 8 * TM * (TN + 4) * 4;
+  return stages > parts ? stages : parts;
+}
+
+constexpr unsigned kOutside = 0xFFFFFFF0u;         // a byte offset no buffer reaches: the load returns zeros
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Wait until at most V of this wave's loads are outstanding.
+template <int V>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(V >= 0 && V < 64, "more loads in flight than the counter holds");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (V & 15) | ((V >> 4) << 14));
+}
+
+template <int TM, int TN, int SLOTS, int AMODE, int EPI>
+__global__ void __launch_bounds__(512) gemm_slice_kernel(GemmArgs p) {
+#ifdef __HIP_DEVICE_COMPILE__       // buffer resources are a device type: the host only needs the kernel's name
+  constexpr int NW = 8, TB = TM / 16, FB = TN / 16, XL = TM / 8, WL = TN / 8, LPS = XL + WL;
+  constexpr int SLOT = (TM + TN) * 128, PITCH = TN + 4;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_slice[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lq = lane >> 4, rr = lane >> 3;
+  const int tiles_n = p.N / TN;
+  const int m0 = blockIdx.x / tiles_n * TM, n0 = blockIdx.x % tiles_n * TN;      // a column of tiles keeps to an XCD or two
+  unsigned char *ring = smem_slice + wave * SLOTS * SLOT;
+
+  // ---- this thread's outputs, and what the epilogue adds to them (requested first: nothing later waits for them)
+  constexpr int VEC = TM * TN >= 2048 ? 4 : 2, PER = TM * TN / VEC > 512 ? TM * TN / VEC / 512 : 1, COLS = TN / VEC;
+  const bool has = PER > 1 || TM * TN / VEC == 512 || tid < TM * TN / VEC;
+  typedef float vec __attribute__((ext_vector_type(VEC)));
+  const int ec = tid % COLS * VEC, er = tid / COLS % TM;           // (threads without an output repeat another's)
+  const vec bias = *(const vec *)(p.bias + n0 + ec);
+  vec add[PER];
+  [[maybe_unused]] int prow[PER];
+  if constexpr (EPI == EPI_BIAS_RESID) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) add[u] = *(const vec *)((const float *)p.out + (size_t)min(m0 + er + u * (512 / COLS), p.M - 1) * p.ldo + n0 + ec);
+  } else if constexpr (EPI == EPI_BIAS_GELU_POS) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) prow[u] = p.row_pos[min(m0 + er + u * (512 / COLS), p.M - 1)];
+  }
+
+  // ---- loads: eight rows of 128 bytes per instruction, 16-byte chunk c of row r at c ^ ((r >> 1) & 7); K steps past the end
+  // load from outside the buffer (zeros), so that every wave makes the same number of turns
+  const int nk = p.K >> 6, ns = (nk + NW - 1) / NW;
+  const size_t a_bytes = p.a_panels ? (size_t)((p.M + 255) >> 8) * 256 * p.K * 2 : ((size_t)(p.M - 1) * p.lda + p.K) * 2;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void *)p.A, 0, AMODE == A_CONV3 ? (int)kOutside : (int)a_bytes, 0x00027000);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.W, 0, (int)((size_t)(p.w_panels ? (p.N + 255) & ~255 : p.N) * p.K * 2), 0x00027000);
+  const int astep = p.a_panels ? 32768 : 128, wstep = p.w_panels ? 32768 : 128, wrow = p.w_panels ? 128 : p.K * 2;
+  const int wbase = p.w_panels ? (((n0 >> 8) * nk) << 15) + ((n0 & 255) << 7) : (int)((unsigned)n0 * (unsigned)p.K * 2u);        // (a tile lies in one panel)
+  const int piece = ((lane & 7) ^ (rr >> 1)) << 4;                 // of the even groups of eight rows; the odd ones have it at ^ 64
+  const int woff[2] = {rr * wrow + piece, rr * wrow + (piece ^ 64)};
+  int aoff[XL];
+  [[maybe_unused]] int aflags[AMODE == A_CONV3 ? XL : 1];
+#pragma unroll
+  for (int i = 0; i < XL; ++i) {
+    const int row = min(m0 + i * 8 + rr, p.M - 1);                 // rows past M are computed but never stored
+    if constexpr (AMODE == A_CONV3) { aoff[i] = p.row_src[row]; aflags[i] = p.row_flags[row]; }      // (batches of a few thousand frames)
+    else aoff[i] = (p.a_panels ? (((row >> 8) * nk) << 15) + ((row & 255) << 7) : (int)((unsigned)row * (unsigned)p.lda * 2u)) + (piece ^ ((i & 1) << 6));
+  }
+  auto load_w = [&](int i, int slot) {
+    const int kt = wave + i * NW, off = kt < nk ? wbase + kt * wstep : 0;
+    const int v[2] = {kt < nk ? woff[0] : (int)kOutside, kt < nk ? woff[1] : (int)kOutside};
+#pragma unroll
+    for (int q = 0; q < WL; ++q)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(ring + slot * SLOT + TM * 128 + q * 1024), 16, v[q & 1],
+                                               kt < nk ? off + q * 8 * wrow : 0, 0, 0);
+  };
+  auto load_a = [&](int i, int slot) {
+    const int kt = wave + i * NW;
+#pragma unroll
+    for (int q = 0; q < XL; ++q) {
+      if constexpr (AMODE == A_CONV3) {            // pieces never straddle taps: C % 8 == 0
+        const int kk = kt * 64 + ((piece ^ ((q & 1) << 6)) >> 1);
+        const bool live = kk < 3 * p.C && !(kk < p.C && (aflags[q] & 1)) && !(kk >= 2 * p.C && (aflags[q] & 2));
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(ring + slot * SLOT + q * 1024), 16,
+                                                 live ? (aoff[q] * p.C + kk) * 2 : (int)kOutside, 0, 0, 0);
+      } else {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(ring + slot * SLOT + q * 1024), 16,
+                                                 kt < nk ? aoff[q] : (int)kOutside, kt < nk ? kt * astep : 0, 0, 0);
+      }
+    }
+  };
+  if constexpr (AMODE == A_CONV3) {                // the weights first: the windows' places are still on their way
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (s < ns) load_w(s, s);
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (s < ns) load_a(s, s);
+  } else {
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (s < ns) { load_w(s, s); load_a(s, s); }
+  }
+  if constexpr (EPI == EPI_BIAS_GELU_POS) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) add[u] = *(const vec *)(p.pos + (size_t)prow[u] * p.N + n0 + ec);
+  }
+
+  f32x4 acc[TB][FB];
+#pragma unroll
+  for (int i = 0; i < TB; ++i)
+#pragma unroll
+    for (int j = 0; j < FB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  int slot = 0;
+  for (int i = 0; i < ns; ++i) {
+    // The loads of step i have landed when at most those of the steps requested after it are outstanding.  (Windows of a convolution:
+    // counted as if only activations followed, and the positions requested behind the first steps not at all; both wait for more
+    // than they have to, never for less.)
+    constexpr int N = AMODE == A_CONV3 ? XL : LPS;
+    const int ahead = min(ns - 1 - i, SLOTS - 1);
+    if (SLOTS > 3 && ahead >= 3) wait_loads<(SLOTS > 3 ? 3 * N : 0)>();
+    else if (SLOTS > 2 && ahead >= 2) wait_loads<(SLOTS > 2 ? 2 * N : 0)>();
+    else if (SLOTS > 1 && ahead >= 1) wait_loads<(SLOTS > 1 ? N : 0)>();
+    else wait_loads<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    const unsigned char *cx = ring + slot * SLOT, *cw = cx + TM * 128;
+    bf16x8 xf[2][TB], wf[2][FB];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int off = l16 * 128 + (((4 * t + lq) ^ ((l16 >> 1) & 7)) << 4);
+#pragma unroll
+      for (int j = 0; j < FB; ++j) wf[t][j] = *(const bf16x8 *)(cw + j * 2048 + off);
+#pragma unroll
+      for (int r = 0; r < TB; ++r) xf[t][r] = *(const bf16x8 *)(cx + r * 2048 + off);
+    }
+    if (i + SLOTS < ns) {
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): the slot has been read and may be refilled
+      __builtin_amdgcn_sched_barrier(0);
+      load_w(i + SLOTS, slot);
+      load_a(i + SLOTS, slot);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < TB; ++r)
+#pragma unroll
+        for (int j = 0; j < FB; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[t][j], xf[t][r], acc[r][j], 0, 0, 0);
+    slot = slot + 1 == SLOTS ? 0 : slot + 1;
+  }
+
+  // ---- lane holds, of token l16 of a row block, features 16 j + 4 lq .. + 3
+  __syncthreads();                                 // every wave is done with its ring
+  float *part = (float *)smem_slice;
+#pragma unroll
+  for (int r = 0; r < TB; ++r)
+#pragma unroll
+    for (int j = 0; j < FB; ++j) *(f32x4 *)(part + (wave * TM + r * 16 + l16) * PITCH + j * 16 + lq * 4) = acc[r][j];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int row = er + u * (512 / COLS), m = m0 + row, nn = n0 + ec;
+    vec v = *(const vec *)(part + row * PITCH + ec);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      const vec t = *(const vec *)(part + (w * TM + row) * PITCH + ec);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) v[e] += t[e];
+    }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) v[e] += bias[e];
+    if constexpr (EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_GELU_POS) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) v[e] = gelu_fast(v[e]);
+    }
+    if constexpr (EPI == EPI_BIAS_RESID || EPI == EPI_BIAS_GELU_POS) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) v[e] += add[u][e];
+    }
+    if (!has || m >= p.M) continue;
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) {
+      typedef __bf16 bvec __attribute__((ext_vector_type(VEC)));
+      __bf16 *dst = p.out_panels ? (__bf16 *)p.out + ((((size_t)(m >> 8) * (p.N >> 6) + (nn >> 6)) << 14) + ((m & 255) << 6) + (nn & 63))
+                    : (EPI == EPI_BIAS && p.out2 && nn >= p.n_split) ? (__bf16 *)p.out2 + (size_t)m * p.ldo2 + (nn - p.n_split)
+                                                                     : (__bf16 *)p.out + (size_t)m * p.ldo + nn;
+      *(bvec *)dst = __builtin_convertvector(v, bvec);
+    } else {
+      *(vec *)((float *)p.out + (size_t)m * p.ldo + nn) = v;
+    }
+  }
+#endif
+}
+
+template <int TM, int TN, int SLOTS, int AMODE, int EPI>
+hipError_t launch_slice_tile(const GemmArgs &a, hipStream_t s) {
+  constexpr int smem = slice_smem<TM, TN, SLOTS>();
+  static_assert(smem <= 163840, "LDS of one compute unit");
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [&] {
+    attr_err = hipFuncSetAttribute((const void *)gemm_slice_kernel<TM, TN, SLOTS, AMODE, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  hipLaunchKernelGGL((gemm_slice_kernel<TM, TN, SLOTS, AMODE, EPI>), dim3((unsigned)((a.M + TM - 1) / TM * (a.N / TN))), dim3(512), smem, s, a);
+  return hipGetLastError();
+}
+
+// The tile with the shortest time by the bounds above: rounds of the chip times a tile's operand bytes at one L1's rate (10.9 ns a KB
+// measured, 12.5 for 64 x 64 tiles), or all tiles' bytes at the chip's; a further round costs a start, the larger tiles their
+// sums.  Fits sweeps of every tile over 13 to 1020 rows and 384 to 5120 columns and values of reduction: the tile it
+// takes is the fastest or within 3 % of it throughout.
+struct SliceTile { int m, n; };
+constexpr SliceTile kSliceTiles[] = {{16, 16}, {16, 32}, {32, 32}, {64, 32}, {64, 64}};
+
+struct SlicePick { int tile; double us; };          // us: beyond the launch and the first memory latency (about 2 us)
+SlicePick pick_slice(int M, int N, int K) {
+  SlicePick best{-1, 0.0};
+  for (int t = 0; t < 5; ++t) {
+    if (N % kSliceTiles[t].n) continue;
+    const long tiles = (long)((M + kSliceTiles[t].m - 1) / kSliceTiles[t].m) * (N / kSliceTiles[t].n), rounds = (tiles + 255) / 256;
+    const double kb = (kSliceTiles[t].m + kSliceTiles[t].n) * (double)K * 2 / 1024, one = 0.3 + kb * (t < 4 ? 10.9e-3 : 12.5e-3);
+    const double us = std::max(rounds * one + 0.9 * (rounds - 1), tiles * kb * 1024 / (t < 3 ? 20e6 : 17.5e6)) + (t == 4 ? 1.0 : t == 3 ? 0.3 : 0.0);
+    if (best.tile < 0 || us < best.us) best = {t, us};
+  }
+  return best;
+}
+
+template <int AMODE, int EPI>
+hipError_t launch_slice(const GemmArgs &a, hipStream_t s) {
+  switch (pick_slice(a.M, a.N, a.K).tile) {
+    case 0: return launch_slice_tile<16, 16, 4, AMODE, EPI>(a, s);
+    case 1: return launch_slice_tile<16, 32, 3, AMODE, EPI>(a, s);
+    case 2: return launch_slice_tile<32, 32, 2, AMODE, EPI>(a, s);
+    case 3: return launch_slice_tile<64, 32, 1, AMODE, EPI>(a, s);
+    default: return launch_slice_tile<64, 64, 1, AMODE, EPI>(a, s);
+  }
+}
+
 // Widest tile (in 32-column blocks) that divides N and still leaves at least 160 workgroups; 1 if even that gives fewer.
 int pick_blocks(const GemmArgs &a) {
   constexpr int min_wgs = 160;     // measured: 425 tokens prefer 168-224 wide tiles to 336-448 narrower ones, 125 tokens 192-256 to 96-128
@@ -441,13 +648,13 @@ int pick_blocks(const GemmArgs &a) {
   return 1;
 }
 
-template <int AMODE, int EPI>
+template <int EPI>
 hipError_t launch_small(const GemmArgs &a, hipStream_t s) {
   const int nb = pick_blocks(a);
   const dim3 grid((unsigned)((long)((a.M + SBM - 1) / SBM) * (a.N / (nb * SBN)))), block(256);
-  if (nb == 4) hipLaunchKernelGGL((gemm_small_kernel<AMODE, EPI, 4>), grid, block, 0, s, a);
-  else if (nb == 2) hipLaunchKernelGGL((gemm_small_kernel<AMODE, EPI, 2>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gemm_small_kernel<AMODE, EPI, 1>), grid, block, 0, s, a);
+  if (nb == 4) hipLaunchKernelGGL((gemm_small_kernel<EPI, 4>), grid, block, 0, s, a);
+  else if (nb == 2) hipLaunchKernelGGL((gemm_small_kernel<EPI, 2>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemm_small_kernel<EPI, 1>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -456,7 +663,7 @@ hipError_t launch_small(const GemmArgs &a, hipStream_t s) {
 // Products outside of the encoder (whose rows keep one order of sums whatever the batch) that give every compute unit at most
 // one 32 x 32 tile: this kernel's four waves share the reduction, and against the pipelined kernel's 32 x 64 tile a call takes
 // 3.9 against 5.2 us (100 x 768 x 768), 4.7 / 5.8 (256 x 1024 x 1024), 5.4 / 6.5 (160 x 1280 x 1280), 4.2 / 5.4 (64 x 2304 x 768);
-// one row tile further the two are level.  Beyond 4 MB of weights (what one XCD's L2 holds; 1 us a call at 3840 x 1280) the
+// one row tile further the two were level (figures of the kernel before this one, which is up to 1.7 times as fast).  Beyond 4 MB of weights (what one XCD's L2 holds; 1 us a call at 3840 x 1280) the
 // rows of a bf16 result keep the order of sums of the larger batches; residual updates go here whatever their depth (100 x 768 x
 // 3072 9.3 / 10.2 us, 100 x 1280 x 5120 15.2 / 17.0).
 bool gemm_small_few_rows(int32_t M, int32_t N, int32_t K, Epilogue epi) {
@@ -464,18 +671,28 @@ bool gemm_small_few_rows(int32_t M, int32_t N, int32_t K, Epilogue epi) {
   return (long)((M + SBM - 1) / SBM) * (N / SBN) <= 256 && (epi == EPI_BIAS_RESID || (long)N * K <= 2L << 20);
 }
 
+// Products of a wide model on the sliced kernel: up to one 64 x 32 tile per compute unit (us, this kernel and the pipelined one:
+// 100 x 2304 x 768 4.5 and 5.3, 200 x 1280 x 1280 5.3 and 6.5, 640 x 768 x 768 4.7 and 5.4; one tile more and it is the other way round,
+// 200 x 2304 x 768 5.9 and 5.6).  A long reduction that may be cut into parts instead (may_cut) is left to the pipelined kernel where that
+// is estimated to be faster by 0.3 us (100 x 768 x 3072 loses 0.7 us a block, 60 x 768 x 3072 gains 0.5).
+bool gemm_slice_applies(int32_t M, int32_t N, int32_t K, bool may_cut) {
+  if (N % 32 || K % 64 || (long)((M + 63) / 64) * (N / 32) > 256) return false;
+  return !may_cut || K < 2 * N || pick_slice(M, N, K).us <= gemm_cut_estimate(M, N, K) + 0.3;
+}
+
 bool gemm_small_applies(int32_t M, int32_t N, int32_t K) { return M <= kSmallRows && std::min(N, K) <= 512 && std::max(N, K) <= 2048; }
 
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if (a.N % SBN != 0 || a.K % SBK != 0 || a.K <= 0 || a.a_panels || a.out_panels) return hipErrorInvalidValue;
+  if (a.N % SBN != 0 || a.K % SBK != 0 || a.K <= 0) return hipErrorInvalidValue;
+  if ((a.a_panels && amode != A_PLAIN) || (a.out_panels && (amode == A_LN || a.out2 || (epi != EPI_BIAS && epi != EPI_BIAS_GELU)))) return hipErrorInvalidValue;
   if (a.out2 && (epi != EPI_BIAS || a.n_split % 4 != 0 || a.n_split <= 0 || a.n_split >= a.N)) return hipErrorInvalidValue;
   if (amode == A_PLAIN) {
     if (a.lda % 8 != 0) return hipErrorInvalidValue;
     switch (epi) {
-      case EPI_BIAS: return launch_small<A_PLAIN, EPI_BIAS>(a, s);
-      case EPI_BIAS_GELU: return launch_small<A_PLAIN, EPI_BIAS_GELU>(a, s);
-      case EPI_BIAS_RESID: return launch_small<A_PLAIN, EPI_BIAS_RESID>(a, s);
+      case EPI_BIAS: return launch_slice<A_PLAIN, EPI_BIAS>(a, s);
+      case EPI_BIAS_GELU: return launch_slice<A_PLAIN, EPI_BIAS_GELU>(a, s);
+      case EPI_BIAS_RESID: return launch_slice<A_PLAIN, EPI_BIAS_RESID>(a, s);
       default: return hipErrorInvalidValue;
     }
   }
@@ -483,17 +700,17 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
     if (a.lda % 8 != 0 || !a.ln_g || !a.ln_b || !(a.ln_eps > 0.0f) || a.K > kMaxLnK) return hipErrorInvalidValue;
     if (a.K <= kLnRowK && (epi == EPI_BIAS || epi == EPI_BIAS_GELU)) return epi == EPI_BIAS ? launch_ln<EPI_BIAS>(a, s) : launch_ln<EPI_BIAS_GELU>(a, s);
     switch (epi) {
-      case EPI_BIAS: return launch_small<A_LN, EPI_BIAS>(a, s);
-      case EPI_BIAS_GELU: return launch_small<A_LN, EPI_BIAS_GELU>(a, s);
+      case EPI_BIAS: return launch_small<EPI_BIAS>(a, s);
+      case EPI_BIAS_GELU: return launch_small<EPI_BIAS_GELU>(a, s);
       default: return hipErrorInvalidValue;
     }
   }
   if (a.C % 8 != 0 || 3 * a.C > a.K || !a.row_src || !a.row_flags) return hipErrorInvalidValue;
   switch (epi) {
-    case EPI_BIAS_GELU: return launch_small<A_CONV3, EPI_BIAS_GELU>(a, s);
+    case EPI_BIAS_GELU: return launch_slice<A_CONV3, EPI_BIAS_GELU>(a, s);
     case EPI_BIAS_GELU_POS:
       if (!a.pos || !a.row_pos) return hipErrorInvalidValue;
-      return launch_small<A_CONV3, EPI_BIAS_GELU_POS>(a, s);
+      return launch_slice<A_CONV3, EPI_BIAS_GELU_POS>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

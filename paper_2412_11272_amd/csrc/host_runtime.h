@@ -232,7 +232,7 @@ inline int run_linear(DevCtx *e, hipStream_t s, int cls, const void *A, int lda,
 // run_ln that has to follow (may_split).
 inline int run_resid(DevCtx *e, hipStream_t s, int cls, GemmArgs a, float *x, float *part, bool may_split, Partials *pt) {
   a.out = x;
-  const int n = may_split && part ? gemm_split_choice(a.M, a.N, a.K) : 1;
+  const int n = may_split && part && !a.prefer_small ? gemm_split_choice(a.M, a.N, a.K) : 1;
   if (n > 1) {
     a.out = part; a.ldo = a.N; a.k_splits = n;
     *pt = Partials{part, a.bias, n, a.M};

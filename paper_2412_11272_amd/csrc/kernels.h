@@ -64,8 +64,8 @@ struct GemmArgs {
   int32_t n_valid;
   int32_t k_splits;         // EPI_PARTIAL only
   int32_t prefer_large;     // never the small-batch kernel (a product that streams a huge weight matrix, a wide model)
-  int32_t prefer_small;     // run on the small-batch kernel even if M is above its usual limit (the first convolution
-                            // of a small batch has twice as many rows as the batch has tokens)
+  int32_t prefer_small;     // run on the small-batch kernels even if M is above their usual limit (the first convolution
+                            // of a small batch has twice as many rows as the batch has tokens) or the model is wide
 };
 
 struct AttnArgs {
@@ -97,10 +97,11 @@ struct PrepArgs {
 
 // bf16 MFMA path -------------------------------------------------------------------------------
 hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
-// small batches (kSmallRows rows) of narrow models: 32-row tiles, reduction split over the waves, optional fused LayerNorm.
+// small batches (kSmallRows rows) of narrow models: reduction split over the waves, or LayerNorm fused into the operand.
 // Whether a product of a small batch goes there depends on its width and depth only, not on the number of rows.
 constexpr int32_t kSmallRows = 1024;
 bool gemm_small_applies(int32_t M, int32_t N, int32_t K);
+bool gemm_slice_applies(int32_t M, int32_t N, int32_t K, bool may_cut);     // products of a few hundred rows of a wide model
 bool gemm_small_few_rows(int32_t M, int32_t N, int32_t K, Epilogue epi);      // plain products of a few rows, any width
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 // products with at most one tile per compute unit, and convolutions whose taps are no whole K steps
@@ -111,6 +112,7 @@ hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
 // Parts the reduction of a residual product should be cut into (1: none); k_splits * M * N <= kPartialFloats
 constexpr int64_t kPartialFloats = 256L * 128 * 128;
 int gemm_split_choice(int32_t M, int32_t N, int32_t K);
+double gemm_cut_estimate(int32_t M, int32_t N, int32_t K);     // us of that product, cut or not (infinite: not on the pipelined kernel)
 // Forms of the non-causal attention (attention_bf16.hip); the choice is a function of the whole batch's sizes
 enum AttnForm : int { ATTN_PLAIN = 0, ATTN_KEYS2 = 1, ATTN_KEYS4 = 2, ATTN_KEYS4_TWO_BUFFERS = 3 };
 AttnForm attention_form(int32_t n_heads, int32_t B, int64_t M, int64_t Mkv, int64_t n_work);
