@@ -190,7 +190,7 @@ __global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
     for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[kb2][r]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    tmax = half_max(tmax);
     const float m_new = fmaxf(m_run, tmax);       // finite: every tile has at least one valid key
     // The softmax reference m_run only has to bound the logits from below by a known margin: it follows the running
     // maximum when some query's maximum has moved up by more than 8 / c (weights up to 2^8 until then; fp32 sums and
@@ -248,7 +248,7 @@ __global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
   }
 
   if (KS == 1 && !wave_active) return;
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const float l_tot = half_sum(l_run);
   __bf16 *orow = (__bf16 *)p.out + (size_t)(tok0 + qrow) * p.d_model + head * 64;
   if constexpr (KS == 1) {
     const float inv = 1.0f / l_tot;
@@ -431,7 +431,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
     for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[kb2][r]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    tmax = half_max(tmax);
     const float m_new = fmaxf(m_run, tmax);
     if (__any(m_new > m_run)) {
       // a query without a finite logit so far has nothing to rescale, and its m_run - m_new may be inf - inf
@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   float *sM = (float *)smem_ks;                   // 4 x 32
   float *sL = sM + 128;                           // 4 x 32
   float *sO = sL + 128;                           // 4 x 32 x 64
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const float l_tot = half_sum(l_run);
   if (lg == 0) sM[wave * 32 + l32] = m_run;
   __syncthreads();
   float M = sM[l32];

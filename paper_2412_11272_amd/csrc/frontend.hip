@@ -322,11 +322,8 @@ __global__ void __launch_bounds__(NT) logmel_kernel(FeArgs p) {
       }
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, off));
-    hi = fmaxf(hi, __shfl_xor(hi, off));
-  }
+  lo = wf::wave_min(lo);
+  hi = wf::wave_max(hi);
   if ((tid & 63) == 0) { sMin[tid >> 6] = lo; sMax[tid >> 6] = hi; }
   __syncthreads();
   if (tid == 0) {
@@ -349,8 +346,7 @@ __global__ void __launch_bounds__(256) clamp_kernel(FeArgs p) {
   const FeStream st = fe_stream(p, stream), nx = fe_stream(p, stream + 1);
   float top = -INFINITY;
   for (int k = st.block0 + lane; k < nx.block0; k += 64) top = fmaxf(top, p.range[k].y);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  top = wf::wave_max(top);
   const float floor_v = top - 2.0f;
   const TOUT fl = (TOUT)floor_v;
   const int r0 = st.frame0 + (b - st.block0) * FPB, rows = min(FPB, nx.frame0 - r0);

@@ -293,8 +293,7 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
         if (j * 128 + l16 * 8 < K)
 #pragma unroll
           for (int e = 0; e < 4; ++e) sum += x[i][j][0][e] + x[i][j][1][e];
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+      sum = row_sum(sum);
       const float mu = sum * inv_k;
 #pragma unroll
       for (int j = 0; j < JV; ++j)
@@ -304,8 +303,7 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
             const float a = x[i][j][0][e] - mu, b = x[i][j][1][e] - mu;
             sq += a * a + b * b;
           }
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+      sq = row_sum(sq);
       const float rstd = rsqrtf(sq * inv_k + p.ln_eps);
       const int r = wave * 8 + i * 4 + lq;
 #pragma unroll

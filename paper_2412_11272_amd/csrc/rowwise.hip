@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(256) prep_inline_kernel(PrepArgs p, int32_t *d
 // (mean, then centred variance -- the biased one), fp32 statistics.  rows: out[i] = LayerNorm(x[rows[i]]) (NULL: x[i]).
 // EARLY: gain and shift are requested together with the row.  For a few hundred rows a call is one chain of latencies, and
 // loading them after the statistics puts a second memory latency into it (425 x 1280: 6.2 -> 5.4 us); once the chip is full
-// the registers they occupy cost more (6361 x 1280: 12.6 us late, 17.3 early).
+// the registers they occupy cost more (6361 x 1280: 12.6 us late, 17.3 early; both with the sums over a wave by shuffles).
 // (ADD: the late form of wide rows adds a piece up as it arrives.  With the additions after all loads the compiler's other order of
 // copies costs large calls 13 %, 31 694 x 1280 52.6 -> 59.6 us; rows of up to 512 values gain 5 % by it, 31 694 x 384 15.3 -> 14.5.)
 // NP > 0: the residual product in front left its result as NP partial sums; they and its bias are added to the row first
@@ -144,8 +144,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
     for (int i = 0; i < MAXV; ++i)
       if (lane + i * 64 < nv) sum += v[i][0] + v[i][1] + v[i][2] + v[i][3];
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  sum = wave_sum(sum);
   const float mu = sum / (float)d;
   float sq = 0.0f;
 #pragma unroll
@@ -156,8 +155,7 @@ __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, c
       for (int e = 0; e < 4; ++e) { const float t = v[i][e] - mu; sq += t * t; }
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+  sq = wave_sum(sq);
   const float rstd = rsqrtf(sq / (float)d + eps);
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
