@@ -24,7 +24,10 @@ namespace {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SBM = 32, SBN = 32, SBK = 64;
-constexpr int kMaxLnK = 2048;     // A_LN keeps the LayerNorm gain and shift of the whole row in LDS
+constexpr int kMaxLnK = 2048;     // gemm_small_kernel keeps the LayerNorm gain and shift of the whole row in LDS
+constexpr unsigned kOutside = 0xFFFFFFF0u;         // a byte offset no buffer reaches: the load returns zeros
+
+typedef __attribute__((address_space(3))) void lds_void;
 
 // LayerNorm(x) operand of any depth up to kMaxLnK.  32-row tiles, 32, 64 or 128 columns wide (NB column blocks of 32): the launcher takes
 // the widest that still leaves about 160 workgroups, because every column tile re-normalises the same 32 rows.  The four waves split
@@ -216,109 +219,104 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
 
 // ---------------------------------------------------------------------------------------------------------------------
 // out = epilogue(LayerNorm(x) . W^T) for rows of at most 512 values.  A call is one chain of latencies, so everything it
-// reads is requested at once: the weight tile [TN, K] goes global -> LDS as a whole, a workgroup's 32 rows into registers,
-// where they are normalised (mean, then centred variance) and left in LDS as the bf16 operand.  One barrier, then the waves
-// multiply the whole of K in order, each a 16-column strip of its own (TN = 64: both 16-row blocks, TN = 32: one), and store
-// without a reduction.  The general kernel above walks K with a barrier every two steps and adds four partial tiles up.
+// reads is requested at once: the weight tile [64, K], gain and shift go global -> LDS as a whole, a workgroup's TM rows into
+// registers, where they are normalised (mean, then centred variance) and left in LDS as the bf16 operand.  Two barriers, then the waves
+// multiply the whole of K in order, each a 16-column strip of its own, and store without a reduction.
 // A workgroup keeps its weight tile for the row tiles g, g + row_groups, ...
-// Encoder calls before -> after: 75 tokens, d = 384 128 -> 120 us; 243 tokens, d = 512 220 -> 200; 925 tokens, d = 384
-// 250 -> 199; prefill of 100 tokens, d = 512 317 -> 299.  (With K known only at run time the exposed LDS latency of every
-// K step took all of that back.)
-constexpr int kLnRowK = 512;
+// What bounds it: the L1 takes 16 clocks an instruction of 1 KB, whether lanes ask for the same lines or not, so gain and shift go to
+// the LDS once instead of to every wave's registers (a third of all load instructions); then the additions of the statistics, which every
+// column tile repeats for its rows, and the LDS reads of the K loop.
+// Before and after gain and shift in the LDS, statistics under the weights' arrival and the choice of 16 to 64 rows (us a launch): 75 x 1152 x
+// 384 3.9 -> 3.4, 100 x 1536 x 512 4.6 -> 3.7, 244 x 2048 x 512 5.7 -> 5.0, 425 x 1536 x 512 8.1 -> 5.8, 925 x 1152 x 384 8.0 -> 6.6.
+// Encoder calls: 75 tokens, d = 384 90.3 -> 84.5; 243 tokens, d = 512 162 -> 157; prefill of 100 tokens, d = 512 250 -> 231 us.
+// (With K known only at run time the exposed LDS latency of every K step took a third of the gain over the unfused kernels back.)
+constexpr int kLnRowK = 512, kLnTN = 64;
 
 // NK: K / 64 where it is known when compiled (the loads and the K loop are then straight-line code), else 0.
-template <int TN, int EPI, int NK>
+template <int TM, int EPI, int NK>
 __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups) {
-  constexpr int TB = TN == 64 ? 2 : 1;
-  constexpr int JV = ((NK ? NK * 64 : kLnRowK) + 127) / 128;      // 128-column pieces of a row
+#ifdef __HIP_DEVICE_COMPILE__       // buffer resources are a device type: the host only needs the kernel's name
+  constexpr int TN = kLnTN, TB = TM / 16, RI = TM / 16;           // row blocks of the product; turns of four rows a wave
+  constexpr int JV = NK ? NK : kLnRowK / 64;                      // 64-column pieces of a row
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_ln[];
   const int K = NK ? NK * 64 : p.K, nk = K >> 6;
   unsigned char *sW = smem_ln, *sA = smem_ln + nk * TN * 128;      // [K step][row][64 bf16], chunk c of row r at c ^ ((r >> 1) & 7)
+  float *sGain = (float *)(sA + nk * TM * 128), *sShift = sGain + kLnRowK;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lq = lane >> 4;
-  const int tiles_n = p.N / TN, tiles_m = (p.M + SBM - 1) / SBM;
+  const int tiles_n = p.N / TN, tiles_m = (p.M + TM - 1) / TM;
   const int n0 = blockIdx.x % tiles_n * TN;
 
-  // ---- rows: 16 lanes a row, eight columns of every 128; this lane's rows of a tile are 8 wave + lq and the same + 4
-  f32x4 x[2][JV][2], gg[JV][2], bb[JV][2];
+  // ---- gain and shift: one load instruction a wave.  (Loads to the LDS in the buffer form: behind the global form the compiler waits
+  // for every load at the first use of any, and the statistics would not run while the weights arrive.)
+  {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)(wave < 2 ? p.ln_g : p.ln_b), 0, K * 4, 0x00027000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)((wave < 2 ? sGain : sShift) + (wave & 1) * 256), 16, lane * 16, (wave & 1) * 1024, 0, 0);
+  }
+  // ---- rows: 16 lanes a row, four columns of every 64; this lane's rows of a tile are RI * 4 * wave + 4 i + lq
+  f32x4 x[RI][JV];
   auto request = [&](int tile) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const float *xr = (const float *)p.A + (size_t)min(tile * SBM + wave * 8 + i * 4 + lq, p.M - 1) * p.lda + l16 * 8;
+    for (int i = 0; i < RI; ++i) {
+      const float *xr = (const float *)p.A + (size_t)min(tile * TM + (wave * RI + i) * 4 + lq, p.M - 1) * p.lda + l16 * 4;
 #pragma unroll
       for (int j = 0; j < JV; ++j)
-        if (j * 128 + l16 * 8 < K) {
-          x[i][j][0] = *(const f32x4 *)(xr + j * 128);
-          x[i][j][1] = *(const f32x4 *)(xr + j * 128 + 4);
-        }
+        if (j < nk) x[i][j] = *(const f32x4 *)(xr + j * 64);
     }
   };
   int tile = blockIdx.x / tiles_n;
   request(tile);
-#pragma unroll
-  for (int j = 0; j < JV; ++j)
-    if (j * 128 + l16 * 8 < K) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        gg[j][h] = *(const f32x4 *)(p.ln_g + j * 128 + l16 * 8 + h * 4);
-        bb[j][h] = *(const f32x4 *)(p.ln_b + j * 128 + l16 * 8 + h * 4);
-      }
-    }
-  const int wn = TN == 64 ? wave : wave & 1, wm = TN == 64 ? 0 : wave >> 1;     // this wave's strip and first row block
-  const f32x4 bias = *(const f32x4 *)(p.bias + n0 + wn * 16 + lq * 4);
+  const f32x4 bias = *(const f32x4 *)(p.bias + n0 + wave * 16 + lq * 4);
   {
-    const int rr = lane >> 3;
-    const __bf16 *src[TN / 32];
-    const int wstep = p.w_panels ? 1 << 14 : 64;
-#pragma unroll
-    for (int i = 0; i < TN / 32; ++i) {
-      const int r = (i * 4 + wave) * 8 + rr, n = n0 + r;
-      src[i] = (const __bf16 *)p.W + (p.w_panels ? ((size_t)(n >> 8) * nk << 14) + ((n & 255) << 6) : (size_t)n * K) + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
-    }
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)p.W, 0, (int)((size_t)(p.w_panels ? (p.N + 255) & ~255 : p.N) * K * 2), 0x00027000);
+    const int rr = lane >> 3, wrow = p.w_panels ? 128 : K * 2, wstep = p.w_panels ? 32768 : 128;
+    const int base = (p.w_panels ? (((n0 >> 8) * nk) << 15) + ((n0 & 255) << 7) : n0 * K * 2) + wave * 8 * wrow;      // (a tile lies in one panel)
+    const int off = rr * wrow + (((lane & 7) ^ ((wave * 4 + (rr >> 1)) & 7)) << 4);
 #pragma unroll NK ? NK : 1
     for (int kt = 0; kt < nk; ++kt)
 #pragma unroll
       for (int i = 0; i < TN / 32; ++i)            // eight rows of 128 bytes per instruction
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[i] + (size_t)kt * wstep),
-                                         (__attribute__((address_space(3))) void *)(sW + (kt * TN + (i * 4 + wave) * 8) * 128), 16, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(sW + (kt * TN + (i * 4 + wave) * 8) * 128), 16, off, base + i * 32 * wrow + kt * wstep, 0, 0);
   }
   const float inv_k = 1.0f / (float)K;
-  auto process = [&](int tile) {
+  auto process = [&](int tile, bool first) {
+    float mu[RI], rstd[RI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < RI; ++i) {
       float sum = 0.0f, sq = 0.0f;
 #pragma unroll
       for (int j = 0; j < JV; ++j)
-        if (j * 128 + l16 * 8 < K)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sum += x[i][j][0][e] + x[i][j][1][e];
-      sum = row_sum(sum);
-      const float mu = sum * inv_k;
+        if (j < nk) sum += (x[i][j][0] + x[i][j][1]) + (x[i][j][2] + x[i][j][3]);
+      mu[i] = row_sum(sum) * inv_k;
 #pragma unroll
       for (int j = 0; j < JV; ++j)
-        if (j * 128 + l16 * 8 < K)
+        if (j < nk)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float a = x[i][j][0][e] - mu, b = x[i][j][1][e] - mu;
-            sq += a * a + b * b;
+            x[i][j][e] -= mu[i];
+            sq += x[i][j][e] * x[i][j][e];
           }
-      sq = row_sum(sq);
-      const float rstd = rsqrtf(sq * inv_k + p.ln_eps);
-      const int r = wave * 8 + i * 4 + lq;
-#pragma unroll
-      for (int j = 0; j < JV; ++j)
-        if (j * 128 + l16 * 8 < K) {
-          f32x4 y[2];
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[h][e] = (x[i][j][h][e] - mu) * rstd * gg[j][h][e] + bb[j][h][e];
-          const bf16x4 c0 = to_bf16x4(y[0]), c1 = to_bf16x4(y[1]);
-          *(bf16x8 *)(sA + (2 * j + (l16 >> 3)) * SBM * 128 + r * 128 + (((l16 & 7) ^ ((r >> 1) & 7)) << 4)) =
-              __builtin_shufflevector(c0, c1, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+      rstd[i] = rsqrtf(row_sum(sq) * inv_k + p.ln_eps);
     }
+    if (first) {          // gain and shift were requested before the rows: this wave's part of them is in the LDS by now
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < JV; ++j)
+      if (j < nk) {
+        const f32x4 g = *(const f32x4 *)(sGain + j * 64 + l16 * 4), b = *(const f32x4 *)(sShift + j * 64 + l16 * 4);
+#pragma unroll
+        for (int i = 0; i < RI; ++i) {
+          const int r = (wave * RI + i) * 4 + lq;
+          f32x4 y;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = x[i][j][e] * rstd[i] * g[e] + b[e];
+          *(bf16x4 *)(sA + (j * TM + r) * 128 + (((l16 >> 1) ^ ((r >> 1) & 7)) << 4) + (l16 & 1) * 8) = to_bf16x4(y);
+        }
+      }
     __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0) lgkmcnt(0): this wave's rows are in LDS, its weights too
     __syncthreads();
     if (tile + row_groups < tiles_m) request(tile + row_groups);
@@ -326,7 +324,7 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
 #pragma unroll
     for (int i = 0; i < TB; ++i) acc[i] = bias;
     const int sw = (l16 >> 1) & 7;
-    const unsigned char *cw = sW + (wn * 16 + l16) * 128, *cx = sA + (wm * 16 + l16) * 128;
+    const unsigned char *cw = sW + (wave * 16 + l16) * 128, *cx = sA + l16 * 128;
 #pragma unroll NK ? NK : 1
     for (int kt = 0; kt < nk; ++kt)
 #pragma unroll
@@ -335,14 +333,14 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
         const bf16x8 wf = *(const bf16x8 *)(cw + kt * TN * 128 + off);
 #pragma unroll
         for (int i = 0; i < TB; ++i) {
-          const bf16x8 xf = *(const bf16x8 *)(cx + (kt * SBM + i * 16) * 128 + off);
+          const bf16x8 xf = *(const bf16x8 *)(cx + (kt * TM + i * 16) * 128 + off);
           acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf, acc[i], 0, 0, 0);
         }
       }
-    // lane holds, of token l16 of a row block, features 16 wn + 4 lq .. + 3
+    // lane holds, of token l16 of a row block, features 16 wave + 4 lq .. + 3
 #pragma unroll
     for (int i = 0; i < TB; ++i) {
-      const int m = tile * SBM + (wm + i) * 16 + l16, nn = n0 + wn * 16 + lq * 4;
+      const int m = tile * TM + i * 16 + l16, nn = n0 + wave * 16 + lq * 4;
       f32x4 v = acc[i];
       if constexpr (EPI == EPI_BIAS_GELU) {
 #pragma unroll
@@ -355,38 +353,66 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
       }
     }
   };
-  process(tile);          // by itself: its first wait is for the rows only, the weights arrive under the statistics
+  process(tile, true);    // by itself: its first wait is for the rows only, the weights arrive under the statistics
   for (tile += row_groups; tile < tiles_m; tile += row_groups) {
     __syncthreads();      // the operand has been read; the next rows may take its place
-    process(tile);
+    process(tile, false);
   }
+#endif
 }
 
-template <int TN, int EPI, int NK>
+constexpr int ln_smem(int tm, int k) { return (kLnTN + tm) * k * 2 + 2 * kLnRowK * 4; }
+
+template <int TM, int EPI, int NK>
 hipError_t launch_ln_tile(const GemmArgs &a, hipStream_t s) {
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] {
-    attr_err = hipFuncSetAttribute((const void *)gemm_ln_kernel<TN, EPI, NK>, hipFuncAttributeMaxDynamicSharedMemorySize, (TN + SBM) * kLnRowK * 2);
+    attr_err = hipFuncSetAttribute((const void *)gemm_ln_kernel<TM, EPI, NK>, hipFuncAttributeMaxDynamicSharedMemorySize, ln_smem(TM, kLnRowK));
   });
   if (attr_err != hipSuccess) return attr_err;
-  const int smem = (TN + SBM) * a.K * 2, tiles_n = a.N / TN, tiles_m = (a.M + SBM - 1) / SBM;
+  const int smem = ln_smem(TM, a.K), tiles_n = a.N / kLnTN, tiles_m = (a.M + TM - 1) / TM;
   const int slots = 256 * std::min(4, 163840 / smem);               // workgroups the chip holds at a time
   const int groups = std::min(tiles_m, std::max(1, slots / tiles_n));
-  hipLaunchKernelGGL((gemm_ln_kernel<TN, EPI, NK>), dim3((unsigned)(groups * tiles_n)), dim3(256), smem, s, a, groups);
+  hipLaunchKernelGGL((gemm_ln_kernel<TM, EPI, NK>), dim3((unsigned)(groups * tiles_n)), dim3(256), smem, s, a, groups);
   return hipGetLastError();
+}
+
+// Rows of a tile.  Up to 384 values two workgroups share a CU: 16 rows (3.4 us with one a CU, 4.1 .. 4.4 with two) while two a CU are
+// enough, then 32 (5.2 .. 5.5 us), beyond that 16 again (700 x 1536 6.6 and 7.1 us).  Longer rows, one workgroup a CU: the least
+// of start + further rounds, fitted to 13 .. 1020 rows of 512 (us: 16 rows 3.7 + 1.45 a round, 32 4.75 + 2.8, 48 5.55 + 4.1, 64
+// 6.7 + 4.8); the taken size is the fastest or within 3 % of it.
+int pick_ln_rows(int M, int N, int K) {
+  const int tiles_n = N / kLnTN;
+  auto units = [&](int tm) { return (long)((M + tm - 1) / tm) * tiles_n; };
+  if (K <= 384) return units(16) > 512 && units(32) <= 512 ? 32 : 16;
+  constexpr struct { int rows; double first, more; } kCost[] = {{16, 3.7, 1.45}, {32, 4.75, 2.8}, {48, 5.55, 4.1}, {64, 6.7, 4.8}};
+  int best = 0;
+  double cost = 0.0;
+  for (const auto &c : kCost) {
+    const int tiles_m = (M + c.rows - 1) / c.rows, groups = std::max(1, 256 / tiles_n);
+    const double us = c.first + c.more * ((tiles_m + groups - 1) / groups - 1);
+    if (!best || us < cost) { best = c.rows; cost = us; }
+  }
+  return best;
+}
+
+template <int EPI, int NK>
+hipError_t launch_ln_rows(const GemmArgs &a, hipStream_t s) {
+  const int rows = pick_ln_rows(a.M, a.N, a.K);
+  if (rows == 16) return launch_ln_tile<16, EPI, NK>(a, s);
+  if (rows == 32) return launch_ln_tile<32, EPI, NK>(a, s);
+  if constexpr (NK != 6) return rows == 48 ? launch_ln_tile<48, EPI, NK>(a, s) : launch_ln_tile<64, EPI, NK>(a, s);
+  return hipErrorInvalidValue;
 }
 
 template <int EPI>
 hipError_t launch_ln(const GemmArgs &a, hipStream_t s) {
-  const long rows = (a.M + SBM - 1) / SBM;
-  // (75 x 384, one tile per 54 CUs or 108: 2.5 % of an encoder call; from 160 workgroups on the wide tile, which normalises its
-  // rows half as often, is level or up to 5 % of a call ahead)
-  const bool wide = a.N % 64 == 0 && rows * (a.N / 64) >= 160;
+  if (a.N % kLnTN) return hipErrorInvalidValue;
   switch (a.K) {
-    case 512: return wide ? launch_ln_tile<64, EPI, 8>(a, s) : launch_ln_tile<32, EPI, 8>(a, s);
-    case 384: return wide ? launch_ln_tile<64, EPI, 6>(a, s) : launch_ln_tile<32, EPI, 6>(a, s);
-    default: return wide ? launch_ln_tile<64, EPI, 0>(a, s) : launch_ln_tile<32, EPI, 0>(a, s);
+    case 512: return launch_ln_rows<EPI, 8>(a, s);
+    case 384: return launch_ln_rows<EPI, 6>(a, s);
+    default: return launch_ln_rows<EPI, 0>(a, s);
   }
 }
 
@@ -407,10 +433,6 @@ constexpr int slice_smem() {
   constexpr int stages = 8 * SLOTS * (TM + TN) * 128, parts = 8 * TM * (TN + 4) * 4;
   return stages > parts ? stages : parts;
 }
-
-constexpr unsigned kOutside = 0xFFFFFFF0u;         // a byte offset no buffer reaches: the load returns zeros
-
-typedef __attribute__((address_space(3))) void lds_void;
 
 // Wait until at most V of this wave's loads are outstanding.
 template <int V>
