@@ -82,10 +82,12 @@ __device__ __forceinline__ void dl_tile(const GemmArgs &p, unsigned char *smem, 
   const __bf16 *xptr[OFFS ? 1 : XL];
   unsigned xoff[OFFS ? XL : 1], woff[WL];
   [[maybe_unused]] int xflags[XL];      // A_CONV3: bit 0 = first tap lies before the stream, bit 1 = last tap lies after it
+  const RowPlace wplace(p.w_panels, p.K >> 6, p.K), aplace(p.a_panels, p.K >> 6, p.lda);
+  const int lch = (lane & 7) ^ ((wave * 4 + (lrow >> 1)) & 7);          // (row >> 1) & 7 of every row this lane fetches: NW is even
+  static_assert(NW % 2 == 0, "the swizzle of a lane's rows repeats with the load instructions");
 #pragma unroll
   for (int i = 0; i < XL; ++i) {
     const int rt = (i * NW + wave) * 8 + lrow;
-    const int lch = (lane & 7) ^ ((rt >> 1) & 7);
     int row = m0 + rt;
     row = row < p.M ? row : p.M - 1;              // rows past M are computed but never stored
     if constexpr (AMODE == A_CONV3) {
@@ -93,17 +95,12 @@ __device__ __forceinline__ void dl_tile(const GemmArgs &p, unsigned char *smem, 
       xptr[i] = A + (long)p.row_src[row] * p.C + lch * 8;
       xflags[i] = p.row_flags[row];
     } else {
-      xoff[i] = 2u * (p.a_panels ? (((unsigned)(row >> 8) * (unsigned)(p.K >> 6)) << 14) + ((row & 255) << 6) + lch * 8   // panel layout
-                                 : (unsigned)row * (unsigned)p.lda + lch * 8);
+      xoff[i] = (unsigned)aplace(row) + lch * 16;
     }
   }
 #pragma unroll
   for (int i = 0; i < WL; ++i) {
-    const int rt = (i * NW + wave) * 8 + lrow;
-    const int lch = (lane & 7) ^ ((rt >> 1) & 7);
-    const int n = n0 + rt;
-    woff[i] = 2u * (p.w_panels ? (((unsigned)(n >> 8) * (unsigned)(p.K >> 6)) << 14) + ((n & 255) << 6) + lch * 8
-                               : (unsigned)n * (unsigned)p.K + lch * 8);
+    woff[i] = (unsigned)wplace(n0 + wave * 8) + (unsigned)(lrow + i * NW * 8) * (unsigned)wplace.row + lch * 16;      // (a tile's columns lie in one panel)
   }
 
   [[maybe_unused]] const int kpt = AMODE == A_CONV3 ? p.C / BK : 0;     // K steps per tap
@@ -291,6 +288,9 @@ __host__ inline int dl_plan(GemmArgs &b, int tiles_m, int tiles_n) {
   b.full_per_xcd = (b.n_full + 7) / 8;
   b.half_per_xcd = (b.n_half + 7) / 8;
   b.group_n = tiles_n >= 8 ? 4 : tiles_n;     // column groups only pay when a row of tiles is long
+  b.div_group = order_mul(tiles_m * b.group_n);
+  b.div_row = order_mul(b.group_n);
+  b.div_last = order_mul(tiles_n % b.group_n ? tiles_n % b.group_n : b.group_n);
   return 8 * (b.full_per_xcd + b.half_per_xcd);
 }
 
@@ -301,9 +301,9 @@ __host__ __device__ inline bool dl_unit(const GemmArgs &p, int bid, int tiles_m,
   const int G = min(max(p.group_n, 1), tiles_n);
   auto locate = [&](int t) {
     const int gs = tiles_m * G;
-    const int g = t / gs, rem = t - g * gs;
+    const int g = order_div(t, gs, p.div_group), rem = t - g * gs;
     const int gw = min(G, tiles_n - g * G);
-    u.row = rem / gw;
+    u.row = order_div(rem, gw, gw == G ? p.div_row : p.div_last);
     u.col = g * G + (rem - u.row * gw);
   };
   const int xcd = bid & 7, l = bid >> 3;

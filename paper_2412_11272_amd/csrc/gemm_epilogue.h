@@ -7,6 +7,23 @@ namespace wf {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// n / d by a multiplication with order_mul(d) = floor(2^32 / d) + 1, exact for n, d < 2^16: a tile finds its place before its first
+// load, and a division there is a chain of 30 instructions (a tile 3 of them; with the branches per load instruction that the two
+// operand layouts used to make, an encoder call of 425 rows of 1280 2211 -> 2184 us).
+__host__ __device__ inline uint32_t order_mul(int d) { return d > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d + 1) : 0; }
+__host__ __device__ inline int order_div(int n, int d, uint32_t mul) {
+  if (d == 1) return n;
+  return (n | d) < 65536 ? (int)(((uint64_t)(uint32_t)n * mul) >> 32) : n / d;
+}
+
+// Byte offset of a row of a bf16 operand, row-major or in panels of 256 rows, without a branch.
+struct RowPlace {
+  int shift, mask, panel, row;
+  __device__ __forceinline__ RowPlace(bool panels, int nk, int ld)
+      : shift(panels ? 8 : 31), mask(panels ? 255 : -1), panel(panels ? nk << 15 : 0), row(panels ? 128 : ld * 2) {}
+  __device__ __forceinline__ int operator()(int r) const { return (int)((unsigned)(r >> shift) * (unsigned)panel + (unsigned)(r & mask) * (unsigned)row); }
+};
+
 // One wave stores its TM x TN sub-tile at (mw0, nw0).  The accumulators (v_mfma_f32_16x16x32_bf16 with the weight
 // fragment as first operand) give a lane 4 consecutive features of ONE token, which would make every store instruction
 // touch 16 different rows.  The wave therefore transposes its sub-tile through its own slice `stg` of the LDS (TM rows of

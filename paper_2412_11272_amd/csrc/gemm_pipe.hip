@@ -20,6 +20,7 @@
 // Against the 128 x 128 kernel with two workgroups per CU it replaced (us, same shapes): 3156 x 768 x 3072 31.8 -> 22,
 // 2600 x 1024 x 4096 41 -> 28.5, 6400 x 1280 x 5120 86 -> 74; against the small-batch kernel at 425 rows: 1280 x 5120
 // 28.9 -> 20.5, 3840 x 1280 16.9 -> 10.2.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -87,15 +88,17 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
   const int n_tiles = tiles_m * tiles_n, n_units = n_tiles * splits, per_xcd = (n_units + 7) >> 3;
   const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (unit >= n_units || (int)(blockIdx.x >> 3) >= per_xcd) return;
-  const int split = EPI == EPI_PARTIAL ? unit / n_tiles : 0, tile = unit - split * n_tiles;    // a split's tiles share operands
+  const int split = EPI == EPI_PARTIAL ? (unit >= n_tiles) + (unit >= 2 * n_tiles) + (unit >= 3 * n_tiles) : 0;    // (at most four)
+  const int tile = unit - split * n_tiles;         // a split's tiles share operands
   const int G = min(p.group_n, tiles_n), gs = tiles_m * G;
-  const int grp = tile / gs, rem = tile - grp * gs, gw = min(G, tiles_n - grp * G);
-  const int m0 = rem / gw * BM, n0 = (grp * G + rem % gw) * BN;
+  const int grp = order_div(tile, gs, p.div_group), rem = tile - grp * gs, gw = min(G, tiles_n - grp * G);
+  const int trow = order_div(rem, gw, gw == G ? p.div_row : p.div_last);
+  const int m0 = trow * BM, n0 = (grp * G + rem - trow * gw) * BN;
 
   // ---- loads: instruction i of this wave fetches rows (4 i + wave) * 8 .. + 7 of the tile
   const int nkt = p.K >> 6;                        // K steps of the whole reduction, and [k0, k0 + nk) of this part
-  const int k0 = EPI == EPI_PARTIAL ? nkt * split / splits : 0;
-  const int nk = EPI == EPI_PARTIAL ? nkt * (split + 1) / splits - k0 : nkt;
+  const int k0 = EPI == EPI_PARTIAL ? order_div(nkt * split, splits, p.div_split) : 0;
+  const int nk = EPI == EPI_PARTIAL ? order_div(nkt * (split + 1), splits, p.div_split) - k0 : nkt;
   const size_t a_bytes = p.a_panels ? (size_t)((p.M + 255) >> 8) * 256 * p.K * 2 : ((size_t)(p.M - 1) * p.lda + p.K) * 2;
   // The gathered operand may exceed what 32 bits reach (row_src counts rows of the whole packed batch), so its buffer starts at
   // the tile's first window and the offsets are differences (windows come in ascending order, a tile's within a few rows).
@@ -109,12 +112,12 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
   const int woff = rr * (p.w_panels ? 128 : p.K * 2) + piece;
   const int wstep = p.w_panels ? 32768 : 128, astep = p.a_panels ? 32768 : 128;    // bytes from one K step to the next
   int wbase[WL], abase[AMODE == A_CONV3 ? 1 : XL];                                  // uniform
+  const RowPlace wplace(p.w_panels, nkt, p.K), aplace(p.a_panels, nkt, p.lda);
   int aoff[AMODE == A_CONV3 ? XL : 1];
   [[maybe_unused]] int aflags[AMODE == A_CONV3 ? XL : 1];
 #pragma unroll
   for (int i = 0; i < WL; ++i) {
-    const int n = n0 + (i * 4 + wave) * 8;
-    wbase[i] = (p.w_panels ? (((n >> 8) * nkt) << 15) + ((n & 255) << 7) : n * p.K * 2) + k0 * wstep;
+    wbase[i] = wplace(n0 + wave * 8) + i * 32 * wplace.row + k0 * wstep;      // (a tile's columns lie in one panel)
   }
   if constexpr (AMODE == A_CONV3) {
 #pragma unroll
@@ -128,7 +131,7 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       const int r0 = min(m0 + (i * 4 + wave) * 8, (p.M - 1) & ~7);        // a group past the last row repeats the last one
-      abase[i] = (p.a_panels ? (((r0 >> 8) * nkt) << 15) + ((r0 & 255) << 7) : r0 * p.lda * 2) + k0 * astep;
+      abase[i] = aplace(r0) + k0 * astep;
     }
   }
   // Loads [first, last) of a refill: the weights of K step kw into ring slot sw_, then the activations of K step kx into
@@ -263,6 +266,8 @@ hipError_t launch_tile(GemmArgs a, hipStream_t s) {
   // Tile columns per group: the 32 tiles an XCD works on at a time should form a block of about 5 x 6 tiles, which needs
   // the fewest operand panels in its L2; few rows of tiles need no grouping.
   a.group_n = tiles_m <= 6 ? 1 : tiles_n <= 6 ? tiles_n : tiles_n % 5 == 0 ? 5 : 4;
+  const int G = std::min(a.group_n, tiles_n);
+  a.div_group = order_mul(tiles_m * G); a.div_row = order_mul(G); a.div_last = order_mul(tiles_n % G ? tiles_n % G : G); a.div_split = order_mul(a.k_splits);
   hipLaunchKernelGGL(kern, dim3(8 * ((tiles + 7) / 8)), dim3(256), smem, s, a);
   return hipGetLastError();
 }

@@ -40,6 +40,8 @@ struct GemmArgs {
   // work-unit split of the direct-load GEMM (set by its launcher): full tiles, then half-width units
   int32_t n_full, n_half, full_per_xcd, half_per_xcd;
   int32_t group_n;          // tiles walk column groups of this many tile columns (>= tiles per row: plain row-major)
+  uint32_t div_group, div_row, div_last, div_split;      // order_mul of the tile order's divisors (set by the launchers): tiles of a group,
+                            // columns of a group, of the last group, parts of a cut reduction
   // Panel layout (direct-load GEMM only): instead of row-major, a matrix is stored as [rows/256][cols/64][256][64],
   // i.e. every (256-row panel, 64-column chunk) is one contiguous 32 KB block -- exactly one K step of a
   // tile's operand.  a_panels: A is read in that layout; w_panels: W is (rows = output features, padded to a
