@@ -74,6 +74,10 @@ __global__ void __launch_bounds__(256 * KS) attention_bf16_kernel(AttnArgs p) {
   // advances by n_heads % 8 from one stream to the next in the (cost-sorted) work list, so the XCDs that get
   // one head more than the others change from stream to stream.  Slots without a head leave at once.
   const int heads8 = (p.n_heads + 7) & ~7;
+  if (blockIdx.x >= (unsigned)(p.n_work * heads8)) {
+    prefetch_block(p.pf, blockIdx.x - p.n_work * heads8, smem_att);
+    return;
+  }
   const int item = blockIdx.x / heads8;
   const int w1 = p.work[2 * item + 1];
   const int rot = (((w1 >> 20) & 7) * (p.n_heads & 7)) & 7;
@@ -316,7 +320,7 @@ hipError_t launch_keys(const AttnArgs &a, hipStream_t s) {
     attr_err = hipFuncSetAttribute((const void *)attention_bf16_kernel<CAUSAL, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
   if (attr_err != hipSuccess) return attr_err;
-  hipLaunchKernelGGL((attention_bf16_kernel<CAUSAL, KS>), dim3(a.n_work * ((a.n_heads + 7) & ~7)), dim3(256 * KS), smem, s, a);
+  hipLaunchKernelGGL((attention_bf16_kernel<CAUSAL, KS>), dim3(a.n_work * ((a.n_heads + 7) & ~7) + (a.pf.bytes ? a.pf.blocks : 0)), dim3(256 * KS), smem, s, a);
   return hipGetLastError();
 }
 
@@ -337,6 +341,10 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_ks[];   // per wave: K [NB][8 KB], V [NB][8 KB]
 
   const int heads8 = (p.n_heads + 7) & ~7;
+  if (blockIdx.x >= (unsigned)(4 * p.n_work * heads8)) {
+    prefetch_block(p.pf, blockIdx.x - 4 * p.n_work * heads8, smem_ks);
+    return;
+  }
   // All first quarters of the items' 128 queries, then all second ones, ..: prompts shorter than a quarter leave three of
   // four workgroups without queries, and interleaved with the others those would keep three quarters of the CUs empty (the
   // dispatcher deals consecutive workgroups out round robin).
@@ -543,7 +551,7 @@ hipError_t launch_keysplit(const AttnArgs &a, hipStream_t s) {
     attr_err = hipFuncSetAttribute((const void *)attention_bf16_keysplit_kernel<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
   if (attr_err != hipSuccess) return attr_err;
-  hipLaunchKernelGGL(attention_bf16_keysplit_kernel<NB>, dim3(4 * a.n_work * ((a.n_heads + 7) & ~7)), dim3(256), smem, s, a);
+  hipLaunchKernelGGL(attention_bf16_keysplit_kernel<NB>, dim3(4 * a.n_work * ((a.n_heads + 7) & ~7) + (a.pf.bytes ? a.pf.blocks : 0)), dim3(256), smem, s, a);
   return hipGetLastError();
 }
 
@@ -589,6 +597,7 @@ AttnForm attention_form(int32_t n_heads, int32_t B, int64_t M, int64_t Mkv, int6
 hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
   if (a.n_work <= 0) return hipSuccess;
   if (a.d_model != a.n_heads * 64) return hipErrorInvalidValue;
+  if (a.pf.bytes && (!a.pf.p || a.pf.bytes % 16 || a.pf.bytes >= 1u << 31)) return hipErrorInvalidValue;
   if (a.ldq % 8 != 0 || a.ldkv % 8 != 0 || !a.q || !a.k || !a.v || !a.cu_q || !a.cu_kv) return hipErrorInvalidValue;
   if (a.causal) {
     if (a.cu_q != a.cu_kv) return hipErrorInvalidValue;

@@ -293,12 +293,13 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
     a.prefer_small = e->bf16 && gemm_slice_applies(Pt, d, K, true);
     return run_resid(e, s, cls, a, e->x, e->part, e->bf16 && !small && !gemm_small_applies(Pt, d, K), &pt);
   };
-  auto after_ln = [&](int cls, const float *g, const float *b, GemmArgs a, Epilogue ep) -> int {
+  auto ahead = [&](const void *w, int n, int k) { return prefetch_weights(e, !small && Pt <= kPrefetchRows, w, n, k); };
+  auto after_ln = [&](int cls, const float *g, const float *b, GemmArgs a, Epilogue ep, Prefetch pf = {}) -> int {
     int rc;
     if (small) {
       a.A = e->x; a.ln_g = g; a.ln_b = b; a.ln_eps = c.ln_eps;
     } else {
-      if ((rc = run_ln(e, s, DC_LN, e->x, g, b, e->u, act_bf16, Pt, d, c.ln_eps, nullptr, &pt))) return rc;
+      if ((rc = run_ln(e, s, DC_LN, e->x, g, b, e->u, act_bf16, Pt, d, c.ln_eps, nullptr, &pt, pf))) return rc;
       a.A = e->u;
     }
     a.M = Pt; a.K = d; a.lda = d;
@@ -313,7 +314,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
     if (e->bf16) {     // one product for q | k | v: the first d result columns go to the query buffer, the rest to the K/V cache
       GemmArgs a{};
       a.W = w.wqkv; a.bias = w.bqkv; a.out = e->qbuf; a.N = 3 * d; a.ldo = d; a.out2 = skv; a.n_split = d; a.ldo2 = 2 * d;
-      if ((rc = after_ln(DC_SELF_QKV, w.ln1_g, w.ln1_b, a, EPI_BIAS))) return rc;
+      if ((rc = after_ln(DC_SELF_QKV, w.ln1_g, w.ln1_b, a, EPI_BIAS, ahead(w.wqkv, 3 * d, d)))) return rc;
     } else {
       if ((rc = run_ln(e, s, DC_LN, e->x, w.ln1_g, w.ln1_b, e->u, act_bf16, Pt, d, c.ln_eps))) return rc;
       if ((rc = run_linear(e, s, DC_SELF_Q, e->u, d, w.wq, w.bq, e->qbuf, d, Pt, d, d, EPI_BIAS))) return rc;
@@ -338,6 +339,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
       a.q = e->qbuf; a.ldq = d; a.k = xkv; a.v = xkv + (size_t)d * es; a.ldkv = 2 * d; a.out = e->u;
       a.cu_q = d_cup; a.cu_kv = d_cus; a.work = d_work; a.n_work = n_work; a.n_heads = c.n_heads; a.d_model = d;
       a.B = B; a.M = Pt; a.Mkv = M; a.causal = 0; a.scale = 0.125f;
+      a.pf = ahead(w.w1, f, d);
       if ((rc = run_attention(e, s, DC_CROSS_ATTN, a, cross_flops, ((double)Pt * 2 + (double)M * 2) * d * es))) return rc;
     }
     if ((rc = resid(DC_CROSS_OUT, e->u, d, w.xwo, w.xbo))) return rc;
@@ -345,7 +347,7 @@ int wf_prefill(wf_decoder *e, const int32_t *tokens, const int32_t *cu_prompt, c
     {
       GemmArgs a{};
       a.W = w.w1; a.bias = w.b1; a.out = e->h; a.N = f; a.ldo = f;
-      if ((rc = after_ln(DC_FC1, w.ln2_g, w.ln2_b, a, EPI_BIAS_GELU))) return rc;
+      if ((rc = after_ln(DC_FC1, w.ln2_g, w.ln2_b, a, EPI_BIAS_GELU, ahead(w.w2, d, f)))) return rc;
     }
     if ((rc = resid(DC_FC2, e->h, f, w.w2, w.b2))) return rc;
   }

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels.h"
+
 namespace wf {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -79,6 +81,19 @@ __device__ __forceinline__ float wave_max(float v) {
   return half_max(fmaxf(p.a, p.b));
 }
 __device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
+
+// The share of workgroup `block` of f.blocks (256 threads or more, the first 256 take part) in fetching f: loads into 4 KB of
+// LDS that nobody reads.
+__device__ __forceinline__ void prefetch_block(const Prefetch &f, int block, unsigned char *lds) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave >= 4) return;
+  const uint32_t share = ((f.bytes + f.blocks * 4096u - 1) / (f.blocks * 4096u)) * 4096, begin = block * share;
+  const uint32_t end = begin + share < f.bytes ? begin + share : f.bytes;
+  for (uint32_t off = begin + threadIdx.x * 16; off < end; off += 4096)
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((const unsigned char *)f.p + off),
+                                     (__attribute__((address_space(3))) void *)(lds + wave * 1024), 16, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the LDS is this workgroup's until they have landed
+}
 
 // First stream index i with cu[i+1] > r, for a row r in [0, cu[B]).
 __device__ __forceinline__ int find_stream(const int32_t *cu, int B, int r) {

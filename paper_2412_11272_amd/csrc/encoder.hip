@@ -453,9 +453,11 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
     // (the memory is shared between lanes, and the order of the sums must not depend on how many there are).
     const bool may_split = e->bf16 && !small && M < 2 * kLaneTokens;
     Partials pt{};
+    // The weights of the next products but one are fetched under the kernels that leave most of the memory idle.
+    auto ahead = [&](const void *w, int n, int k) { return prefetch_weights(e, !small && M <= kPrefetchRows, w, n, k); };
     for (int l = 0; l < c.n_layers; ++l) {
       const LayerDev &w = e->layers[l];
-      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln1_g, w.ln1_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt))) return rc;
+      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln1_g, w.ln1_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt, ahead(w.wqkv, 3 * d, d)))) return rc;
       {
         GemmArgs a{};
         a.A = u; a.W = w.wqkv; a.bias = w.bqkv; a.out = qkv; a.M = Mg; a.N = 3 * d; a.K = d; a.lda = d; a.ldo = 3 * d;
@@ -470,6 +472,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
         a.ldq = a.ldkv = 3 * d; a.out = e->u; a.cu_q = a.cu_kv = d_cu_seq; a.work = work;
         a.n_work = nw; a.n_work_batch = n_work; a.n_heads = c.n_heads; a.d_model = d; a.B = B; a.M = M;
         a.scale = 0.125f;
+        a.pf = ahead(w.w1, f, d);
         Scope sc(e, ls, KC_ATTN, attn_flops, (double)Mg * 4 * d * es);
         hipError_t err = e->bf16 ? launch_attention_bf16(a, ls) : launch_attention_f32(a, ls);
         if (err != hipSuccess) return fail(WF_E_HIP, "attention launch: %s", hipGetErrorString(err));
@@ -481,7 +484,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
         place(a, true);
         if ((rc = run_resid(e, ls, KC_OUT, a, x, e->part, may_split, &pt))) return rc;
       }
-      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln2_g, w.ln2_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt))) return rc;
+      if (!small && (rc = run_ln(e, ls, KC_LN, x, w.ln2_g, w.ln2_b, u, act_bf16, Mg, d, c.ln_eps, nullptr, &pt, ahead(w.w2, d, f)))) return rc;
       {   // fc1 writes the hidden activations as [rows/256][f/64][256][64] panels: one contiguous 32 KB block per
           // K step of fc2's activation operand (whose rows would otherwise be 2 f bytes apart in memory)
         GemmArgs a{};

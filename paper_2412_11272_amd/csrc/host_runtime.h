@@ -242,13 +242,26 @@ inline int run_resid(DevCtx *e, hipStream_t s, int cls, GemmArgs a, float *x, fl
 
 // pt: parts left by run_resid, taken into x here (and cleared).
 inline int run_ln(DevCtx *e, hipStream_t s, int cls, float *x, const float *g, const float *b, void *out, int out_bf16,
-                  int M, int d, float eps, const int32_t *rows = nullptr, Partials *pt = nullptr) {
+                  int M, int d, float eps, const int32_t *rows = nullptr, Partials *pt = nullptr, Prefetch pf = {}) {
   const Partials p = pt ? *pt : Partials{};
   if (pt && !rows) *pt = Partials{};
   Scope sc(e, s, cls, 0.0, (double)M * d * (4 + (out_bf16 ? 2 : 4) + (p.n ? 4 * p.n + 4 : 0)));
-  hipError_t err = launch_layernorm(x, rows, g, b, out, out_bf16, M, d, eps, s, p);
+  hipError_t err = launch_layernorm(x, rows, g, b, out, out_bf16, M, d, eps, s, p, pf);
   if (err != hipSuccess) return fail(WF_E_HIP, "%s launch: %s", e->class_names[cls], hipGetErrorString(err));
   return WF_OK;
+}
+
+// Weights [n, k] for a kernel to fetch ahead of the product that reads them.  A wide model's weights (from 4 MB a matrix on) come from
+// memory in every layer: its blocks together exceed what the memory-side cache holds beside the activations.  In calls of up to
+// several thousand rows that is a fifth of a product's time (425 x 5120 x 1280 15.3 us from memory, 12.5 from the cache), while LayerNorm
+// and attention leave most of the memory idle and, in small calls, most of the chip.  128 workgroups: 32 take longer than the kernel
+// they ride on, 256 hold it up.  Encoder calls of d = 1280: 425 rows 2191 -> 2121 us, 2100 4865 -> 4593, 6200 10.03 -> 9.88 ms; d = 1024: 2600
+// rows 2997 -> 2924, 225 rows 1099 -> 1031; prefill of 6400 rows of 1280 15.54 -> 15.06 ms.  From about 8000 rows on it is level or
+// loses (8000 x 1280 11.42 -> 11.59, 10 000 x 1024 7.35 -> 7.48), and so it does with the matrices of narrow models (2000 x 512 386 -> 389 us).
+constexpr int kPrefetchRows = 7168;
+inline Prefetch prefetch_weights(const DevCtx *e, bool on, const void *w, int n, int k) {
+  const size_t bytes = (size_t)n * k * 2;
+  return e->bf16 && on && bytes >= 4u << 20 && bytes < 1u << 31 ? Prefetch{w, (uint32_t)bytes, 128} : Prefetch{};
 }
 
 // Attention work list: one item per (stream, block of q_tile queries), longest streams first so the

@@ -70,6 +70,13 @@ struct GemmArgs {
                             // of a small batch has twice as many rows as the batch has tokens) or the model is wide
 };
 
+// Memory a later kernel will read (weights), fetched towards the caches by workgroups that a kernel with few of its own adds to its grid.
+struct Prefetch {
+  const void *p;
+  uint32_t bytes;           // a multiple of 16; 0: none
+  int32_t blocks;
+};
+
 struct AttnArgs {
   // Head h owns columns [64h, 64h+64) counted from each of the three base pointers.  Queries of stream i
   // are rows [cu_q[i], cu_q[i+1]) of q (row stride ldq elements), its keys/values rows
@@ -85,6 +92,7 @@ struct AttnArgs {
   int32_t n_work_batch;     // work items of the whole batch where this launch is one lane of it, 0: n_work
   int32_t causal;
   float scale;              // 1/sqrt(64)
+  Prefetch pf;
 };
 
 struct PrepArgs {
@@ -127,7 +135,7 @@ struct Partials {
 };
 // out[i] = LayerNorm(x[rows[i]]), rows == NULL: x[i].  x is written only with partials and without rows.
 hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
-                            int32_t M, int32_t d, float eps, hipStream_t s, Partials pt = {});
+                            int32_t M, int32_t d, float eps, hipStream_t s, Partials pt = {}, Prefetch pf = {});
 // The first kernel of a call may bring the call's index arrays along in its arguments (at most kInlineInts of them: a launch takes
 // 4 KB) and leave them at `dst` for the kernels after it, which spares the call a copy ahead of its first kernel.
 constexpr int32_t kInlineInts = 960;

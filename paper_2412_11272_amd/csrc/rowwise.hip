@@ -92,7 +92,12 @@ __global__ void __launch_bounds__(256) prep_inline_kernel(PrepArgs p, int32_t *d
 template <typename TOUT, int MAXV, bool EARLY, int NP = 0>   // MAXV float4 per lane: d <= 256 * MAXV
 __global__ void __launch_bounds__(256) layernorm_kernel(float *__restrict__ x, const int32_t *__restrict__ rows,
                                                         const float *__restrict__ g, const float *__restrict__ b,
-                                                        TOUT *__restrict__ out, int M, int d, float eps, Partials pt) {
+                                                        TOUT *__restrict__ out, int M, int d, float eps, Partials pt, Prefetch pf) {
+  __shared__ __attribute__((aligned(16))) unsigned char unread[4096];
+  if (blockIdx.x >= (unsigned)(M + 3) / 4) {
+    prefetch_block(pf, blockIdx.x - (M + 3) / 4, unread);
+    return;
+  }
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
   const int lane = threadIdx.x & 63;
@@ -237,13 +242,14 @@ hipError_t launch_embed(const void *table, int table_bf16, const float *pos, con
 }
 
 hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const float *b, void *out, int out_bf16,
-                            int32_t M, int32_t d, float eps, hipStream_t s, Partials pt) {
+                            int32_t M, int32_t d, float eps, hipStream_t s, Partials pt, Prefetch pf) {
   if (M <= 0) return hipSuccess;
   if (pt.n == 1 || pt.n < 0 || pt.n > 4 || (pt.n && (!pt.part || !pt.bias || pt.M < M))) return hipErrorInvalidValue;
   if (d % 4 != 0 || d > 256 * 8) return hipErrorInvalidValue;
-  const dim3 grid((M + 3) / 4), block(256);
+  if (pf.bytes && (!pf.p || pf.bytes % 16 || pf.bytes >= 1u << 31)) return hipErrorInvalidValue;
+  const dim3 grid((M + 3) / 4 + (pf.bytes ? pf.blocks : 0)), block(256);
   const bool early = M <= 2048 || rows;        // two workgroups per compute unit; rows by index exist in that form only
-#define WF_LN2(T, V, E, P) hipLaunchKernelGGL((layernorm_kernel<T, V, E, P>), grid, block, 0, s, x, rows, g, b, (T *)out, M, d, eps, pt)
+#define WF_LN2(T, V, E, P) hipLaunchKernelGGL((layernorm_kernel<T, V, E, P>), grid, block, 0, s, x, rows, g, b, (T *)out, M, d, eps, pt, pf)
 #define WF_LN1(T, V, E)                    \
   do {                                     \
     if (pt.n == 2) WF_LN2(T, V, true, 2);  \
