@@ -117,8 +117,9 @@ def lib() -> C.CDLL:
     L = C.CDLL(LIB_PATH)
     L.wf_last_error.restype = C.c_char_p
     L.wf_encoder_create.argtypes = [C.POINTER(WfConfig), C.POINTER(WfWeights), C.POINTER(C.c_void_p)]
-    L.wf_encode_batch.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, _ip, _ip, C.c_int32, C.c_void_p, C.c_int32,
-                                  C.c_int64, _ip, C.c_void_p]
+    # the per-round calls take plain addresses (_addr): building a typed pointer per array costs more than a launch
+    L.wf_encode_batch.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32,
+                                  C.c_int64, C.c_void_p, C.c_void_p]
     L.wf_encoder_destroy.argtypes = [C.c_void_p]
     L.wf_encoder_destroy.restype = None
     L.wf_plan_batch.argtypes = [C.POINTER(WfConfig), _ip, C.c_int32, _ip, C.POINTER(C.c_int64), C.POINTER(C.c_int64)]
@@ -132,14 +133,14 @@ def lib() -> C.CDLL:
     L.wf_op_attention.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, _ip, C.c_int32, C.c_int32, C.c_void_p]
     L.wf_op_attention_noalloc.argtypes = [C.c_int32, C.c_void_p, C.c_void_p, _ip, C.c_int32, C.c_int32, C.c_void_p]
     L.wf_frontend_create.argtypes = [C.POINTER(WfFrontendConfig), C.c_void_p, C.POINTER(C.c_void_p)]
-    L.wf_logmel_batch.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_int64), _ip, C.c_int32, C.c_void_p, C.c_int32,
-                                  C.c_int64, _ip, C.c_void_p]
+    L.wf_logmel_batch.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32,
+                                  C.c_int64, C.c_void_p, C.c_void_p]
     L.wf_frontend_destroy.argtypes = [C.c_void_p]
     L.wf_frontend_destroy.restype = None
     L.wf_decoder_config_check.argtypes = [C.POINTER(WfDecoderConfig)]
     L.wf_decoder_create.argtypes = [C.POINTER(WfDecoderConfig), C.POINTER(WfDecoderWeights), C.POINTER(C.c_void_p)]
     L.wf_cross_kv.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
-    L.wf_prefill.argtypes = [C.c_void_p, _ip, _ip, _ip, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_int32, C.c_void_p,
+    L.wf_prefill.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_int32, C.c_void_p,
                              C.c_void_p, C.c_int64, C.c_void_p]
     L.wf_decoder_destroy.argtypes = [C.c_void_p]
     L.wf_decoder_destroy.restype = None
@@ -181,6 +182,16 @@ def lib() -> C.CDLL:
 def _check(rc: int):
     if rc != WF_OK:
         raise WfError(rc, lib().wf_last_error().decode())
+
+
+def _addr(a: np.ndarray) -> int:
+    return a.__array_interface__["data"][0]
+
+
+def _raw_stream(stream) -> int:
+    """The caller's stream, else torch's current one (its raw handle, without building a Stream object)."""
+    import torch
+    return stream if stream is not None else torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def last_error() -> str:
@@ -241,18 +252,29 @@ class Encoder:
         Asynchronous on `stream` (default: torch's current stream)."""
         import torch
         B = len(n_frames)
-        cu, _, M = plan_batch(self.cfg, n_frames) if 1 <= B <= self.cfg.max_streams else (np.zeros(B + 1, np.int32), 0, 0)
-        if out is None:      # at least one row, so that an invalid batch reaches the library's own checks
-            out = torch.empty((max(M, 1), self.cfg.d_model), device=mel.device, dtype=out_dtype or torch.float32)[:M]
-        s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
         off = np.ascontiguousarray(frame_offset, dtype=np.int32)
         nf = np.ascontiguousarray(n_frames, dtype=np.int32)
+        M = self._tokens(nf, B)
+        if out is None:      # at least one row, so that an invalid batch reaches the library's own checks
+            out = torch.empty((max(M, 1), self.cfg.d_model), device=mel.device, dtype=out_dtype or torch.float32)
+            if M < 1:
+                out = out[:M]
         cu_out = np.zeros(B + 1, dtype=np.int32)
-        _check(lib().wf_encode_batch(self._h, C.c_void_p(mel.data_ptr()), _torch_dtype_code(mel.dtype),
-                                     off.ctypes.data_as(_ip), nf.ctypes.data_as(_ip), B,
-                                     C.c_void_p(out.data_ptr() or out.untyped_storage().data_ptr()), _torch_dtype_code(out.dtype), out.shape[0],
-                                     cu_out.ctypes.data_as(_ip), C.c_void_p(s)))
+        _check(lib().wf_encode_batch(self._h, mel.data_ptr(), _torch_dtype_code(mel.dtype), _addr(off), _addr(nf), B,
+                                     out.data_ptr() or out.untyped_storage().data_ptr(), _torch_dtype_code(out.dtype), out.shape[0],
+                                     _addr(cu_out), _raw_stream(stream)))
         return out, cu_out
+
+    def _tokens(self, nf: np.ndarray, B: int) -> int:
+        """Tokens of a batch; one that the planner refuses is left to it (it raises)."""
+        c = self.cfg
+        if not 1 <= B <= c.max_streams:
+            return 0
+        H = c.hush_frames
+        t = nf.tolist()
+        if nf.ndim == 1 and min(t) >= 1 and max(t) + H <= c.max_frames_per_stream and sum(t) + B * H <= c.max_total_frames:
+            return sum([(v + H + 1) >> 1 for v in t])
+        return plan_batch(c, nf)[2]
 
     def set_profiling(self, on: bool):
         _check(lib().wf_encoder_set_profiling(self._h, 1 if on else 0))
@@ -309,16 +331,18 @@ class Frontend:
         """audio: CUDA float32 tensor of samples.  Returns (mel [sum T', n_mels] CUDA tensor, cu_frames ndarray)."""
         import torch
         B = len(n_samples)
-        F = sum(self.n_frames(n_samples))
-        if out is None:
-            out = torch.empty((max(F, 1), self.cfg.n_mels), device=audio.device, dtype=out_dtype or torch.float32)[:F]
-        s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
         off = np.ascontiguousarray(sample_offset, dtype=np.int64)
         ns = np.ascontiguousarray(n_samples, dtype=np.int32)
+        if out is None:
+            H = self.cfg.hush_samples
+            F = sum([(n + H) // 160 for n in ns.tolist()])
+            out = torch.empty((max(F, 1), self.cfg.n_mels), device=audio.device, dtype=out_dtype or torch.float32)
+            if F < 1:
+                out = out[:F]
         cu = np.zeros(B + 1, dtype=np.int32)
-        _check(lib().wf_logmel_batch(self._h, C.c_void_p(audio.data_ptr()), off.ctypes.data_as(C.POINTER(C.c_int64)),
-                                     ns.ctypes.data_as(_ip), B, C.c_void_p(out.data_ptr() or out.untyped_storage().data_ptr()),
-                                     _torch_dtype_code(out.dtype), out.shape[0], cu.ctypes.data_as(_ip), C.c_void_p(s)))
+        _check(lib().wf_logmel_batch(self._h, audio.data_ptr(), _addr(off), _addr(ns), B,
+                                     out.data_ptr() or out.untyped_storage().data_ptr(), _torch_dtype_code(out.dtype), out.shape[0],
+                                     _addr(cu), _raw_stream(stream)))
         return out, cu
 
     def close(self):
@@ -370,8 +394,7 @@ class Decoder:
         M = enc.shape[0]
         if out is None:
             out = torch.empty((self.cfg.n_layers, max(M, 1), 2 * self.cfg.d_model), device=enc.device, dtype=self.act_dtype)
-        s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
-        _check(lib().wf_cross_kv(self._h, C.c_void_p(enc.data_ptr()), M, C.c_void_p(out.data_ptr()), out.shape[1], C.c_void_p(s)))
+        _check(lib().wf_cross_kv(self._h, enc.data_ptr(), M, out.data_ptr(), out.shape[1], _raw_stream(stream)))
         return out
 
     def prefill(self, prompts: Sequence[Sequence[int]], cu_seqlens: Sequence[int], cross_kv, hidden_dtype=None,
@@ -393,14 +416,11 @@ class Decoder:
             logits = torch.empty((max(B, 1), self.cfg.n_vocab), device=dev, dtype=torch.float32)
         if self_kv is None and want_self_kv:
             self_kv = torch.empty((self.cfg.n_layers, max(Pt, 1), 2 * self.cfg.d_model), device=dev, dtype=self.act_dtype)
-        s = stream if stream is not None else torch.cuda.current_stream().cuda_stream
-        _check(lib().wf_prefill(self._h, tok.ctypes.data_as(_ip), cup.ctypes.data_as(_ip), cus.ctypes.data_as(_ip), B,
-                                C.c_void_p(cross_kv.data_ptr()), cross_kv.shape[1],
-                                C.c_void_p(hidden.data_ptr()) if hidden is not None else None,
-                                _torch_dtype_code(hidden.dtype) if hidden is not None else 0,
-                                C.c_void_p(logits.data_ptr()) if logits is not None else None,
-                                C.c_void_p(self_kv.data_ptr()) if self_kv is not None else None,
-                                self_kv.shape[1] if self_kv is not None else 0, C.c_void_p(s)))
+        _check(lib().wf_prefill(self._h, _addr(tok), _addr(cup), _addr(cus), B, cross_kv.data_ptr(), cross_kv.shape[1],
+                                hidden.data_ptr() if hidden is not None else None, _torch_dtype_code(hidden.dtype) if hidden is not None else 0,
+                                logits.data_ptr() if logits is not None else None,
+                                self_kv.data_ptr() if self_kv is not None else None,
+                                self_kv.shape[1] if self_kv is not None else 0, _raw_stream(stream)))
         return {"hidden": hidden[:Pt] if hidden is not None else None, "logits": logits[:B] if logits is not None else None,
                 "self_kv": self_kv, "cu_prompt": cup}
 
