@@ -335,6 +335,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_bf16_dl_kernel(GemmArgs p) 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   DlUnit u;
   if (!dl_unit(p, blockIdx.x, (p.M + BM - 1) / BM, p.N / BN, u)) return;
+  if constexpr (EPI == EPI_BIAS) p.out = group_out(p, u.col * BN);
   if (u.half == 0) dl_tile<BM, BN, WM, WN, EPI, SMEM, NT, AMODE, DEEP>(p, smem, u.row * BM, u.col * BN);
   else dl_tile<BM, BN / 2, WM, WN, EPI, SMEM, NT, AMODE, DEEP>(p, smem, u.row * BM, u.col * BN + (u.half - 1) * (BN / 2));
 }
@@ -398,6 +399,7 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   if (amode == A_CONV3 && (a.C % 8 != 0 || 3 * a.C > a.K || !a.row_src || !a.row_flags)) return hipErrorInvalidValue;
   if (epi == EPI_BIAS_GELU_POS && (!a.pos || !a.row_pos)) return hipErrorInvalidValue;
   if (a.out_panels && epi != EPI_BIAS && epi != EPI_BIAS_GELU) return hipErrorInvalidValue;   // bf16 results only
+  if (a.n_group && (epi != EPI_BIAS || amode != A_PLAIN || a.out_panels || a.out2 || a.n_group % 256 || a.N % a.n_group)) return hipErrorInvalidValue;
   if (a.out2 && (epi != EPI_BIAS || a.out_panels || a.n_split % 8 != 0 || a.n_split <= 0 || a.n_split >= a.N)) return hipErrorInvalidValue;
   // At most one tile per compute unit, or a convolution whose taps are no whole K steps (C not a multiple of 64, or padding
   // after the third tap): the pipelined kernel.  It adds a row up in the same order as the kernels below, so the choice

@@ -16,6 +16,13 @@ __host__ __device__ inline int order_div(int n, int d, uint32_t mul) {
   return (n | d) < 65536 ? (int)(((uint64_t)(uint32_t)n * mul) >> 32) : n / d;
 }
 
+// The result of the matrix that column n0 belongs to (GemmArgs::n_group), as a base for columns of the whole product.
+__device__ __forceinline__ void *group_out(const GemmArgs &p, int n0) {
+  if (p.n_group == 0) return p.out;
+  const int g = n0 / p.n_group;
+  return (__bf16 *)p.out + (size_t)g * (p.group_stride - p.n_group);
+}
+
 // Byte offset of a row of a bf16 operand, row-major or in panels of 256 rows, without a branch.
 struct RowPlace {
   int shift, mask, panel, row;

@@ -249,6 +249,7 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
   __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0) lgkmcnt(0)
   __builtin_amdgcn_s_barrier();                    // every wave is done with the stages
   if constexpr (EPI == EPI_PARTIAL) p.out = (float *)p.out + (size_t)split * p.M * p.N;
+  if constexpr (EPI == EPI_BIAS) p.out = group_out(p, n0);
   store_subtile<TM, TN, EPI == EPI_PARTIAL ? (int)EPI_BIAS_F32 : EPI, false>(p, smem + wave * (TM * 256), acc, m0 + wm * TM, n0 + wn * TN, lane);
 #endif
 }

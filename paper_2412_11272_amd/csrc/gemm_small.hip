@@ -14,14 +14,11 @@
 #include <algorithm>
 #include <mutex>
 
-#include "device_utils.h"
-#include "kernels.h"
+#include "gemm_epilogue.h"
 
 namespace wf {
 
 namespace {
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SBM = 32, SBN = 32, SBK = 64;
 constexpr int kMaxLnK = 2048;     // gemm_small_kernel keeps the LayerNorm gain and shift of the whole row in LDS
@@ -452,6 +449,7 @@ __global__ void __launch_bounds__(512) gemm_slice_kernel(GemmArgs p) {
   const int l16 = lane & 15, lq = lane >> 4, rr = lane >> 3;
   const int tiles_n = p.N / TN;
   const int m0 = blockIdx.x / tiles_n * TM, n0 = blockIdx.x % tiles_n * TN;      // a column of tiles keeps to an XCD or two
+  if constexpr (EPI == EPI_BIAS) p.out = group_out(p, n0);
   unsigned char *ring = smem_slice + wave * SLOTS * SLOT;
 
   // ---- this thread's outputs, and what the epilogue adds to them (requested first: nothing later waits for them)
@@ -706,6 +704,7 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
   if (a.M <= 0) return hipSuccess;
   if (a.N % SBN != 0 || a.K % SBK != 0 || a.K <= 0) return hipErrorInvalidValue;
   if ((a.a_panels && amode != A_PLAIN) || (a.out_panels && (amode == A_LN || a.out2 || (epi != EPI_BIAS && epi != EPI_BIAS_GELU)))) return hipErrorInvalidValue;
+  if (a.n_group && (epi != EPI_BIAS || amode != A_PLAIN || a.out_panels || a.out2 || a.n_group % 64 || a.N % a.n_group)) return hipErrorInvalidValue;
   if (a.out2 && (epi != EPI_BIAS || a.n_split % 4 != 0 || a.n_split <= 0 || a.n_split >= a.N)) return hipErrorInvalidValue;
   if (amode == A_PLAIN) {
     if (a.lda % 8 != 0) return hipErrorInvalidValue;

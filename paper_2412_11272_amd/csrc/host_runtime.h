@@ -91,18 +91,20 @@ inline int upload_f32(DevCtx *e, float **dst, const float *src, size_t n) {
   return WF_OK;
 }
 
-// Upload a host fp32 array in the object's weight dtype (bf16 RNE or fp32).
-inline int upload_w(DevCtx *e, void **dst, const float *src, size_t n) {
-  int rc = dev_alloc(e, dst, n * e->es);
-  if (rc) return rc;
+// A host fp32 array to device memory in the object's weight dtype (bf16 RNE or fp32).
+inline int copy_w(DevCtx *e, void *dst, const float *src, size_t n) {
   if (e->bf16) {
     std::vector<uint16_t> tmp(n);
     for (size_t i = 0; i < n; ++i) tmp[i] = f32_to_bf16_rne(src[i]);
-    WF_HIP_TRY(hipMemcpy(*dst, tmp.data(), n * 2, hipMemcpyHostToDevice));
+    WF_HIP_TRY(hipMemcpy(dst, tmp.data(), n * 2, hipMemcpyHostToDevice));
   } else {
-    WF_HIP_TRY(hipMemcpy(*dst, src, n * 4, hipMemcpyHostToDevice));
+    WF_HIP_TRY(hipMemcpy(dst, src, n * 4, hipMemcpyHostToDevice));
   }
   return WF_OK;
+}
+inline int upload_w(DevCtx *e, void **dst, const float *src, size_t n) {
+  int rc = dev_alloc(e, dst, n * e->es);
+  return rc ? rc : copy_w(e, *dst, src, n);
 }
 inline int upload_w(DevCtx *e, void **dst, const std::vector<float> &src) { return upload_w(e, dst, src.data(), src.size()); }
 

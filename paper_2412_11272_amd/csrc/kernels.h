@@ -64,6 +64,10 @@ struct GemmArgs {
   // EPI_BIAS_F32 only: columns [n_valid, N) of the result are not stored (the weight rows that pad a vocabulary to whole
   // tiles), ldo = n_valid may be odd; 0: all columns, ldo a multiple of 4
   int32_t n_valid;
+  // One product over several weight matrices side by side (bf16 results, no panels): columns [g n_group, (g + 1) n_group) of the result go
+  // to out + g group_stride (elements), row stride ldo.  n_group is a multiple of every tile's width; 0: one matrix.
+  int32_t n_group;
+  int64_t group_stride;
   int32_t k_splits;         // EPI_PARTIAL only
   int32_t prefer_large;     // never the small-batch kernel (a product that streams a huge weight matrix, a wide model)
   int32_t prefer_small;     // run on the small-batch kernels even if M is above their usual limit (the first convolution
