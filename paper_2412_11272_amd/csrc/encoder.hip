@@ -425,6 +425,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
     auto place = [&](GemmArgs &a, bool may_cut = false) {
       a.prefer_small = e->bf16 && (small || (M < 2 * kLaneTokens && gemm_slice_applies(a.M, a.N, a.K, may_cut)));
       a.prefer_large = !a.prefer_small;
+      a.shares_chip = n_lanes > 1;
     };
     int rc;
     {   // a1: conv1 + GELU as a GEMM over 3-frame windows (row maps hold absolute rows of the packed input)

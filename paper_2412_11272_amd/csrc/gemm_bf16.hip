@@ -31,6 +31,7 @@
 // weight panels and 8 activation panels instead of a whole row of weight panels, which cuts the L2 fill
 // traffic (the dominant off-chip energy of these kernels on a power-limited part) by more than half:
 // fc1 -7 %, QKV -2..-6 %.  Short rows (the 5 tile columns of the d x d and d x f projections) stay row-major.
+#include <algorithm>
 #include <mutex>
 
 #include "gemm_epilogue.h"
@@ -365,14 +366,28 @@ bool use_large_tile(const GemmArgs &a) {
 // these kernels) and measures about 7 % faster per flop, but a product is as slow as its last round of the chip,
 // so the choice goes by the estimated makespan: rounds of 256 tiles (a last round cut into half units counts
 // 0.5) times the measured per-tile time ratio of 1.18.
+double large_rounds(long tiles) {
+  const long rest = tiles % 256;
+  return (double)(tiles / 256) + (rest == 0 ? 0.0 : (2 * rest <= 256 ? 0.5 : 1.0));
+}
 int large_tile_rows(int M, int N) {
-  auto rounds = [](long tiles) {
-    const long rest = tiles % 256;
-    return (double)(tiles / 256) + (rest == 0 ? 0.0 : (2 * rest <= 256 ? 0.5 : 1.0));
-  };
+  auto rounds = large_rounds;
   const double t256 = rounds((long)((M + 255) / 256) * (N / 256));
   const double t320 = 1.18 * rounds((long)((M + 319) / 320) * (N / 256));
   return t320 < t256 ? 320 : 256;
+}
+
+// A product with bf16 results whose large tiles end in a poorly filled round takes the pipelined kernel's 192 x 256 tile where that ends in
+// a better one: its one round takes 0.95 of a round of 256 x 256 tiles, two take 0.83 each (2600 x 4096 x 1024 31.3 -> 29.8 us, 6420 x 3840 x
+// 1280 63.6 -> 59.3; 6000 x 4096 x 1024, whose large tiles take one round and a half, would lose 8 %).  Reductions of at least 768:
+// below, start and end of a tile weigh more.  Not beside another lane's kernels, which find no room on a CU with such a tile (9500 rows of
+// 768 in two lanes 2.47 -> 2.51 ms).
+bool takes_tall(int M, int N, int K, Epilogue epi) {
+  if ((epi != EPI_BIAS && epi != EPI_BIAS_GELU) || N % 256 || K < 768 || (long)((M + 255) / 256) * (N / 256) < 160) return false;
+  const long tiles = (long)((M + 191) / 192) * (N / 256);
+  if (tiles > 512) return false;
+  const double large = std::min(large_rounds((long)((M + 255) / 256) * (N / 256)), 1.18 * large_rounds((long)((M + 319) / 320) * (N / 256)));
+  return (tiles <= 256 ? 0.95 : 1.66) < 0.97 * large;
 }
 
 // Does a product run on the small-batch kernel?  (What is too narrow for the tiles below is refused by all of them.)
@@ -408,6 +423,7 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   if (epi == EPI_PARTIAL) return launch_gemm_pipe(a, amode, epi, s);
   if (epi == EPI_BIAS_F32 ? gemm_pipe_logits_applies(a.M, a.N) : !whole_taps || gemm_pipe_applies(a.M, a.N, a.K))
     return launch_gemm_pipe(a, amode, epi, s);
+  if (amode == A_PLAIN && !a.shares_chip && takes_tall(a.M, a.N, a.K, epi)) return launch_gemm_pipe(a, amode, epi, s);
   const bool big = use_large_tile(a);
   if (amode == A_PLAIN) {
     // streaming stores for bf16 results no cache level could hand on whole (threshold: twice the 32 MB of L2)
@@ -463,6 +479,7 @@ int gemm_kernel_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *b
   *bm = 0; *bn = 0;
   if (takes_small(a, A_PLAIN, epi)) return 0;
   if (gemm_pipe_tile(M, N, K, bm, bn)) return 1;
+  if (takes_tall(M, N, K, epi)) { *bm = 192; *bn = 256; return 1; }
   const bool big = use_large_tile(a);
   *bm = big ? large_tile_rows(M, N) : 128;
   *bn = big ? 256 : 128;

@@ -382,7 +382,8 @@ hipError_t launch_gemm_pipe(const GemmArgs &a, AMode amode, Epilogue epi, hipStr
   // took 49).
   if (t < 0 && amode == A_CONV3 && epi == EPI_BIAS_GELU && !a.a_panels && a.N % 128 == 0 && a.K % 64 == 0 && a.K > 0)
     return launch_tile<128, 128, 2, 2, false, EPI_BIAS_GELU, A_CONV3>(a, s);
-  if (t < 0) t = kTile128;           // more than one tile per CU: convolutions whose taps are no whole K steps
+  if (t < 0) t = amode == A_PLAIN ? kTileCount - 1 : kTile128;      // more than one tile per CU: products that ask for the tallest tile, and
+                                     // convolutions whose taps are no whole K steps
   if (a.N % kTiles[t].bn || a.K % 64 || a.K <= 0) return hipErrorInvalidValue;
   if (amode == A_PLAIN) {
     switch (epi) {

@@ -69,6 +69,7 @@ struct GemmArgs {
   int32_t n_group;
   int64_t group_stride;
   int32_t k_splits;         // EPI_PARTIAL only
+  int32_t shares_chip;      // another lane's kernels run beside this one
   int32_t prefer_large;     // never the small-batch kernel (a product that streams a huge weight matrix, a wide model)
   int32_t prefer_small;     // run on the small-batch kernels even if M is above their usual limit (the first convolution
                             // of a small batch has twice as many rows as the batch has tokens) or the model is wide

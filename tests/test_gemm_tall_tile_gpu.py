@@ -1,0 +1,26 @@
+"""Products whose large tiles end in a poorly filled round run on 192 x 256 tiles: both sides of the rule, ragged last rows, one and two
+rounds of the chip, against float64."""
+import pytest
+
+from paper_2412_11272_amd import binding as wf
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K,tall", [(2600, 4096, 1024, True), (3072, 4096, 768, True), (3073, 4096, 768, False), (2561, 4096, 832, True), (2560, 4096, 704, False),
+                                        (6420, 3840, 1280, True), (6401, 3840, 768, True), (6145, 3840, 768, False), (6000, 4096, 1024, False)])
+@pytest.mark.parametrize("epi", [0, 1])
+def test_product(M, N, K, tall, epi):
+    import torch
+    assert (wf.gemm_kernel_choice(M, N, K, epi) == (1, 192, 256)) == tall
+    g = torch.Generator(device="cuda").manual_seed(M + N + K + epi)
+    a = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    w = (0.05 * torch.randn(N, K, generator=g, device="cuda")).bfloat16()
+    b = torch.randn(N, generator=g, device="cuda")
+    out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wf.op_linear(wf.WF_PRECISION_BF16, a, w, b, out, epi)
+    ref = a.double() @ w.double().T + b.double()
+    if epi:
+        ref = torch.nn.functional.gelu(ref)
+    # exact products of bf16 values, fp32 sums, the result rounded to bf16 (2^-9; GELU 4.7e-4 before it)
+    assert float((out.double() - ref).abs().max() / ref.abs().max()) <= 5e-3
