@@ -248,8 +248,9 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
   // ---- gain and shift: one load instruction a wave.  (Loads to the LDS in the buffer form: behind the global form the compiler waits
   // for every load at the first use of any, and the statistics would not run while the weights arrive.)
   {
+    // The place of a wave's half is part of the vector offset, which the bounds check against K values covers by definition.
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)(wave < 2 ? p.ln_g : p.ln_b), 0, K * 4, 0x00027000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)((wave < 2 ? sGain : sShift) + (wave & 1) * 256), 16, lane * 16, (wave & 1) * 1024, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)((wave < 2 ? sGain : sShift) + (wave & 1) * 256), 16, (wave & 1) * 1024 + lane * 16, 0, 0, 0);
   }
   // ---- rows: 16 lanes a row, four columns of every 64; this lane's rows of a tile are RI * 4 * wave + 4 i + lq
   f32x4 x[RI][JV];
