@@ -252,6 +252,9 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)(wave < 2 ? p.ln_g : p.ln_b), 0, K * 4, 0x00027000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)((wave < 2 ? sGain : sShift) + (wave & 1) * 256), 16, (wave & 1) * 1024 + lane * 16, 0, 0, 0);
   }
+  // A wave's loads complete in order, so this one has landed once the rows are in registers, if it was issued before them: the fence sees
+  // to that.  The first barrier below publishes gain and shift on the strength of it, without a wait for the weights.
+  __builtin_amdgcn_sched_barrier(0x1);             // (arithmetic may cross: held back as well, the rows leave 0.1 .. 0.2 us later)
   // ---- rows: 16 lanes a row, four columns of every 64; this lane's rows of a tile are RI * 4 * wave + 4 i + lq
   f32x4 x[RI][JV];
   auto request = [&](int tile) {
@@ -298,6 +301,8 @@ __global__ void __launch_bounds__(256) gemm_ln_kernel(GemmArgs p, int row_groups
       rstd[i] = rsqrtf(row_sum(sq) * inv_k + p.ln_eps);
     }
     if (first) {          // gain and shift were requested before the rows: this wave's part of them is in the LDS by now
+#pragma unroll
+      for (int i = 0; i < RI; ++i) asm volatile("" : "+v"(rstd[i]));        // (the rows have been read: not an instruction, but no way round it)
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
