@@ -209,6 +209,13 @@ int wf_gemm_tile_map(int32_t M, int32_t N, int32_t tile_m, int32_t tile_n, int32
 int wf_gemm_tile_choice(int32_t M, int32_t N, int32_t *tile_m, int32_t *tile_n);
 
 /*
+ * Diagnostic, host only: by which routes wf_encode_batch would run a batch (arguments as in wf_plan_batch), as a sum of
+ * WF_ROUTE_* flags.  Negative WF_E_* code on a batch that the encoder would refuse.
+ */
+#define WF_ROUTE_INLINE_INDEX 1   /* the index arrays travel in the first kernel's arguments, without a copy ahead of it */
+int wf_encode_route(const wf_config *cfg, const int32_t *n_frames, int32_t B);
+
+/*
  * Diagnostic, host only: the kernel a wf_op_linear call in bf16 runs on and its tile: 0 = small-batch kernel (tile 0 x 0: 32
  * rows, columns by the number of workgroups), 1 = pipelined kernel (at most one tile per compute unit), 2 = large-batch
  * kernels.  Same decision code as the launch.  Negative WF_E_* code on bad arguments.

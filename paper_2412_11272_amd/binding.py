@@ -101,7 +101,7 @@ EXPORTS = ["wf_encoder_create", "wf_encode_batch", "wf_encoder_destroy", "wf_las
            "wf_rounds_destroy", "wf_run_rounds",
            "wf_beam_pruner_create", "wf_beam_pruner_step", "wf_beam_pruner_reset", "wf_beam_prune_session",
            "wf_beam_pruner_destroy", "wf_op_attention_noalloc",
-           "wf_encoder_set_graphs", "wf_encoder_graph_stats", "wf_gemm_tile_map", "wf_gemm_tile_choice", "wf_gemm_kernel_choice", "wf_attention_form", "wf_gelu_host", "wf_device_info", "wf_op_ln_linear"]
+           "wf_encoder_set_graphs", "wf_encoder_graph_stats", "wf_gemm_tile_map", "wf_gemm_tile_choice", "wf_gemm_kernel_choice", "wf_attention_form", "wf_encode_route", "wf_gelu_host", "wf_device_info", "wf_op_ln_linear"]
 
 
 def lib() -> C.CDLL:
@@ -156,6 +156,7 @@ def lib() -> C.CDLL:
     L.wf_gemm_tile_choice.argtypes = [C.c_int32, C.c_int32, _ip, _ip]
     L.wf_gemm_kernel_choice.argtypes = [C.c_int32] * 4 + [_ip, _ip]
     L.wf_attention_form.argtypes = [_ip, _ip, C.c_int32, C.c_int32]
+    L.wf_encode_route.argtypes = [C.POINTER(WfConfig), _ip, C.c_int32]
     L.wf_gelu_host.argtypes = [C.POINTER(C.c_float), C.POINTER(C.c_float), C.c_int32]
     L.wf_encoder_set_graphs.argtypes = [C.c_void_p, C.c_int32]
     _lp = C.POINTER(C.c_int64)
@@ -624,6 +625,17 @@ def gemm_kernel_choice(M: int, N: int, K: int, epilogue: int = 0) -> tuple:
     kernel = lib().wf_gemm_kernel_choice(M, N, K, epilogue, C.byref(tm), C.byref(tn))
     _check(min(kernel, 0))
     return kernel, tm.value, tn.value
+
+
+WF_ROUTE_INLINE_INDEX = 1
+
+
+def encode_route(cfg: WfConfig, n_frames: Sequence[int]) -> int:
+    """Sum of the WF_ROUTE_* flags of the routes by which Encoder.encode would run a batch (host only)."""
+    nf = np.ascontiguousarray(n_frames, dtype=np.int32)
+    flags = lib().wf_encode_route(C.byref(cfg), nf.ctypes.data_as(_ip), len(nf))
+    _check(min(flags, 0))
+    return flags
 
 
 def attention_form(n_heads: int, q_lens: Sequence[int], kv_lens: Optional[Sequence[int]] = None) -> int:

@@ -182,6 +182,17 @@ int wf_plan_batch(const wf_config *cfg, const int32_t *n_frames, int32_t B, int3
   return WF_OK;
 }
 
+int wf_encode_route(const wf_config *cfg, const int32_t *n_frames, int32_t B) {
+  int rc = check_config(cfg);
+  if (rc) return rc;
+  Plan plan;
+  std::vector<int32_t> cu(B >= 1 && B <= cfg->max_streams ? B + 1 : 0);
+  if ((rc = plan_batch(*cfg, n_frames, B, nullptr, cu.data(), &plan))) return rc;
+  int64_t n_ints = 4 * ((int64_t)B + 1);
+  for (int i = 0; i < B; ++i) n_ints += 2 * (((int64_t)cu[i + 1] - cu[i] + attention_q_tile() - 1) / attention_q_tile());
+  return prep_takes_ints(n_ints, prep_threads(plan.total_frames, cfg->n_mels, plan.total_tokens)) ? WF_ROUTE_INLINE_INDEX : 0;
+}
+
 int wf_kernel_class_count(void) { return KC_COUNT; }
 
 void wf_encoder_destroy(wf_encoder *e) {
@@ -625,7 +636,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
   ++e->direct_calls;
   // What fits a launch's arguments needs no copy ahead of the first kernel (a copy and its event hold every call up by 7 us: 75 tokens,
   // d = 384 116.7 -> 109.6 us).
-  if (idx_bytes <= kInlineInts * 4) return enqueue(s, e->idx_dev, InlineInts{e->idx_dev, hs, (int32_t)(idx_bytes / 4)});
+  if (prep_takes_ints(idx_bytes / 4, prep_threads(TF, c.n_mels, M))) return enqueue(s, e->idx_dev, InlineInts{e->idx_dev, hs, (int32_t)(idx_bytes / 4)});
   if ((rc = staging_submit(e, slot, e->idx_dev, idx_bytes, s))) return rc;
   return enqueue(s, e->idx_dev, {});
 }

@@ -149,6 +149,10 @@ struct InlineInts {
   const int32_t *src;       // host
   int32_t n;                // 0: the arrays are on the device already
 };
+// Threads of the packing kernel: one per eight features of a frame, one per token.
+inline int64_t prep_threads(int64_t total_frames, int64_t n_mels, int64_t tokens) { return total_frames * (n_mels / 8) + tokens; }
+// Do a batch's n_ints index values travel in the packing kernel's arguments?  That form counts its threads in 32 bits.
+inline bool prep_takes_ints(int64_t n_ints, int64_t threads) { return n_ints <= kInlineInts && threads < ((int64_t)1 << 31); }
 // (a.cu_frames, cu_seqlens, frame_offset and n_frames are the first 4 (B + 1) of the ints, in that order)
 hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s, InlineInts in = {});
 // x[r, :] = table[tok[r], :] + pos[pos_idx[r], :]  (fp32 out; table bf16 or fp32, pos fp32); tok and pos_idx are the first 2 rows

@@ -272,13 +272,13 @@ hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const
 }
 
 hipError_t launch_prep(const PrepArgs &a, int packed_bf16, hipStream_t s, InlineInts in) {
-  const long n = (long)a.total_frames * (a.n_mels / 8) + a.M;
+  const long n = prep_threads(a.total_frames, a.n_mels, a.M);
   if (n <= 0) return hipSuccess;
   const dim3 grid((unsigned)((n + 255) / 256)), block(256);
   if (in.n > 0) {
     IntsArg ints;
-    const hipError_t err = take_ints(in, 4 * (a.B + 1), &ints);
-    if (err != hipSuccess || n >= (1L << 31)) return err != hipSuccess ? err : hipErrorInvalidValue;
+    const hipError_t err = prep_takes_ints(in.n, n) ? take_ints(in, 4 * (a.B + 1), &ints) : hipErrorInvalidValue;
+    if (err != hipSuccess) return err;
 #define WF_PREP(TI, TO) hipLaunchKernelGGL((prep_inline_kernel<TI, TO>), grid, block, 0, s, a, in.dst, ints)
     if (packed_bf16) { if (a.mel_is_bf16) WF_PREP(__bf16, __bf16); else WF_PREP(float, __bf16); }
     else { if (a.mel_is_bf16) WF_PREP(__bf16, float); else WF_PREP(float, float); }

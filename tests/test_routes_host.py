@@ -1,0 +1,31 @@
+"""Which way a batch takes through the encoder, from the code that decides it (CPU only): every batch that the encoder accepts has
+one, whatever its size."""
+import pytest
+
+from paper_2412_11272_amd import binding as wf
+
+
+def _cfg(n_mels, streams, frames, d=128):
+    return wf.WfConfig(n_mels=n_mels, d_model=d, n_layers=0, n_heads=d // 64, d_mlp=128, hush_frames=0, max_streams=streams,
+                       max_total_frames=streams * frames, max_frames_per_stream=frames, precision=0, ln_eps=1e-5)
+
+
+@pytest.mark.parametrize("streams,inline", [(1, True), (159, True), (160, False)])
+def test_index_arrays_of_many_streams_go_by_copy(streams, inline):
+    """4 (B + 1) prefix sums and offsets + 2 ints per work item, 960 ints in the arguments."""
+    flags = wf.encode_route(_cfg(80, streams, 200), [200] * streams)
+    assert bool(flags & wf.WF_ROUTE_INLINE_INDEX) == inline
+
+
+@pytest.mark.parametrize("frames,inline", [(16000, True), (16400, False)])
+def test_index_arrays_of_huge_features_go_by_copy(frames, inline):
+    """The form that takes the index arrays in its arguments counts its threads in 32 bits: 2^31 of them and more (here 2 streams of
+    65 536 features of eight values a frame) go by the other form, not to an error."""
+    cfg = _cfg(8 * 65536, 2, frames)
+    assert wf.config_check(cfg) == wf.WF_OK
+    assert bool(wf.encode_route(cfg, [frames, frames]) & wf.WF_ROUTE_INLINE_INDEX) == inline
+
+
+def test_a_refused_batch_has_no_route():
+    with pytest.raises(wf.WfError):
+        wf.encode_route(_cfg(80, 2, 100), [101, 5])
