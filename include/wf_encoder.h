@@ -213,6 +213,7 @@ int wf_gemm_tile_choice(int32_t M, int32_t N, int32_t *tile_m, int32_t *tile_n);
  * WF_ROUTE_* flags.  Negative WF_E_* code on a batch that the encoder would refuse.
  */
 #define WF_ROUTE_INLINE_INDEX 1   /* the index arrays travel in the first kernel's arguments, without a copy ahead of it */
+#define WF_ROUTE_SLICED_CONV1 2   /* the first convolution runs on the small-batch kernel whose waves share the reduction (bf16) */
 int wf_encode_route(const wf_config *cfg, const int32_t *n_frames, int32_t B);
 
 /*

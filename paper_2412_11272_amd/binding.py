@@ -627,7 +627,7 @@ def gemm_kernel_choice(M: int, N: int, K: int, epilogue: int = 0) -> tuple:
     return kernel, tm.value, tn.value
 
 
-WF_ROUTE_INLINE_INDEX = 1
+WF_ROUTE_INLINE_INDEX, WF_ROUTE_SLICED_CONV1 = 1, 2
 
 
 def encode_route(cfg: WfConfig, n_frames: Sequence[int]) -> int:

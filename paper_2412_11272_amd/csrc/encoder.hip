@@ -131,6 +131,19 @@ int plan_batch(const wf_config &c, const int32_t *n_frames, int32_t B, int32_t *
   return WF_OK;
 }
 
+int padded_conv1_depth(const wf_config &c) { return (int)round_up(3 * (int64_t)c.n_mels, 64); }
+
+// Does a batch of M tokens in bf16 run all of its products on the small-batch kernels?
+bool small_batch(const wf_config &c, int M) {
+  return gemm_small_applies(M, 3 * c.d_model, c.d_model) && gemm_small_applies(M, c.d_mlp, c.d_model) && gemm_small_applies(M, c.d_model, 3 * c.d_model);
+}
+
+// Does the first convolution of M tokens in TF packed frames, in bf16, run on the sliced kernel?
+bool conv1_sliced(const wf_config &c, int k1p, int64_t M, int64_t TF) {
+  if (M >= 2 * kLaneTokens || !gemm_slice_reaches(TF, c.n_mels)) return false;
+  return small_batch(c, (int)M) || gemm_slice_applies((int)TF, c.d_model, k1p, false);
+}
+
 int check_config(const wf_config *c) {
   if (!c) return fail(WF_E_INVALID_ARG, "cfg is NULL");
   if (c->n_mels < 8 || c->n_mels % 8) return fail(WF_E_INVALID_ARG, "n_mels = %d must be a positive multiple of 8", c->n_mels);
@@ -190,7 +203,8 @@ int wf_encode_route(const wf_config *cfg, const int32_t *n_frames, int32_t B) {
   if ((rc = plan_batch(*cfg, n_frames, B, nullptr, cu.data(), &plan))) return rc;
   int64_t n_ints = 4 * ((int64_t)B + 1);
   for (int i = 0; i < B; ++i) n_ints += 2 * (((int64_t)cu[i + 1] - cu[i] + attention_q_tile() - 1) / attention_q_tile());
-  return prep_takes_ints(n_ints, prep_threads(plan.total_frames, cfg->n_mels, plan.total_tokens)) ? WF_ROUTE_INLINE_INDEX : 0;
+  return (prep_takes_ints(n_ints, prep_threads(plan.total_frames, cfg->n_mels, plan.total_tokens)) ? WF_ROUTE_INLINE_INDEX : 0) |
+         (cfg->precision == WF_PRECISION_BF16 && conv1_sliced(*cfg, padded_conv1_depth(*cfg), plan.total_tokens, plan.total_frames) ? WF_ROUTE_SLICED_CONV1 : 0);
 }
 
 int wf_kernel_class_count(void) { return KC_COUNT; }
@@ -223,7 +237,7 @@ static int create_impl(wf_encoder *e, const wf_config *cfg, const wf_weights *w)
   HIP_TRY(hipGetDevice(&e->device));
   HIP_TRY(init_kernels());
   const int d = cfg->d_model, f = cfg->d_mlp, C = cfg->n_mels, H = cfg->hush_frames;
-  e->k1p = (int)round_up(3 * C, 64);
+  e->k1p = padded_conv1_depth(*cfg);
   e->max_tokens = ((int64_t)cfg->max_total_frames + cfg->max_streams + 1) / 2;
   e->max_pos = (cfg->max_frames_per_stream + 1) / 2;
   e->max_work = e->max_tokens / attention_q_tile() + cfg->max_streams + 1;
@@ -429,7 +443,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
     // that a row's arithmetic does not depend on which other streams share the batch; the whole batch decides, not the lane:
     // a long stream may leave a short one a lane to itself), which also normalises its activation operand itself: the two LayerNorm launches of a block disappear and the MLP's hidden activations stay row-major.
     // (Every column tile recomputes the statistics of its rows: at d = 1280 that costs more than the LayerNorm kernel.)
-    const bool small = e->bf16 && gemm_small_applies(M, 3 * d, d) && gemm_small_applies(M, f, d) && gemm_small_applies(M, d, 3 * d);
+    const bool small = e->bf16 && small_batch(c, M);
     const int hpanels = small ? 0 : panels;
     // A batch of a few hundred tokens of a wide model takes the same kernel for the products it is the faster one for (batches that
     // always run on one lane: these products add a row up in another order).
@@ -445,6 +459,7 @@ int wf_encode_batch(wf_encoder *e, const void *mel_dev, int32_t mel_dtype, const
       a.M = Fg; a.N = d; a.K = e->k1p; a.lda = C; a.ldo = d;
       a.row_src = e->frame_src + f0; a.row_flags = e->frame_flags + f0; a.C = C;
       place(a);
+      if (!conv1_sliced(c, e->k1p, M, TF)) { a.prefer_small = 0; a.prefer_large = 1; }
       if ((rc = run_gemm(e, ls, KC_CONV1, a, A_CONV3, EPI_BIAS_GELU, 3 * C, (int)es, Fg, C))) return rc;
     }
     {   // a2: conv2 (stride 2) + GELU + positions -> fp32 residual stream

@@ -489,7 +489,7 @@ __global__ void __launch_bounds__(512) gemm_slice_kernel(GemmArgs p) {
 #pragma unroll
   for (int i = 0; i < XL; ++i) {
     const int row = min(m0 + i * 8 + rr, p.M - 1);                 // rows past M are computed but never stored
-    if constexpr (AMODE == A_CONV3) { aoff[i] = p.row_src[row]; aflags[i] = p.row_flags[row]; }      // (batches of a few thousand frames)
+    if constexpr (AMODE == A_CONV3) { aoff[i] = p.row_src[row]; aflags[i] = p.row_flags[row]; }      // (gemm_slice_reaches)
     else aoff[i] = (p.a_panels ? (((row >> 8) * nk) << 15) + ((row & 255) << 7) : (int)((unsigned)row * (unsigned)p.lda * 2u)) + (piece ^ ((i & 1) << 6));
   }
   auto load_w = [&](int i, int slot) {
@@ -508,7 +508,7 @@ __global__ void __launch_bounds__(512) gemm_slice_kernel(GemmArgs p) {
         const int kk = kt * 64 + ((piece ^ ((q & 1) << 6)) >> 1);
         const bool live = kk < 3 * p.C && !(kk < p.C && (aflags[q] & 1)) && !(kk >= 2 * p.C && (aflags[q] & 2));
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(ring + slot * SLOT + q * 1024), 16,
-                                                 live ? (aoff[q] * p.C + kk) * 2 : (int)kOutside, 0, 0, 0);
+                                                 live ? (int)((unsigned)(aoff[q] * p.C + kk) * 2u) : (int)kOutside, 0, 0, 0);
       } else {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)(ring + slot * SLOT + q * 1024), 16,
                                                  kt < nk ? aoff[q] : (int)kOutside, kt < nk ? kt * astep : 0, 0, 0);
@@ -703,6 +703,10 @@ bool gemm_slice_applies(int32_t M, int32_t N, int32_t K, bool may_cut) {
   if (N % 32 || K % 64 || (long)((M + 63) / 64) * (N / 32) > 256) return false;
   return !may_cut || K < 2 * N || pick_slice(M, N, K).us <= gemm_cut_estimate(M, N, K) + 0.3;
 }
+
+// The sliced kernel finds a convolution's windows by 32-bit byte offsets from the first row of the whole packed batch (the other kernels by
+// pointers, or by offsets from a tile's first window).
+bool gemm_slice_reaches(int64_t rows, int64_t values) { return rows * values * 2 <= (int64_t)kOutside; }
 
 bool gemm_small_applies(int32_t M, int32_t N, int32_t K) { return M <= kSmallRows && std::min(N, K) <= 512 && std::max(N, K) <= 2048; }
 

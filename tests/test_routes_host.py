@@ -26,6 +26,17 @@ def test_index_arrays_of_huge_features_go_by_copy(frames, inline):
     assert bool(wf.encode_route(cfg, [frames, frames]) & wf.WF_ROUTE_INLINE_INDEX) == inline
 
 
+@pytest.mark.parametrize("n_mels,frames,d,sliced", [(80, 300, 384, True), (128, 300, 1280, True), (128, 3000, 1280, False), (80, 20000, 384, False),
+                                                    (1 << 20, 2000, 128, True), (1 << 20, 2046, 128, True), (1 << 20, 2048, 128, False),
+                                                    (1 << 21, 1100, 128, False)])
+def test_sliced_first_convolution_reaches_its_windows(n_mels, frames, d, sliced):
+    """It addresses the packed features with 32-bit byte offsets: 4 GiB of them and more (2048 frames of 2^20 values) go to a kernel
+    that does not, however few the rows."""
+    cfg = _cfg(n_mels, 1, frames, d)
+    assert wf.config_check(cfg) == wf.WF_OK
+    assert bool(wf.encode_route(cfg, [frames]) & wf.WF_ROUTE_SLICED_CONV1) == sliced
+
+
 def test_a_refused_batch_has_no_route():
     with pytest.raises(wf.WfError):
         wf.encode_route(_cfg(80, 2, 100), [101, 5])
