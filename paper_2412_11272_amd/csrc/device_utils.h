@@ -40,7 +40,7 @@ __host__ __device__ __forceinline__ float gelu_fast(float z) {
   return z * (c * q + 0.5f);              // z (1/2 + erf(z / sqrt 2) / 2)
 }
 
-// Sums and maxima over the lanes of a wave in the vector unit: rotations inside a row of 16 lanes, then swaps of rows and of halves.
+// Sums and maxima over the lanes of a wave in the vector unit: rotations inside a row of 16 lanes, swaps of rows and of halves.
 // A step takes about 10 cycles where a shuffle through the LDS takes about 100, and these steps lie on the critical chain of every
 // kernel that uses them (LayerNorm of 425 x 1280 4.0 -> 3.2 us a launch, 6420 x 1280 11.4 -> 9.7, 75 x 384 2.6 -> 2.3; an encoder call of 31 694 rows
 // 40.08 -> 39.58 ms).
@@ -68,9 +68,10 @@ __device__ __forceinline__ float row_sum(float v) {          // over the 16 lane
 }
 __device__ __forceinline__ float half_sum(float v) { const Pair p = half_pair(v); return p.a + p.b; }         // of lanes l and l + 32
 __device__ __forceinline__ float half_max(float v) { const Pair p = half_pair(v); return fmaxf(p.a, p.b); }
+// (lanes 32 apart first, then 16, .. 1: bit for bit the sum that shuffles of the lane number's bits from the highest down give)
 __device__ __forceinline__ float wave_sum(float v) {
-  const Pair p = row_pair(row_sum(v));
-  return half_sum(p.a + p.b);
+  const Pair p = row_pair(half_sum(v));
+  return row_sum(p.a + p.b);
 }
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, row_rotate<8>(v));
