@@ -518,22 +518,23 @@ __global__ void __launch_bounds__(256) attention_bf16_keysplit_kernel(AttnArgs p
   // thread -> query tid / 8, features (tid % 8) * 8 .. + 7
   const int qq = tid >> 3, f0 = (tid & 7) * 8;
   if (q0 + qq < Lq) {
-    float M = sM[qq], sc[4], lsum = 0.0f;
+#pragma clang fp contract(off)                    // parts are rounded when scaled, as if each wave had scaled its own: no bit depends on who does
+    float M = sM[qq], lsum = 0.0f;
 #pragma unroll
     for (int w = 1; w < 4; ++w) M = fmaxf(M, sM[w * 32 + qq]);
+    f32x4 a0, a1;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      sc[w] = __builtin_amdgcn_exp2f((sM[w * 32 + qq] - M) * c);     // 0 for a wave that saw no tile (its reference is -inf)
-      lsum += sL[w * 32 + qq] * sc[w];
+      const float sc = __builtin_amdgcn_exp2f((sM[w * 32 + qq] - M) * c);     // 0 for a wave that saw no tile (its reference is -inf)
+      const f32x4 b0 = *(const f32x4 *)(sO + (w * 32 + qq) * PITCH + f0), b1 = *(const f32x4 *)(sO + (w * 32 + qq) * PITCH + f0 + 4);
+      lsum += sL[w * 32 + qq] * sc;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        a0[e] = w == 0 ? b0[e] * sc : a0[e] + b0[e] * sc;
+        a1[e] = w == 0 ? b1[e] * sc : a1[e] + b1[e] * sc;
+      }
     }
     const float inv = 1.0f / lsum;
-    f32x4 a0 = {0.0f, 0.0f, 0.0f, 0.0f}, a1 = a0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const f32x4 b0 = *(const f32x4 *)(sO + (w * 32 + qq) * PITCH + f0), b1 = *(const f32x4 *)(sO + (w * 32 + qq) * PITCH + f0 + 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { a0[e] += b0[e] * sc[w]; a1[e] += b1[e] * sc[w]; }
-    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) { a0[e] *= inv; a1[e] *= inv; }
     const bf16x4 c0 = to_bf16x4(a0), c1 = to_bf16x4(a1);
