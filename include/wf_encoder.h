@@ -217,11 +217,18 @@ int wf_gemm_tile_choice(int32_t M, int32_t N, int32_t *tile_m, int32_t *tile_n);
 int wf_encode_route(const wf_config *cfg, const int32_t *n_frames, int32_t B);
 
 /*
- * Diagnostic, host only: the kernel a wf_op_linear call in bf16 runs on and its tile: 0 = small-batch kernel (tile 0 x 0: 32
- * rows, columns by the number of workgroups), 1 = pipelined kernel (at most one tile per compute unit), 2 = large-batch
+ * Diagnostic, host only: the kernel a wf_op_linear call in bf16 runs on and its tile: 0 = small-batch kernels (tile 0 x 0: see
+ * wf_gemm_small_choice), 1 = pipelined kernel (at most one tile per compute unit), 2 = large-batch
  * kernels.  Same decision code as the launch.  Negative WF_E_* code on bad arguments.
  */
 int wf_gemm_kernel_choice(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t *tile_m, int32_t *tile_n);
+
+/*
+ * Diagnostic, host only: how the small-batch kernels run a product with a row-major operand that is given to them (by
+ * wf_op_linear: kernel 0 of wf_gemm_kernel_choice): the number of waves that share the reduction, 4 or 8, and the tile of a
+ * workgroup.  Same decision code as the launch.  Negative WF_E_* code on bad arguments.
+ */
+int wf_gemm_small_choice(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t *tile_m, int32_t *tile_n);
 
 /*
  * Diagnostic, host only: the form the bf16 attention takes for B streams of cu_q (HOST [B+1] prefix sums) queries over cu_kv

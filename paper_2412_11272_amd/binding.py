@@ -101,7 +101,7 @@ EXPORTS = ["wf_encoder_create", "wf_encode_batch", "wf_encoder_destroy", "wf_las
            "wf_rounds_destroy", "wf_run_rounds",
            "wf_beam_pruner_create", "wf_beam_pruner_step", "wf_beam_pruner_reset", "wf_beam_prune_session",
            "wf_beam_pruner_destroy", "wf_op_attention_noalloc",
-           "wf_encoder_set_graphs", "wf_encoder_graph_stats", "wf_gemm_tile_map", "wf_gemm_tile_choice", "wf_gemm_kernel_choice", "wf_attention_form", "wf_encode_route", "wf_gelu_host", "wf_device_info", "wf_op_ln_linear"]
+           "wf_encoder_set_graphs", "wf_encoder_graph_stats", "wf_gemm_tile_map", "wf_gemm_tile_choice", "wf_gemm_kernel_choice", "wf_gemm_small_choice", "wf_attention_form", "wf_encode_route", "wf_gelu_host", "wf_device_info", "wf_op_ln_linear"]
 
 
 def lib() -> C.CDLL:
@@ -155,6 +155,7 @@ def lib() -> C.CDLL:
     L.wf_gemm_tile_map.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, _ip, C.c_int32]
     L.wf_gemm_tile_choice.argtypes = [C.c_int32, C.c_int32, _ip, _ip]
     L.wf_gemm_kernel_choice.argtypes = [C.c_int32] * 4 + [_ip, _ip]
+    L.wf_gemm_small_choice.argtypes = [C.c_int32] * 4 + [_ip, _ip]
     L.wf_attention_form.argtypes = [_ip, _ip, C.c_int32, C.c_int32]
     L.wf_encode_route.argtypes = [C.POINTER(WfConfig), _ip, C.c_int32]
     L.wf_gelu_host.argtypes = [C.POINTER(C.c_float), C.POINTER(C.c_float), C.c_int32]
@@ -625,6 +626,14 @@ def gemm_kernel_choice(M: int, N: int, K: int, epilogue: int = 0) -> tuple:
     kernel = lib().wf_gemm_kernel_choice(M, N, K, epilogue, C.byref(tm), C.byref(tn))
     _check(min(kernel, 0))
     return kernel, tm.value, tn.value
+
+
+def gemm_small_choice(M: int, N: int, K: int, epilogue: int = 0) -> tuple:
+    """(waves that share the reduction, tile rows, tile columns) of a product on the small-batch kernels (host only)."""
+    tm, tn = C.c_int32(0), C.c_int32(0)
+    waves = lib().wf_gemm_small_choice(M, N, K, epilogue, C.byref(tm), C.byref(tn))
+    _check(min(waves, 0))
+    return waves, tm.value, tn.value
 
 
 WF_ROUTE_INLINE_INDEX, WF_ROUTE_SLICED_CONV1 = 1, 2

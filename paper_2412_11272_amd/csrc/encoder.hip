@@ -741,6 +741,13 @@ int wf_gemm_kernel_choice(int32_t M, int32_t N, int32_t K, int32_t epilogue, int
   return gemm_kernel_choice(M, N, K, (Epilogue)epilogue, tile_m, tile_n);
 }
 
+int wf_gemm_small_choice(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t *tile_m, int32_t *tile_n) {
+  if (!tile_m || !tile_n) return fail(WF_E_INVALID_ARG, "NULL pointer");
+  if (M < 1 || N < 128 || N % 128 || K < 64 || K % 64 || epilogue < 0 || epilogue > 2)
+    return fail(WF_E_INVALID_ARG, "need M >= 1, N %% 128 == 0, K %% 64 == 0, epilogue 0 .. 2");
+  return gemm_small_choice(M, N, K, (Epilogue)epilogue, tile_m, tile_n);
+}
+
 int wf_attention_form(const int32_t *cu_q, const int32_t *cu_kv, int32_t B, int32_t n_heads) {
   if (!cu_q || !cu_kv || B < 1 || n_heads < 1) return fail(WF_E_INVALID_ARG, "NULL pointer, or B or n_heads < 1");
   int64_t n_work = 0;

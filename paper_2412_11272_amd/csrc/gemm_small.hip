@@ -5,11 +5,11 @@
 //   out = epilogue(A . W^T),  A [M, K], W [N, K], fp32 accumulation, M up to about a thousand rows of a narrow model, or few
 //   enough rows of any product (gemm_small_few_rows, gemm_slice_applies).
 //
-//   gemm_slice_kernel   the operand is in memory as it is needed: plain rows or the windows of a convolution
+//   gemm_slice_kernel   the operand is in memory as it is needed: plain rows or the windows of a convolution, eight waves share K
 //   gemm_ln_kernel      the operand is LayerNorm(x) of an fp32 matrix x with rows of at most 512 values (every model narrow enough
 //                       for this file), normalised on the way in.  This removes two kernels per transformer block; with a few
 //                       hundred tokens each kernel in the chain costs 3-5 us whatever it does.
-//   gemm_small_kernel   the same for longer rows (wf_op_ln_linear only)
+//   gemm_small_kernel   four waves share K: short reductions (takes_four_waves), and LayerNorm(x) of longer rows (wf_op_ln_linear only)
 
 #include <algorithm>
 #include <mutex>
@@ -21,19 +21,20 @@ namespace wf {
 namespace {
 
 constexpr int SBM = 32, SBN = 32, SBK = 64;
-constexpr int kMaxLnK = 2048;     // gemm_small_kernel keeps the LayerNorm gain and shift of the whole row in LDS
+constexpr int kMaxLnK = 2048;     // gemm_small_kernel keeps the LayerNorm gain and shift of the whole row in LDS (A_LN)
 constexpr unsigned kOutside = 0xFFFFFFF0u;         // a byte offset no buffer reaches: the load returns zeros
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-// LayerNorm(x) operand of any depth up to kMaxLnK.  32-row tiles, 32, 64 or 128 columns wide (NB column blocks of 32): the launcher takes
-// the widest that still leaves about 160 workgroups, because every column tile re-normalises the same 32 rows.  The four waves split
-// the reduction: in every 64-deep K step wave w multiplies the k slice [16 w, 16 w + 16) with one 32x32x16 MFMA, and the four
-// partial tiles are added in a fixed order through LDS at the end (deterministic).  Chunks are requested eight (widest tile: four)
-// K steps ahead into registers, two K steps are staged in LDS per barrier.  The workgroup first computes mean and 1/sqrt(var + eps)
-// of its 32 rows (one pass, sums shifted by the row's first element so that the variance does not cancel), then every
-// chunk is (x - mean) * rstd * gamma + beta rounded to bf16 -- exactly what the LayerNorm kernel would have stored.
-template <int EPI, int NB>
+// Plain rows and windows of a short reduction, and LayerNorm(x) operands of up to kMaxLnK values.  32-row tiles, 32, 64 or 128 columns
+// wide (NB column blocks of 32): the launcher takes the widest that still leaves about 160 workgroups, because every column tile
+// re-reads (and re-normalises) the same 32 rows.  The four waves split the reduction: in every 64-deep K step wave w multiplies the
+// k slice [16 w, 16 w + 16) with one 32x32x16 MFMA, and the four partial tiles are added in a fixed order through LDS at the end
+// (deterministic).  Chunks are requested eight (widest tile: four) K steps ahead into registers, two K steps are staged in LDS per
+// barrier.  A_LN: the workgroup first computes mean and 1/sqrt(var + eps) of its 32 rows (one pass, sums shifted by the row's
+// first element so that the variance does not cancel), then every chunk is (x - mean) * rstd * gamma + beta rounded to bf16 --
+// exactly what the LayerNorm kernel would have stored.
+template <int AMODE, int EPI, int NB>
 __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
   constexpr int TN = NB * SBN;                                               // tile width in columns
   constexpr int DEPTH = NB >= 4 ? 4 : 8;                                     // K steps in flight (register ring)
@@ -45,10 +46,11 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
   unsigned char(*sA)[SBM * 128] = (unsigned char(*)[SBM * 128])sMem;                     // [stage][row][64 bf16]
   unsigned char(*sW)[TN * 128] = (unsigned char(*)[TN * 128])(sMem + NS * SBM * 128);
   float(*sPart)[SBM][TN + 4] = (float(*)[SBM][TN + 4])sMem;
-  __shared__ __attribute__((aligned(16))) float sGain[kMaxLnK], sShift[kMaxLnK];
+  __shared__ __attribute__((aligned(16))) float sGain[AMODE == A_LN ? kMaxLnK : 4], sShift[AMODE == A_LN ? kMaxLnK : 4];
 
   const int tiles_n = p.N / TN;
   const int m0 = (blockIdx.x / tiles_n) * SBM, n0 = (blockIdx.x % tiles_n) * TN;
+  if constexpr (AMODE == A_PLAIN && EPI == EPI_BIAS) p.out = group_out(p, n0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lg = lane >> 5;
 
@@ -65,34 +67,57 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
     wptr[j] = p.w_panels ? W + ((size_t)(n >> 8) * (p.K >> 6) << 14) + ((n & 255) << 6) + ch * 8 : W + (size_t)n * p.K + ch * 8;
   }
   const int wstep = p.w_panels ? 1 << 14 : SBK;
-  const float *xptr = (const float *)p.A + (size_t)row * p.lda + ch * 8;
+  const __bf16 *aptr = nullptr;
+  const float *xptr = nullptr;
+  int flags = 0;
+  if constexpr (AMODE == A_PLAIN) aptr = (const __bf16 *)p.A + (size_t)row * p.lda + ch * 8;
+  else if constexpr (AMODE == A_CONV3) {
+    aptr = (const __bf16 *)p.A + (long)p.row_src[row] * p.C + ch * 8;
+    flags = p.row_flags[row];
+  } else xptr = (const float *)p.A + (size_t)row * p.lda + ch * 8;
 
-  float mu = 0.0f, rstd = 0.0f;                  // statistics of this thread's row
+  [[maybe_unused]] float mu = 0.0f, rstd = 0.0f;     // A_LN: statistics of this thread's row
   // ---- operand pipeline: chunks of K step kt + DEPTH - 1 are requested while step kt is multiplied
   u32x4 wreg[DEPTH][NB];
-  f32x4 xreg[DEPTH][2];
+  [[maybe_unused]] u32x4 areg[DEPTH];
+  [[maybe_unused]] f32x4 xreg[DEPTH][2];
   const int nk = p.K / SBK;
   auto request = [&](int kt, int slot) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) wreg[slot][j] = *(const u32x4 *)(wptr[j] + (size_t)kt * wstep);
-    xreg[slot][0] = *(const f32x4 *)(xptr + kt * SBK);
-    xreg[slot][1] = *(const f32x4 *)(xptr + kt * SBK + 4);
+    if constexpr (AMODE == A_PLAIN) {
+      areg[slot] = *(const u32x4 *)(aptr + kt * SBK);
+    } else if constexpr (AMODE == A_CONV3) {
+      const int kk = kt * SBK + ch * 8;          // chunks never straddle taps: C % 8 == 0
+      const int tap = kk / p.C;
+      const bool ok = (kk < 3 * p.C) && !((tap == 0) && (flags & 1)) && !((tap == 2) && (flags & 2));
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (ok) v = *(const u32x4 *)(aptr + kt * SBK);
+      areg[slot] = v;
+    } else {
+      xreg[slot][0] = *(const f32x4 *)(xptr + kt * SBK);
+      xreg[slot][1] = *(const f32x4 *)(xptr + kt * SBK + 4);
+    }
   };
   auto commit = [&](int kt, int slot) {          // registers -> LDS stage kt % NS
     unsigned char *dA = sA[kt & (NS - 1)] + lds_off, *dW = sW[kt & (NS - 1)] + lds_off;
 #pragma unroll
     for (int j = 0; j < NB; ++j) *(u32x4 *)(dW + j * SBN * 128) = wreg[slot][j];
-    const int k = kt * SBK + ch * 8;
-    const f32x4 g0 = *(const f32x4 *)&sGain[k], g1 = *(const f32x4 *)&sGain[k + 4];
-    const f32x4 b0 = *(const f32x4 *)&sShift[k], b1 = *(const f32x4 *)&sShift[k + 4];
-    f32x4 y0, y1;
+    if constexpr (AMODE == A_LN) {
+      const int k = kt * SBK + ch * 8;
+      const f32x4 g0 = *(const f32x4 *)&sGain[k], g1 = *(const f32x4 *)&sGain[k + 4];
+      const f32x4 b0 = *(const f32x4 *)&sShift[k], b1 = *(const f32x4 *)&sShift[k + 4];
+      f32x4 y0, y1;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      y0[e] = (xreg[slot][0][e] - mu) * rstd * g0[e] + b0[e];
-      y1[e] = (xreg[slot][1][e] - mu) * rstd * g1[e] + b1[e];
+      for (int e = 0; e < 4; ++e) {
+        y0[e] = (xreg[slot][0][e] - mu) * rstd * g0[e] + b0[e];
+        y1[e] = (xreg[slot][1][e] - mu) * rstd * g1[e] + b1[e];
+      }
+      const bf16x4 c0 = to_bf16x4(y0), c1 = to_bf16x4(y1);
+      *(bf16x8 *)dA = __builtin_shufflevector(c0, c1, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      *(u32x4 *)dA = areg[slot];
     }
-    const bf16x4 c0 = to_bf16x4(y0), c1 = to_bf16x4(y1);
-    *(bf16x8 *)dA = __builtin_shufflevector(c0, c1, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
   f32x16 acc[NB];
@@ -103,9 +128,9 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d)
     if (d < nk) request(d, d);
-  // ---- statistics of the tile's 32 rows (after the first operand requests, so that their latencies overlap).
+  // ---- A_LN: statistics of the tile's 32 rows (after the first operand requests, so that their latencies overlap).
   // Eight threads per row, each over every eighth 32-byte piece, eight pieces requested at a time.
-  {
+  if constexpr (AMODE == A_LN) {
     for (int k = tid * 4; k < p.K; k += 1024) {   // gain and shift of the whole row -> LDS (a load per K step would sit
       *(f32x4 *)&sGain[k] = *(const f32x4 *)(p.ln_g + k);   // on the critical path of every step)
       *(f32x4 *)&sShift[k] = *(const f32x4 *)(p.ln_b + k);
@@ -188,6 +213,8 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
   // thread -> row er, 4 consecutive features from ec in each of the NB column blocks
   const int er = tid >> 3, m = m0 + er;
   if (m >= p.M) return;
+  [[maybe_unused]] int prow = 0;
+  if constexpr (EPI == EPI_BIAS_GELU_POS) prow = p.row_pos[m];
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int ec = j * SBN + (tid & 7) * 4;
@@ -206,10 +233,21 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(GemmArgs p) {
       __bf16 *dst = (p.out2 && nn >= p.n_split) ? (__bf16 *)p.out2 + (size_t)m * p.ldo2 + (nn - p.n_split)
                                                  : (__bf16 *)p.out + (size_t)m * p.ldo + nn;
       *(bf16x4 *)dst = to_bf16x4(v);
-    } else {
+    } else if constexpr (EPI == EPI_BIAS_GELU) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]);
       *(bf16x4 *)((__bf16 *)p.out + (size_t)m * p.ldo + nn) = to_bf16x4(v);
+    } else if constexpr (EPI == EPI_BIAS_RESID) {
+      f32x4 *o = (f32x4 *)((float *)p.out + (size_t)m * p.ldo + nn);
+      const f32x4 x = *o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += x[e];
+      *o = v;
+    } else {
+      const f32x4 pe = *(const f32x4 *)(p.pos + (size_t)prow * p.N + nn);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]) + pe[e];
+      *(f32x4 *)((float *)p.out + (size_t)m * p.ldo + nn) = v;
     }
   }
 }
@@ -672,17 +710,45 @@ int pick_blocks(const GemmArgs &a) {
   return 1;
 }
 
-template <int EPI>
+template <int AMODE, int EPI>
 hipError_t launch_small(const GemmArgs &a, hipStream_t s) {
   const int nb = pick_blocks(a);
   const dim3 grid((unsigned)((long)((a.M + SBM - 1) / SBM) * (a.N / (nb * SBN)))), block(256);
-  if (nb == 4) hipLaunchKernelGGL((gemm_small_kernel<EPI, 4>), grid, block, 0, s, a);
-  else if (nb == 2) hipLaunchKernelGGL((gemm_small_kernel<EPI, 2>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gemm_small_kernel<EPI, 1>), grid, block, 0, s, a);
+  if (nb == 4) hipLaunchKernelGGL((gemm_small_kernel<AMODE, EPI, 4>), grid, block, 0, s, a);
+  else if (nb == 2) hipLaunchKernelGGL((gemm_small_kernel<AMODE, EPI, 2>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemm_small_kernel<AMODE, EPI, 1>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
+// Short reductions: fewer than six K steps leave waves of the sliced kernel idle, and its eight partial tiles cost more to add up than the
+// loop gains.  Four waves and eight (us a launch): 130 x 384 x 64 2.4 and 2.8, 1024 x 384 x 64 2.9 and 4.1, 500 x 768 x 256 3.4 and
+// 4.1, 1024 x 384 x 320 3.7 and 4.1; from 448 on eight are ahead by up to 12 %.  At 384 plain products with bf16 results of 128 to 512 tiles
+// of 32 x 32 (130 x 1152 3.0 and 3.3, 300 x 1536 4.0 and 4.2; 75 x 1152 3.0 on both, 650 x 1152 5.5 and 5.2), windows and residual updates not (their rows
+// keep one order of sums whatever their number).
+bool takes_four_waves(const GemmArgs &a, AMode amode, Epilogue epi) {
+  if (a.a_panels || a.out_panels) return false;        // row-major only
+  const long tiles = (long)((a.M + SBM - 1) / SBM) * (a.N / SBN);
+  return a.K <= 320 || (a.K <= 384 && amode == A_PLAIN && epi != EPI_BIAS_RESID && tiles > 128 && tiles <= 512);
+}
+
+template <int AMODE, int EPI>
+hipError_t launch_operand(const GemmArgs &a, hipStream_t s) {
+  return takes_four_waves(a, (AMode)AMODE, (Epilogue)EPI) ? launch_small<AMODE, EPI>(a, s) : launch_slice<AMODE, EPI>(a, s);
+}
+
 }  // namespace
+
+int gemm_small_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *bm, int32_t *bn) {
+  GemmArgs a{};
+  a.M = M; a.N = N; a.K = K;
+  if (takes_four_waves(a, A_PLAIN, epi)) {
+    *bm = SBM; *bn = SBN * pick_blocks(a);
+    return 4;
+  }
+  const SliceTile t = kSliceTiles[pick_slice(M, N, K).tile];
+  *bm = t.m; *bn = t.n;
+  return 8;
+}
 
 // Products outside of the encoder (whose rows keep one order of sums whatever the batch) that give every compute unit at most
 // one 32 x 32 tile: this kernel's four waves share the reduction, and against the pipelined kernel's 32 x 64 tile a call takes
@@ -719,9 +785,9 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
   if (amode == A_PLAIN) {
     if (a.lda % 8 != 0) return hipErrorInvalidValue;
     switch (epi) {
-      case EPI_BIAS: return launch_slice<A_PLAIN, EPI_BIAS>(a, s);
-      case EPI_BIAS_GELU: return launch_slice<A_PLAIN, EPI_BIAS_GELU>(a, s);
-      case EPI_BIAS_RESID: return launch_slice<A_PLAIN, EPI_BIAS_RESID>(a, s);
+      case EPI_BIAS: return launch_operand<A_PLAIN, EPI_BIAS>(a, s);
+      case EPI_BIAS_GELU: return launch_operand<A_PLAIN, EPI_BIAS_GELU>(a, s);
+      case EPI_BIAS_RESID: return launch_operand<A_PLAIN, EPI_BIAS_RESID>(a, s);
       default: return hipErrorInvalidValue;
     }
   }
@@ -729,17 +795,17 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
     if (a.lda % 8 != 0 || !a.ln_g || !a.ln_b || !(a.ln_eps > 0.0f) || a.K > kMaxLnK) return hipErrorInvalidValue;
     if (a.K <= kLnRowK && (epi == EPI_BIAS || epi == EPI_BIAS_GELU)) return epi == EPI_BIAS ? launch_ln<EPI_BIAS>(a, s) : launch_ln<EPI_BIAS_GELU>(a, s);
     switch (epi) {
-      case EPI_BIAS: return launch_small<EPI_BIAS>(a, s);
-      case EPI_BIAS_GELU: return launch_small<EPI_BIAS_GELU>(a, s);
+      case EPI_BIAS: return launch_small<A_LN, EPI_BIAS>(a, s);
+      case EPI_BIAS_GELU: return launch_small<A_LN, EPI_BIAS_GELU>(a, s);
       default: return hipErrorInvalidValue;
     }
   }
   if (a.C % 8 != 0 || 3 * a.C > a.K || !a.row_src || !a.row_flags) return hipErrorInvalidValue;
   switch (epi) {
-    case EPI_BIAS_GELU: return launch_slice<A_CONV3, EPI_BIAS_GELU>(a, s);
+    case EPI_BIAS_GELU: return launch_operand<A_CONV3, EPI_BIAS_GELU>(a, s);
     case EPI_BIAS_GELU_POS:
       if (!a.pos || !a.row_pos) return hipErrorInvalidValue;
-      return launch_slice<A_CONV3, EPI_BIAS_GELU_POS>(a, s);
+      return launch_operand<A_CONV3, EPI_BIAS_GELU_POS>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

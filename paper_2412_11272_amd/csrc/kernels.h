@@ -118,6 +118,7 @@ constexpr int32_t kSmallRows = 1024;
 bool gemm_small_applies(int32_t M, int32_t N, int32_t K);
 bool gemm_slice_applies(int32_t M, int32_t N, int32_t K, bool may_cut);     // products of a few hundred rows of a wide model
 bool gemm_slice_reaches(int64_t rows, int64_t values);      // of a convolution: windows that lie in this many rows of so many values
+int gemm_small_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *bm, int32_t *bn);      // waves that share K, and the tile (diagnostic)
 bool gemm_small_few_rows(int32_t M, int32_t N, int32_t K, Epilogue epi);      // plain products of a few rows, any width
 hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
 // products with at most one tile per compute unit, and convolutions whose taps are no whole K steps

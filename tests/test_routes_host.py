@@ -1,5 +1,4 @@
-"""Which way a batch takes through the encoder, from the code that decides it (CPU only): every batch that the encoder accepts has
-one, whatever its size."""
+"""Which way a batch takes through the encoder and a product through the small-batch kernels, from the code that decides it (CPU only)."""
 import pytest
 
 from paper_2412_11272_amd import binding as wf
@@ -40,3 +39,12 @@ def test_sliced_first_convolution_reaches_its_windows(n_mels, frames, d, sliced)
 def test_a_refused_batch_has_no_route():
     with pytest.raises(wf.WfError):
         wf.encode_route(_cfg(80, 2, 100), [101, 5])
+
+
+@pytest.mark.parametrize("M,N,K,epi,waves", [(16, 128, 64, 0, 4), (1024, 384, 64, 2, 4), (500, 768, 256, 0, 4), (130, 1536, 320, 2, 4), (1300, 128, 192, 2, 4),
+                                             (130, 1152, 384, 0, 4), (300, 1536, 384, 1, 4), (75, 1152, 384, 0, 8), (650, 1152, 384, 0, 8),
+                                             (300, 384, 384, 2, 8), (800, 384, 384, 2, 8), (500, 1536, 448, 0, 8), (75, 384, 1536, 2, 8)])
+def test_short_reductions_stay_on_four_waves(M, N, K, epi, waves):
+    """Eight waves share long reductions; short ones (by measurement up to 320 values, and wide products of 384) lose by it."""
+    assert wf.gemm_kernel_choice(M, N, K, epi)[0] == 0
+    assert wf.gemm_small_choice(M, N, K, epi)[0] == waves
