@@ -85,6 +85,7 @@ struct FeArgs {
   int32_t B, H, n_mels, n_taps, n_empty, blocks;
   FeStream local[kInline + 1];
 };
+static_assert(sizeof(FeArgs) <= wf::kLaunchBytes, "arguments of a launch");
 
 __device__ __forceinline__ FeStream fe_stream(const FeArgs &p, int i) { return p.streams ? p.streams[i] : p.local[i]; }
 

@@ -146,6 +146,7 @@ hipError_t launch_layernorm(float *x, const int32_t *rows, const float *g, const
 // The first kernel of a call may bring the call's index arrays along in its arguments (at most kInlineInts of them: a launch takes
 // 4 KB) and leave them at `dst` for the kernels after it, which spares the call a copy ahead of its first kernel.
 constexpr int32_t kInlineInts = 960;
+constexpr size_t kLaunchBytes = 4096;          // all arguments of a launch together
 struct InlineInts {
   int32_t *dst;             // device, n ints
   const int32_t *src;       // host

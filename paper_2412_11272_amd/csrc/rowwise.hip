@@ -63,6 +63,8 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepArgs p) {
 
 // The index arrays come along in the arguments; block 0 also leaves them on the device for the kernels that follow.
 struct IntsArg { int32_t n; int32_t v[kInlineInts]; };
+static_assert(sizeof(PrepArgs) + sizeof(int32_t *) + sizeof(IntsArg) <= kLaunchBytes, "arguments of prep_inline_kernel");
+static_assert(4 * sizeof(void *) + 2 * sizeof(int) + sizeof(IntsArg) <= kLaunchBytes, "arguments of embed_inline_kernel");
 
 __device__ __forceinline__ void stage_ints(int32_t *lds, const IntsArg &a, int n, int32_t *dst) {
   for (int i = threadIdx.x; i < n; i += 256) lds[i] = a.v[i];
