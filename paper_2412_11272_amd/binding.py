@@ -191,9 +191,13 @@ def _addr(a: np.ndarray) -> int:
 
 
 def _raw_stream(stream) -> int:
-    """The caller's stream, else torch's current one (its raw handle, without building a Stream object)."""
+    """The caller's stream, else torch's current one (its raw handle where this torch gives it away: building a Stream object costs
+    more than a launch)."""
+    if stream is not None:
+        return stream
     import torch
-    return stream if stream is not None else torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def last_error() -> str:
