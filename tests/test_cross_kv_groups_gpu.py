@@ -33,3 +33,23 @@ def test_every_layer(d, layers, M, precision, tol):
             assert float((got[l, :M].double() - ref).abs().max() / ref.abs().max()) <= tol, l
     finally:
         dec.close()
+
+
+def test_more_layers_than_one_launch_reaches():
+    """32-bit offsets reach 127 layers of d = 2048: 129 take two launches, the second of which starts within every array."""
+    import torch
+    d, layers, M = 2048, 129, 3
+    shape = synth.DecoderShape(d, layers, d // 64, 128, 128, 8)
+    assert (((1 << 31) - 1) // (4 * d * d)) == 127
+    one = synth.make_decoder_weights(synth.DecoderShape(d, 3, d // 64, 128, 128, 8), 9, affine_random=True)
+    w = dict(one, layers=[dict(one["layers"][l % 3], xbv=one["layers"][l % 3]["xbv"] + np.float32(0.25 * l)) for l in range(layers)])
+    dec = wf.Decoder(shape, w, 1, M, 8, wf.WF_PRECISION_BF16)
+    try:
+        x = torch.from_numpy(synth.make_enc_states(M, d, 6)).cuda().to(dec.act_dtype)
+        got = dec.cross_kv(x)
+        for l, lw in enumerate(w["layers"]):
+            m = torch.from_numpy(np.concatenate([lw["xwk"], lw["xwv"]])).cuda().to(dec.act_dtype).double()
+            ref = x.double() @ m.T + torch.from_numpy(np.concatenate([np.zeros(d), lw["xbv"]])).cuda()
+            assert float((got[l, :M].double() - ref).abs().max() / ref.abs().max()) <= H.BF16_TOL, l
+    finally:
+        dec.close()

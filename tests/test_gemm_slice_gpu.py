@@ -13,9 +13,31 @@ pytestmark = pytest.mark.gpu
 
 
 # 16 x 16, 16 x 32, 32 x 32, 64 x 32 and 64 x 64 tiles (by the estimate of pick_slice), one row and rows off the tile's edge
-@pytest.mark.parametrize("M,N,K", [(1, 384, 64), (75, 384, 1536), (33, 256, 448), (15, 128, 576), (100, 1280, 1280), (244, 512, 2048), (150, 512, 512),
-                                   (250, 512, 1088), (425, 512, 1984), (925, 384, 1536), (700, 384, 1024), (1024, 512, 192), (1023, 384, 128),
-                                   (1020, 1024, 512), (1024, 1024, 64), (700, 1536, 384), (64, 2304, 768), (100, 1280, 5120), (17, 640, 5056)])
+SLICED = [(75, 384, 1536), (33, 256, 448), (15, 128, 576), (100, 1280, 1280), (244, 512, 2048), (150, 512, 512), (250, 512, 1088), (425, 512, 1984),
+          (925, 384, 1536), (700, 384, 1024), (1020, 1024, 512), (64, 2304, 768), (1, 384, 384), (17, 384, 5056), (1024, 512, 448), (1023, 1024, 448),
+          (600, 1536, 448), (33, 128, 512)]
+# in the model's residual updates only: with bf16 results the pipelined kernel takes them
+SLICED_RESIDUAL = [(100, 1280, 5120), (17, 640, 5056), (1023, 384, 384)]
+# beside them: short reductions on four waves, one tile too many
+OTHERS = [(1, 384, 64), (1024, 512, 192), (1023, 384, 128), (1024, 1024, 64), (700, 1536, 384), (130, 1152, 384), (1024, 256, 320)]
+
+
+def _sliced(M, N, K, epi):
+    return wf.gemm_kernel_choice(M, N, K, epi)[0] == 0 and wf.gemm_small_choice(M, N, K, epi)[0] == 8
+
+
+def test_shapes_reach_every_tile():
+    assert all(_sliced(*s, epi) for s in SLICED for epi in (0, 1, 2))
+    assert all(_sliced(*s, 2) for s in SLICED_RESIDUAL) and not any(_sliced(*s, epi) for s in SLICED_RESIDUAL for epi in (0, 1))
+    assert not any(_sliced(*s, epi) for s in OTHERS for epi in (0, 1))
+    tiles = [wf.gemm_small_choice(*s, 0)[1:] for s in SLICED]
+    assert set(tiles) == {(16, 16), (16, 32), (32, 32), (64, 32), (64, 64)}
+    ragged = {t for (M, _, _), t in zip(SLICED, tiles) if M % t[0]}
+    assert ragged == set(tiles)                    # each of them with a last row tile that is not full
+    assert {-(-K // 64) % 8 for _, _, K in SLICED} >= {0, 1, 6, 7}      # waves with one K step less, and with none
+
+
+@pytest.mark.parametrize("M,N,K", SLICED + SLICED_RESIDUAL + OTHERS)
 @pytest.mark.parametrize("epi", [0, 1, 2])
 def test_product(M, N, K, epi):
     import torch

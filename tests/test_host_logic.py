@@ -117,7 +117,9 @@ def test_workload_recipes():
                                        (12000, 4096, 256, 256), (6400, 1280, 128, 128), (75, 384, 128, 128), (1, 128, 128, 128),
                                        (65536, 2560, 256, 256), (257, 256, 256, 256), (63408, 1280, 256, 256),
                                        (31694, 3840, 320, 256), (31694, 5120, 320, 256), (31694, 1280, 320, 256), (12000, 5120, 320, 256),
-                                       (321, 256, 320, 256)])
+                                       (321, 256, 320, 256),
+                                       # more than 65 536 tiles, and in a column group: past the range of the multiplications
+                                       (128 * 66000 + 1, 128, 128, 128), (256 * 17000, 2048, 256, 256)])
 def test_gemm_work_units_cover_every_tile_exactly_once(M, N, tm, tn):
     """The workgroup -> tile decoding the GEMM kernel runs (XCD striping, column groups, half-width units for the
     last partial round), enumerated on the host: every column block of every tile row exactly once."""

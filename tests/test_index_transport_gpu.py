@@ -26,6 +26,7 @@ def test_encoder_stream_counts(precision, tol):
         for B in (160, 159, 161, 1):
             flat, offs, nf = wf.pack_mels(mels[:B])
             out, cu = enc.encode(torch.from_numpy(flat).cuda(), offs, nf)
+            assert bool(wf.encode_route(enc.cfg, nf) & wf.WF_ROUTE_INLINE_INDEX) == (B < 160)
             ref, cu_ref = O.encode_batch(w, wl.shape.n_heads, mels[:B], hush)
             assert cu.tolist() == cu_ref.tolist()
             assert H.rel_err(out.cpu().numpy(), ref) <= tol, B
