@@ -341,7 +341,7 @@ class Frontend:
         ns = np.ascontiguousarray(n_samples, dtype=np.int32)
         if out is None:
             H = self.cfg.hush_samples
-            F = sum([(n + H) // 160 for n in ns.tolist()])
+            F = sum([(n + H) // 160 for n in ns.ravel().tolist()])
             out = torch.empty((max(F, 1), self.cfg.n_mels), device=audio.device, dtype=out_dtype or torch.float32)
             if F < 1:
                 out = out[:F]

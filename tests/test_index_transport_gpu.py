@@ -72,3 +72,17 @@ def test_frontend_stream_counts(frames):
             assert np.abs(out.cpu().numpy() - ref).max() <= 1e-4, B
     finally:
         fe.close()
+
+
+def test_lengths_in_a_column():
+    """Stream lengths as a [B, 1] array, as they come from an array of records."""
+    import torch
+    audio = torch.from_numpy(synth.make_audio(4000, 3)).cuda()
+    fe = wf.Frontend(80, None, 2, 4000)
+    try:
+        lens = np.array([[1600], [2400]], np.int32)
+        got, cu = fe.logmel(audio, np.array([[0], [1600]]), lens)
+        ref, cu_ref = fe.logmel(audio, [0, 1600], [1600, 2400])
+        assert cu.tolist() == cu_ref.tolist() and torch.equal(got, ref)
+    finally:
+        fe.close()
