@@ -19,8 +19,8 @@
 // included); the VALU of a SIMD is busy 71 % of the kernel, the LDS 32 % (a quarter of that bank conflicts), and the ten waves a CU
 // holds next to 30 KB of LDS a workgroup spend 45 % of their time at barriers and loads.  (The dense DFT on the fp32
 // matrix cores that this replaced took 358 kflop a frame.)  55 625 frames of 128 filters: 333 -> 57 us per call (this kernel 47, the
-// clamp 10; 77 while the table of 64 streams came by a copy); one stream of 437 frames: 65 -> 17 us (8 + 4 on the GPU, two
-// launches, no upload).
+// clamp 10; 77 while the table of 64 streams came by a copy); one stream of 437 frames: 65 -> 12 us (8.5 + 3 on the GPU,
+// two launches, no upload).
 #include "../../include/wf_encoder.h"
 
 #include <hip/hip_runtime.h>

@@ -471,8 +471,8 @@ void gemm_tile_choice(int32_t M, int32_t N, int32_t *bm, int32_t *bn) {
   else { *bm = large_tile_rows(M, N); *bn = 256; }
 }
 
-// Diagnostic: the kernel wf_op_linear's product runs on and its tile: 0 small-batch (32 rows, as many columns as leave enough
-// workgroups: 0 x 0), 1 pipelined, 2 the kernels of this file.
+// Diagnostic: the kernel wf_op_linear's product runs on and its tile: 0 the small-batch kernels (0 x 0, see gemm_small_choice), 1 pipelined,
+// 2 the kernels of this file.
 int gemm_kernel_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *bm, int32_t *bn) {
   GemmArgs a{};
   a.M = M; a.N = N; a.K = K;

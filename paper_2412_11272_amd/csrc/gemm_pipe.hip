@@ -108,6 +108,8 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(GemmArgs p) {
       (char *)p.A + (AMODE == A_CONV3 ? (long)src0 * p.C * 2 : 0L), 0, AMODE == A_CONV3 ? (int)kOutside : (int)a_bytes, 0x00027000);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       (void *)p.W, 0, (int)((size_t)(p.w_panels ? (p.N + 255) & ~255 : p.N) * p.K * 2), 0x00027000);
+  // (The bounds check takes scalar and vector offset together, both unsigned and without wrapping: measured on this part with
+  // addresses on both sides of the end, below and above 2 GiB.  It cuts off the rows past the last one of the operand's last group of eight.)
   const int piece = ((lane & 7) ^ ((4 * wave + (rr >> 1)) & 7)) << 4;       // (row >> 1) & 7 of every row this lane fetches
   const int woff = rr * (p.w_panels ? 128 : p.K * 2) + piece;
   const int wstep = p.w_panels ? 32768 : 128, astep = p.a_panels ? 32768 : 128;    // bytes from one K step to the next

@@ -750,12 +750,11 @@ int gemm_small_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *bm
   return 8;
 }
 
-// Products outside of the encoder (whose rows keep one order of sums whatever the batch) that give every compute unit at most
-// one 32 x 32 tile: this kernel's four waves share the reduction, and against the pipelined kernel's 32 x 64 tile a call takes
-// 3.9 against 5.2 us (100 x 768 x 768), 4.7 / 5.8 (256 x 1024 x 1024), 5.4 / 6.5 (160 x 1280 x 1280), 4.2 / 5.4 (64 x 2304 x 768);
-// one row tile further the two were level (figures of the kernel before this one, which is up to 1.7 times as fast).  Beyond 4 MB of weights (what one XCD's L2 holds; 1 us a call at 3840 x 1280) the
-// rows of a bf16 result keep the order of sums of the larger batches; residual updates go here whatever their depth (100 x 768 x
-// 3072 9.3 / 10.2 us, 100 x 1280 x 5120 15.2 / 17.0).
+// Plain products outside of the encoder that give every compute unit at most one 32 x 32 tile (us a launch in a chain, these kernels and
+// the pipelined one): 160 x 768 x 768 3.5 and 4.7, 320 x 768 x 768 3.9 and 4.8, 256 x 1024 x 1024 4.0 and 5.3, 192 x 1280 x 1280 4.5 and
+// 5.8, 96 x 2304 x 768 3.9 and 4.8; residual updates whatever their depth: 160 x 768 x 3072 5.2 and 10.1, 192 x 1280 x 5120 9.4 and
+// 15.2.  The line is narrower than the kernel's reach (gemm_slice_applies): beyond it, and beyond 4 MB of weights with a bf16 result, rows
+// keep the order of sums that larger batches have.
 bool gemm_small_few_rows(int32_t M, int32_t N, int32_t K, Epilogue epi) {
   if (epi != EPI_BIAS && epi != EPI_BIAS_GELU && epi != EPI_BIAS_RESID) return false;
   return (long)((M + SBM - 1) / SBM) * (N / SBN) <= 256 && (epi == EPI_BIAS_RESID || (long)N * K <= 2L << 20);

@@ -112,8 +112,10 @@ struct PrepArgs {
 
 // bf16 MFMA path -------------------------------------------------------------------------------
 hipError_t launch_gemm_bf16(const GemmArgs &a, AMode amode, Epilogue epi, hipStream_t s);
-// small batches (kSmallRows rows) of narrow models: reduction split over the waves, or LayerNorm fused into the operand.
-// Whether a product of a small batch goes there depends on its width and depth only, not on the number of rows.
+// small batches (kSmallRows rows) of narrow models: reduction split over the waves, or LayerNorm fused into the operand.  An encoder whose
+// whole batch is that small runs all of its products there, so the other streams of such a batch do not change the order of a row's
+// sums in any product.  Elsewhere (wf_op_linear, wide models, larger batches) the number of rows has a say in the kernel and with it in
+// the last bits: products that fill the chip with tiles, or that few enough rows make faster here, go by their tile counts.
 constexpr int32_t kSmallRows = 1024;
 bool gemm_small_applies(int32_t M, int32_t N, int32_t K);
 bool gemm_slice_applies(int32_t M, int32_t N, int32_t K, bool may_cut);     // products of a few hundred rows of a wide model
