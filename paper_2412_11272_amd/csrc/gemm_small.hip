@@ -9,7 +9,8 @@
 //   gemm_ln_kernel      the operand is LayerNorm(x) of an fp32 matrix x with rows of at most 512 values (every model narrow enough
 //                       for this file), normalised on the way in.  This removes two kernels per transformer block; with a few
 //                       hundred tokens each kernel in the chain costs 3-5 us whatever it does.
-//   gemm_small_kernel   four waves share K: short reductions (takes_four_waves), and LayerNorm(x) of longer rows (wf_op_ln_linear only)
+//   gemm_small_kernel   four waves share K: short reductions and weights of 4 GiB and more (takes_four_waves), LayerNorm(x) of longer rows
+//                       (wf_op_ln_linear only)
 
 #include <algorithm>
 #include <mutex>
@@ -725,14 +726,21 @@ hipError_t launch_small(const GemmArgs &a, hipStream_t s) {
 // 4.1, 1024 x 384 x 320 3.7 and 4.1; from 448 on eight are ahead by up to 12 %.  At 384 plain products with bf16 results of 128 to 512 tiles
 // of 32 x 32 (130 x 1152 3.0 and 3.3, 300 x 1536 4.0 and 4.2; 75 x 1152 3.0 on both, 650 x 1152 5.5 and 5.2), windows and residual updates not (their rows
 // keep one order of sums whatever their number).
+// They also find their operands by pointers, where the other kernels' 32-bit offsets end.
+bool offsets_reach(const GemmArgs &a, AMode amode) {
+  const int64_t limit = kOutside, w = (int64_t)(a.w_panels ? (a.N + 255) & ~255 : a.N) * a.K * 2;
+  return w <= limit && (amode != A_PLAIN || (int64_t)(a.a_panels ? (a.M + 255) & ~255 : a.M) * std::max(a.lda, a.K) * 2 <= limit);
+}
 bool takes_four_waves(const GemmArgs &a, AMode amode, Epilogue epi) {
   if (a.a_panels || a.out_panels) return false;        // row-major only
+  if (!offsets_reach(a, amode)) return true;
   const long tiles = (long)((a.M + SBM - 1) / SBM) * (a.N / SBN);
   return a.K <= 320 || (a.K <= 384 && amode == A_PLAIN && epi != EPI_BIAS_RESID && tiles > 128 && tiles <= 512);
 }
 
 template <int AMODE, int EPI>
 hipError_t launch_operand(const GemmArgs &a, hipStream_t s) {
+  if ((a.a_panels || a.out_panels) && !offsets_reach(a, (AMode)AMODE)) return hipErrorInvalidValue;
   return takes_four_waves(a, (AMode)AMODE, (Epilogue)EPI) ? launch_small<AMODE, EPI>(a, s) : launch_slice<AMODE, EPI>(a, s);
 }
 
@@ -740,7 +748,7 @@ hipError_t launch_operand(const GemmArgs &a, hipStream_t s) {
 
 int gemm_small_choice(int32_t M, int32_t N, int32_t K, Epilogue epi, int32_t *bm, int32_t *bn) {
   GemmArgs a{};
-  a.M = M; a.N = N; a.K = K;
+  a.M = M; a.N = N; a.K = a.lda = K;
   if (takes_four_waves(a, A_PLAIN, epi)) {
     *bm = SBM; *bn = SBN * pick_blocks(a);
     return 4;
@@ -792,7 +800,7 @@ hipError_t launch_gemm_small(const GemmArgs &a, AMode amode, Epilogue epi, hipSt
   }
   if (amode == A_LN) {
     if (a.lda % 8 != 0 || !a.ln_g || !a.ln_b || !(a.ln_eps > 0.0f) || a.K > kMaxLnK) return hipErrorInvalidValue;
-    if (a.K <= kLnRowK && (epi == EPI_BIAS || epi == EPI_BIAS_GELU)) return epi == EPI_BIAS ? launch_ln<EPI_BIAS>(a, s) : launch_ln<EPI_BIAS_GELU>(a, s);
+    if (a.K <= kLnRowK && offsets_reach(a, amode) && (epi == EPI_BIAS || epi == EPI_BIAS_GELU)) return epi == EPI_BIAS ? launch_ln<EPI_BIAS>(a, s) : launch_ln<EPI_BIAS_GELU>(a, s);
     switch (epi) {
       case EPI_BIAS: return launch_small<A_LN, EPI_BIAS>(a, s);
       case EPI_BIAS_GELU: return launch_small<A_LN, EPI_BIAS_GELU>(a, s);

@@ -30,3 +30,21 @@ def test_ln_product(M, N, K, epi):
     # the operand is rounded to bf16 on both sides (a value next to a boundary may round the other way: 2^-8 of one of K terms), the
     # result once more (2^-9)
     assert np.abs(got - ref).max() <= 6e-3 * np.abs(ref).max()
+
+
+def test_weights_of_more_than_4_gib():
+    """Short rows against 4 194 432 columns: byte offsets of the weights pass 2^32."""
+    import torch
+    M, N, K = 2, (1 << 22) + 128, 512
+    assert N * K * 2 > 1 << 32
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(M, K, generator=gen, device="cuda")
+    w = torch.randn(N, K, generator=gen, device="cuda", dtype=torch.bfloat16)
+    b = torch.randn(N, generator=gen, device="cuda")
+    out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wf.op_ln_linear(x, torch.ones(K, device="cuda"), torch.zeros(K, device="cuda"), w, b, out, 0)
+    u = torch.nn.functional.layer_norm(x.double(), (K,)).float().bfloat16().float()
+    for n in range(0, N, 1 << 20):
+        ref = u @ w[n:n + (1 << 20)].float().T + b[n:n + (1 << 20)]
+        # operands rounded on both sides, fp32 sums, the result rounded to bf16 (2^-9)
+        assert float((out[:, n:n + (1 << 20)].float() - ref).abs().max() / ref.abs().max()) <= 6e-3, n

@@ -48,3 +48,11 @@ def test_short_reductions_stay_on_four_waves(M, N, K, epi, waves):
     """Eight waves share long reductions; short ones (by measurement up to 320 values, and wide products of 384) lose by it."""
     assert wf.gemm_kernel_choice(M, N, K, epi)[0] == 0
     assert wf.gemm_small_choice(M, N, K, epi)[0] == waves
+
+
+@pytest.mark.parametrize("M,N,K,epi", [(1, 128, (1 << 24) + 64, 2), (16, 256, 1 << 23, 2), (1023, 128, (1 << 21) + 128, 2)])
+def test_operands_beyond_32_bit_offsets_stay_on_pointers(M, N, K, epi):
+    """Weights or activations of 4 GiB: the four-wave kernel, whatever the depth."""
+    assert max(N, M) * K * 2 >= 1 << 32
+    assert wf.gemm_small_choice(M, N, K, epi)[0] == 4
+    assert wf.gemm_small_choice(M, N, K // 256 * 64, epi)[0] == 8
