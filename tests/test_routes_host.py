@@ -50,7 +50,7 @@ def test_short_reductions_stay_on_four_waves(M, N, K, epi, waves):
     assert wf.gemm_small_choice(M, N, K, epi)[0] == waves
 
 
-@pytest.mark.parametrize("M,N,K,epi", [(1, 128, (1 << 24) + 64, 2), (16, 256, 1 << 23, 2), (1023, 128, (1 << 21) + 128, 2)])
+@pytest.mark.parametrize("M,N,K,epi", [(1, 128, (1 << 24) + 64, 2), (16, 256, 1 << 23, 2), (1024, 128, (1 << 21) + 128, 2)])
 def test_operands_beyond_32_bit_offsets_stay_on_pointers(M, N, K, epi):
     """Weights or activations of 4 GiB: the four-wave kernel, whatever the depth."""
     assert max(N, M) * K * 2 >= 1 << 32
