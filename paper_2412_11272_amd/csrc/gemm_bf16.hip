@@ -380,13 +380,16 @@ int large_tile_rows(int M, int N) {
 // A product with bf16 results whose large tiles end in a poorly filled round takes the pipelined kernel's 192 x 256 tile where that ends in
 // a better one: its one round takes 0.95 of a round of 256 x 256 tiles, two take 0.83 each (2600 x 4096 x 1024 31.3 -> 29.8 us, 6420 x 3840 x
 // 1280 63.6 -> 59.3; 6000 x 4096 x 1024, whose large tiles take one round and a half, would lose 8 %).  Reductions of at least 768:
-// below, start and end of a tile weigh more.  Not beside another lane's kernels, which find no room on a CU with such a tile (9500 rows of
+// below, start and end of a tile weigh more.  Two rounds with GELU from 1280 on: its end of a tile is not covered by a second workgroup's
+// loop here (8768 x 2816, K = 768 48.8 -> 49.3, 1024 56.9 -> 57.0, 1280 68.3 -> 65.0; 6464 x 3840, K = 768 47.0 -> 49.3; without GELU K = 768 43.6 ->
+// 42.3 and 41.3 -> 41.8).  Not beside another lane's kernels, which find no room on a CU with such a tile (9500 rows of
 // 768 in two lanes 2.47 -> 2.51 ms).
 bool takes_tall(int M, int N, int K, Epilogue epi) {
   if ((epi != EPI_BIAS && epi != EPI_BIAS_GELU) || N % 256 || K < 768 || (long)((M + 255) / 256) * (N / 256) < 160) return false;
   const long tiles = (long)((M + 191) / 192) * (N / 256);
   if (tiles > 512) return false;
   const double large = std::min(large_rounds((long)((M + 255) / 256) * (N / 256)), 1.18 * large_rounds((long)((M + 319) / 320) * (N / 256)));
+  if (tiles > 256 && epi == EPI_BIAS_GELU && K < 1280) return false;
   return (tiles <= 256 ? 0.95 : 1.66) < 0.97 * large;
 }
 

@@ -256,8 +256,8 @@ inline int run_ln(DevCtx *e, hipStream_t s, int cls, float *x, const float *g, c
 // Weights [n, k] for a kernel to fetch ahead of the product that reads them.  A wide model's weights (from 4 MB a matrix on) come from
 // memory in every layer: its blocks together exceed what the memory-side cache holds beside the activations.  In calls of up to
 // several thousand rows that is a fifth of a product's time (425 x 5120 x 1280 15.3 us from memory, 12.5 from the cache), while LayerNorm
-// and attention leave most of the memory idle and, in small calls, most of the chip.  128 workgroups: 32 take longer than the kernel
-// they ride on, 256 hold it up.  Encoder calls of d = 1280: 425 rows 2191 -> 2121 us, 2100 4865 -> 4593, 6200 10.03 -> 9.88 ms; d = 1024: 2600
+// and attention leave most of the memory idle and, in small calls, most of the chip.  128 workgroups: 256 hold the kernel they ride on
+// up, 32 take longer still.  At 425 rows of 1280 the fetch outlasts the LayerNorm (6.2 to 6.4 us together, 3.2 alone), which the products win back.  Encoder calls of d = 1280: 425 rows 2191 -> 2121 us, 2100 4865 -> 4593, 6200 10.03 -> 9.88 ms; d = 1024: 2600
 // rows 2997 -> 2924, 225 rows 1099 -> 1031; prefill of 6400 rows of 1280 15.54 -> 15.06 ms.  From about 8000 rows on it is level or
 // loses (8000 x 1280 11.42 -> 11.59, 10 000 x 1024 7.35 -> 7.48), and so it does with the matrices of narrow models (2000 x 512 386 -> 389 us).
 constexpr int kPrefetchRows = 7168;

@@ -234,7 +234,7 @@ def test_cut_residual_products(d, heads, frames, hush):
 # Batches whose lanes have sizes on the other side of a kernel choice than the batch as a whole: the attention form (twice), the
 # small-batch products, a second MLP product whose reduction is cut, 192 x 256 tiles (on one lane only)
 @pytest.mark.parametrize("d,heads,d_mlp,tokens", [(384, 6, 1536, [1408, 1280, 1525, 1525, 1525, 1000]), (384, 6, 1536, [1280, 1300, 1525, 1525, 1525, 1040]),
-                                                  (384, 6, 1536, [500, 8000]), (128, 2, 4096, [1500] * 6), (768, 12, 2816, [1500] * 5 + [1300])])
+                                                  (384, 6, 1536, [500, 8000]), (128, 2, 4096, [1500] * 6), (1280, 20, 2816, [1500] * 5 + [1300])])
 def test_lanes_do_not_change_a_bit(d, heads, d_mlp, tokens):
     import torch
     wl = synth.Workload("lanes", synth.Shape(80, d, 2, heads, d_mlp), [2 * t for t in tokens], hush_frames=0, seed_index=4)

@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("epi", [0, 1])
 def test_product(M, N, K, tall, epi):
     import torch
+    if M > 6144 and epi == 1 and K < 1280:         # two rounds of the chip with GELU: deeper reductions only
+        tall = False
     assert (wf.gemm_kernel_choice(M, N, K, epi) == (1, 192, 256)) == tall
     g = torch.Generator(device="cuda").manual_seed(M + N + K + epi)
     a = torch.randn(M, K, generator=g, device="cuda").bfloat16()
@@ -26,7 +28,7 @@ def test_product(M, N, K, tall, epi):
     assert float((out.double() - ref).abs().max() / ref.abs().max()) <= 5e-3
 
 
-@pytest.mark.parametrize("M,N,K", [(2600, 4096, 1024), (2561, 4096, 832), (6420, 3840, 1280), (8800, 2816, 768)])
+@pytest.mark.parametrize("M,N,K", [(2600, 4096, 1024), (2561, 4096, 832), (6420, 3840, 1280), (8800, 2816, 1280)])
 @pytest.mark.parametrize("epi", [0, 1])
 def test_same_bits_as_the_large_tiles(M, N, K, epi):
     """A batch takes this tile on one lane and not on several, where it has to give the same rows."""

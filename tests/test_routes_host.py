@@ -56,3 +56,9 @@ def test_operands_beyond_32_bit_offsets_stay_on_pointers(M, N, K, epi):
     assert max(N, M) * K * 2 >= 1 << 32
     assert wf.gemm_small_choice(M, N, K, epi)[0] == 4
     assert wf.gemm_small_choice(M, N, K // 256 * 64, epi)[0] == 8
+
+
+@pytest.mark.parametrize("M,N,K,epi,tall", [(8768, 2816, 768, 1, False), (6464, 3840, 1024, 1, False), (8768, 2816, 1280, 1, True), (6464, 3840, 1280, 0, True),
+                                            (8768, 2816, 768, 0, True), (3072, 4096, 768, 1, True)])
+def test_two_rounds_of_tall_tiles_with_gelu_need_a_deep_reduction(M, N, K, epi, tall):
+    assert (wf.gemm_kernel_choice(M, N, K, epi) == (1, 192, 256)) == tall
