@@ -380,8 +380,8 @@ int large_tile_rows(int M, int N) {
 // A product with bf16 results whose large tiles end in a poorly filled round takes the pipelined kernel's 192 x 256 tile where that ends in
 // a better one: its one round takes 0.95 of a round of 256 x 256 tiles, two take 0.83 each (2600 x 4096 x 1024 31.3 -> 29.8 us, 6420 x 3840 x
 // 1280 63.6 -> 59.3; 6000 x 4096 x 1024, whose large tiles take one round and a half, would lose 8 %).  Reductions of at least 768:
-// below, start and end of a tile weigh more.  Two rounds with GELU from 1280 on: its end of a tile is not covered by a second workgroup's
-// loop here (8768 x 2816, K = 768 48.8 -> 49.3, 1024 56.9 -> 57.0, 1280 68.3 -> 65.0; 6464 x 3840, K = 768 47.0 -> 49.3; without GELU K = 768 43.6 ->
+// below, start and end of a tile weigh more.  Two rounds with GELU from 1280 on: its four waves evaluate 384 values a lane in them,
+// the eight of a large tile and a half 240 (8768 x 2816, K = 768 48.8 -> 49.3, 1024 56.9 -> 57.0, 1280 68.3 -> 65.0; 6464 x 3840, K = 768 47.0 -> 49.3; without GELU K = 768 43.6 ->
 // 42.3 and 41.3 -> 41.8).  Not beside another lane's kernels, which find no room on a CU with such a tile (9500 rows of
 // 768 in two lanes 2.47 -> 2.51 ms).
 bool takes_tall(int M, int N, int K, Epilogue epi) {
